@@ -91,7 +91,9 @@ typedef struct nebem_images {
 } nebem_images;
 
 typedef enum nebem_precision {
-    NEBEM_FP64 = 0,  /* exact closed forms in FP64 everywhere; FP64 LU + FP64 refinement */
+    NEBEM_FP64 = 0,  /* FP64 everywhere: exact closed forms; in evaluations, copies of a 64-element group far from the
+                        point by the group's multipole expansion, truncated below 1e-12 of the group's summed absolute
+                        charge over distance (less than the closed forms' own rounding there); FP64 LU + refinement */
     NEBEM_MIXED = 1  /* FP64 near field, FP64 monopole + FP32 correction far away; FP32 LU + FP64 refinement */
 } nebem_precision;
 
@@ -422,7 +424,7 @@ nebem_status nebem_spacecharge_step_lines(nebem_session *s, double *qx, double *
  * > 0 at most that many large requests are active at once -- first come
  * first served among them -- and a large one beyond it waits at the head
  * like one that does not fit), sorts the
- * points of requests of >= 4096 points into Morton order, cuts the
+ * points of requests of more than 64 points into Morton order, cuts the
  * admitted requests into work items of 64 points x one element segment, and
  * evaluates work items of several requests and geometries in each kernel
  * launch (round-robin, up to batch_interactions element-copy x point pairs

@@ -159,7 +159,7 @@ nebem_status eval_with_workspace(const double *drec, const double *sigma, int64_
                                  int64_t m, double *phi, double *ex, double *ey, double *ez, hipStream_t stream,
                                  const char *what)
 {
-    const size_t wb = eval_workspace(n, ia, m, ncol);
+    const size_t wb = eval_workspace(n, ia, m, ncol, mixed);
     DevBuf ws;
     if (wb && ws.alloc(wb, stream) != hipSuccess)
         return fail(NEBEM_ENOMEM, std::string(what) + ": evaluation workspace");

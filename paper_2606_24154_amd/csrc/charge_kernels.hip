@@ -387,7 +387,7 @@ hipError_t launch_coulomb(const double *qx, const double *qy, const double *qz, 
     double *se = reinterpret_cast<double *>(w + w0 + align256c(4 * n) + align256c(24 * n) + align256c(8 * n));
     double *bx = reinterpret_cast<double *>(w + w0 + align256c(4 * n) + align256c(24 * n) + align256c(8 * n) +
                                             align256c(24 * n));
-    hipError_t e = launch_order_points(qx, qy, qz, nq, sp, sp + n, sp + 2 * n, perm, ws, w0, s);
+    hipError_t e = launch_order_points(qx, qy, qz, nq, sp, sp + n, sp + 2 * n, perm, false, ws, w0, s);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_gather1, dim3(blocks(nq)), dim3(kCB), 0, s, q, perm, (int)nq, sq);
     hipLaunchKernelGGL(k_tile_boxes, dim3(runs(nq)), dim3(kRun), 0, s, sp, sp + n, sp + 2 * n, (int)nq, bx);

@@ -21,6 +21,7 @@
 
 #include "nebem_internal.hpp"
 #include "farfield_mixed.hpp"
+#include "group_far.hpp"
 #include "panel_fp64.hpp"
 
 namespace nebem {
@@ -1132,6 +1133,371 @@ void launch_eval_multi_seg(const double *drec, const double *sigma, int64_t n, i
     }
 }
 
+// Segment partial sums -> results: for column k < ncol and component c,
+// out.c[c][k * out.stride + i] = k_e (0 + sum over s = 0 .. nseg-1, in that
+// order, of part[s * seg_stride + (4 k + c) m + i]); null components skipped.
+__global__ __launch_bounds__(kBlock) void k_reduce_segments(const double *__restrict__ part, int nseg, int ncol,
+                                                             int m, int64_t seg_stride, OutCols out)
+{
+    const int i = blockIdx.x * kBlock + threadIdx.x;
+    if (i >= m) return;
+    for (int k = 0; k < ncol; ++k)
+        for (int c = 0; c < 4; ++c) {
+            if (!out.c[c]) continue;
+            const double *p = part + (size_t)(4 * k + c) * m + i;
+            double acc = 0.0;
+            for (int s = 0; s < nseg; ++s) acc += p[(size_t)s * (size_t)seg_stride];
+            out.c[c][(size_t)k * out.stride + i] = kKe * acc;
+        }
+}
+
+void launch_reduce_segments(const double *part, int nseg, int ncol, int64_t m, int64_t seg_stride,
+                            const OutCols &out, hipStream_t s)
+{
+    if (m <= 0) return;
+    hipLaunchKernelGGL(k_reduce_segments, dim3((unsigned)((m + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, part, nseg,
+                       ncol, (int)m, seg_stride, out);
+}
+
+// ------------------------------------------------- grouped FP64: near part
+// The copies of a group that are nearer to a point than the expansion's
+// range (group_far.hpp), element by element with the closed forms.  Per wave,
+// group and chunk of copies: a first loop tests every copy with the far
+// pass's own arithmetic and lists those that are near for any lane, with the
+// mask of the lanes they are near for; then each element (or triangle pair)
+// of the group walks the listed copies only.  The list is the wave's own (LDS,
+// no workgroup barrier), and the records come through scalar loads: with a
+// few copies per element, staging them in LDS and moving them to scalar
+// registers would cost as much as the closed forms.
+constexpr int kNearCopies = 128;  // copies per list: the 121 of an 11 x 11 lattice in one
+constexpr int kSubElems = kGroupElems / kNearParts;
+
+__device__ __forceinline__ Elem load_elem_c(cdouble_p d)
+{
+    return {d[R_OX],  d[R_OY],  d[R_OZ], d[R_E1X], d[R_E1Y], d[R_E1Z], d[R_E2X],  d[R_E2Y],  d[R_E2Z], d[R_E3X],
+            d[R_E3Y], d[R_E3Z], d[R_LX], d[R_LZ],  d[R_HYP], d[R_IHYP], d[R_DIAM], d[R_AREA], uni((int)d[R_KIND])};
+}
+
+// one copy by the closed forms (tiers of sum_translations), added to s
+template <int KIND>
+__device__ __forceinline__ void copy_fp64(const Elem &e, double X, double Z, double H, double far2, double vfar2,
+                                          double (&s)[4])
+{
+    Kern k;
+    const double r0sq = fma(X, X, fma(Z, Z, H * H));
+    if (r0sq >= vfar2) {
+        k = KIND == 0 ? rect_far<true>(X, H, Z, e.lx, e.lz, r0sq, s[0])
+                      : rtri_far<true>(X, H, Z, e.lx, e.lz, e.hyp, r0sq, s[0]);
+    } else if (r0sq >= far2) {
+        k = KIND == 0 ? rect_far<false>(X, H, Z, e.lx, e.lz, r0sq, s[0])
+                      : rtri_far<false>(X, H, Z, e.lx, e.lz, e.hyp, r0sq, s[0]);
+    } else {
+        k = KIND == 0 ? rect_fp64(X, H, Z, e.lx, e.lz, r0sq)
+                      : rtri_fp64(X, H, Z, e.lx, e.lz, e.hyp, e.ihyp, r0sq);
+        k.phi += s[0];
+    }
+    s[0] = k.phi;
+    s[1] += k.ex;
+    s[2] += k.ez;
+    s[3] += k.en;
+}
+
+// the same for both triangles of a pair, in the first one's frame
+__device__ __forceinline__ void pair_copy_fp64(const Elem &e, const PairB &f, double X, double Z, double H,
+                                               double far2, double vfar2, double (&s1)[4], double (&s2)[4])
+{
+    const double r0sq = fma(X, X, fma(Z, Z, H * H));
+    Kern k1, k2;
+    if (r0sq >= vfar2) {
+        rtri_pair_far<true>(X, H, Z, e.lx, f.lz, e.lz, e.hyp, f.hyp, r0sq, s1[0], s2[0], k1, k2);
+    } else if (r0sq >= far2) {
+        rtri_pair_far<false>(X, H, Z, e.lx, f.lz, e.lz, e.hyp, f.hyp, r0sq, s1[0], s2[0], k1, k2);
+    } else {
+        k1 = rtri_fp64(X, H, Z, e.lx, e.lz, e.hyp, e.ihyp, r0sq);
+        k2 = rtri_fp64(Z, H, -X, e.lz, f.lz, f.hyp, f.ihyp, r0sq);
+        k1.phi += s1[0];
+        k2.phi += s2[0];
+    }
+    s1[0] = k1.phi;
+    s1[1] += k1.ex;
+    s1[2] += k1.ez;
+    s1[3] += k1.en;
+    s2[0] = k2.phi;
+    s2[1] += k2.ex;
+    s2[2] += k2.ez;
+    s2[3] += k2.en;
+}
+
+// A wave's list of near copies: translations as the factors of a1, a2, the
+// lanes they are near for, and where each reflection's entries begin.
+struct NearList {
+    double f1[kNearCopies], f2[kNearCopies];
+    uint64_t lanes[kNearCopies];
+    int begin[9];
+};
+
+// copies [c0, c1) (reflection-major, then i1, i2) of the group with header h
+__device__ __forceinline__ int list_near(NearList &nl, cdouble_p h, const ImgArgs &img, int c0, int c1, double Px,
+                                         double Py, double Pz)
+{
+    const int w2 = 2 * img.n2 + 1, per = (2 * img.n1 + 1) * w2;
+    int cnt = 0;
+    for (int r = 0; r < img.nref; ++r) {
+        nl.begin[r] = cnt;
+        const int lo = max(c0 - r * per, 0), hi = min(c1 - r * per, per);
+        if (lo >= hi) continue;
+        const GroupVec v0 = group_origin(img, img.axes[r], Px, Py, Pz, h);
+        int i1 = lo / w2 - img.n1, i2 = lo % w2 - img.n2;
+        GroupVec v1 = group_step(v0, -(double)i1, img.a1[r]);
+#pragma unroll 1
+        for (int q = lo; q < hi; ++q) {
+            const double r2 = group_r2(group_step(v1, -(double)i2, img.a2[r]));
+            const uint64_t b = __ballot(!(r2 >= h[kHeadTier]));
+            if (b) {
+                nl.f1[cnt] = -(double)i1;
+                nl.f2[cnt] = -(double)i2;
+                nl.lanes[cnt] = b;
+                ++cnt;
+            }
+            if (++i2 > img.n2) {
+                i2 = -img.n2;
+                ++i1;
+                v1 = group_step(v0, -(double)i1, img.a1[r]);
+            }
+        }
+    }
+    nl.begin[img.nref] = cnt;
+    return cnt;
+}
+
+// One element, or pair of triangles, over the listed copies: adds
+// sum_k density x (phi', E') to acc.
+template <int K, bool PAIR>
+__device__ __forceinline__ void near_element(const NearList &nl, const Elem &e, const PairB &f, const double (&sg1)[K],
+                                             const double (&sg2)[K], const ImgArgs &img, double Px, double Py,
+                                             double Pz, double (&acc)[K][4])
+{
+    const int lane = threadIdx.x & 63;
+    const double dp = PAIR ? fmax(e.diam, f.diam) : e.diam;
+    const double far2 = (kFarDiam * kFarDiam) * (dp * dp), vfar2 = (kVeryFarDiam * kVeryFarDiam) * (dp * dp);
+#pragma unroll 1
+    for (int r = 0; r < img.nref; ++r) {
+        const int lo = uni(nl.begin[r]), hi = uni(nl.begin[r + 1]);
+        if (lo >= hi) continue;
+        const int ax = img.axes[r];
+        const double Qx = (ax & 1) ? 2.0 * img.mpos[0] - Px : Px;
+        const double Qy = (ax & 2) ? 2.0 * img.mpos[1] - Py : Py;
+        const double Qz = (ax & 4) ? 2.0 * img.mpos[2] - Pz : Pz;
+        const double rx = Qx - e.ox, ry = Qy - e.oy, rz = Qz - e.oz;
+        const double X0 = rx * e.e1x + ry * e.e1y + rz * e.e1z;
+        const double Z0 = rx * e.e2x + ry * e.e2y + rz * e.e2z;
+        const double H0 = rx * e.e3x + ry * e.e3y + rz * e.e3z;
+        const double *a = img.a1[r], *b = img.a2[r];
+        const double aX = a[0] * e.e1x + a[1] * e.e1y + a[2] * e.e1z;
+        const double aZ = a[0] * e.e2x + a[1] * e.e2y + a[2] * e.e2z;
+        const double aH = a[0] * e.e3x + a[1] * e.e3y + a[2] * e.e3z;
+        const double bX = b[0] * e.e1x + b[1] * e.e1y + b[2] * e.e1z;
+        const double bZ = b[0] * e.e2x + b[1] * e.e2y + b[2] * e.e2z;
+        const double bH = b[0] * e.e3x + b[1] * e.e3y + b[2] * e.e3z;
+        double s1[4] = {0.0, 0.0, 0.0, 0.0}, s2[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 1
+        for (int l = lo; l < hi; ++l) {
+            const double f1 = nl.f1[l], f2 = nl.f2[l];
+            if ((nl.lanes[l] >> lane) & 1) {
+                const double X = fma(f2, bX, fma(f1, aX, X0)), Z = fma(f2, bZ, fma(f1, aZ, Z0)),
+                             H = fma(f2, bH, fma(f1, aH, H0));
+                if (PAIR)
+                    pair_copy_fp64(e, f, X, Z, H, far2, vfar2, s1, s2);
+                else if (e.kind == 0)
+                    copy_fp64<0>(e, X, Z, H, far2, vfar2, s1);
+                else
+                    copy_fp64<1>(e, X, Z, H, far2, vfar2, s1);
+            }
+        }
+        const double par = img.parity[r];
+        const double px = (ax & 1) ? -par : par, py = (ax & 2) ? -par : par, pz = (ax & 4) ? -par : par;
+        const double p1 = par * s1[0];
+        const double x1 = px * fma(s1[1], e.e1x, fma(s1[2], e.e2x, s1[3] * e.e3x));
+        const double y1 = py * fma(s1[1], e.e1y, fma(s1[2], e.e2y, s1[3] * e.e3y));
+        const double z1 = pz * fma(s1[1], e.e1z, fma(s1[2], e.e2z, s1[3] * e.e3z));
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            acc[k][0] = fma(sg1[k], p1, acc[k][0]);
+            acc[k][1] = fma(sg1[k], x1, acc[k][1]);
+            acc[k][2] = fma(sg1[k], y1, acc[k][2]);
+            acc[k][3] = fma(sg1[k], z1, acc[k][3]);
+        }
+        if (PAIR) {  // second triangle: frame (e2, -e1, e3)
+            const double p2 = par * s2[0];
+            const double x2 = px * fma(s2[1], e.e2x, fma(-s2[2], e.e1x, s2[3] * e.e3x));
+            const double y2 = py * fma(s2[1], e.e2y, fma(-s2[2], e.e1y, s2[3] * e.e3y));
+            const double z2 = pz * fma(s2[1], e.e2z, fma(-s2[2], e.e1z, s2[3] * e.e3z));
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                acc[k][0] = fma(sg2[k], p2, acc[k][0]);
+                acc[k][1] = fma(sg2[k], x2, acc[k][1]);
+                acc[k][2] = fma(sg2[k], y2, acc[k][2]);
+                acc[k][3] = fma(sg2[k], z2, acc[k][3]);
+            }
+        }
+    }
+}
+
+// Near copies of groups [g0, g1) of one segment (records drec, densities
+// sigma of the segment's n elements), quarters [u0, u1) of each group:
+// quarters added into the group's sum, groups into acc, in that order.
+template <int K>
+__device__ __forceinline__ void near_unit(NearList &nl, cdouble_p drec, cdouble_p sigma, int64_t sig_stride,
+                                          cdouble_p gd, int n, const ImgArgs &img, double Px, double Py, double Pz,
+                                          int g0, int g1, int u0, int u1, double (&acc)[K][4])
+{
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int k = 0; k < K; ++k)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) acc[k][c] = 0.0;
+    const int ncopy = img.nref * (2 * img.n1 + 1) * (2 * img.n2 + 1);
+#pragma unroll 1
+    for (int g = g0; g < g1; ++g) {
+        cdouble_p h = gd + (int64_t)g * kGroupStride;
+        const int e0 = g * kGroupElems, cnt = min(kGroupElems, n - e0);
+        int listed = -1;
+        if (ncopy <= kNearCopies) {
+            listed = list_near(nl, h, img, 0, ncopy, Px, Py, Pz);
+            if (listed == 0) continue;
+        }
+        // triangle pairs inside the group, taken greedily from its start
+        const double kd = lane + 1 < cnt ? drec[(int64_t)(e0 + lane) * R_STRIDE + R_KIND] : 0.0;
+        uint64_t rem = __ballot(kd >= 2.0), first = 0;
+        while (rem) {
+            const uint64_t b = rem & (0 - rem);
+            first |= b;
+            rem &= ~(b | (b << 1));
+        }
+        const uint64_t second = first << 1;
+        double grp[K][4];
+#pragma unroll
+        for (int k = 0; k < K; ++k)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) grp[k][c] = 0.0;
+#pragma unroll 1
+        for (int u = u0; u < u1; ++u) {
+            double sub[K][4];
+#pragma unroll
+            for (int k = 0; k < K; ++k)
+#pragma unroll
+                for (int c = 0; c < 4; ++c) sub[k][c] = 0.0;
+#pragma unroll 1
+            for (int c0 = 0; c0 < ncopy; c0 += kNearCopies) {
+                if (ncopy > kNearCopies)
+                    listed = list_near(nl, h, img, c0, min(c0 + kNearCopies, ncopy), Px, Py, Pz);
+                if (listed == 0) continue;
+                const int i1 = min((u + 1) * kSubElems, cnt);
+#pragma unroll 1
+                for (int i = u * kSubElems; i < i1; ++i) {
+                    if ((second >> i) & 1) continue;
+                    cdouble_p p = drec + (int64_t)(e0 + i) * R_STRIDE;
+                    const bool pair = (first >> i) & 1;
+                    double sg1[K], sg2[K];
+                    if (pair) {
+                        const bool fst = uni((int)p[R_KIND]) == 2;  // the pair's first triangle is element i
+                        cdouble_p pf = p + (fst ? 0 : R_STRIDE), ps = p + (fst ? R_STRIDE : 0);
+                        const PairB f = {ps[R_LZ], ps[R_HYP], ps[R_IHYP], ps[R_DIAM], ps[R_AREA]};
+#pragma unroll
+                        for (int k = 0; k < K; ++k) {
+                            sg1[k] = sigma[k * sig_stride + e0 + i + (fst ? 0 : 1)];
+                            sg2[k] = sigma[k * sig_stride + e0 + i + (fst ? 1 : 0)];
+                        }
+                        near_element<K, true>(nl, load_elem_c(pf), f, sg1, sg2, img, Px, Py, Pz, sub);
+                    } else {
+#pragma unroll
+                        for (int k = 0; k < K; ++k) sg1[k] = sg2[k] = sigma[k * sig_stride + e0 + i];
+                        near_element<K, false>(nl, load_elem_c(p), PairB{}, sg1, sg2, img, Px, Py, Pz, sub);
+                    }
+                }
+            }
+#pragma unroll
+            for (int k = 0; k < K; ++k)
+#pragma unroll
+                for (int c = 0; c < 4; ++c) grp[k][c] += sub[k][c];
+        }
+#pragma unroll
+        for (int k = 0; k < K; ++k)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) acc[k][c] += grp[k][c];
+    }
+}
+
+// Grid: x over points, y over units -- segments (split 0: added to the far
+// pass's sums), groups (split 1) or quarters of groups (split 2).
+template <int K>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_group_near(const double *__restrict__ drec,
+                                                       const double *__restrict__ sigma,
+                                                       const double *__restrict__ gdata, int n, int64_t sig_stride,
+                                                       int segsz, int gps, ImgArgs img, int split,
+                                                       const double *__restrict__ px, const double *__restrict__ py,
+                                                       const double *__restrict__ pz, int m, OutCols out,
+                                                       int64_t unit_stride)
+{
+    __shared__ NearList lists[kBlock / 64];
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    const int j = min(i, m - 1);
+    int y = blockIdx.y, u0 = 0, u1 = kNearParts;
+    if (split == 2) {
+        u0 = y % (kNearParts);
+        u1 = u0 + 1;
+        y /= kNearParts;
+    }
+    const int seg = split ? y / gps : y;
+    const int ns = min(segsz, n - seg * segsz);
+    const int ng = (ns + kGroupElems - 1) / kGroupElems;
+    const int g0 = split ? y % gps : 0, g1 = split ? min(g0 + 1, ng) : ng;
+    double acc[K][4];
+    near_unit<K>(lists[threadIdx.x >> 6], uniform_ptr(drec + (int64_t)seg * segsz * R_STRIDE),
+                 uniform_ptr(sigma + (int64_t)seg * segsz), sig_stride,
+                 uniform_ptr(gdata + (int64_t)seg * gps * kGroupStride), ns, img, px[j], py[j], pz[j], g0, g1, u0, u1,
+                 acc);
+    if (i >= m) return;
+    const int64_t o = (int64_t)blockIdx.y * unit_stride + i;
+#pragma unroll
+    for (int k = 0; k < K; ++k)
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+            if (out.c[c]) {
+                double *d = out.c[c] + o + k * out.stride;
+                *d = split ? acc[k][c] : *d + acc[k][c];
+            }
+}
+
+template <int K>
+static void launch_near_k(const double *drec, const double *sigma, const double *gdata, int64_t n, int64_t sig_stride,
+                          const SegPlan &sp, const ImgArgs &img, int split, const double *px, const double *py,
+                          const double *pz, int64_t m, const OutCols &out, int64_t unit_stride, hipStream_t s)
+{
+    const int gps = groups_per_seg(sp);
+    const int64_t ng = (int64_t)sp.nseg * gps;
+    const int64_t units = split == 0 ? sp.nseg : split == 1 ? ng : ng * (kNearParts);
+    const int bs = split == 0 ? kBlock : 64;
+    hipLaunchKernelGGL(k_group_near<K>, dim3((unsigned)((m + bs - 1) / bs), (unsigned)units), dim3(bs), 0, s, drec,
+                       sigma, gdata, (int)n, sig_stride, sp.segsz, gps, img, split, px, py, pz, (int)m, out,
+                       unit_stride);
+}
+
+void launch_group_near(const double *drec, const double *sigma, const double *gdata, int64_t n, int64_t sig_stride,
+                       int ncol, const SegPlan &sp, const ImgArgs &img, int split, const double *px, const double *py,
+                       const double *pz, int64_t m, const OutCols &out, int64_t unit_stride, hipStream_t s)
+{
+    if (m <= 0 || n <= 0) return;
+#define NEAR_ARGS drec, sigma, gdata, n, sig_stride, sp, img, split, px, py, pz, m, out, unit_stride, s
+    switch (ncol) {
+    case 1: launch_near_k<1>(NEAR_ARGS); break;
+    case 2: launch_near_k<2>(NEAR_ARGS); break;
+    case 3: launch_near_k<3>(NEAR_ARGS); break;
+    default: launch_near_k<4>(NEAR_ARGS); break;
+    }
+#undef NEAR_ARGS
+}
+
 // Continuous-batching evaluation: workgroup (one wave) b takes work item b --
 // up to 64 points of one request against one segment of the elements of one
 // resident geometry -- and writes the segment's unscaled partial sums.  The
@@ -1139,7 +1505,20 @@ void launch_eval_multi_seg(const double *drec, const double *sigma, int64_t n, i
 __global__ __launch_bounds__(64) void k_eval_items_fp64(const WorkItem *__restrict__ items,
                                                        const ImgArgs *__restrict__ imgs, double near_factor)
 {
+    __shared__ NearList list;
     const WorkItem &w = items[blockIdx.x];
+    if (w.gdata) {  // grouped geometry: the near part, added to k_items_far's
+        const int j = min((int)threadIdx.x, w.count - 1);
+        double acc[1][4];
+        near_unit<1>(list, uniform_ptr(w.drec), uniform_ptr(w.sigma), 0, uniform_ptr(w.gdata), w.n, imgs[w.geom],
+                     w.px[j], w.py[j], w.pz[j], 0, (w.n + kGroupElems - 1) / kGroupElems, 0, kNearParts, acc);
+        if ((int)threadIdx.x >= w.count) return;
+        w.phi[threadIdx.x] += acc[0][0];
+        w.ex[threadIdx.x] += acc[0][1];
+        w.ey[threadIdx.x] += acc[0][2];
+        w.ez[threadIdx.x] += acc[0][3];
+        return;
+    }
     eval_block<false, 64>(w.drec, w.sigma, w.n, imgs[w.geom], near_factor, w.px, w.py, w.pz, w.count, 0, 1.0, w.phi,
                           w.ex, w.ey, w.ez);
 }
@@ -1168,36 +1547,12 @@ void launch_eval_items(const WorkItem *items, int nitems, const ImgArgs *imgs, i
                        hipStream_t s)
 {
     if (nitems <= 0) return;
-    if (mixed)
+    if (mixed) {
         hipLaunchKernelGGL(k_eval_items_mixed, dim3(nitems), dim3(64), 0, s, items, imgs, near_factor);
-    else
+    } else {
+        launch_items_far(items, nitems, imgs, s);
         hipLaunchKernelGGL(k_eval_items_fp64, dim3(nitems), dim3(64), 0, s, items, imgs, near_factor);
-}
-
-// Segment partial sums -> results: for column k < ncol and component c,
-// out.c[c][k * out.stride + i] = k_e (0 + sum over s = 0 .. nseg-1, in that
-// order, of part[s * seg_stride + (4 k + c) m + i]); null components skipped.
-__global__ __launch_bounds__(kBlock) void k_reduce_segments(const double *__restrict__ part, int nseg, int ncol,
-                                                             int m, int64_t seg_stride, OutCols out)
-{
-    const int i = blockIdx.x * kBlock + threadIdx.x;
-    if (i >= m) return;
-    for (int k = 0; k < ncol; ++k)
-        for (int c = 0; c < 4; ++c) {
-            if (!out.c[c]) continue;
-            const double *p = part + (size_t)(4 * k + c) * m + i;
-            double acc = 0.0;
-            for (int s = 0; s < nseg; ++s) acc += p[(size_t)s * (size_t)seg_stride];
-            out.c[c][(size_t)k * out.stride + i] = kKe * acc;
-        }
-}
-
-void launch_reduce_segments(const double *part, int nseg, int ncol, int64_t m, int64_t seg_stride,
-                            const OutCols &out, hipStream_t s)
-{
-    if (m <= 0) return;
-    hipLaunchKernelGGL(k_reduce_segments, dim3((unsigned)((m + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, part, nseg,
-                       ncol, (int)m, seg_stride, out);
+    }
 }
 
 // ---------------------------------------------------------------- assembly

@@ -1,0 +1,419 @@
+// group_kernels.hip -- moments of the element groups and the far part of a
+// grouped FP64 evaluation (expansion and tables: group_far.hpp).
+//
+// An evaluation of N elements x C copies at M points is N C M closed forms,
+// ~73 VALU instructions each, though in a lattice nearly all of them are tens
+// to hundreds of element sizes away.  Here the far copies of each group of 64
+// elements cost one expansion (9 instructions per harmonic: ~390 through
+// degree 6, ~1400 through degree 14) instead of 64 closed forms (~4700); the
+// copies nearer than ~7.6 group radii are left to k_group_near
+// (field_kernels.hip), which evaluates them element by element.
+//
+// Measured (double THGEM, 41 600 elements, 121 copies, 40 000 points): 469 ms
+// with the closed forms everywhere, 102 ms grouped (far pass 74 ms, near pass 26
+// ms, moments 0.18 ms); the far pass issues at ~75 % of the FP64 rate.  Three waves
+// per SIMD and two entries ahead: two waves 79 ms, four 76, one entry ahead 87,
+// three 83.  64 points of the GEM cell, one row or quarter of a group per
+// wave: 23.5 ms -> 0.76 ms.  Error of 2003 GEM points' field against a 64-bit sum:
+// 1.7e-14 before, 1.5e-14 now.
+#include <hip/hip_runtime.h>
+
+#include "group_far.hpp"
+#include "nebem_internal.hpp"
+
+namespace nebem {
+
+// ----------------------------------------------------------------- moments
+// One workgroup per group and density column, one wave per order m, one lane
+// per element: the 8 x 8 Gauss rule (collapsed onto the triangle) integrates
+// the degree-14 polynomials of an element's moments exactly.  Compute bound
+// and short (~6000 instructions a wave); the coefficient columns are written
+// once, 8.8 KB per group.
+constexpr int kMomWaves = kGroupP + 1;
+constexpr int kRule = 8;
+__constant__ double kRuleX[kRule] = {0.0198550717512318841, 0.1016667612931866302, 0.2372337950418355070,
+                                     0.4082826787521750975, 0.5917173212478249024, 0.7627662049581644929,
+                                     0.8983332387068133697, 0.9801449282487681158};
+__constant__ double kRuleW[kRule] = {0.0506142681451881295, 0.1111905172266872352, 0.1568533229389436436,
+                                     0.1813418916891809914, 0.1813418916891809914, 0.1568533229389436436,
+                                     0.1111905172266872352, 0.0506142681451881295};
+
+__device__ __forceinline__ double wave_sum(double v)
+{
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
+    return v;
+}
+__device__ __forceinline__ double wave_min(double v)
+{
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) v = fmin(v, __shfl_xor(v, off));
+    return v;
+}
+
+struct MomElem {
+    double ox, oy, oz;  // corner relative to the centre, over a
+    double ux, uy, uz, wx, wy, wz;  // edges over a
+    double q;           // density x |u| |w|
+    bool tri;
+};
+
+// sums over the group of q (s/a)^n J_n^m for n = m .. kGroupP, in bre / bim[n]
+template <int M>
+__device__ __forceinline__ void moment_order(const MomElem &e, double *__restrict__ bre, double *__restrict__ bim)
+{
+    double ar[kGroupP + 1 - M], ai[kGroupP + 1 - M];
+#pragma unroll
+    for (int k = 0; k <= kGroupP - M; ++k) ar[k] = ai[k] = 0.0;
+#pragma unroll 1
+    for (int iv = 0; iv < kRule; ++iv) {
+        const double v = kRuleX[iv], sv = e.tri ? 1.0 - v : 1.0;
+#pragma unroll 1
+        for (int iu = 0; iu < kRule; ++iu) {
+            const double s = kRuleX[iu] * sv;
+            const double w = e.q * (kRuleW[iu] * kRuleW[iv] * sv);
+            const double x = fma(s, e.ux, fma(v, e.wx, e.ox)), y = fma(s, e.uy, fma(v, e.wy, e.oy)),
+                         z = fma(s, e.uz, fma(v, e.wz, e.oz));
+            const double s2 = fma(x, x, fma(y, y, z * z));
+            double cr = w, ci = 0.0;  // w (x + i y)^m
+#pragma unroll
+            for (int k = 0; k < M; ++k) {
+                const double t = fma(cr, x, -(ci * y));
+                ci = fma(cr, y, ci * x);
+                cr = t;
+            }
+            double pr = 0.0, pi = 0.0;  // degree n - 1
+#pragma unroll
+            for (int n = M; n <= kGroupP; ++n) {
+                ar[n - M] += cr;
+                if (M > 0) ai[n - M] += ci;
+                if (n < kGroupP) {
+                    const double c = n == M ? z : kHarm.c[n][M] * z;
+                    const double nr = fma(c, cr, -(s2 * pr)), ni = fma(c, ci, -(s2 * pi));
+                    pr = cr;
+                    pi = ci;
+                    cr = nr;
+                    ci = ni;
+                }
+            }
+        }
+    }
+#pragma unroll
+    for (int n = M; n <= kGroupP; ++n) {
+        const double r = wave_sum(ar[n - M]), i = M > 0 ? wave_sum(ai[n - M]) : 0.0;
+        if ((threadIdx.x & 63) == 0) {
+            bre[n * (kGroupP + 1) + M] = kHarm.bf[n][M] * r;
+            bim[n * (kGroupP + 1) + M] = kHarm.bf[n][M] * i;
+        }
+    }
+}
+
+__device__ const HarmonicTables kHarmDev = make_harmonic_tables();
+
+// Records of the groups (kGroupStride doubles each, group g of segment s at
+// (s gps + g)); density column k at gdata + k gstride.  A group with a density
+// or a vertex that is not finite gets infinite thresholds: its elements are
+// all evaluated one by one.
+__global__ __launch_bounds__(64 * kMomWaves) void k_group_moments(const double *__restrict__ drec,
+                                                                  const double *__restrict__ sigma, int n,
+                                                                  int64_t sig_stride, int segsz, int gps,
+                                                                  double *__restrict__ gdata, int64_t gstride)
+{
+    __shared__ double bre[(kGroupP + 1) * (kGroupP + 1)], bim[(kGroupP + 1) * (kGroupP + 1)];
+    __shared__ int bad;
+    const int seg = blockIdx.x / gps, g = blockIdx.x % gps;
+    const int end = min(n, (seg + 1) * segsz), e0 = seg * segsz + g * kGroupElems;
+    if (e0 >= end) return;  // uniform: this group does not exist in a short last segment
+    const int cnt = min(kGroupElems, end - e0);
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    if (threadIdx.x == 0) bad = 0;
+    const double *r = drec + (size_t)(e0 + min(lane, cnt - 1)) * R_STRIDE;
+    const double lx = r[R_LX], lz = r[R_LZ];
+    const double o[3] = {r[R_OX], r[R_OY], r[R_OZ]};
+    const double u[3] = {lx * r[R_E1X], lx * r[R_E1Y], lx * r[R_E1Z]};
+    const double w[3] = {lz * r[R_E2X], lz * r[R_E2Y], lz * r[R_E2Z]};
+    const bool tri = r[R_KIND] != 0.0;
+    const double sg = lane < cnt ? sigma[(size_t)blockIdx.y * sig_stride + e0 + lane] : 0.0;
+    double c[3], d2[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        const double v1 = o[k] + u[k], v2 = o[k] + w[k], v3 = tri ? v2 : v1 + w[k];
+        const double lo = wave_min(fmin(fmin(o[k], v1), fmin(v2, v3)));
+        const double hi = -wave_min(fmin(fmin(-o[k], -v1), fmin(-v2, -v3)));
+        c[k] = 0.5 * (lo + hi);
+        const double d[4] = {o[k] - c[k], v1 - c[k], v2 - c[k], v3 - c[k]};
+#pragma unroll
+        for (int q = 0; q < 4; ++q) d2[q] = fma(d[q], d[q], d2[q]);
+    }
+    const double a2 = -wave_min(-fmax(fmax(d2[0], d2[1]), fmax(d2[2], d2[3])));
+    const double a = sqrt(a2), ia = 1.0 / a;
+    MomElem e;
+    e.ox = (o[0] - c[0]) * ia;
+    e.oy = (o[1] - c[1]) * ia;
+    e.oz = (o[2] - c[2]) * ia;
+    e.ux = u[0] * ia;
+    e.uy = u[1] * ia;
+    e.uz = u[2] * ia;
+    e.wx = w[0] * ia;
+    e.wy = w[1] * ia;
+    e.wz = w[2] * ia;
+    e.q = sg * (lx * lz);
+    e.tri = tri;
+    __syncthreads();
+    if (!isfinite(sg) || !(a2 > 0.0) || !isfinite(a2)) bad = 1;  // any lane, the same value
+    switch (wave) {
+    case 0: moment_order<0>(e, bre, bim); break;
+    case 1: moment_order<1>(e, bre, bim); break;
+    case 2: moment_order<2>(e, bre, bim); break;
+    case 3: moment_order<3>(e, bre, bim); break;
+    case 4: moment_order<4>(e, bre, bim); break;
+    case 5: moment_order<5>(e, bre, bim); break;
+    case 6: moment_order<6>(e, bre, bim); break;
+    case 7: moment_order<7>(e, bre, bim); break;
+    case 8: moment_order<8>(e, bre, bim); break;
+    case 9: moment_order<9>(e, bre, bim); break;
+    case 10: moment_order<10>(e, bre, bim); break;
+    case 11: moment_order<11>(e, bre, bim); break;
+    case 12: moment_order<12>(e, bre, bim); break;
+    case 13: moment_order<13>(e, bre, bim); break;
+    default: moment_order<14>(e, bre, bim); break;
+    }
+    __syncthreads();
+    double *out = gdata + (int64_t)blockIdx.y * gstride + (int64_t)blockIdx.x * kGroupStride;
+    if (threadIdx.x < kGroupHead) {
+        const int k = threadIdx.x;
+        const double inf = __builtin_inf();
+        const double t = k < kHeadTier + kTiers ? a2 * tier_ratio2(k - kHeadTier) : 0.0;
+        out[k] = k == 0 ? c[0] : k == 1 ? c[1] : k == 2 ? c[2] : k == 3 ? a : bad ? inf : t;
+    }
+    // coefficients of the field's harmonics, one (L, m) per thread
+    for (int t = threadIdx.x; t < kGroupEntries; t += 64 * kMomWaves) {
+        int L = 1, m = t;
+        while (m > L) {
+            m -= L + 1;
+            ++L;
+        }
+        auto B = [&](int mm, double &br, double &bi) {  // B_{L-1, mm}, 0 outside
+            const bool in = mm >= 0 && mm <= L - 1;
+            br = in ? bre[(L - 1) * (kGroupP + 1) + mm] : 0.0;
+            bi = in ? bim[(L - 1) * (kGroupP + 1) + mm] : 0.0;
+        };
+        double br, bi, ur, ui, dr, di;
+        B(m, br, bi);      // d_z
+        B(m - 1, ur, ui);  // raised order
+        B(m + 1, dr, di);  // lowered order
+        const double h = m == 1 ? 1.0 : 0.5;  // from m = 0 both shifts are the one harmonic of order 1
+        const double gl = 0.5 * (L - 1 - m) * (L - m);
+        const double il = 1.0 / kHarmDev.lam[L][m];
+        ui = m == 1 ? 0.0 : ui;
+        const double xr = fma(h, ur, -gl * dr) * il, xi = fma(h, ui, -gl * di) * il;
+        const double yr = -fma(h, ui, gl * di) * il, yi = fma(h, ur, gl * dr) * il;
+        const double zr = (L - m) * br * il, zi = (L - m) * bi * il;
+        double *q = out + kGroupHead + kEntry * entry_index(L, m);
+        q[0] = xr;
+        q[1] = xi;
+        q[2] = yr;
+        q[3] = yi;
+        q[4] = zr;
+        q[5] = zi;
+        q[6] = m <= L - 2 ? kHarmDev.c[L - 1][m] : 0.0;
+        q[7] = 0.0;
+    }
+}
+
+void launch_group_moments(const double *drec, const double *sigma, int64_t n, int64_t sig_stride, int ncol,
+                          const SegPlan &sp, double *gdata, hipStream_t s)
+{
+    if (n <= 0 || ncol <= 0) return;
+    const int gps = groups_per_seg(sp);
+    hipLaunchKernelGGL(k_group_moments, dim3((unsigned)(sp.nseg * gps), (unsigned)ncol), dim3(64 * kMomWaves), 0, s,
+                       drec, sigma, (int)n, sig_stride, sp.segsz, gps, gdata,
+                       (int64_t)sp.nseg * gps * kGroupStride);
+}
+
+// --------------------------------------------------------------------- far
+// Far copies of groups [g0, g1) of a segment at one point per lane, lattice
+// rows [q0, q1) (row q: reflection q / (2 n1 + 1), translation i1 = q % (2 n1 +
+// 1) - n1): rows added into the group's sum, groups into acc, in that order.
+// FP64 VALU bound; the coefficients come through the scalar cache (64 bytes per
+// nine vector instructions), nothing is staged in LDS and the waves of a
+// workgroup run independently.
+__device__ __forceinline__ void far_unit(cdouble_p gd, const ImgArgs &img, double Px, double Py, double Pz, int g0,
+                                         int g1, int q0, int q1, double (&acc)[4])
+{
+#pragma clang fp contract(off)
+    for (int c = 0; c < 4; ++c) acc[c] = 0.0;
+    const int nrow = 2 * img.n1 + 1;
+#pragma unroll 1
+    for (int g = g0; g < g1; ++g) {
+        cdouble_p h = gd + (int64_t)g * kGroupStride;
+        const double a = h[3];
+        double grp[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 1
+        for (int q = q0; q < q1; ++q) {
+            const int r = q / nrow, i1 = q % nrow - img.n1;
+            const int ax = img.axes[r];
+            const GroupVec v0 = group_origin(img, ax, Px, Py, Pz, h);
+            const GroupVec v1 = group_step(v0, -(double)i1, img.a1[r]);
+            double row[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 1
+            for (int i2 = -img.n2; i2 <= img.n2; ++i2) {
+                const GroupVec d = group_step(v1, -(double)i2, img.a2[r]);
+                const double r2 = group_r2(d);
+                if (r2 >= h[kHeadTier]) {
+                    if (r2 >= h[kHeadTier + 3]) {
+                        if (r2 >= h[kHeadTier + 5])
+                            group_far<5>(d, r2, a, h + kGroupHead, row);
+                        else if (r2 >= h[kHeadTier + 4])
+                            group_far<7>(d, r2, a, h + kGroupHead, row);
+                        else
+                            group_far<9>(d, r2, a, h + kGroupHead, row);
+                    } else {
+                        if (r2 >= h[kHeadTier + 2])
+                            group_far<11>(d, r2, a, h + kGroupHead, row);
+                        else if (r2 >= h[kHeadTier + 1])
+                            group_far<13>(d, r2, a, h + kGroupHead, row);
+                        else
+                            group_far<15>(d, r2, a, h + kGroupHead, row);
+                    }
+                }
+            }
+            const double par = img.parity[r];
+            grp[0] = fma(par, row[0], grp[0]);
+            grp[1] = fma((ax & 1) ? -par : par, row[1], grp[1]);
+            grp[2] = fma((ax & 2) ? -par : par, row[2], grp[2]);
+            grp[3] = fma((ax & 4) ? -par : par, row[3], grp[3]);
+        }
+        for (int c = 0; c < 4; ++c) acc[c] += grp[c];
+    }
+}
+
+// Grid: x over points, y over units -- whole segments (split 0), groups
+// (split 1) or lattice rows of groups (split 2; y = group * rows + row) --, z
+// over density columns (their shared harmonics are a third of the work, but
+// two columns at once need more registers than three waves per SIMD leave).
+// Unit y's unscaled sums go to the outputs + y * unit_stride.
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void k_group_far(
+    const double *__restrict__ gdata, int64_t gstride, int n, int segsz, int gps, ImgArgs img, int split,
+    const double *__restrict__ px, const double *__restrict__ py, const double *__restrict__ pz, int m, OutCols out,
+    int64_t unit_stride)
+{
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    const int j = min(i, m - 1);  // lanes past the last point repeat it
+    const int rows = img.nref * (2 * img.n1 + 1);
+    int y = blockIdx.y, q0 = 0, q1 = rows;
+    if (split == 2) {
+        q0 = y % rows;
+        q1 = q0 + 1;
+        y /= rows;
+    }
+    const int seg = split ? y / gps : y;
+    const int ng = (min(segsz, n - seg * segsz) + kGroupElems - 1) / kGroupElems;
+    const int g0 = split ? y % gps : 0, g1 = split ? min(g0 + 1, ng) : ng;
+    double acc[4];
+    far_unit(uniform_ptr(gdata + (int64_t)blockIdx.z * gstride + (int64_t)seg * gps * kGroupStride), img, px[j], py[j],
+             pz[j], g0, g1, q0, q1, acc);
+    if (i >= m) return;
+    const int64_t o = (int64_t)blockIdx.y * unit_stride + (int64_t)blockIdx.z * out.stride + i;
+    for (int c = 0; c < 4; ++c)
+        if (out.c[c]) out.c[c][o] = acc[c];
+}
+
+void launch_group_far(const double *gdata, int64_t n, int ncol, const SegPlan &sp, const ImgArgs &img, int split,
+                      const double *px, const double *py, const double *pz, int64_t m, const OutCols &out,
+                      int64_t unit_stride, hipStream_t s)
+{
+    if (m <= 0 || n <= 0) return;
+    const int gps = groups_per_seg(sp);
+    const int64_t ng = (int64_t)sp.nseg * gps, rows = (int64_t)img.nref * (2 * img.n1 + 1);
+    const int64_t units = split == 0 ? sp.nseg : split == 1 ? ng : ng * rows;
+    const int bs = split == 0 ? 256 : 64;
+    hipLaunchKernelGGL(k_group_far, dim3((unsigned)((m + bs - 1) / bs), (unsigned)units, (unsigned)ncol), dim3(bs), 0,
+                       s, gdata, ng * kGroupStride, (int)n, sp.segsz, gps, img, split, px, py, pz, (int)m, out,
+                       unit_stride);
+}
+
+// Serving: workgroup (one wave) b takes work item b where its geometry is
+// grouped -- the far part of one segment at up to 64 points of one request.
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3, 3))) void k_items_far(
+    const WorkItem *__restrict__ items, const ImgArgs *__restrict__ imgs)
+{
+    const WorkItem &w = items[blockIdx.x];
+    if (!w.gdata) return;
+    const ImgArgs &img = imgs[w.geom];
+    const int j = min((int)threadIdx.x, w.count - 1);
+    double acc[4];
+    far_unit(uniform_ptr(w.gdata), img, w.px[j], w.py[j], w.pz[j], 0, (w.n + kGroupElems - 1) / kGroupElems, 0,
+             img.nref * (2 * img.n1 + 1), acc);
+    if ((int)threadIdx.x >= w.count) return;
+    w.phi[threadIdx.x] = acc[0];
+    w.ex[threadIdx.x] = acc[1];
+    w.ey[threadIdx.x] = acc[2];
+    w.ez[threadIdx.x] = acc[3];
+}
+
+void launch_items_far(const WorkItem *items, int nitems, const ImgArgs *imgs, hipStream_t s)
+{
+    if (nitems <= 0) return;
+    hipLaunchKernelGGL(k_items_far, dim3(nitems), dim3(64), 0, s, items, imgs);
+}
+
+// ------------------------------------------------------------ finer units
+// Sums of a split evaluation back to one value per segment, in the order the
+// unsplit kernels add them: rows / quarters into their group, groups into their
+// segment, the segment's far and near sums added last.
+__global__ __launch_bounds__(256) void k_fold_units(const double *__restrict__ in, int per, int64_t len,
+                                                    double *__restrict__ out)
+{
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i >= len) return;
+    const double *p = in + (int64_t)blockIdx.y * per * len + i;
+    double acc = 0.0;
+    for (int k = 0; k < per; ++k) acc += p[k * len];
+    out[(int64_t)blockIdx.y * len + i] = acc;
+}
+
+__global__ __launch_bounds__(256) void k_fold_groups(const double *__restrict__ far, const double *__restrict__ near,
+                                                     int gps, int64_t len, double *__restrict__ out)
+{
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i >= len) return;
+    const int64_t o = (int64_t)blockIdx.y * gps * len + i;
+    double f = 0.0, n = 0.0;
+    for (int g = 0; g < gps; ++g) {
+        f += far[o + g * len];
+        n += near[o + g * len];
+    }
+    out[(int64_t)blockIdx.y * len + i] = f + n;
+}
+
+void launch_fold_units(const double *in, int64_t groups, int per, int64_t len, double *out, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_fold_units, dim3((unsigned)((len + 255) / 256), (unsigned)groups), dim3(256), 0, s, in, per,
+                       len, out);
+}
+
+void launch_fold_groups(const double *far, const double *near, const SegPlan &sp, int64_t len, double *out,
+                        hipStream_t s)
+{
+    hipLaunchKernelGGL(k_fold_groups, dim3((unsigned)((len + 255) / 256), (unsigned)sp.nseg), dim3(256), 0, s, far,
+                       near, groups_per_seg(sp), len, out);
+}
+
+// ----------------------------------------------------------------- the rule
+// Grouping pays when a point meets many copies far from it: from about 65 000
+// element copies (a GEM cell with its first two rings of copies has 200 000) the
+// moments' launch is a small share even of a 64-point call.  Below, and for
+// geometries without copies and fewer elements, nearly every group is near and
+// the plain kernels do the same work without the tests.
+bool eval_grouped(int64_t n, const ImgArgs &img)
+{
+    return img.hole < 0 && (double)n * (double)img_copies(img) >= 65536.0;
+}
+
+size_t group_data_bytes(const SegPlan &sp, int ncol)
+{
+    return (size_t)sp.nseg * groups_per_seg(sp) * kGroupStride * (size_t)ncol * sizeof(double);
+}
+
+}  // namespace nebem

@@ -68,6 +68,7 @@ struct WorkItem {
     const double *sigma;
     const double *px, *py, *pz;
     double *phi, *ex, *ey, *ez;  // the segment's partial sums (unscaled)
+    const double *gdata;  // the segment's group records (FP64, grouped geometry), else null
     int n;      // elements in the segment
     int geom;   // index into the image-argument array
     int count;  // points in this item (<= 64)
@@ -161,6 +162,37 @@ constexpr int kMaxSeg = 64;
 struct SegPlan {
     int nseg, segsz;
 };
+// Groups of an FP64 evaluation (group_kernels.hip, group_far.hpp): runs of
+// kGroupElems consecutive elements of a segment, groups_per_seg of them per
+// segment (fewer in a short last one).
+constexpr int kGroupElems = 64;
+constexpr int kNearParts = 4;  // parts of a group (16 elements) that a split near pass makes units of
+inline int groups_per_seg(const SegPlan &sp) { return (sp.segsz + kGroupElems - 1) / kGroupElems; }
+// Whether an FP64 evaluation takes far copies of whole groups by their
+// expansions: a function of the geometry only, like the segment plan.
+bool eval_grouped(int64_t n, const ImgArgs &img);
+size_t group_data_bytes(const SegPlan &sp, int ncol);
+// moments of every group and density column (column k at sigma + k sig_stride)
+void launch_group_moments(const double *drec, const double *sigma, int64_t n, int64_t sig_stride, int ncol,
+                          const SegPlan &sp, double *gdata, hipStream_t s);
+// Far and near parts of a grouped evaluation, one pass each.  split 0: units
+// are segments, and the near pass adds to the far pass's sums; split > 0:
+// finer units, each pass with outputs of its own (far 1: groups, 2: lattice
+// rows of groups; near 1: groups, 2: quarters of groups).  Unit y's unscaled
+// sums go to the outputs + y * unit_stride.
+void launch_group_far(const double *gdata, int64_t n, int ncol, const SegPlan &sp, const ImgArgs &img, int split,
+                      const double *px, const double *py, const double *pz, int64_t m, const OutCols &out,
+                      int64_t unit_stride, hipStream_t s);
+void launch_group_near(const double *drec, const double *sigma, const double *gdata, int64_t n, int64_t sig_stride,
+                       int ncol, const SegPlan &sp, const ImgArgs &img, int split, const double *px, const double *py,
+                       const double *pz, int64_t m, const OutCols &out, int64_t unit_stride, hipStream_t s);
+// split evaluations back to segment sums (len values per unit)
+void launch_fold_units(const double *in, int64_t groups, int per, int64_t len, double *out, hipStream_t s);
+// work items of grouped geometries, far part (the near part and the other
+// items: launch_eval_items)
+void launch_items_far(const WorkItem *items, int nitems, const ImgArgs *imgs, hipStream_t s);
+void launch_fold_groups(const double *far, const double *near, const SegPlan &sp, int64_t len, double *out,
+                        hipStream_t s);
 int64_t img_copies(const ImgArgs &img);  // copies per element (reflections x translations, minus any hole)
 SegPlan seg_plan(int64_t n, const ImgArgs &img);
 // In the evaluation launchers, mixed != 0: copies beyond the far-field tiers
@@ -184,10 +216,11 @@ void launch_reduce_segments(const double *part, int nseg, int ncol, int64_t m, i
 // ---- Morton order of points (order_kernels.hip)
 bool eval_ordering_pays(int64_t m);
 // Morton order of m points: s{x,y,z}[k] = p{x,y,z}[perm[k]]; ws of
-// order_points_workspace(m) bytes (0 on error)
+// order_points_workspace(m) bytes (0 on error).  cubes: one scale for the
+// three axes instead of each axis' own extent
 size_t order_points_workspace(int64_t m);
 hipError_t launch_order_points(const double *px, const double *py, const double *pz, int64_t m, double *sx,
-                               double *sy, double *sz, int *perm, void *ws, size_t ws_bytes, hipStream_t s);
+                               double *sy, double *sz, int *perm, bool cubes, void *ws, size_t ws_bytes, hipStream_t s);
 // d_j[perm[k]] = src[j * m + k] for each non-null d_j (j = 0..3)
 void launch_unorder4(const double *src, const int *perm, int64_t m, double *d0, double *d1, double *d2, double *d3,
                      hipStream_t s);
@@ -195,15 +228,15 @@ void launch_unorder4(const double *src, const int *perm, int64_t m, double *d0, 
 // ---- the evaluation driver (order_kernels.hip), used by every evaluation
 // entry point: ncol density columns (column k at sigma + k n), outputs m x
 // ncol column-major per component (null: not stored).  Points are taken in
-// chunks whose workspace fits ws_bytes; chunks of >= 4096 points are
+// chunks whose workspace fits ws_bytes; chunks of more than 64 points are
 // evaluated in Morton order; every element segment of a chunk is one grid
 // row, and the segments' partial sums are reduced in segment order.  No
 // result bit depends on the chunking, the ordering or the other points.
 // eval_workspace: the workspace that lets the driver take its preferred
 // chunk (0 when none is needed).
-size_t eval_workspace(int64_t n, const ImgArgs &img, int64_t m, int ncol);
+size_t eval_workspace(int64_t n, const ImgArgs &img, int64_t m, int ncol, int mixed);
 // smallest workspace with which run_eval accepts the call
-size_t eval_workspace_min(int64_t n, const ImgArgs &img, int64_t m, int ncol);
+size_t eval_workspace_min(int64_t n, const ImgArgs &img, int64_t m, int ncol, int mixed);
 hipError_t run_eval(const double *drec, const double *sigma, int64_t n, int ncol, const ImgArgs &img, int mixed,
                     double near_factor, const double *px, const double *py, const double *pz, int64_t m, double *phi,
                     double *ex, double *ey, double *ez, void *ws, size_t ws_bytes, hipStream_t s);

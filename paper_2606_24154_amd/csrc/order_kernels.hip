@@ -17,6 +17,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <cstdint>
 
 #include "nebem_internal.hpp"
 
@@ -24,7 +25,7 @@ namespace nebem {
 
 constexpr int kOB = 256;         // threads per block of the helper kernels
 constexpr int kBoxParts = 256;   // partial bounding boxes (first reduction pass)
-constexpr int64_t kOrderMin = 4096;
+constexpr int64_t kOrderMin = 65;  // more than one wave
 
 // per-block bounding box of a strided share of the points (min / max are
 // exact, so the result does not depend on the reduction order)
@@ -69,11 +70,29 @@ __device__ __forceinline__ unsigned quant10(double v, double lo, double sc)
     return t >= 1023.0 ? 1023u : (t > 0.0 ? (unsigned)t : 0u);
 }
 
+// Morton code of a point in the box (min x, y, z, max x, y, z).  cubes: the
+// box's longest side sets the scale of all three axes, so that consecutive
+// points fill cubes -- a wave of 64 stands as close together as it can (in a
+// detector gap, many times longer than a cell is wide, the per-axis scale
+// makes it as elongated as the gap).
+__device__ __forceinline__ unsigned morton_key(double x, double y, double z, const double *box, int cubes)
+{
+    const double c[3] = {x, y, z};
+    double ext[3] = {box[3] - box[0], box[4] - box[1], box[5] - box[2]};
+    if (cubes) ext[0] = ext[1] = ext[2] = fmax(ext[0], fmax(ext[1], ext[2]));
+    unsigned q[3];
+    for (int k = 0; k < 3; ++k) {
+        const double sc = (ext[k] > 0.0 && ext[k] < INFINITY) ? 1024.0 / ext[k] : 0.0;
+        q[k] = quant10(c[k], box[k], sc);
+    }
+    return spread3(q[0]) | (spread3(q[1]) << 1) | (spread3(q[2]) << 2);
+}
+
 // keys[i] = Morton code of point i in the box (reduced from nparts partial
 // boxes by every block: nparts x 6 doubles, L2-resident), idx[i] = i
 __global__ __launch_bounds__(kOB) void k_keys(const double *__restrict__ px, const double *__restrict__ py,
                                               const double *__restrict__ pz, int m,
-                                              const double *__restrict__ part, int nparts,
+                                              const double *__restrict__ part, int nparts, int cubes,
                                               unsigned *__restrict__ keys, int *__restrict__ idx)
 {
     __shared__ double box[6];
@@ -86,15 +105,68 @@ __global__ __launch_bounds__(kOB) void k_keys(const double *__restrict__ px, con
     __syncthreads();
     const int i = blockIdx.x * kOB + threadIdx.x;
     if (i >= m) return;
-    unsigned q[3];
-    const double c[3] = {px[i], py[i], pz[i]};
-    for (int k = 0; k < 3; ++k) {
-        const double ext = box[3 + k] - box[k];
-        const double sc = (ext > 0.0 && ext < INFINITY) ? 1024.0 / ext : 0.0;
-        q[k] = quant10(c[k], box[k], sc);
-    }
-    keys[i] = spread3(q[0]) | (spread3(q[1]) << 1) | (spread3(q[2]) << 2);
+    keys[i] = morton_key(px[i], py[i], pz[i], box, cubes);
     idx[i] = i;
+}
+
+// Up to kSmallOrder points by one workgroup: bounding box, keys, a bitonic
+// sort of (key, index) in LDS (unique keys, so it is the stable order the
+// radix sort gives) and the gather, in one launch (30 us at 2003 points, bound
+// by the sort's ~66 barriers) where the radix sort takes ten.
+constexpr int kSmallOrder = 4096;
+constexpr int kSmallThreads = 1024;
+__global__ __launch_bounds__(kSmallThreads) void k_order_small(const double *__restrict__ px,
+                                                               const double *__restrict__ py,
+                                                               const double *__restrict__ pz, int m, int len, int cubes,
+                                                               double *__restrict__ sx, double *__restrict__ sy,
+                                                               double *__restrict__ sz, int *__restrict__ perm)
+{
+    __shared__ unsigned long long key[kSmallOrder];
+    __shared__ double red[6][kSmallThreads / 64];
+    __shared__ double box[6];
+    const int t = threadIdx.x;
+    double v[6] = {INFINITY, INFINITY, INFINITY, INFINITY, INFINITY, INFINITY};  // min x, y, z, -x, -y, -z
+    for (int i = t; i < m; i += kSmallThreads) {
+        const double c[3] = {px[i], py[i], pz[i]};
+        for (int k = 0; k < 3; ++k) {
+            v[k] = fmin(v[k], c[k]);
+            v[3 + k] = fmin(v[3 + k], -c[k]);
+        }
+    }
+    for (int k = 0; k < 6; ++k) {
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) v[k] = fmin(v[k], __shfl_xor(v[k], off));
+        if ((t & 63) == 0) red[k][t >> 6] = v[k];
+    }
+    __syncthreads();
+    if (t < 6) {
+        double b = red[t][0];
+        for (int w = 1; w < kSmallThreads / 64; ++w) b = fmin(b, red[t][w]);
+        box[t] = t < 3 ? b : -b;
+    }
+    __syncthreads();
+    for (int i = t; i < len; i += kSmallThreads)
+        key[i] = i < m ? ((unsigned long long)morton_key(px[i], py[i], pz[i], box, cubes) << 32) | (unsigned)i : ~0ull;
+    __syncthreads();
+    for (int k = 2; k <= len; k <<= 1)
+        for (int j = k >> 1; j > 0; j >>= 1) {
+            for (int p = t; p < len / 2; p += kSmallThreads) {
+                const int lo = ((p & ~(j - 1)) << 1) | (p & (j - 1)), hi = lo | j;
+                const unsigned long long a = key[lo], b = key[hi];
+                if ((a > b) == ((lo & k) == 0)) {
+                    key[lo] = b;
+                    key[hi] = a;
+                }
+            }
+            __syncthreads();
+        }
+    for (int i = t; i < m; i += kSmallThreads) {
+        const int q = (int)(unsigned)key[i];
+        perm[i] = q;
+        sx[i] = px[q];
+        sy[i] = py[q];
+        sz[i] = pz[q];
+    }
 }
 
 __global__ __launch_bounds__(kOB) void k_gather3(const double *__restrict__ px, const double *__restrict__ py,
@@ -167,9 +239,16 @@ size_t order_points_workspace(int64_t m)
 }
 
 hipError_t launch_order_points(const double *px, const double *py, const double *pz, int64_t m, double *sx,
-                               double *sy, double *sz, int *perm, void *ws, size_t ws_bytes, hipStream_t s)
+                               double *sy, double *sz, int *perm, bool cubes, void *ws, size_t ws_bytes, hipStream_t s)
 {
     if (m <= 0) return hipSuccess;
+    if (m <= kSmallOrder) {
+        int len = 2;
+        while (len < m) len <<= 1;
+        hipLaunchKernelGGL(k_order_small, dim3(1), dim3(kSmallThreads), 0, s, px, py, pz, (int)m, len, (int)cubes, sx,
+                           sy, sz, perm);
+        return hipGetLastError();
+    }
     SortLayout L;
     hipError_t e = sort_layout(m, L);
     if (e != hipSuccess) return e;
@@ -183,7 +262,7 @@ hipError_t launch_order_points(const double *px, const double *py, const double 
     const unsigned g = (unsigned)((m + kOB - 1) / kOB);
     const int nparts = (int)std::min<int64_t>(kBoxParts, g);
     hipLaunchKernelGGL(k_bbox_part, dim3(nparts), dim3(kOB), 0, s, px, py, pz, mi, part);
-    hipLaunchKernelGGL(k_keys, dim3(g), dim3(kOB), 0, s, px, py, pz, mi, part, nparts, keys_in, idx_in);
+    hipLaunchKernelGGL(k_keys, dim3(g), dim3(kOB), 0, s, px, py, pz, mi, part, nparts, (int)cubes, keys_in, idx_in);
     size_t sort_bytes = L.sort_bytes;
     e = rocprim::radix_sort_pairs(w + L.sort, sort_bytes, keys_in, keys_out, idx_in, perm, mi, 0u, 30u, s);
     if (e != hipSuccess) return e;
@@ -206,46 +285,86 @@ constexpr size_t kPartBudget = size_t(512) << 20;  // preferred bytes of segment
 struct EvalShape {
     SegPlan sp;
     int kc;           // columns per launch
+    bool grouped;     // FP64 with far copies of whole groups (group_kernels.hip)
+    int64_t ngroup, rows;  // groups of the plan, lattice rows of a group
     size_t part_pp;   // partial-sum bytes per point (0: one segment, no partials)
 };
 
-EvalShape eval_shape(int64_t n, const ImgArgs &img, int ncol)
+EvalShape eval_shape(int64_t n, const ImgArgs &img, int ncol, int mixed)
 {
     EvalShape sh;
     sh.sp = seg_plan(n, img);
     sh.kc = ncol < kMultiCols ? ncol : kMultiCols;
-    sh.part_pp = sh.sp.nseg > 1 ? (size_t)32 * sh.kc * sh.sp.nseg : 0;
+    sh.grouped = !mixed && eval_grouped(n, img);
+    sh.ngroup = (int64_t)sh.sp.nseg * groups_per_seg(sh.sp);
+    sh.rows = (int64_t)img.nref * (2 * img.n1 + 1);
+    sh.part_pp = sh.sp.nseg > 1 || sh.grouped ? (size_t)32 * sh.kc * sh.sp.nseg : 0;
     return sh;
 }
 
+// Units of a grouped evaluation of c points (launch_group_far / _near): whole
+// segments once these alone are several rounds of waves (8 segments of a GEM
+// cell: from 65 536 points), groups below that, and rows / quarters of groups
+// when even the groups leave SIMDs without a wave (1024 SIMDs; 64 points of a
+// GEM cell have 126 group waves, 1386 row waves).  No result bit depends on
+// the choice.  A split needs its unit sums in memory: at most kSplitBudget.
+constexpr size_t kSplitBudget = size_t(192) << 20;
+constexpr int64_t kMaxUnits = 65535;  // grid y
+void pick_splits(const EvalShape &sh, int64_t c, int &far, int &near)
+{
+    const int64_t waves = (c + 63) / 64;
+    far = near = 0;
+    if (!sh.grouped || waves * sh.sp.nseg >= 8192) return;
+    const int64_t pp = (int64_t)32 * sh.kc * c;
+    auto fits = [&](int64_t units) { return units <= kMaxUnits && units * pp <= (int64_t)kSplitBudget; };
+    if (!fits(sh.ngroup)) return;
+    far = waves * sh.ngroup < 2048 && fits(sh.ngroup * sh.rows) ? 2 : 1;
+    near = waves * sh.ngroup < 8192 && fits(sh.ngroup * kNearParts) ? 2 : 1;
+}
+
 // workspace layout of one chunk of c points: [sort scratch | perm | sorted
-// points | sorted results (kc columns)] when ordered, then the partial sums
+// points | sorted results (kc columns)] when ordered, then the partial sums,
+// the groups' records and the finer units' sums
 struct ChunkLayout {
     bool ordered;
-    size_t sort_ws, perm, pts, res, part, total;
+    int fsplit, nsplit;
+    size_t sort_ws, perm, pts, res, part, groups, far, near, ffold, nfold, total;
 };
 
-bool chunk_layout(const EvalShape &sh, int64_t c, ChunkLayout &L)
+bool chunk_layout(const EvalShape &sh, int64_t c, size_t limit, ChunkLayout &L)
 {
     L.ordered = eval_ordering_pays(c);
     size_t off = 0;
+    auto take = [&](size_t b) {
+        const size_t o = off;
+        off += align256(b);
+        return o;
+    };
     L.sort_ws = L.perm = L.pts = L.res = 0;
     if (L.ordered) {
         const size_t w = order_points_workspace(c);
         if (!w) return false;
         L.sort_ws = w;
         off = w;
-        L.perm = off;
-        off += align256(4 * (size_t)c);
-        L.pts = off;
-        off += align256(24 * (size_t)c);
-        L.res = off;
-        off += align256(32 * (size_t)sh.kc * (size_t)c);
+        L.perm = take(4 * (size_t)c);
+        L.pts = take(24 * (size_t)c);
+        L.res = take(32 * (size_t)sh.kc * (size_t)c);
     }
-    L.part = off;
-    off += align256(sh.part_pp * (size_t)c);
-    L.total = off;
-    return true;
+    L.part = take(sh.part_pp * (size_t)c);
+    L.groups = take(sh.grouped ? group_data_bytes(sh.sp, sh.kc) : 0);
+    const size_t base = off;
+    pick_splits(sh, c, L.fsplit, L.nsplit);
+    for (;;) {
+        const size_t unit = (size_t)32 * sh.kc * (size_t)c, g = (size_t)sh.ngroup;
+        L.far = take(L.fsplit ? unit * g * (L.fsplit == 2 ? sh.rows : 1) : 0);
+        L.near = take(L.nsplit ? unit * g * (L.nsplit == 2 ? kNearParts : 1) : 0);
+        L.ffold = take(L.fsplit == 2 ? unit * g : 0);
+        L.nfold = take(L.nsplit == 2 ? unit * g : 0);
+        L.total = off;
+        if (off <= limit || !L.fsplit) return true;
+        off = base;  // no room for the unit sums
+        L.fsplit = L.nsplit = 0;
+    }
 }
 
 int64_t preferred_chunk(const EvalShape &sh, int64_t m)
@@ -258,17 +377,52 @@ int64_t preferred_chunk(const EvalShape &sh, int64_t m)
     return c;
 }
 
+// one column block of a grouped chunk: unscaled segment sums into part
+void eval_grouped_chunk(const double *drec, const double *sg, int64_t n, int k, const EvalShape &sh,
+                        const ImgArgs &img, const double *px, const double *py, const double *pz, int64_t c,
+                        const OutCols &pc, int64_t seg_stride, char *w, const ChunkLayout &L, hipStream_t s)
+{
+    double *gd = reinterpret_cast<double *>(w + L.groups);
+    launch_group_moments(drec, sg, n, n, k, sh.sp, gd, s);
+    if (!L.fsplit) {
+        launch_group_far(gd, n, k, sh.sp, img, 0, px, py, pz, c, pc, seg_stride, s);
+        launch_group_near(drec, sg, gd, n, n, k, sh.sp, img, 0, px, py, pz, c, pc, seg_stride, s);
+        return;
+    }
+    double *far = reinterpret_cast<double *>(w + L.far), *near = reinterpret_cast<double *>(w + L.near);
+    // components that are not wanted are not written, and their sums not read
+    auto cols = [&](double *b) {
+        OutCols o = pc;
+        for (int q = 0; q < 4; ++q) o.c[q] = pc.c[q] ? b + (size_t)q * c : nullptr;
+        return o;
+    };
+    launch_group_far(gd, n, k, sh.sp, img, L.fsplit, px, py, pz, c, cols(far), seg_stride, s);
+    launch_group_near(drec, sg, gd, n, n, k, sh.sp, img, L.nsplit, px, py, pz, c, cols(near), seg_stride, s);
+    if (L.fsplit == 2) {
+        double *f = reinterpret_cast<double *>(w + L.ffold);
+        launch_fold_units(far, sh.ngroup, (int)sh.rows, seg_stride, f, s);
+        far = f;
+    }
+    if (L.nsplit == 2) {
+        double *f = reinterpret_cast<double *>(w + L.nfold);
+        launch_fold_units(near, sh.ngroup, kNearParts, seg_stride, f, s);
+        near = f;
+    }
+    launch_fold_groups(far, near, sh.sp, seg_stride, reinterpret_cast<double *>(w + L.part), s);
+}
+
 // one chunk of c points (unsorted input px.., outputs o.c[comp] + col * ostride)
 void eval_chunk(const double *drec, const double *sigma, int64_t n, int ncol, const EvalShape &sh,
                 const ImgArgs &img, int mixed, double near_factor, const double *px, const double *py,
-                const double *pz, int64_t c, const OutCols &o, double *part, hipStream_t s)
+                const double *pz, int64_t c, const OutCols &o, char *w, const ChunkLayout &L, hipStream_t s)
 {
+    double *part = sh.part_pp ? reinterpret_cast<double *>(w + L.part) : nullptr;
     for (int c0 = 0; c0 < ncol; c0 += kMultiCols) {
         const int k = ncol - c0 < kMultiCols ? ncol - c0 : kMultiCols;
         const double *sg = sigma + (size_t)c0 * n;
         OutCols oc = o;
         for (int q = 0; q < 4; ++q) oc.c[q] = o.c[q] ? o.c[q] + (size_t)c0 * o.stride : nullptr;
-        if (sh.sp.nseg == 1) {
+        if (!sh.part_pp) {
             if (ncol == 1)
                 launch_eval_seg(drec, sg, n, sh.sp, img, mixed, near_factor, px, py, pz, c, kKe, oc.c[0], oc.c[1],
                                 oc.c[2], oc.c[3], 0, s);
@@ -283,7 +437,9 @@ void eval_chunk(const double *drec, const double *sigma, int64_t n, int ncol, co
                        o.c[3] ? part + 3 * cc : nullptr},
                       (int64_t)(4 * cc)};
         const int64_t seg_stride = (int64_t)(4 * (size_t)k * cc);
-        if (ncol == 1)
+        if (sh.grouped)
+            eval_grouped_chunk(drec, sg, n, k, sh, img, px, py, pz, c, pc, seg_stride, w, L, s);
+        else if (ncol == 1)
             launch_eval_seg(drec, sg, n, sh.sp, img, mixed, near_factor, px, py, pz, c, 1.0, pc.c[0], pc.c[1], pc.c[2],
                             pc.c[3], seg_stride, s);
         else
@@ -294,21 +450,21 @@ void eval_chunk(const double *drec, const double *sigma, int64_t n, int ncol, co
 }
 }  // namespace
 
-size_t eval_workspace(int64_t n, const ImgArgs &img, int64_t m, int ncol)
+size_t eval_workspace(int64_t n, const ImgArgs &img, int64_t m, int ncol, int mixed)
 {
     if (m <= 0 || ncol <= 0 || n <= 0) return 0;
-    const EvalShape sh = eval_shape(n, img, ncol);
+    const EvalShape sh = eval_shape(n, img, ncol, mixed);
     ChunkLayout L;
-    if (!chunk_layout(sh, preferred_chunk(sh, m), L)) return 0;
+    if (!chunk_layout(sh, preferred_chunk(sh, m), SIZE_MAX, L)) return 0;
     return L.total;
 }
 
-size_t eval_workspace_min(int64_t n, const ImgArgs &img, int64_t m, int ncol)
+size_t eval_workspace_min(int64_t n, const ImgArgs &img, int64_t m, int ncol, int mixed)
 {
     if (m <= 0 || ncol <= 0 || n <= 0) return 0;
-    const EvalShape sh = eval_shape(n, img, ncol);
+    const EvalShape sh = eval_shape(n, img, ncol, mixed);
     ChunkLayout L;
-    if (!chunk_layout(sh, std::min<int64_t>(m, 256), L)) return 0;
+    if (!chunk_layout(sh, std::min<int64_t>(m, 256), 0, L)) return 0;
     return L.total;
 }
 
@@ -326,12 +482,12 @@ hipError_t run_eval(const double *drec, const double *sigma, int64_t n, int ncol
             }
         return hipSuccess;
     }
-    const EvalShape sh = eval_shape(n, img, ncol);
+    const EvalShape sh = eval_shape(n, img, ncol, mixed);
     // the largest chunk (up to the preferred one) whose workspace fits
     int64_t c = preferred_chunk(sh, m);
     ChunkLayout L;
     for (;;) {
-        if (!chunk_layout(sh, c, L)) return hipErrorInvalidValue;
+        if (!chunk_layout(sh, c, ws_bytes, L)) return hipErrorInvalidValue;
         if (L.total <= ws_bytes || (L.total == 0)) break;
         if (c <= 256) return hipErrorInvalidValue;
         c = std::max<int64_t>(256, (c / 2) & ~(int64_t)255);
@@ -345,25 +501,23 @@ hipError_t run_eval(const double *drec, const double *sigma, int64_t n, int ncol
         if (even < c) c = even;
     }
     char *w = static_cast<char *>(ws);
-    double *part = sh.part_pp ? reinterpret_cast<double *>(w + L.part) : nullptr;
     for (int64_t p0 = 0; p0 < m; p0 += c) {
         const int64_t cnt = std::min<int64_t>(c, m - p0);
         ChunkLayout Lc;
-        if (!chunk_layout(sh, cnt, Lc) || Lc.total > ws_bytes) return hipErrorInvalidValue;
+        if (!chunk_layout(sh, cnt, ws_bytes, Lc) || Lc.total > ws_bytes) return hipErrorInvalidValue;
         if (!Lc.ordered) {
             OutCols o = {{phi ? phi + p0 : nullptr, ex ? ex + p0 : nullptr, ey ? ey + p0 : nullptr,
                           ez ? ez + p0 : nullptr},
                          m};
-            eval_chunk(drec, sigma, n, ncol, sh, img, mixed, near_factor, px + p0, py + p0, pz + p0, cnt, o, part, s);
+            eval_chunk(drec, sigma, n, ncol, sh, img, mixed, near_factor, px + p0, py + p0, pz + p0, cnt, o, w, Lc, s);
             continue;
         }
         const size_t cc = (size_t)cnt;
         int *perm = reinterpret_cast<int *>(w + Lc.perm);
         double *sp = reinterpret_cast<double *>(w + Lc.pts);
         double *so = reinterpret_cast<double *>(w + Lc.res);
-        double *pc = sh.part_pp ? reinterpret_cast<double *>(w + Lc.part) : nullptr;
-        hipError_t e = launch_order_points(px + p0, py + p0, pz + p0, cnt, sp, sp + cc, sp + 2 * cc, perm, ws,
-                                           Lc.sort_ws, s);
+        hipError_t e = launch_order_points(px + p0, py + p0, pz + p0, cnt, sp, sp + cc, sp + 2 * cc, perm, true,
+                                           ws, Lc.sort_ws, s);
         if (e != hipSuccess) return e;
         for (int c0 = 0; c0 < ncol; c0 += kMultiCols) {
             const int k = ncol - c0 < kMultiCols ? ncol - c0 : kMultiCols;
@@ -372,7 +526,7 @@ hipError_t run_eval(const double *drec, const double *sigma, int64_t n, int ncol
                           ez ? so + 3 * cc : nullptr},
                          (int64_t)(4 * cc)};
             eval_chunk(drec, sigma + (size_t)c0 * n, n, k, sh, img, mixed, near_factor, sp, sp + cc, sp + 2 * cc,
-                       cnt, o, pc, s);
+                       cnt, o, w, Lc, s);
             for (int j = 0; j < k; ++j) {
                 const size_t col = (size_t)(c0 + j) * mm + (size_t)p0;
                 launch_unorder4(so + 4 * (size_t)j * cc, perm, cnt, phi ? phi + col : nullptr,

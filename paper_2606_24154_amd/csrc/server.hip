@@ -16,8 +16,8 @@
 //      at once (by default one: first come first served among them, the
 //      smaller ones sharing the device with them), so that the largest
 //      requests do not all slow each other down.
-//      Admitted points are copied in and, for requests of 4096 points or
-//      more, sorted into Morton order on the device (so that the lanes of a
+//      Admitted points are copied in and, for requests of more than 64
+//      points, sorted into Morton order on the device (so that the lanes of a
 //      work item share the near/far branches; each lane's arithmetic is
 //      unchanged);
 //   2. batching: the active requests are cut into work items of 64 points x
@@ -46,6 +46,7 @@
 
 #include <algorithm>
 #include <chrono>
+#include <cstdint>
 #include <condition_variable>
 #include <cstring>
 #include <deque>
@@ -55,6 +56,7 @@
 #include <thread>
 #include <vector>
 
+#include "group_far.hpp"
 #include "host_util.hpp"
 #include "nebem_internal.hpp"
 #include "server_admission.hpp"
@@ -97,6 +99,9 @@ struct nebem_server {
     std::vector<int64_t> geom_n;
     std::vector<int> geom_nseg;   // element segments per geometry
     std::vector<int> geom_segsz;  // elements per segment (last may be shorter)
+    std::vector<size_t> geom_groups;  // offset of a grouped geometry's records in group_dev, else SIZE_MAX
+    double *group_dev = nullptr;      // group records, 2 x group_len: one set per launch stream
+    size_t group_len = 0;             // doubles
     int mixed = 0;
     double near_factor = 4.0;
     hipStream_t stream = nullptr;            // admission: point copies and sorts
@@ -192,7 +197,7 @@ static void worker_main(nebem_server *s)
                 if (e == hipSuccess)
                     e = launch_order_points(stage(s, r, 3), stage(s, r, 4), stage(s, r, 5), r->m, stage(s, r, 0),
                                             stage(s, r, 1), stage(s, r, 2), reinterpret_cast<int *>(stage(s, r, 7)),
-                                            s->sort_ws, s->sort_ws_bytes, s->stream);
+                                            true, s->sort_ws, s->sort_ws_bytes, s->stream);
             }
             if (e != hipSuccess) {
                 std::lock_guard<std::mutex> lk(s->mu);
@@ -208,6 +213,8 @@ static void worker_main(nebem_server *s)
         // This stream's previous list (launch nlaunch - 2) has completed.
         WorkItem *items_host = s->items_host + (size_t)cur * s->items_cap;
         WorkItem *items_dev = s->items_dev + (size_t)cur * s->items_cap;
+        double *group_cur = s->group_dev + (size_t)cur * s->group_len;
+        std::vector<char> used(s->geoms.size(), 0);
         int nitems = 0;
         double budget = s->opt.batch_interactions;
         bool progress = true;
@@ -230,6 +237,11 @@ static void worker_main(nebem_server *s)
                 w.geom = r->geom;
                 w.count = cnt;
                 w.pad = 0;
+                const size_t go = s->geom_groups[r->geom];
+                const SegPlan gp = {r->nseg, s->geom_segsz[r->geom]};
+                w.gdata = go == SIZE_MAX ? nullptr
+                                         : group_cur + go + (size_t)seg * groups_per_seg(gp) * kGroupStride;
+                used[r->geom] = 1;
                 w.px = stage(s, r, 0) + p0;
                 w.py = stage(s, r, 1) + p0;
                 w.pz = stage(s, r, 2) + p0;
@@ -253,6 +265,13 @@ static void worker_main(nebem_server *s)
                 e = hipMemcpyAsync(items_dev, items_host, (size_t)nitems * sizeof(WorkItem), hipMemcpyHostToDevice,
                                    s->lst[cur]);
             if (e == hipSuccess) {
+                // moments of this launch's geometries, from their sessions'
+                // current densities
+                for (size_t k = 0; k < s->geoms.size(); ++k)
+                    if (used[k] && s->geom_groups[k] != SIZE_MAX)
+                        launch_group_moments(s->geoms[k]->drec.as<double>(), s->geoms[k]->sigma.as<double>(),
+                                             s->geoms[k]->n, 0, 1, {s->geom_nseg[k], s->geom_segsz[k]},
+                                             group_cur + s->geom_groups[k], s->lst[cur]);
                 launch_eval_items(items_dev, nitems, s->imgs_dev, s->mixed, s->near_factor, s->lst[cur]);
                 e = hipGetLastError();
             }
@@ -373,6 +392,9 @@ nebem_status nebem_server_create(nebem_session *const *sessions, int32_t nsessio
         const SegPlan sp = seg_plan(sessions[k]->n, sessions[k]->img);
         s->geom_segsz.push_back(sp.segsz);
         s->geom_nseg.push_back(sp.nseg);
+        const bool grouped = !mixed && eval_grouped(sessions[k]->n, sessions[k]->img);
+        s->geom_groups.push_back(grouped ? s->group_len : SIZE_MAX);
+        if (grouped) s->group_len += group_data_bytes(sp, 1) / sizeof(double);
     }
     auto bail = [&](hipError_t e, const char *what) {
         nebem_status st = hip_fail(e, what);
@@ -399,6 +421,9 @@ nebem_status nebem_server_create(nebem_session *const *sessions, int32_t nsessio
         return bail(e, "hipMalloc(images)");
     if ((e = hipMemcpy(s->imgs_dev, imgs.data(), sizeof(ImgArgs) * nsessions, hipMemcpyHostToDevice)) != hipSuccess)
         return bail(e, "hipMemcpy(images)");
+    if (s->group_len &&
+        (e = hipMalloc((void **)&s->group_dev, 2 * s->group_len * sizeof(double))) != hipSuccess)
+        return bail(e, "hipMalloc(group records)");
     s->items_cap = o.max_items;
     s->round_items = eval_items_slots(mixed);
     if (s->round_items < 1 || s->round_items > s->items_cap) s->round_items = 1;
@@ -508,6 +533,7 @@ void nebem_server_destroy(nebem_server *s)
     if (s->items_dev) (void)hipFree(s->items_dev);
     if (s->sort_ws) (void)hipFree(s->sort_ws);
     if (s->imgs_dev) (void)hipFree(s->imgs_dev);
+    if (s->group_dev) (void)hipFree(s->group_dev);
     if (s->arena_dev) (void)hipFree(s->arena_dev);
     for (int k = 0; k < 2; ++k) {
         if (s->ev_launch[k]) (void)hipEventDestroy(s->ev_launch[k]);

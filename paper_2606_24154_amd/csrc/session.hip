@@ -87,7 +87,7 @@ static nebem_status session_eval_points(nebem_session *s, const double *px, cons
                                         int64_t m, double *phi, double *ex, double *ey, double *ez, hipStream_t st)
 {
     const int mixed = s->opt.precision == NEBEM_MIXED;
-    const size_t wb = eval_workspace(s->n, s->img, m, 1);
+    const size_t wb = eval_workspace(s->n, s->img, m, 1, mixed);
     if (wb) NEBEM_HIP(s->ows.ensure(wb));
     NEBEM_HIP(run_eval(s->drec.as<double>(), s->sigma.as<double>(), s->n, 1, s->img, mixed, s->opt.near_factor, px,
                        py, pz, m, phi, ex, ey, ez, s->ows.p, s->ows.bytes, st));
@@ -329,7 +329,7 @@ nebem_status nebem_session_eval_noalloc(nebem_session *s, const double *px, cons
     if (m < 0 || m > (int64_t)INT32_MAX - 256) return fail(NEBEM_EINVAL, "session_eval_noalloc: m out of range");
     if (m == 0) return NEBEM_OK;
     if (!px || !py || !pz) return fail(NEBEM_EINVAL, "session_eval_noalloc: NULL point array");
-    if (eval_workspace_min(s->n, s->img, m, 1) > kNoAllocScratch)
+    if (eval_workspace_min(s->n, s->img, m, 1, s->opt.precision == NEBEM_MIXED) > kNoAllocScratch)
         return fail(NEBEM_EINVAL, "session_eval_noalloc: the evaluation needs more than the " +
                                       std::to_string(kNoAllocScratch >> 20) + " MiB scratch");
     void *ws = nullptr;

@@ -1,0 +1,113 @@
+"""Grouped FP64 evaluation: far copies of 64-element groups by multipole
+expansions, near ones element by element, in units of several sizes.
+
+Bound against the oracle: 1e-10 pointwise on non-negligible points, the FP64
+evaluation's own (the expansions are truncated below 1e-12 of a group's summed
+absolute charge over distance, the closed forms round at 1e-11 of an element's
+field).  Everything that only regroups the work is held to equal bits.
+"""
+import numpy as np
+import pytest
+
+import oracle
+from synth import Images, gem_cell, gem_eval_points
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def nb():
+    assert torch.cuda.is_available(), "GPU tests need a visible GPU"
+    import paper_2606_24154_amd as nb
+    return nb
+
+
+def dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).to("cuda:0", dtype=torch.float64)
+
+
+def evaluate(nb, geom, sigma, pts):
+    dp = nb.DevicePanels.from_geometry(geom, "cuda:0")
+    out = nb.eval_points(dp, dev(sigma), *[dev(pts[:, k]) for k in range(3)])
+    return torch.stack(out, 1).cpu().numpy()
+
+
+def geometry(copies):
+    """A ragged mesh (1242 elements: 19 groups and 26 elements over) with 121
+    copies, with more copies than one list of near ones holds (169), or with
+    reflections."""
+    g = gem_cell(k=17, nr=2, n_images=5)
+    if copies == "121":
+        return g
+    im = g.images
+    if copies == "169":
+        return g.with_images(Images(a1=im.a1, a2=im.a2, n1=6, n2=6))
+    return g.with_images(Images(a1=im.a1, a2=im.a2, n1=2, n2=3, mirror_mask=5,
+                                mirror_pos=np.array([-2e-4, 0.0, -1.5e-3]),
+                                mirror_parity=np.array([1, 1, -1], np.int32)))
+
+
+def points(geom, m, seed=5):
+    """Field-map points, and among them points in the hole and a few element
+    sizes above the copper, where groups of the own cell are near."""
+    p = gem_eval_points(geom, m, seed)
+    rng = np.random.default_rng(seed)
+    c = 0.5 * (geom.images.a1 + geom.images.a2)
+    near = p[::3]
+    near[:] = c + rng.normal(size=near.shape) * np.array([12e-6, 12e-6, 30e-6])
+    return p
+
+
+@pytest.mark.parametrize("copies", ["121", "169", "mirror"])
+def test_grouped_eval_against_oracle(nb, copies):
+    g = geometry(copies)
+    rng = np.random.default_rng(7)
+    sigma = 1e-5 * np.where(g.value > 0, 1.0, -1.0) * (0.5 + rng.random(g.n))
+    p = points(g, 61)
+    ref = oracle.eval_points(g, sigma, p)
+    got = evaluate(nb, g, sigma, p)
+    ap = np.abs(ref[:, 0])
+    en = np.linalg.norm(ref[:, 1:], axis=1)
+    s, t = ap >= 1e-3 * ap.max(), en >= 1e-3 * en.max()
+    assert np.max(np.abs(got[s, 0] - ref[s, 0]) / ap[s]) <= 1e-10
+    assert np.max(np.linalg.norm(got[t, 1:] - ref[t, 1:], axis=1) / en[t]) <= 1e-10
+
+
+@pytest.mark.parametrize("copies", ["121", "169", "mirror"])
+def test_unit_sizes_give_equal_bits(nb, copies):
+    """Calls of 1 to 530 000 points take units from lattice rows and quarters
+    of groups to whole segments, unordered, small-sorted and radix-sorted."""
+    g = geometry(copies)
+    rng = np.random.default_rng(8)
+    sigma = 1e-5 * rng.standard_normal(g.n)
+    p = points(g, 530_000)
+    full = evaluate(nb, g, sigma, p)
+    for m in (1, 63, 64, 65, 700, 4096, 4097, 40_000):
+        at = rng.choice(len(p), m, replace=False)
+        assert np.array_equal(evaluate(nb, g, sigma, p[at]), full[at]), m
+
+
+@pytest.mark.parametrize("ncol", [2, 3, 5])
+def test_columns_equal_single_evaluations(nb, ncol):
+    g = geometry("121")
+    sigma = 1e-5 * np.random.default_rng(9).standard_normal((ncol, g.n))
+    p = points(g, 777)
+    dp = nb.DevicePanels.from_geometry(g, "cuda:0")
+    out = torch.stack(nb.eval_points_multi(dp, dev(sigma), *[dev(p[:, k]) for k in range(3)]), 2).cpu().numpy()
+    for k in range(ncol):
+        assert np.array_equal(out[k], evaluate(nb, g, sigma[k], p)), k
+
+
+def test_density_that_is_not_finite(nb):
+    """A group with such a density is evaluated element by element: infinite
+    results keep their sign instead of turning into NaN in an expansion."""
+    g = geometry("121")
+    sigma = np.full(g.n, 1e-6)
+    sigma[100] = np.inf
+    got = evaluate(nb, g, sigma, points(g, 200))
+    assert np.all(got[:, 0] == np.inf)
+    assert np.all(np.isinf(got[:, 1:]))
+    sigma[100] = np.nan
+    assert np.all(np.isnan(evaluate(nb, g, sigma, points(g, 200))))
