@@ -3,11 +3,10 @@
 //
 // Work decomposition (both field kernels): one lane owns one observation
 // point (an evaluation point, or a collocation row of the matrix) and keeps
-// its sums in FP64 registers; a workgroup of 256 lanes (4 wave64) streams the
-// derived element records through LDS in tiles, and every lane of the
-// workgroup walks the same element of the tile at the same time, so element
-// data are wave-uniform: they are read from LDS once per wave and moved to
-// scalar registers.  The element kind (rectangle / right triangle) is
+// its sums in FP64 registers; the lanes of a wave walk the elements together,
+// so element data are wave-uniform and live in scalar registers (evaluation:
+// scalar loads; assembly: an LDS tile shared by a workgroup's four waves).  The
+// element kind (rectangle / right triangle) is
 // therefore a uniform branch, and the copy loops (lattice translations and
 // reflections) are uniform loops.  Each point sums elements in index order
 // and copies in lattice order, independent of which other points share its
@@ -27,7 +26,8 @@
 namespace nebem {
 
 constexpr int kBlock = 256;
-constexpr int kTileE = 64;   // elements per LDS tile, evaluation
+constexpr int kTileE = kGroupElems;  // elements per LDS tile, evaluation
+constexpr int kSubElems = kGroupElems / kNearParts;  // elements per unit of a split evaluation
 constexpr int kTileA = 32;   // elements (columns) per workgroup, assembly
 
 // wave-uniform copy of a value held identically by all lanes -> SGPRs
@@ -187,15 +187,17 @@ struct PairB {
     double lz, hyp, ihyp, diam, area;
 };
 
-__device__ __forceinline__ PairB load_pair_b(const double *d)
+// The same from the records in memory, by scalar loads: no staging in LDS and
+// no moves to scalar registers (38 per element, a tenth of an element's work when
+// it has one copy), and the waves of a workgroup run independently.
+__device__ __forceinline__ Elem load_elem_c(cdouble_p d)
 {
-    PairB f;
-    f.lz = uni(d[R_LZ]);
-    f.hyp = uni(d[R_HYP]);
-    f.ihyp = uni(d[R_IHYP]);
-    f.diam = uni(d[R_DIAM]);
-    f.area = uni(d[R_AREA]);
-    return f;
+    return {d[R_OX],  d[R_OY],  d[R_OZ], d[R_E1X], d[R_E1Y], d[R_E1Z], d[R_E2X],  d[R_E2Y],  d[R_E2Z], d[R_E3X],
+            d[R_E3Y], d[R_E3Z], d[R_LX], d[R_LZ],  d[R_HYP], d[R_IHYP], d[R_DIAM], d[R_AREA], uni((int)d[R_KIND])};
+}
+__device__ __forceinline__ PairB load_pair_b_c(cdouble_p d)
+{
+    return {d[R_LZ], d[R_HYP], d[R_IHYP], d[R_DIAM], d[R_AREA]};
 }
 
 // Sum over lattice translations of one element, local frame; (X0,Z0,H0) is
@@ -690,73 +692,105 @@ __device__ __forceinline__ void element_pair_copies_mixed(const Elem &e, const P
 }
 
 // -------------------------------------------------------------- evaluation
-// One workgroup's share of an evaluation: points [base, base + BS) of the
-// m points, all n elements (records drec, densities sigma) and their copies,
-// FP64 sums per lane; outputs scaled by `scale`.
-template <bool MIXED, int BS, bool HOLE = false>
-__device__ __forceinline__ void eval_block(const double *__restrict__ drec, const double *__restrict__ sigma, int n,
-                                           const ImgArgs &img, double near_factor, const double *__restrict__ px,
-                                           const double *__restrict__ py, const double *__restrict__ pz, int m,
-                                           int base_pt, double scale, double *__restrict__ phi,
-                                           double *__restrict__ ex, double *__restrict__ ey,
-                                           double *__restrict__ ez)
+// The elements of a tile that an evaluation starts work on: all but the second
+// triangles of pairs.  Pairs are taken greedily from the tile's start, as a
+// walk through the whole tile takes them, so that a walk through any part of it
+// agrees.  first / second: bits of the pairs' elements.
+__device__ __forceinline__ void tile_pairs(bool flag, uint64_t &first, uint64_t &second)
 {
-    __shared__ double t_rec[kTileE * R_STRIDE];
-    __shared__ double t_sig[kTileE];
-    const int i = base_pt + threadIdx.x;
-    const bool act = i < m;
-    const double Px = act ? px[i] : 0.0;
-    const double Py = act ? py[i] : 0.0;
-    const double Pz = act ? pz[i] : 0.0;
+    uint64_t rem = __ballot(flag);
+    first = 0;
+    while (rem) {
+        const uint64_t b = rem & (0 - rem);
+        first |= b;
+        rem &= ~(b | (b << 1));
+    }
+    second = first << 1;
+}
+
+// The first element at or after s0 that a walk through the tile (records rec,
+// cnt of them) starts work on: s0, or s0 + 1 if s0 ends a pair.
+__device__ __forceinline__ int first_start(cdouble_p rec, int cnt, int s0)
+{
+    if (s0 == 0) return 0;
+    const int lane = threadIdx.x & 63;
+    uint64_t first, second;
+    tile_pairs(lane + 1 < cnt && rec[min(lane, cnt - 1) * R_STRIDE + R_KIND] >= 2.0, first, second);
+    return s0 + (int)((second >> s0) & 1);
+}
+
+// One wave's share of an evaluation: its lanes' points of the m points, elements
+// [p0, p1) of the n (records drec, densities sigma; p0 a multiple of kSubElems)
+// and their copies, FP64 sums per lane; outputs scaled by `scale`.  Runs of
+// kSubElems elements are summed on their own and then added up in order, so
+// that launches which give every run its own wave (split evaluations)
+// reproduce the same bits: 100 points between two plates of 256 elements, which
+// two waves of 512 elements took 1.06 ms for, take 81 us as 64 waves.  With the
+// records staged in LDS the runs made 10^6 points at 1152 elements 5 % slower
+// (17.6 ms); from scalar loads it is 16.8 ms, as without runs.
+template <bool MIXED, bool HOLE = false>
+__device__ __forceinline__ void eval_block(const double *__restrict__ drec, const double *__restrict__ sigma, int n,
+                                           int p0, int p1, const ImgArgs &img, double near_factor,
+                                           const double *__restrict__ px, const double *__restrict__ py,
+                                           const double *__restrict__ pz, int m, int i, double scale,
+                                           double *__restrict__ phi, double *__restrict__ ex,
+                                           double *__restrict__ ey, double *__restrict__ ez)
+{
+    const int j = min(i, m - 1);  // lanes past the last point repeat it
+    const double Px = px[j], Py = py[j], Pz = pz[j];
+    const cdouble_p recs = uniform_ptr(drec), sg = uniform_ptr(sigma);
     double aphi = 0.0, aex = 0.0, aey = 0.0, aez = 0.0;
-    for (int base = 0; base < n; base += kTileE) {
-        const int cnt = min(kTileE, n - base);
-        __syncthreads();
-        for (int k = threadIdx.x; k < cnt * R_STRIDE; k += BS) t_rec[k] = drec[(size_t)base * R_STRIDE + k];
-        for (int k = threadIdx.x; k < cnt; k += BS) t_sig[k] = sigma[base + k];
-        __syncthreads();
-        for (int p = 0; p < cnt; ++p) {
-            const Elem e = load_elem(t_rec + p * R_STRIDE);
-            if (MIXED && e.kind >= 2 && p + 1 < cnt) {
-                // a triangle pair inside this tile, sigma-weighted in one pass
-                const int q1 = e.kind == 2 ? p : p + 1, q2 = e.kind == 2 ? p + 1 : p;
-                const double sg1[1] = {uni(t_sig[q1])}, sg2[1] = {uni(t_sig[q2])};
-                double c[1][4];
-                element_pair_copies_mixed<1, HOLE>(load_elem(t_rec + q1 * R_STRIDE), load_pair_b(t_rec + q2 * R_STRIDE),
-                                                   sg1, sg2, img, near_factor, Px, Py, Pz, c);
-                aphi += c[0][0];
-                aex += c[0][1];
-                aey += c[0][2];
-                aez += c[0][3];
+    for (int base = p0 & ~(kTileE - 1); base < p1; base += kTileE) {
+        const int cnt = min(kTileE, n - base), hi = min(cnt, p1 - base);
+        const cdouble_p tile = recs + (int64_t)base * R_STRIDE, tsg = sg + base;
+        int p = first_start(tile, cnt, max(0, p0 - base));
+        for (int s0 = max(0, p0 - base); s0 < hi; s0 += kSubElems) {
+            double sphi = 0.0, sex = 0.0, sey = 0.0, sez = 0.0;
+            const int s1 = min(s0 + kSubElems, hi);
+            while (p < s1) {
+                const int kind = uni((int)tile[p * R_STRIDE + R_KIND]);
+                if (kind >= 2 && p + 1 < cnt) {
+                    // a triangle pair inside this tile, both in one pass (q1 is the pair's first)
+                    const int q1 = kind == 2 ? p : p + 1, q2 = kind == 2 ? p + 1 : p;
+                    const Elem e = load_elem_c(tile + q1 * R_STRIDE);
+                    const PairB f = load_pair_b_c(tile + q2 * R_STRIDE);
+                    if (MIXED) {  // sigma-weighted
+                        const double sg1[1] = {tsg[q1]}, sg2[1] = {tsg[q2]};
+                        double c[1][4];
+                        element_pair_copies_mixed<1, HOLE>(e, f, sg1, sg2, img, near_factor, Px, Py, Pz, c);
+                        sphi += c[0][0];
+                        sex += c[0][1];
+                        sey += c[0][2];
+                        sez += c[0][3];
+                    } else {  // c[0] for element p, c[1] for p + 1
+                        double c[2][4];
+                        element_pair_copies<HOLE>(e, f, img, Px, Py, Pz, c[q1 - p], c[q2 - p]);
+                        const double g1 = tsg[p], g2 = tsg[p + 1];
+                        sphi = fma(g2, c[1][0], fma(g1, c[0][0], sphi));
+                        sex = fma(g2, c[1][1], fma(g1, c[0][1], sex));
+                        sey = fma(g2, c[1][2], fma(g1, c[0][2], sey));
+                        sez = fma(g2, c[1][3], fma(g1, c[0][3], sez));
+                    }
+                    p += 2;
+                    continue;
+                }
+                double cp, cx, cy, cz;
+                element_copies<MIXED, HOLE>(load_elem_c(tile + p * R_STRIDE), img, Px, Py, Pz, false, near_factor, cp,
+                                            cx, cy, cz);
+                const double g = tsg[p];
+                sphi = fma(g, cp, sphi);
+                sex = fma(g, cx, sex);
+                sey = fma(g, cy, sey);
+                sez = fma(g, cz, sez);
                 ++p;
-                continue;
             }
-            if (!MIXED && e.kind >= 2 && p + 1 < cnt) {
-                // a triangle pair inside this tile: both in one pass (c1 for
-                // element p, c2 for p + 1, whichever is the pair's first)
-                const int q1 = e.kind == 2 ? p : p + 1, q2 = e.kind == 2 ? p + 1 : p;
-                double c[2][4];
-                element_pair_copies<HOLE>(load_elem(t_rec + q1 * R_STRIDE), load_pair_b(t_rec + q2 * R_STRIDE), img,
-                                          Px, Py, Pz, c[q1 - p], c[q2 - p]);
-                const double(&c1)[4] = c[0], (&c2)[4] = c[1];
-                const double s1 = uni(t_sig[p]), s2 = uni(t_sig[p + 1]);
-                aphi = fma(s2, c2[0], fma(s1, c1[0], aphi));
-                aex = fma(s2, c2[1], fma(s1, c1[1], aex));
-                aey = fma(s2, c2[2], fma(s1, c1[2], aey));
-                aez = fma(s2, c2[3], fma(s1, c1[3], aez));
-                ++p;
-                continue;
-            }
-            double cp, cx, cy, cz;
-            element_copies<MIXED, HOLE>(e, img, Px, Py, Pz, false, near_factor, cp, cx, cy, cz);
-            const double sg = uni(t_sig[p]);
-            aphi = fma(sg, cp, aphi);
-            aex = fma(sg, cx, aex);
-            aey = fma(sg, cy, aey);
-            aez = fma(sg, cz, aez);
+            aphi += sphi;
+            aex += sex;
+            aey += sey;
+            aez += sez;
         }
     }
-    if (act) {
+    if (i < m) {
         if (phi) phi[i] = scale * aphi;
         if (ex) ex[i] = scale * aex;
         if (ey) ey[i] = scale * aey;
@@ -803,50 +837,70 @@ SegPlan seg_plan(int64_t n, const ImgArgs &img)
 // the per-element setup to scratch (10.6 GB of HBM writes per 10^6-point
 // launch) for no measurable gain.  HOLE: img.hole is honoured (a separate
 // instantiation, so the plain launch carries no test for it).
-// Grid: x over blocks of kBlock points, y over element segments of segsz
-// elements; segment y writes its sums (times `scale`) at outputs + y * seg_stride.
-template <bool HOLE>
-__global__ __launch_bounds__(kBlock) void k_eval_fp64(
-    const double *__restrict__ drec, const double *__restrict__ sigma, int n, int segsz, ImgArgs img,
+// Grid: x over blocks of BS points, y over units -- element segments of segsz
+// elements (units 1), or `units` runs of kSubElems elements per segment; unit y
+// writes its sums (times `scale`) at outputs + y * seg_stride.
+template <bool HOLE, int BS>
+__global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_eval_fp64(
+    const double *__restrict__ drec, const double *__restrict__ sigma, int n, int segsz, int units, ImgArgs img,
     double near_factor, const double *__restrict__ px, const double *__restrict__ py, const double *__restrict__ pz,
     int m, double scale, double *__restrict__ phi, double *__restrict__ ex, double *__restrict__ ey,
     double *__restrict__ ez, int64_t seg_stride)
 {
-    const int e0 = blockIdx.y * segsz;
+    const int per = units, seg = blockIdx.y / per, e0 = seg * segsz;
+    const int ns = min(segsz, n - e0), p0 = per > 1 ? (blockIdx.y % per) * kSubElems : 0;
     const size_t so = (size_t)blockIdx.y * (size_t)seg_stride;
-    eval_block<false, kBlock, HOLE>(drec + (size_t)e0 * R_STRIDE, sigma + e0, min(segsz, n - e0), img, near_factor,
-                                    px, py, pz, m, blockIdx.x * kBlock, scale, phi ? phi + so : nullptr,
-                                    ex ? ex + so : nullptr, ey ? ey + so : nullptr, ez ? ez + so : nullptr);
+    eval_block<false, HOLE>(drec + (size_t)e0 * R_STRIDE, sigma + e0, ns, p0, per > 1 ? min(p0 + kSubElems, ns) : ns,
+                                img, near_factor, px, py, pz, m, blockIdx.x * BS + threadIdx.x, scale, phi ? phi + so : nullptr,
+                                ex ? ex + so : nullptr, ey ? ey + so : nullptr, ez ? ez + so : nullptr);
 }
 
 // Mixed: two waves per SIMD (the triangle-pair path holds two triangles'
 // unit-density sums and the pair's weighted ones at once; at three waves it
 // spilled inside the copy loop).
-template <bool HOLE>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_eval_mixed(
-    const double *__restrict__ drec, const double *__restrict__ sigma, int n, int segsz, ImgArgs img,
+template <bool HOLE, int BS>
+__global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_eval_mixed(
+    const double *__restrict__ drec, const double *__restrict__ sigma, int n, int segsz, int units, ImgArgs img,
     double near_factor, const double *__restrict__ px, const double *__restrict__ py, const double *__restrict__ pz,
     int m, double scale, double *__restrict__ phi, double *__restrict__ ex, double *__restrict__ ey,
     double *__restrict__ ez, int64_t seg_stride)
 {
-    const int e0 = blockIdx.y * segsz;
+    const int per = units, seg = blockIdx.y / per, e0 = seg * segsz;
+    const int ns = min(segsz, n - e0), p0 = per > 1 ? (blockIdx.y % per) * kSubElems : 0;
     const size_t so = (size_t)blockIdx.y * (size_t)seg_stride;
-    eval_block<true, kBlock, HOLE>(drec + (size_t)e0 * R_STRIDE, sigma + e0, min(segsz, n - e0), img, near_factor,
-                                   px, py, pz, m, blockIdx.x * kBlock, scale, phi ? phi + so : nullptr,
-                                   ex ? ex + so : nullptr, ey ? ey + so : nullptr, ez ? ez + so : nullptr);
+    eval_block<true, HOLE>(drec + (size_t)e0 * R_STRIDE, sigma + e0, ns, p0, per > 1 ? min(p0 + kSubElems, ns) : ns,
+                                img, near_factor, px, py, pz, m, blockIdx.x * BS + threadIdx.x, scale, phi ? phi + so : nullptr,
+                                ex ? ex + so : nullptr, ey ? ey + so : nullptr, ez ? ez + so : nullptr);
 }
 
+template <int BS>
+static void launch_eval_bs(const double *drec, const double *sigma, int64_t n, const SegPlan &sp, const ImgArgs &img,
+                           int mixed, double near_factor, int units, const double *px, const double *py,
+                           const double *pz, int64_t m, double scale, double *phi, double *ex, double *ey, double *ez,
+                           int64_t seg_stride, hipStream_t s)
+{
+    const dim3 g((unsigned)((m + BS - 1) / BS), (unsigned)(sp.nseg * units));
+    const bool hole = img.hole >= 0;
+    auto k = mixed ? (hole ? k_eval_mixed<true, BS> : k_eval_mixed<false, BS>)
+                   : (hole ? k_eval_fp64<true, BS> : k_eval_fp64<false, BS>);
+    hipLaunchKernelGGL(k, g, dim3(BS), 0, s, drec, sigma, (int)n, sp.segsz, units, img, near_factor, px, py, pz,
+                       (int)m, scale, phi, ex, ey, ez, seg_stride);
+}
+
+int eval_subunits(const SegPlan &sp) { return groups_per_seg(sp) * kNearParts; }
+
 void launch_eval_seg(const double *drec, const double *sigma, int64_t n, const SegPlan &sp, const ImgArgs &img,
-                     int mixed, double near_factor, const double *px, const double *py, const double *pz, int64_t m,
-                     double scale, double *phi, double *ex, double *ey, double *ez, int64_t seg_stride, hipStream_t s)
+                     int mixed, double near_factor, bool split, const double *px, const double *py, const double *pz,
+                     int64_t m, double scale, double *phi, double *ex, double *ey, double *ez, int64_t seg_stride,
+                     hipStream_t s)
 {
     if (m <= 0 || n <= 0) return;
-    const dim3 g((unsigned)((m + kBlock - 1) / kBlock), (unsigned)sp.nseg);
-    const bool hole = img.hole >= 0;
-    auto k = mixed ? (hole ? k_eval_mixed<true> : k_eval_mixed<false>)
-                   : (hole ? k_eval_fp64<true> : k_eval_fp64<false>);
-    hipLaunchKernelGGL(k, g, dim3(kBlock), 0, s, drec, sigma, (int)n, sp.segsz, img, near_factor, px, py, pz, (int)m,
-                       scale, phi, ex, ey, ez, seg_stride);
+    if (split)
+        launch_eval_bs<64>(drec, sigma, n, sp, img, mixed, near_factor, eval_subunits(sp), px, py, pz, m, scale, phi,
+                           ex, ey, ez, seg_stride, s);
+    else
+        launch_eval_bs<kBlock>(drec, sigma, n, sp, img, mixed, near_factor, 1, px, py, pz, m, scale, phi, ex, ey, ez,
+                               seg_stride, s);
 }
 
 // out[c][i] += add[c m + i] for the non-null outputs
@@ -960,94 +1014,84 @@ hipError_t launch_prim_density(const double *drec, const double *sigma, const in
 // results equal a single-column evaluation with that column bit for bit.
 // Output (component c, column k) goes to out[c] + k * ostride (out[c] may be
 // null: that component is not stored).
-template <bool MIXED, int K>
+template <bool MIXED, int K, int BS>
 __device__ __forceinline__ void eval_block_multi(const double *__restrict__ drec, const double *__restrict__ sigma,
-                                                 int n, int64_t sig_stride, const ImgArgs &img, double near_factor,
-                                                 const double *__restrict__ px, const double *__restrict__ py,
-                                                 const double *__restrict__ pz, int m, int base_pt, double scale,
-                                                 OutCols out)
+                                                 int n, int p0, int p1, int64_t sig_stride, const ImgArgs &img,
+                                                 double near_factor, const double *__restrict__ px,
+                                                 const double *__restrict__ py, const double *__restrict__ pz, int m,
+                                                 int i, double scale, OutCols out)
 {
-    __shared__ double t_rec[kTileE * R_STRIDE];
-    __shared__ double t_sig[kTileE * K];
-    const int i = base_pt + threadIdx.x;
-    const bool act = i < m;
-    const double Px = act ? px[i] : 0.0;
-    const double Py = act ? py[i] : 0.0;
-    const double Pz = act ? pz[i] : 0.0;
-    double aphi[K], aex[K], aey[K], aez[K];
+    __shared__ double t_acc[K][4][BS];  // each lane's sums over runs: touched once per run
+    const int j = min(i, m - 1);
+    const double Px = px[j], Py = py[j], Pz = pz[j];
+    const cdouble_p recs = uniform_ptr(drec), sg = uniform_ptr(sigma);
+    for (int k = 0; k < K; ++k)
+        for (int q = 0; q < 4; ++q) t_acc[k][q][threadIdx.x] = 0.0;
+    for (int base = p0 & ~(kTileE - 1); base < p1; base += kTileE) {
+        const int cnt = min(kTileE, n - base), hi = min(cnt, p1 - base);
+        const cdouble_p tile = recs + (int64_t)base * R_STRIDE, tsg = sg + base;
+        int p = first_start(tile, cnt, max(0, p0 - base));
+        for (int s0 = max(0, p0 - base); s0 < hi; s0 += kSubElems) {
+            double sub[K][4];
 #pragma unroll
-    for (int k = 0; k < K; ++k) aphi[k] = aex[k] = aey[k] = aez[k] = 0.0;
-    for (int base = 0; base < n; base += kTileE) {
-        const int cnt = min(kTileE, n - base);
-        __syncthreads();
-        for (int q = threadIdx.x; q < cnt * R_STRIDE; q += kBlock) t_rec[q] = drec[(size_t)base * R_STRIDE + q];
-        for (int q = threadIdx.x; q < cnt * K; q += kBlock) {
-            const int pp = q / K, k = q % K;
-            t_sig[q] = sigma[(size_t)k * sig_stride + base + pp];
-        }
-        __syncthreads();
-        for (int p = 0; p < cnt; ++p) {
-            const Elem e = load_elem(t_rec + p * R_STRIDE);
-            if (MIXED && e.kind >= 2 && p + 1 < cnt) {
-                // a triangle pair inside this tile, as in eval_block
-                const int q1 = e.kind == 2 ? p : p + 1, q2 = e.kind == 2 ? p + 1 : p;
-                double sg1[K], sg2[K], c[K][4];
+            for (int k = 0; k < K; ++k) sub[k][0] = sub[k][1] = sub[k][2] = sub[k][3] = 0.0;
+            const int s1 = min(s0 + kSubElems, hi);
+            while (p < s1) {
+                const int kind = uni((int)tile[p * R_STRIDE + R_KIND]);
+                if (kind >= 2 && p + 1 < cnt) {
+                    // a triangle pair inside this tile, as in eval_block
+                    const int q1 = kind == 2 ? p : p + 1, q2 = kind == 2 ? p + 1 : p;
+                    const Elem e = load_elem_c(tile + q1 * R_STRIDE);
+                    const PairB f = load_pair_b_c(tile + q2 * R_STRIDE);
+                    if (MIXED) {
+                        double sg1[K], sg2[K], c[K][4];
 #pragma unroll
-                for (int k = 0; k < K; ++k) {
-                    sg1[k] = uni(t_sig[q1 * K + k]);
-                    sg2[k] = uni(t_sig[q2 * K + k]);
+                        for (int k = 0; k < K; ++k) {
+                            sg1[k] = tsg[k * sig_stride + q1];
+                            sg2[k] = tsg[k * sig_stride + q2];
+                        }
+                        element_pair_copies_mixed<K, false>(e, f, sg1, sg2, img, near_factor, Px, Py, Pz, c);
+#pragma unroll
+                        for (int k = 0; k < K; ++k)
+#pragma unroll
+                            for (int q = 0; q < 4; ++q) sub[k][q] += c[k][q];
+                    } else {
+                        double c[2][4];
+                        element_pair_copies<false>(e, f, img, Px, Py, Pz, c[q1 - p], c[q2 - p]);
+#pragma unroll
+                        for (int k = 0; k < K; ++k) {
+                            const double g1 = tsg[k * sig_stride + p], g2 = tsg[k * sig_stride + p + 1];
+#pragma unroll
+                            for (int q = 0; q < 4; ++q) sub[k][q] = fma(g2, c[1][q], fma(g1, c[0][q], sub[k][q]));
+                        }
+                    }
+                    p += 2;
+                    continue;
                 }
-                element_pair_copies_mixed<K, false>(load_elem(t_rec + q1 * R_STRIDE),
-                                                    load_pair_b(t_rec + q2 * R_STRIDE), sg1, sg2, img, near_factor, Px,
-                                                    Py, Pz, c);
+                double cc[4];
+                element_copies<MIXED>(load_elem_c(tile + p * R_STRIDE), img, Px, Py, Pz, false, near_factor, cc[0],
+                                      cc[1], cc[2], cc[3]);
 #pragma unroll
                 for (int k = 0; k < K; ++k) {
-                    aphi[k] += c[k][0];
-                    aex[k] += c[k][1];
-                    aey[k] += c[k][2];
-                    aez[k] += c[k][3];
-                }
-                ++p;
-                continue;
-            }
-            if (!MIXED && e.kind >= 2 && p + 1 < cnt) {
-                // a triangle pair inside this tile, as in eval_block
-                const int q1 = e.kind == 2 ? p : p + 1, q2 = e.kind == 2 ? p + 1 : p;
-                double c[2][4];
-                element_pair_copies<false>(load_elem(t_rec + q1 * R_STRIDE), load_pair_b(t_rec + q2 * R_STRIDE), img,
-                                           Px, Py, Pz, c[q1 - p], c[q2 - p]);
-                const double(&c1)[4] = c[0], (&c2)[4] = c[1];
+                    const double g = tsg[k * sig_stride + p];
 #pragma unroll
-                for (int k = 0; k < K; ++k) {
-                    const double s1 = uni(t_sig[p * K + k]), s2 = uni(t_sig[(p + 1) * K + k]);
-                    aphi[k] = fma(s2, c2[0], fma(s1, c1[0], aphi[k]));
-                    aex[k] = fma(s2, c2[1], fma(s1, c1[1], aex[k]));
-                    aey[k] = fma(s2, c2[2], fma(s1, c1[2], aey[k]));
-                    aez[k] = fma(s2, c2[3], fma(s1, c1[3], aez[k]));
+                    for (int q = 0; q < 4; ++q) sub[k][q] = fma(g, cc[q], sub[k][q]);
                 }
                 ++p;
-                continue;
             }
-            double cp, cx, cy, cz;
-            element_copies<MIXED>(e, img, Px, Py, Pz, false, near_factor, cp, cx, cy, cz);
 #pragma unroll
-            for (int k = 0; k < K; ++k) {
-                const double sg = uni(t_sig[p * K + k]);
-                aphi[k] = fma(sg, cp, aphi[k]);
-                aex[k] = fma(sg, cx, aex[k]);
-                aey[k] = fma(sg, cy, aey[k]);
-                aez[k] = fma(sg, cz, aez[k]);
-            }
+            for (int k = 0; k < K; ++k)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) t_acc[k][q][threadIdx.x] += sub[k][q];
         }
     }
-    if (act) {
+    if (i < m) {
 #pragma unroll
         for (int k = 0; k < K; ++k) {
             const size_t o = (size_t)k * out.stride + i;
-            if (out.c[0]) out.c[0][o] = scale * aphi[k];
-            if (out.c[1]) out.c[1][o] = scale * aex[k];
-            if (out.c[2]) out.c[2][o] = scale * aey[k];
-            if (out.c[3]) out.c[3][o] = scale * aez[k];
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                if (out.c[q]) out.c[q][o] = scale * t_acc[k][q][threadIdx.x];
         }
     }
 }
@@ -1061,76 +1105,80 @@ __device__ __forceinline__ OutCols seg_out(OutCols o, int seg, int64_t seg_strid
     return o;
 }
 
-// grid as k_eval_fp64: x over point blocks, y over element segments
-template <int K>
-__global__ __launch_bounds__(kBlock) void k_eval_multi_fp64(const double *__restrict__ drec,
-                                                            const double *__restrict__ sigma, int n,
-                                                            int64_t sig_stride, int segsz, ImgArgs img,
-                                                            double near_factor, const double *__restrict__ px,
-                                                            const double *__restrict__ py,
-                                                            const double *__restrict__ pz, int m, double scale,
-                                                            OutCols out, int64_t seg_stride)
+// grid as k_eval_fp64: x over point blocks, y over units
+template <int K, int BS>
+__global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_eval_multi_fp64(const double *__restrict__ drec,
+                                                        const double *__restrict__ sigma, int n, int64_t sig_stride,
+                                                        int segsz, int units, ImgArgs img, double near_factor,
+                                                        const double *__restrict__ px, const double *__restrict__ py,
+                                                        const double *__restrict__ pz, int m, double scale,
+                                                        OutCols out, int64_t seg_stride)
 {
-    const int e0 = blockIdx.y * segsz;
-    eval_block_multi<false, K>(drec + (size_t)e0 * R_STRIDE, sigma + e0, min(segsz, n - e0), sig_stride, img,
-                               near_factor, px, py, pz, m, blockIdx.x * kBlock, scale,
-                               seg_out(out, blockIdx.y, seg_stride));
+    const int per = units, e0 = (blockIdx.y / per) * segsz;
+    const int ns = min(segsz, n - e0), p0 = per > 1 ? (blockIdx.y % per) * kSubElems : 0;
+    eval_block_multi<false, K, BS>(drec + (size_t)e0 * R_STRIDE, sigma + e0, ns, p0,
+                                   per > 1 ? min(p0 + kSubElems, ns) : ns, sig_stride, img, near_factor, px, py, pz, m,
+                                   blockIdx.x * BS + threadIdx.x, scale, seg_out(out, blockIdx.y, seg_stride));
 }
 
 // at most 256 VGPRs so that two waves share a SIMD (unbounded, K = 3 and 4
 // would take 258 and 266)
-template <int K>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_eval_multi_mixed(
-    const double *__restrict__ drec, const double *__restrict__ sigma, int n, int64_t sig_stride, int segsz,
+template <int K, int BS>
+__global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_eval_multi_mixed(
+    const double *__restrict__ drec, const double *__restrict__ sigma, int n, int64_t sig_stride, int segsz, int units,
     ImgArgs img, double near_factor, const double *__restrict__ px, const double *__restrict__ py,
     const double *__restrict__ pz, int m, double scale, OutCols out, int64_t seg_stride)
 {
-    const int e0 = blockIdx.y * segsz;
-    eval_block_multi<true, K>(drec + (size_t)e0 * R_STRIDE, sigma + e0, min(segsz, n - e0), sig_stride, img,
-                              near_factor, px, py, pz, m, blockIdx.x * kBlock, scale,
-                              seg_out(out, blockIdx.y, seg_stride));
+    const int per = units, e0 = (blockIdx.y / per) * segsz;
+    const int ns = min(segsz, n - e0), p0 = per > 1 ? (blockIdx.y % per) * kSubElems : 0;
+    eval_block_multi<true, K, BS>(drec + (size_t)e0 * R_STRIDE, sigma + e0, ns, p0,
+                                  per > 1 ? min(p0 + kSubElems, ns) : ns, sig_stride, img, near_factor, px, py, pz, m,
+                                  blockIdx.x * BS + threadIdx.x, scale, seg_out(out, blockIdx.y, seg_stride));
 }
 
-template <int K>
+template <int K, int BS>
 static void launch_multi_k(const double *drec, const double *sigma, int n, int64_t sig_stride, const SegPlan &sp,
-                           const ImgArgs &img, int mixed, double near_factor, const double *px, const double *py,
-                           const double *pz, int m, double scale, const OutCols &out, int64_t seg_stride,
-                           hipStream_t s)
+                           const ImgArgs &img, int mixed, double near_factor, int units, const double *px,
+                           const double *py, const double *pz, int m, double scale, const OutCols &out,
+                           int64_t seg_stride, hipStream_t s)
 {
-    const dim3 g((unsigned)((m + kBlock - 1) / kBlock), (unsigned)sp.nseg);
+    const dim3 g((unsigned)((m + BS - 1) / BS), (unsigned)(sp.nseg * units));
     if (mixed)
-        hipLaunchKernelGGL(k_eval_multi_mixed<K>, g, dim3(kBlock), 0, s, drec, sigma, n, sig_stride, sp.segsz, img,
-                           near_factor, px, py, pz, m, scale, out, seg_stride);
+        hipLaunchKernelGGL((k_eval_multi_mixed<K, BS>), g, dim3(BS), 0, s, drec, sigma, n, sig_stride, sp.segsz, units,
+                           img, near_factor, px, py, pz, m, scale, out, seg_stride);
     else
-        hipLaunchKernelGGL(k_eval_multi_fp64<K>, g, dim3(kBlock), 0, s, drec, sigma, n, sig_stride, sp.segsz, img,
-                           near_factor, px, py, pz, m, scale, out, seg_stride);
+        hipLaunchKernelGGL((k_eval_multi_fp64<K, BS>), g, dim3(BS), 0, s, drec, sigma, n, sig_stride, sp.segsz, units,
+                           img, near_factor, px, py, pz, m, scale, out, seg_stride);
+}
+
+template <int BS>
+static void launch_multi_bs(const double *drec, const double *sigma, int n, int64_t sig_stride, int ncol,
+                            const SegPlan &sp, const ImgArgs &img, int mixed, double near_factor, int units,
+                            const double *px, const double *py, const double *pz, int m, double scale,
+                            const OutCols &out, int64_t seg_stride, hipStream_t s)
+{
+#define MULTI_ARGS drec, sigma, n, sig_stride, sp, img, mixed, near_factor, units, px, py, pz, m, scale, out, seg_stride, s
+    switch (ncol) {
+    case 1: launch_multi_k<1, BS>(MULTI_ARGS); break;
+    case 2: launch_multi_k<2, BS>(MULTI_ARGS); break;
+    case 3: launch_multi_k<3, BS>(MULTI_ARGS); break;
+    default: launch_multi_k<4, BS>(MULTI_ARGS); break;
+    }
+#undef MULTI_ARGS
 }
 
 void launch_eval_multi_seg(const double *drec, const double *sigma, int64_t n, int64_t sig_stride, int ncol,
-                           const SegPlan &sp, const ImgArgs &img, int mixed, double near_factor, const double *px,
-                           const double *py, const double *pz, int64_t m, double scale, const OutCols &out,
-                           int64_t seg_stride, hipStream_t s)
+                           const SegPlan &sp, const ImgArgs &img, int mixed, double near_factor, bool split,
+                           const double *px, const double *py, const double *pz, int64_t m, double scale,
+                           const OutCols &out, int64_t seg_stride, hipStream_t s)
 {
     if (m <= 0 || ncol <= 0 || n <= 0) return;
-    const int nn = (int)n, mm = (int)m;
-    switch (ncol) {
-    case 1:
-        launch_multi_k<1>(drec, sigma, nn, sig_stride, sp, img, mixed, near_factor, px, py, pz, mm, scale, out,
-                          seg_stride, s);
-        break;
-    case 2:
-        launch_multi_k<2>(drec, sigma, nn, sig_stride, sp, img, mixed, near_factor, px, py, pz, mm, scale, out,
-                          seg_stride, s);
-        break;
-    case 3:
-        launch_multi_k<3>(drec, sigma, nn, sig_stride, sp, img, mixed, near_factor, px, py, pz, mm, scale, out,
-                          seg_stride, s);
-        break;
-    default:
-        launch_multi_k<4>(drec, sigma, nn, sig_stride, sp, img, mixed, near_factor, px, py, pz, mm, scale, out,
-                          seg_stride, s);
-        break;
-    }
+    if (split)
+        launch_multi_bs<64>(drec, sigma, (int)n, sig_stride, ncol, sp, img, mixed, near_factor, eval_subunits(sp), px,
+                            py, pz, (int)m, scale, out, seg_stride, s);
+    else
+        launch_multi_bs<kBlock>(drec, sigma, (int)n, sig_stride, ncol, sp, img, mixed, near_factor, 1, px, py, pz,
+                                (int)m, scale, out, seg_stride, s);
 }
 
 // Segment partial sums -> results: for column k < ncol and component c,
@@ -1170,13 +1218,6 @@ void launch_reduce_segments(const double *part, int nseg, int ncol, int64_t m, i
 // few copies per element, staging them in LDS and moving them to scalar
 // registers would cost as much as the closed forms.
 constexpr int kNearCopies = 128;  // copies per list: the 121 of an 11 x 11 lattice in one
-constexpr int kSubElems = kGroupElems / kNearParts;
-
-__device__ __forceinline__ Elem load_elem_c(cdouble_p d)
-{
-    return {d[R_OX],  d[R_OY],  d[R_OZ], d[R_E1X], d[R_E1Y], d[R_E1Z], d[R_E2X],  d[R_E2Y],  d[R_E2Z], d[R_E3X],
-            d[R_E3Y], d[R_E3Z], d[R_LX], d[R_LZ],  d[R_HYP], d[R_IHYP], d[R_DIAM], d[R_AREA], uni((int)d[R_KIND])};
-}
 
 // one copy by the closed forms (tiers of sum_translations), added to s
 template <int KIND>
@@ -1366,15 +1407,9 @@ __device__ __forceinline__ void near_unit(NearList &nl, cdouble_p drec, cdouble_
             listed = list_near(nl, h, img, 0, ncopy, Px, Py, Pz);
             if (listed == 0) continue;
         }
-        // triangle pairs inside the group, taken greedily from its start
-        const double kd = lane + 1 < cnt ? drec[(int64_t)(e0 + lane) * R_STRIDE + R_KIND] : 0.0;
-        uint64_t rem = __ballot(kd >= 2.0), first = 0;
-        while (rem) {
-            const uint64_t b = rem & (0 - rem);
-            first |= b;
-            rem &= ~(b | (b << 1));
-        }
-        const uint64_t second = first << 1;
+        uint64_t first, second;
+        tile_pairs(lane + 1 < cnt && drec[(int64_t)(e0 + min(lane, cnt - 1)) * R_STRIDE + R_KIND] >= 2.0, first,
+                   second);
         double grp[K][4];
 #pragma unroll
         for (int k = 0; k < K; ++k)
@@ -1502,7 +1537,7 @@ void launch_group_near(const double *drec, const double *sigma, const double *gd
 // up to 64 points of one request against one segment of the elements of one
 // resident geometry -- and writes the segment's unscaled partial sums.  The
 // per-point arithmetic does not depend on which other items share the launch.
-__global__ __launch_bounds__(64) void k_eval_items_fp64(const WorkItem *__restrict__ items,
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_eval_items_fp64(const WorkItem *__restrict__ items,
                                                        const ImgArgs *__restrict__ imgs, double near_factor)
 {
     __shared__ NearList list;
@@ -1519,7 +1554,8 @@ __global__ __launch_bounds__(64) void k_eval_items_fp64(const WorkItem *__restri
         w.ez[threadIdx.x] += acc[0][3];
         return;
     }
-    eval_block<false, 64>(w.drec, w.sigma, w.n, imgs[w.geom], near_factor, w.px, w.py, w.pz, w.count, 0, 1.0, w.phi,
+    eval_block<false>(w.drec, w.sigma, w.n, 0, w.n, imgs[w.geom], near_factor, w.px, w.py, w.pz, w.count,
+                      threadIdx.x, 1.0, w.phi,
                           w.ex, w.ey, w.ez);
 }
 
@@ -1528,7 +1564,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
     const WorkItem *__restrict__ items, const ImgArgs *__restrict__ imgs, double near_factor)
 {
     const WorkItem &w = items[blockIdx.x];
-    eval_block<true, 64>(w.drec, w.sigma, w.n, imgs[w.geom], near_factor, w.px, w.py, w.pz, w.count, 0, 1.0, w.phi,
+    eval_block<true>(w.drec, w.sigma, w.n, 0, w.n, imgs[w.geom], near_factor, w.px, w.py, w.pz, w.count,
+                      threadIdx.x, 1.0, w.phi,
                          w.ex, w.ey, w.ez);
 }
 

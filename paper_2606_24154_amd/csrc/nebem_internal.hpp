@@ -200,15 +200,19 @@ SegPlan seg_plan(int64_t n, const ImgArgs &img);
 // FP64 monopole + FP32 correction far field, nearer ones the exact FP64
 // closed forms; mixed == 0: the exact FP64 closed forms everywhere.
 // One launch over all segments: segment y's sums (times `scale`) go to the
-// outputs + y * seg_stride (nseg == 1, scale k_e: the final results).
+// outputs + y * seg_stride (nseg == 1, scale k_e: the final results); split:
+// the same for the eval_subunits 16-element runs of every segment, whose sums
+// add up to the segment's in order, bit for bit.
+int eval_subunits(const SegPlan &sp);
 void launch_eval_seg(const double *drec, const double *sigma, int64_t n, const SegPlan &sp, const ImgArgs &img,
-                     int mixed, double near_factor, const double *px, const double *py, const double *pz, int64_t m,
-                     double scale, double *phi, double *ex, double *ey, double *ez, int64_t seg_stride, hipStream_t s);
+                     int mixed, double near_factor, bool split, const double *px, const double *py, const double *pz,
+                     int64_t m, double scale, double *phi, double *ex, double *ey, double *ez, int64_t seg_stride,
+                     hipStream_t s);
 // ncol <= kMultiCols columns of sigma (column k at sigma + k sig_stride)
 void launch_eval_multi_seg(const double *drec, const double *sigma, int64_t n, int64_t sig_stride, int ncol,
-                           const SegPlan &sp, const ImgArgs &img, int mixed, double near_factor, const double *px,
-                           const double *py, const double *pz, int64_t m, double scale, const OutCols &out,
-                           int64_t seg_stride, hipStream_t s);
+                           const SegPlan &sp, const ImgArgs &img, int mixed, double near_factor, bool split,
+                           const double *px, const double *py, const double *pz, int64_t m, double scale,
+                           const OutCols &out, int64_t seg_stride, hipStream_t s);
 // out.c[c][k stride + i] = k_e * (0 + sum_s part[s seg_stride + (4k + c) m + i]), in segment order
 void launch_reduce_segments(const double *part, int nseg, int ncol, int64_t m, int64_t seg_stride,
                             const OutCols &out, hipStream_t s);

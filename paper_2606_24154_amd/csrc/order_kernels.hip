@@ -314,9 +314,14 @@ void pick_splits(const EvalShape &sh, int64_t c, int &far, int &near)
 {
     const int64_t waves = (c + 63) / 64;
     far = near = 0;
-    if (!sh.grouped || waves * sh.sp.nseg >= 8192) return;
+    if (waves * sh.sp.nseg >= 8192) return;
     const int64_t pp = (int64_t)32 * sh.kc * c;
-    auto fits = [&](int64_t units) { return units <= kMaxUnits && units * pp <= (int64_t)kSplitBudget; };
+    const int64_t most = (int64_t)(sh.grouped ? kSplitBudget : kPartBudget);
+    auto fits = [&](int64_t units) { return units <= kMaxUnits && units * pp <= most; };
+    if (!sh.grouped) {
+        far = fits((int64_t)sh.sp.nseg * eval_subunits(sh.sp)) ? 1 : 0;
+        return;
+    }
     if (!fits(sh.ngroup)) return;
     far = waves * sh.ngroup < 2048 && fits(sh.ngroup * sh.rows) ? 2 : 1;
     near = waves * sh.ngroup < 8192 && fits(sh.ngroup * kNearParts) ? 2 : 1;
@@ -356,7 +361,7 @@ bool chunk_layout(const EvalShape &sh, int64_t c, size_t limit, ChunkLayout &L)
     pick_splits(sh, c, L.fsplit, L.nsplit);
     for (;;) {
         const size_t unit = (size_t)32 * sh.kc * (size_t)c, g = (size_t)sh.ngroup;
-        L.far = take(L.fsplit ? unit * g * (L.fsplit == 2 ? sh.rows : 1) : 0);
+        L.far = take(!L.fsplit ? 0 : !sh.grouped ? unit * g * kNearParts : unit * g * (L.fsplit == 2 ? sh.rows : 1));
         L.near = take(L.nsplit ? unit * g * (L.nsplit == 2 ? kNearParts : 1) : 0);
         L.ffold = take(L.fsplit == 2 ? unit * g : 0);
         L.nfold = take(L.nsplit == 2 ? unit * g : 0);
@@ -422,29 +427,41 @@ void eval_chunk(const double *drec, const double *sigma, int64_t n, int ncol, co
         const double *sg = sigma + (size_t)c0 * n;
         OutCols oc = o;
         for (int q = 0; q < 4; ++q) oc.c[q] = o.c[q] ? o.c[q] + (size_t)c0 * o.stride : nullptr;
-        if (!sh.part_pp) {
+        if (!sh.part_pp && !L.fsplit) {
             if (ncol == 1)
-                launch_eval_seg(drec, sg, n, sh.sp, img, mixed, near_factor, px, py, pz, c, kKe, oc.c[0], oc.c[1],
-                                oc.c[2], oc.c[3], 0, s);
+                launch_eval_seg(drec, sg, n, sh.sp, img, mixed, near_factor, false, px, py, pz, c, kKe, oc.c[0],
+                                oc.c[1], oc.c[2], oc.c[3], 0, s);
             else
-                launch_eval_multi_seg(drec, sg, n, n, k, sh.sp, img, mixed, near_factor, px, py, pz, c, kKe, oc, 0,
-                                      s);
+                launch_eval_multi_seg(drec, sg, n, n, k, sh.sp, img, mixed, near_factor, false, px, py, pz, c, kKe, oc,
+                                      0, s);
             continue;
         }
-        // partials: column j, component q of segment y at part + y * 4 k c + (4 j + q) c
+        // partials: column j, component q of unit y at buf + y * 4 k c + (4 j + q) c
         const size_t cc = (size_t)c;
-        OutCols pc = {{o.c[0] ? part : nullptr, o.c[1] ? part + cc : nullptr, o.c[2] ? part + 2 * cc : nullptr,
-                       o.c[3] ? part + 3 * cc : nullptr},
-                      (int64_t)(4 * cc)};
         const int64_t seg_stride = (int64_t)(4 * (size_t)k * cc);
-        if (sh.grouped)
-            eval_grouped_chunk(drec, sg, n, k, sh, img, px, py, pz, c, pc, seg_stride, w, L, s);
-        else if (ncol == 1)
-            launch_eval_seg(drec, sg, n, sh.sp, img, mixed, near_factor, px, py, pz, c, 1.0, pc.c[0], pc.c[1], pc.c[2],
-                            pc.c[3], seg_stride, s);
-        else
-            launch_eval_multi_seg(drec, sg, n, n, k, sh.sp, img, mixed, near_factor, px, py, pz, c, 1.0, pc,
-                                  seg_stride, s);
+        auto cols = [&](double *b) {
+            return OutCols{{o.c[0] ? b : nullptr, o.c[1] ? b + cc : nullptr, o.c[2] ? b + 2 * cc : nullptr,
+                            o.c[3] ? b + 3 * cc : nullptr},
+                           (int64_t)(4 * cc)};
+        };
+        if (sh.grouped) {
+            eval_grouped_chunk(drec, sg, n, k, sh, img, px, py, pz, c, cols(part), seg_stride, w, L, s);
+        } else {
+            const bool split = L.fsplit != 0;
+            double *units = split ? reinterpret_cast<double *>(w + L.far) : part;
+            const OutCols pc = cols(units);
+            if (ncol == 1)
+                launch_eval_seg(drec, sg, n, sh.sp, img, mixed, near_factor, split, px, py, pz, c, 1.0, pc.c[0],
+                                pc.c[1], pc.c[2], pc.c[3], seg_stride, s);
+            else
+                launch_eval_multi_seg(drec, sg, n, n, k, sh.sp, img, mixed, near_factor, split, px, py, pz, c, 1.0, pc,
+                                      seg_stride, s);
+            if (split && sh.sp.nseg == 1) {  // one segment: its units are the reduction's own terms
+                launch_reduce_segments(units, eval_subunits(sh.sp), k, c, seg_stride, oc, s);
+                continue;
+            }
+            if (split) launch_fold_units(units, sh.sp.nseg, eval_subunits(sh.sp), seg_stride, part, s);
+        }
         launch_reduce_segments(part, sh.sp.nseg, k, c, seg_stride, oc, s);
     }
 }

@@ -28,9 +28,9 @@ def dev(a):
     return torch.from_numpy(np.ascontiguousarray(a)).to("cuda:0", dtype=torch.float64)
 
 
-def evaluate(nb, geom, sigma, pts):
+def evaluate(nb, geom, sigma, pts, precision=0):
     dp = nb.DevicePanels.from_geometry(geom, "cuda:0")
-    out = nb.eval_points(dp, dev(sigma), *[dev(pts[:, k]) for k in range(3)])
+    out = nb.eval_points(dp, dev(sigma), *[dev(pts[:, k]) for k in range(3)], precision=precision)
     return torch.stack(out, 1).cpu().numpy()
 
 
@@ -41,6 +41,8 @@ def geometry(copies):
     g = gem_cell(k=17, nr=2, n_images=5)
     if copies == "121":
         return g
+    if copies == "none":  # one copy: no grouping
+        return g.with_images(Images(a1=g.images.a1, a2=g.images.a2))
     im = g.images
     if copies == "169":
         return g.with_images(Images(a1=im.a1, a2=im.a2, n1=6, n2=6))
@@ -75,18 +77,22 @@ def test_grouped_eval_against_oracle(nb, copies):
     assert np.max(np.linalg.norm(got[t, 1:] - ref[t, 1:], axis=1) / en[t]) <= 1e-10
 
 
-@pytest.mark.parametrize("copies", ["121", "169", "mirror"])
-def test_unit_sizes_give_equal_bits(nb, copies):
+@pytest.mark.parametrize("copies, precision", [("121", 0), ("169", 0), ("mirror", 0), ("none", 0), ("121", 1),
+                                               ("mirror", 1), ("none", 1)])
+def test_unit_sizes_give_equal_bits(nb, copies, precision):
     """Calls of 1 to 530 000 points take units from lattice rows and quarters
-    of groups to whole segments, unordered, small-sorted and radix-sorted."""
+    of groups (16-element runs where nothing is grouped) to whole segments,
+    unordered, small-sorted and radix-sorted."""
     g = geometry(copies)
+    if copies == "none":  # an odd start of the runs of pairs
+        g = g.subset(np.arange(1, g.n))
     rng = np.random.default_rng(8)
     sigma = 1e-5 * rng.standard_normal(g.n)
     p = points(g, 530_000)
-    full = evaluate(nb, g, sigma, p)
+    full = evaluate(nb, g, sigma, p, precision)
     for m in (1, 63, 64, 65, 700, 4096, 4097, 40_000):
         at = rng.choice(len(p), m, replace=False)
-        assert np.array_equal(evaluate(nb, g, sigma, p[at]), full[at]), m
+        assert np.array_equal(evaluate(nb, g, sigma, p[at], precision), full[at]), m
 
 
 @pytest.mark.parametrize("ncol", [2, 3, 5])
