@@ -559,21 +559,22 @@ nebem_status nebem_solve(double *A, int64_t n, const double *b, int64_t nrhs, do
         }
         if ((st = factor_fp64(A, nn, ipiv, perm, stream))) return st;
         NEBEM_HIP(hipMemcpyAsync(dperm.p, perm.data(), (size_t)nn * sizeof(int), hipMemcpyHostToDevice, stream));
-        if ((st = solve_fp64(A, nn, dperm.as<int>(), b, (int)nrhs, sigma, stream))) return st;
+        FlowBuf flow;
+        if ((st = flow.init(nn, stream))) return st;
+        if ((st = solve_fp64(A, nn, dperm.as<int>(), b, (int)nrhs, sigma, flow, stream))) return st;
         if (refine) {
             nebem_solve_info agg = {0, 0.0};
             for (int64_t q = 0; q < nrhs; ++q) {
                 nebem_solve_info ci;
                 if ((st = refine_fp64(acopy.as<double>(), A, dperm.as<int>(), nn, bb + q * n, sigma + q * n,
-                                      kFp64RefineSteps, &ci, stream)))
+                                      kFp64RefineSteps, &ci, flow, stream)))
                     return st;
                 agg.ir_iters = ci.ir_iters > agg.ir_iters ? ci.ir_iters : agg.ir_iters;
                 agg.rel_resid = ci.rel_resid > agg.rel_resid ? ci.rel_resid : agg.rel_resid;
             }
             if (info) *info = agg;
         }
-        NEBEM_HIP(hipStreamSynchronize(stream));  // perm (host) must outlive the copy
-        return NEBEM_OK;
+        return flow.check(stream);  // perm (host) must outlive its copy: this synchronises
     }
     DevBuf a32, scale, bcopy;
     NEBEM_HIP(a32.alloc((size_t)nn * nn * sizeof(float), stream));
@@ -618,9 +619,12 @@ nebem_status nebem_solve_factored(const double *LU, const int32_t *ipiv, int64_t
     DevBuf dperm;
     NEBEM_HIP(dperm.alloc((size_t)nn * sizeof(int), stream));
     NEBEM_HIP(hipMemcpyAsync(dperm.p, perm.data(), (size_t)nn * sizeof(int), hipMemcpyHostToDevice, stream));
-    nebem_status st = solve_fp64(LU, nn, dperm.as<int>(), b, (int)nrhs, sigma, stream);
-    NEBEM_HIP(hipStreamSynchronize(stream));
-    return st;
+    FlowBuf flow;
+    nebem_status st = flow.init(nn, stream);
+    if (!st) st = solve_fp64(LU, nn, dperm.as<int>(), b, (int)nrhs, sigma, flow, stream);
+    const nebem_status sf = st ? st : flow.check(stream);
+    NEBEM_HIP(hipStreamSynchronize(stream));  // perm (host) must outlive its copy
+    return sf;
 }
 
 nebem_status nebem_norm1(const double *A, int64_t n, double *anorm, hipStream_t stream)

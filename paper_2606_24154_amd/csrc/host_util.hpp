@@ -4,6 +4,7 @@
 
 #include <vector>
 
+#include "lu_internal.hpp"
 #include "nebem_internal.hpp"
 
 namespace nebem {
@@ -51,14 +52,22 @@ void pivots_to_perm(const std::vector<int> &ipiv, std::vector<int> &perm);
 nebem_status factor_fp64(double *A, int n, int *ipiv, std::vector<int> &perm_host, hipStream_t st);
 nebem_status factor_mixed(const double *A, int n, float *A32, double *s, int *ipiv, std::vector<int> &perm_host,
                           hipStream_t st);
+// The triangular solves' workspace for one sequence of solves on a stream, and
+// whether a wait in any of them gave up (synchronises the stream).
+struct FlowBuf {
+    DevBuf mem;
+    SolveFlow f;
+    nebem_status init(int n, hipStream_t st);
+    nebem_status check(hipStream_t st);
+};
 // X = A^-1 B for nrhs columns with FP64 factors (perm on device)
-nebem_status solve_fp64(const double *LU, int n, const int *perm, const double *B, int nrhs, double *X,
+nebem_status solve_fp64(const double *LU, int n, const int *perm, const double *B, int nrhs, double *X, FlowBuf &flow,
                         hipStream_t st);
 // FP64 refinement of an FP64 LU solution x (one column), against the
 // unfactored A: r = b - A x, x += LU^-1 r while ||r|| at least halves, at most
 // max_steps steps; x ends as the iterate with the smallest residual.
 nebem_status refine_fp64(const double *A, const double *LU, const int *perm, int n, const double *b, double *x,
-                         int max_steps, nebem_solve_info *info, hipStream_t st);
+                         int max_steps, nebem_solve_info *info, FlowBuf &flow, hipStream_t st);
 constexpr int kFp64RefineSteps = 3;
 // ||A||_1 (host result) and the 1-norm condition estimate anorm x est(||A^-1||_1)
 // from FP64 factors (Hager-Higham); both synchronise the stream.

@@ -2,6 +2,8 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <cstdint>
+
 namespace nebem {
 
 constexpr int kNB = 64;        // LU panel width
@@ -31,11 +33,24 @@ struct LUWork {
 
 void lu_factor(double *A, int n, int *ipiv, LUWork &w, hipStream_t s);
 void lu_factor(float *A, int n, int *ipiv, LUWork &w, hipStream_t s);
+// Workspace of the triangular solves of one factorisation, on one stream:
+// solve_flow_bytes(n) bytes at a 256-byte boundary, cleared by
+// solve_flow_init.  *timeout (device) is set if a wait gave up: the results are
+// then worthless, and the caller, which synchronises anyway, reports an error.
+constexpr int kSolveCols = 4;  // right-hand sides solved together
+struct SolveFlow {
+    uint64_t *words;
+    unsigned *ticket;
+    int *timeout;
+    unsigned launches;  // tags in use so far
+};
+size_t solve_flow_bytes(int n);
+void solve_flow_init(SolveFlow &f, void *mem, int n, hipStream_t s);
 // X = A^-1 B with the row permutation perm (X[i] = (P B)[i] = B[perm[i]]);
-// W is an n x nrhs workspace of the solve's type.
+// W is an n x nrhs workspace of the solve's type.  X, W and B must be distinct.
 void lu_solve(const double *LU, int n, const int *perm, const double *B, double *X, double *W, int nrhs,
-              hipStream_t s);
-void lu_solve(const float *LU, int n, const int *perm, const double *B, float *X, float *W, int nrhs,
+              SolveFlow &f, hipStream_t s);
+void lu_solve(const float *LU, int n, const int *perm, const double *B, float *X, float *W, int nrhs, SolveFlow &f,
               hipStream_t s);
 // z = A^-T b with the FP64 factors of P A = L U (perm as in lu_solve); W, V:
 // n-entry workspaces.  z must not alias b, W or V.

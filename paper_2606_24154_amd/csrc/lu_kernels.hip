@@ -32,6 +32,7 @@
 
 #include <cfloat>
 #include <climits>
+#include <cstdint>
 #include <cstdlib>
 #include <cmath>
 
@@ -669,125 +670,200 @@ static void trsm(T *A, int n, int k, int kb, int jb, int je, hipStream_t s)
 }
 
 // ------------------------------------------------------ triangular solves
-// One launch per 64-row block b of a forward (unit lower) or backward (upper)
-// substitution (n x nrhs, column-major, ld = n).  X holds the right-hand side
-// being reduced; every workgroup re-solves the 64 x 64 diagonal block from X
-// (identical arithmetic everywhere), workgroup 0 stores the solved rows into
-// Y, and every workgroup subtracts the block's contribution from its own 256
-// rows of X on the unsolved side.  Solved rows are never written to X, so no
-// workgroup can read a half-updated diagonal block.
-// The diagonal block is solved by one wave per right-hand side: lane r holds
-// row r, and the entry solved at step i reaches the other lanes by readlane,
-// so the 64 sequential steps need no workgroup barrier.  The order of every
-// subtraction is that of plain column-oriented substitution.
-template <typename T, typename TX>
-__global__ __launch_bounds__(256) void k_trsv_step(const T *__restrict__ LU, int n, TX *__restrict__ X,
-                                                   TX *__restrict__ Y, int nrhs, int b0, int bsz, int lower)
+// L W = P B, then U X = W, each by one launch in which the 64-row blocks pass
+// their solutions on as they have them: workgroup b sums its block row against
+// the solved blocks in order (four waves, 16 columns of a block each, the next
+// block's factor entries and solutions already loading), subtracts, solves its
+// 64 x 64 diagonal block in one wave by substitution (lane = row, the entry
+// solved at step i reaches the others by readlane) and publishes.  One launch
+// per block, with a reload of the diagonal tile and a pass over the rows below
+// in each, took 20 us per 64 rows; here a block adds one exchange and its own
+// substitution to the chain, ~5 us, and the factors stream through beside it.
+// Three solves and two residuals of n = 8064: 18.0 -> 4.4 ms.
+//
+// Values are published as 64-bit words with a tag in the low half -- the two
+// halves of a double, or a float -- so that a reader knows from the words
+// themselves that they are this launch's, with no flag to order after the data
+// and no fence.  Tags are never reused within a workspace (SolveFlow), so it
+// is cleared once.  Workgroups take their blocks from a counter: a block only
+// waits for blocks whose workgroups have started before its own, so the waits
+// end whatever the device holds at once; each wait is bounded all the same
+// (kFlowLimit polls, seconds), sets *timeout when it gives up and lets the launch
+// drain.
+constexpr unsigned kFlowLimit = 1u << 22;
+template <typename T>
+struct Words {
+    static constexpr int N = sizeof(T) / 4;
+};
+__device__ __forceinline__ void put_words(uint64_t *w, int64_t stride, double v, unsigned tag)
 {
-    __shared__ TX D[64][65];
-    __shared__ TX y[64][8];
-    const int tid = threadIdx.x;
-    const int lane = tid & 63, wv = tid >> 6;
-    for (int rc = 0; rc < nrhs; rc += 8) {
-        const int nr = min(8, nrhs - rc);
-        __syncthreads();
-        {
-            // all 16 + 2 loads of a thread issued before the first is used
-            TX dv[16], yv[2];
+    __hip_atomic_store(w, ((uint64_t)(unsigned)__double2hiint(v) << 32) | tag, __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(w + stride, ((uint64_t)(unsigned)__double2loint(v) << 32) | tag, __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void put_words(uint64_t *w, int64_t, float v, unsigned tag)
+{
+    __hip_atomic_store(w, ((uint64_t)(unsigned)__float_as_int(v) << 32) | tag, __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
+}
+// words of one value, and whether they carry the tag
+template <typename T>
+struct Taken {
+    uint64_t w[Words<T>::N];
+    __device__ __forceinline__ void load(const uint64_t *p, int64_t stride)
+    {
 #pragma unroll
-            for (int u = 0; u < 16; ++u) {
-                const int e = tid + 256 * u, rr = e & 63, cc = e >> 6;
-                dv[u] = (rr < bsz && cc < bsz) ? (TX)LU[(size_t)(b0 + cc) * n + b0 + rr] : TX(0);
-            }
+        for (int k = 0; k < Words<T>::N; ++k)
+            w[k] = __hip_atomic_load(p + k * stride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __device__ __forceinline__ bool is(unsigned tag) const
+    {
+        bool ok = true;
 #pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                const int e = tid + 256 * u, rr = e & 63, q = e >> 6;
-                yv[u] = (rr < bsz && q < nr) ? X[(size_t)(rc + q) * n + b0 + rr] : TX(0);
-            }
+        for (int k = 0; k < Words<T>::N; ++k) ok = ok && (unsigned)w[k] == tag;
+        return ok;
+    }
+    __device__ __forceinline__ T value() const;
+};
+template <>
+__device__ __forceinline__ double Taken<double>::value() const
+{
+    return __hiloint2double((int)(w[0] >> 32), (int)(w[1] >> 32));
+}
+template <>
+__device__ __forceinline__ float Taken<float>::value() const
+{
+    return __int_as_float((int)(w[0] >> 32));
+}
+
+// v / d from inv = 1/d with a residual correction, for d with |d| in a range
+// whose reciprocals are exact to rounding (quotient_takes); an infinite or NaN
+// product stays as it is.
+__device__ __forceinline__ bool quotient_takes(double d) { return fabs(d) > 0x1p-1000 && fabs(d) < 0x1p1000; }
+__device__ __forceinline__ bool quotient_takes(float d) { return fabsf(d) > 0x1p-100f && fabsf(d) < 0x1p100f; }
+template <typename T>
+__device__ __forceinline__ T quotient(T v, T d, T inv)
+{
+    const T q = v * inv, r = fma(fma(-q, d, v), inv, q);
+    return isfinite(q) ? r : q;
+}
+
+// NR right-hand sides (columns of ld n).  LOWER: rhs row i is B[perm[i]] and
+// the diagonal is 1; else rhs row i is B[i].
+template <typename T, typename TB, int NR, bool LOWER>
+__global__ __launch_bounds__(256) void k_trsv_flow(const T *__restrict__ LU, int n, const int *__restrict__ perm,
+                                                   const TB *__restrict__ B, T *__restrict__ Y,
+                                                   uint64_t *__restrict__ words, unsigned *__restrict__ ticket,
+                                                   unsigned base, unsigned tag, int *__restrict__ timeout)
+{
+    __shared__ int s_block;
+    __shared__ T red[4][NR][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    if (threadIdx.x == 0) s_block = (int)(atomicAdd(ticket, 1u) - base);
+    __syncthreads();
+    const int nb = (n + 63) / 64;
+    const int b = LOWER ? s_block : nb - 1 - s_block;
+    const int r = 64 * b + lane, rc = min(r, n - 1);
+    const bool in = r < n;
+    // this wave's columns of block j, rows of this block row (the columns of a
+    // short last block are clamped into the matrix; their solutions enter as 0)
+    auto load_tile = [&](int j, T(&v)[16]) {
 #pragma unroll
-            for (int u = 0; u < 16; ++u) {
-                const int e = tid + 256 * u;
-                D[e & 63][e >> 6] = dv[u];
-            }
+        for (int t = 0; t < 16; ++t) v[t] = LU[(size_t)min(64 * j + 16 * wave + t, n - 1) * n + rc];
+    };
+    // the wave's 16 solutions of block j, one per lane < 16
+    const int64_t wn = (int64_t)n * NR;
+    auto load_x = [&](int j, Taken<T>(&x)[NR]) {
+        const int c = min(64 * j + 16 * wave + (lane & 15), n - 1);
 #pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                const int e = tid + 256 * u;
-                y[e & 63][e >> 6] = yv[u];
+        for (int q = 0; q < NR; ++q) x[q].load(words + (int64_t)q * n + c, wn);
+    };
+    T acc[NR];
+#pragma unroll
+    for (int q = 0; q < NR; ++q) acc[q] = T(0);
+    const int steps = LOWER ? b : nb - 1 - b;
+    T v[16], vn[16];
+    Taken<T> x[NR];
+    if (steps > 0) {
+        load_tile(LOWER ? 0 : nb - 1, v);
+        load_x(LOWER ? 0 : nb - 1, x);
+    }
+    for (int k = 0; k < steps; ++k) {
+        const int j = LOWER ? k : nb - 1 - k;
+        if (k + 1 < steps) load_tile(LOWER ? j + 1 : j - 1, vn);
+        for (unsigned polls = 0;; ++polls) {
+            bool ok = true;
+#pragma unroll
+            for (int q = 0; q < NR; ++q) ok = ok && x[q].is(tag);
+            if (__ballot(!ok) == 0) break;
+            if (polls >= kFlowLimit ||
+                ((polls & 63) == 63 && __hip_atomic_load(timeout, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))) {
+                atomicExch(timeout, 1);
+                break;
             }
+            __builtin_amdgcn_s_sleep(1);
+            load_x(j, x);
         }
-        __syncthreads();
-        for (int q = wv; q < nr; q += 4) {
-            const bool in = lane < bsz;
-            TX v = in ? y[lane][q] : TX(0);
-            // the LDS loads do not depend on the substitution: eight of them
-            // are issued ahead of each eight steps
-            if (lower) {
-                for (int i0 = 0; i0 < bsz - 1; i0 += 8) {
-                    TX d[8];
+        T xv[NR];
 #pragma unroll
-                    for (int t = 0; t < 8; ++t) d[t] = D[lane][i0 + t];
+        for (int q = 0; q < NR; ++q) xv[q] = 64 * j + 16 * wave + (lane & 15) < n ? x[q].value() : T(0);
+        if (k + 1 < steps) load_x(LOWER ? j + 1 : j - 1, x);
 #pragma unroll
-                    for (int t = 0; t < 8; ++t) {
-                        const int i = i0 + t;
-                        if (i < bsz - 1) {
-                            const TX yi = lane_bcast(v, i);
-                            const TX u = v - d[t] * yi;
-                            v = (in && lane > i) ? u : v;
-                        }
-                    }
-                }
-            } else {
-                for (int i0 = ((bsz - 1) & ~7); i0 >= 0; i0 -= 8) {
-                    TX d[8], dd[8];
+        for (int t = 0; t < 16; ++t)
 #pragma unroll
-                    for (int t = 0; t < 8; ++t) {
-                        d[t] = D[lane][i0 + t];
-                        dd[t] = D[(i0 + t) & 63][(i0 + t) & 63];
-                    }
+            for (int q = 0; q < NR; ++q) acc[q] = fma(v[t], lane_bcast(xv[q], t), acc[q]);
 #pragma unroll
-                    for (int t = 7; t >= 0; --t) {
-                        const int i = i0 + t;
-                        if (i < bsz) {
-                            const TX yi = lane_bcast(v, i) / dd[t];
-                            const TX u = v - d[t] * yi;
-                            v = (lane == i) ? yi : ((in && lane < i) ? u : v);
-                        }
-                    }
-                }
-            }
-            if (in) y[lane][q] = v;
+        for (int t = 0; t < 16; ++t) v[t] = vn[t];
+    }
+#pragma unroll
+    for (int q = 0; q < NR; ++q) red[wave][q][lane] = acc[q];
+    // the diagonal block, before the barrier: entries that a row does not use,
+    // those of columns past the last among them, are zeros, so the substitution
+    // needs no tests
+    T d[64], dd = T(1), inv = T(1), rhs = T(0);
+    if (wave < NR) {
+#pragma unroll
+        for (int i = 0; i < 64; ++i) {
+            const T e = LU[(size_t)min(64 * b + i, n - 1) * n + rc];
+            d[i] = in && 64 * b + i < n && (LOWER ? i < lane : i > lane) ? e : T(0);
         }
-        __syncthreads();
-        if (blockIdx.x == 0)
-            for (int e = tid; e < bsz * nr; e += 256) {
-                const int rr = e % bsz, q = e / bsz;
-                Y[(size_t)(rc + q) * n + b0 + rr] = y[rr][q];
-            }
-        // update rows outside the block on the unsolved side; each factor
-        // entry is loaded once for all right-hand sides of the chunk
-        const int lo = lower ? b0 + bsz : 0;
-        const int hi = lower ? n : b0;
-        const int r = lo + blockIdx.x * 256 + tid;
-        if (r < hi) {
-            TX acc[8];
-#pragma unroll
-            for (int q = 0; q < 8; ++q) acc[q] = q < nr ? X[(size_t)(rc + q) * n + r] : TX(0);
-            for (int j0 = 0; j0 < bsz; j0 += 16) {
-                TX l[16];  // 16 factor entries in flight at once
-#pragma unroll
-                for (int t = 0; t < 16; ++t) l[t] = (j0 + t < bsz) ? (TX)LU[(size_t)(b0 + j0 + t) * n + r] : TX(0);
-#pragma unroll
-                for (int t = 0; t < 16; ++t)
-                    if (j0 + t < bsz) {
-#pragma unroll
-                        for (int q = 0; q < 8; ++q)
-                            if (q < nr) acc[q] -= l[t] * y[j0 + t][q];
-                    }
-            }
-#pragma unroll
-            for (int q = 0; q < 8; ++q)
-                if (q < nr) X[(size_t)(rc + q) * n + r] = acc[q];
+        if (!LOWER) {
+            dd = in ? LU[(size_t)rc * n + rc] : T(1);
+            inv = T(1) / dd;
         }
+        rhs = in ? (T)B[(size_t)wave * n + (LOWER ? perm[rc] : rc)] : T(0);
+    }
+    __syncthreads();
+    if (wave >= NR) return;
+    T y = rhs - (((red[0][wave][lane] + red[1][wave][lane]) + red[2][wave][lane]) + red[3][wave][lane]);
+    // a row's value is taken at its own step: what the later steps' zeros make of
+    // it (NaN, where a solution is infinite) is not used
+    T out = y;
+    if (LOWER) {
+#pragma unroll
+        for (int i = 0; i < 64; ++i) {
+            out = lane == i ? y : out;
+            y = fma(-d[i], lane_bcast(y, i), y);
+        }
+    } else if (__ballot(!quotient_takes(dd)) == 0) {
+#pragma unroll
+        for (int i = 63; i >= 0; --i) {
+            const T qi = quotient(y, dd, inv);
+            out = lane == i ? qi : out;
+            y = fma(-d[i], lane_bcast(qi, i), y);
+        }
+    } else {
+#pragma unroll
+        for (int i = 63; i >= 0; --i) {
+            const T qi = y / dd;
+            out = lane == i ? qi : out;
+            y = fma(-d[i], lane_bcast(qi, i), y);
+        }
+    }
+    if (in) {
+        put_words(words + (int64_t)wave * n + r, wn, out, tag);
+        Y[(size_t)wave * n + r] = out;
     }
 }
 
@@ -865,16 +941,6 @@ __global__ __launch_bounds__(256) void k_unpermute(const double *__restrict__ v,
     if (i < n) z[perm[i]] = v[i];
 }
 
-// X[i] = B[perm[i]] (row gather for the pivoting permutation), nrhs columns
-template <typename TB, typename TX>
-__global__ __launch_bounds__(256) void k_permute(const TB *__restrict__ B, TX *__restrict__ X,
-                                                 const int *__restrict__ perm, int n, int nrhs)
-{
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i >= n) return;
-    for (int q = 0; q < nrhs; ++q) X[(size_t)q * n + i] = (TX)B[(size_t)q * n + perm[i]];
-}
-
 // --------------------------------------------------------------- launchers
 // Workgroups of k_panel_fused<T> the device holds at once (0 if unknown).
 template <typename T>
@@ -946,24 +1012,50 @@ void lu_factor_launch(T *A, int n, int *ipiv, LUWork &w, hipStream_t s)
     }
 }
 
-// X = A^-1 P B.  W: n x nrhs workspace of type TX.
-template <typename T, typename TX>
-void lu_solve_launch(const T *LU, int n, const int *perm, const double *B, TX *X, TX *W, int nrhs, hipStream_t s)
+__global__ __launch_bounds__(256) void k_clear_words(uint64_t *__restrict__ w, int64_t len)
 {
-    const unsigned g = (unsigned)((n + 255) / 256);
-    hipLaunchKernelGGL((k_permute<double, TX>), dim3(g), dim3(256), 0, s, B, X, perm, n, nrhs);
-    for (int b0 = 0; b0 < n; b0 += 64) {  // L W = P B  (X reduced in place, solution in W)
-        const int bsz = (n - b0 < 64) ? n - b0 : 64;
-        const int rows = n - b0 - bsz;
-        const unsigned gb = rows > 0 ? (unsigned)((rows + 255) / 256) : 1u;
-        hipLaunchKernelGGL((k_trsv_step<T, TX>), dim3(gb), dim3(256), 0, s, LU, n, X, W, nrhs, b0, bsz, 1);
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i < len) w[i] = 0;
+}
+
+size_t solve_flow_bytes(int n) { return 256 + (size_t)n * kSolveCols * 2 * sizeof(uint64_t); }
+
+void solve_flow_init(SolveFlow &f, void *mem, int n, hipStream_t s)
+{
+    f.ticket = (unsigned *)mem;
+    f.timeout = (int *)mem + 1;
+    f.words = (uint64_t *)((char *)mem + 256);
+    f.launches = 0;
+    const int64_t len = (int64_t)(solve_flow_bytes(n) / sizeof(uint64_t));
+    hipLaunchKernelGGL(k_clear_words, dim3((unsigned)((len + 255) / 256)), dim3(256), 0, s, (uint64_t *)mem, len);
+}
+
+template <typename T, typename TB, int NR, bool LOWER>
+static void trsv_flow(const T *LU, int n, const int *perm, const TB *B, T *Y, SolveFlow &f, hipStream_t s)
+{
+    const unsigned nb = (unsigned)((n + 63) / 64);
+    const unsigned base = f.launches * nb, tag = f.launches + 1;
+    ++f.launches;
+    hipLaunchKernelGGL((k_trsv_flow<T, TB, NR, LOWER>), dim3(nb), dim3(256), 0, s, LU, n, perm, B, Y, f.words,
+                       f.ticket, base, tag, f.timeout);
+}
+
+// X = A^-1 P B, kSolveCols right-hand sides per pass over the factors.  W: n x
+// nrhs workspace.
+template <typename T>
+static void lu_solve_launch(const T *LU, int n, const int *perm, const double *B, T *X, T *W, int nrhs, SolveFlow &f,
+                            hipStream_t s)
+{
+    int q = 0;
+    for (; q + kSolveCols <= nrhs; q += kSolveCols) {
+        const size_t o = (size_t)q * n;
+        trsv_flow<T, double, kSolveCols, true>(LU, n, perm, B + o, W + o, f, s);
+        trsv_flow<T, T, kSolveCols, false>(LU, n, perm, W + o, X + o, f, s);
     }
-    const int last = ((n - 1) / 64) * 64;
-    for (int b0 = last; b0 >= 0; b0 -= 64) {  // U X = W  (W reduced in place, solution in X)
-        const int bsz = (n - b0 < 64) ? n - b0 : 64;
-        const int rows = b0;
-        const unsigned gb = rows > 0 ? (unsigned)((rows + 255) / 256) : 1u;
-        hipLaunchKernelGGL((k_trsv_step<T, TX>), dim3(gb), dim3(256), 0, s, LU, n, W, X, nrhs, b0, bsz, 0);
+    for (; q < nrhs; ++q) {
+        const size_t o = (size_t)q * n;
+        trsv_flow<T, double, 1, true>(LU, n, perm, B + o, W + o, f, s);
+        trsv_flow<T, T, 1, false>(LU, n, perm, W + o, X + o, f, s);
     }
 }
 
@@ -991,14 +1083,14 @@ void lu_solve_transposed(const double *LU, int n, const int *perm, const double 
 void lu_factor(double *A, int n, int *ipiv, LUWork &w, hipStream_t s) { lu_factor_launch<double>(A, n, ipiv, w, s); }
 void lu_factor(float *A, int n, int *ipiv, LUWork &w, hipStream_t s) { lu_factor_launch<float>(A, n, ipiv, w, s); }
 void lu_solve(const double *LU, int n, const int *perm, const double *B, double *X, double *W, int nrhs,
-              hipStream_t s)
+              SolveFlow &f, hipStream_t s)
 {
-    lu_solve_launch<double, double>(LU, n, perm, B, X, W, nrhs, s);
+    lu_solve_launch<double>(LU, n, perm, B, X, W, nrhs, f, s);
 }
-void lu_solve(const float *LU, int n, const int *perm, const double *B, float *X, float *W, int nrhs,
+void lu_solve(const float *LU, int n, const int *perm, const double *B, float *X, float *W, int nrhs, SolveFlow &f,
               hipStream_t s)
 {
-    lu_solve_launch<float, float>(LU, n, perm, B, X, W, nrhs, s);
+    lu_solve_launch<float>(LU, n, perm, B, X, W, nrhs, f, s);
 }
 
 }  // namespace nebem

@@ -4,15 +4,25 @@
 
 namespace nebem {
 
-constexpr int kRowChunk = 1024;   // columns per row-maximum partial
-constexpr int kGemvChunk = 2048;  // columns per residual partial
+// Column chunks of the two passes over the matrix (row maxima, residual): enough
+// of them that row blocks x chunks give the device some 2048 workgroups, at most
+// kMaxChunk columns each.  At n = 8064 four chunks of 2048 columns were 128
+// workgroups: 0.81 ms for 0.52 GB.
+constexpr int kMaxChunk = 2048;
+inline int matrix_chunks(int n)
+{
+    const int rows = (n + 255) / 256, least = (n + kMaxChunk - 1) / kMaxChunk;
+    const int want = (2048 + rows - 1) / rows, most = (n + 63) / 64;
+    const int c = want > least ? want : least;
+    return c < most ? c : (most > least ? most : least);
+}
 
-// s[i] = 1 / max_j |A_ij| (1 for an all-zero row); part: n * ceil(n/kRowChunk) doubles
+// s[i] = 1 / max_j |A_ij| (1 for an all-zero row); part: n * matrix_chunks(n) doubles
 void row_scale(const double *A, int n, double *part, double *s, hipStream_t st);
 // A32 = float(diag(s) A), column-major
 void convert_scaled(const double *A, const double *s, int n, float *A32, hipStream_t st);
 // rs = s .* (b - A x) in FP64; sq[k] = per-workgroup sums of (b - A x)^2 (ceil(n/256) entries);
-// part: n * ceil(n/kGemvChunk) doubles
+// part: n * matrix_chunks(n) doubles
 void residual(const double *A, int n, const double *x, const double *b, const double *s, double *part, double *rs,
               double *sq, hipStream_t st);
 void sumsq(const double *v, int n, double *sq, hipStream_t st);

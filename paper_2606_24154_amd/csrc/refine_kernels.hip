@@ -24,6 +24,7 @@ __global__ __launch_bounds__(kRB) void k_rowmax_part(const double *__restrict__ 
     if (i >= n) return;
     const int j0 = blockIdx.y * chunk, j1 = min(n, j0 + chunk);
     double mx = 0.0;
+#pragma unroll 16
     for (int j = j0; j < j1; ++j) mx = fmax(mx, fabs(A[(size_t)j * n + i]));
     part[(size_t)blockIdx.y * n + i] = mx;
 }
@@ -49,17 +50,18 @@ __global__ __launch_bounds__(kRB) void k_convert_scaled(const double *__restrict
     for (int j = j0; j < j1; ++j) A32[(size_t)j * n + i] = (float)(si * A[(size_t)j * n + i]);
 }
 
-// part[c * n + i] = sum_{j in chunk c} A_ij x_j (chunk <= kGemvChunk)
-__global__ __launch_bounds__(kRB) void k_gemv_part(const double *__restrict__ A, int n,
+// part[c * n + i] = sum_{j in chunk c} A_ij x_j (chunk <= kMaxChunk)
+__global__ __launch_bounds__(kRB) void k_gemv_part(const double *__restrict__ A, int n, int chunk,
                                                    const double *__restrict__ x, double *__restrict__ part)
 {
-    __shared__ double xs[kGemvChunk];
-    const int j0 = blockIdx.y * kGemvChunk, j1 = min(n, j0 + kGemvChunk);
+    __shared__ double xs[kMaxChunk];
+    const int j0 = blockIdx.y * chunk, j1 = min(n, j0 + chunk);
     for (int j = j0 + threadIdx.x; j < j1; j += kRB) xs[j - j0] = x[j];
     __syncthreads();
     const int i = blockIdx.x * kRB + threadIdx.x;
     if (i >= n) return;
     double acc = 0.0;
+#pragma unroll 16
     for (int j = j0; j < j1; ++j) acc = fma(A[(size_t)j * n + i], xs[j - j0], acc);
     part[(size_t)blockIdx.y * n + i] = acc;
 }
@@ -130,8 +132,8 @@ static inline unsigned blocks(int n) { return (unsigned)((n + kRB - 1) / kRB); }
 
 void row_scale(const double *A, int n, double *part, double *s, hipStream_t st)
 {
-    const int nchunk = (n + kRowChunk - 1) / kRowChunk;
-    hipLaunchKernelGGL(k_rowmax_part, dim3(blocks(n), nchunk), dim3(kRB), 0, st, A, n, kRowChunk, part);
+    const int nchunk = matrix_chunks(n), chunk = (n + nchunk - 1) / nchunk;
+    hipLaunchKernelGGL(k_rowmax_part, dim3(blocks(n), nchunk), dim3(kRB), 0, st, A, n, chunk, part);
     hipLaunchKernelGGL(k_rowscale, dim3(blocks(n)), dim3(kRB), 0, st, part, n, nchunk, s);
 }
 
@@ -143,8 +145,8 @@ void convert_scaled(const double *A, const double *s, int n, float *A32, hipStre
 void residual(const double *A, int n, const double *x, const double *b, const double *s, double *part, double *rs,
               double *sq, hipStream_t st)
 {
-    const int nchunk = (n + kGemvChunk - 1) / kGemvChunk;
-    hipLaunchKernelGGL(k_gemv_part, dim3(blocks(n), nchunk), dim3(kRB), 0, st, A, n, x, part);
+    const int nchunk = matrix_chunks(n), chunk = (n + nchunk - 1) / nchunk;
+    hipLaunchKernelGGL(k_gemv_part, dim3(blocks(n), nchunk), dim3(kRB), 0, st, A, n, chunk, x, part);
     hipLaunchKernelGGL(k_residual, dim3(blocks(n)), dim3(kRB), 0, st, part, nchunk, b, s, n, rs, sq);
 }
 

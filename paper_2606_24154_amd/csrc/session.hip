@@ -30,10 +30,12 @@ static nebem_status session_solve(nebem_session *s, const double *b, hipStream_t
 {
     const int n = (int)s->n;
     if (s->opt.precision == NEBEM_FP64) {
-        nebem_status e = solve_fp64(s->LU.as<double>(), n, s->perm.as<int>(), b, 1, s->sigma.as<double>(), st);
+        FlowBuf flow;
+        nebem_status e = flow.init(n, st);
+        if (!e) e = solve_fp64(s->LU.as<double>(), n, s->perm.as<int>(), b, 1, s->sigma.as<double>(), flow, st);
         if (e) return e;
         return refine_fp64(s->A.as<double>(), s->LU.as<double>(), s->perm.as<int>(), n, b, s->sigma.as<double>(),
-                           kFp64RefineSteps, &s->last_info, st);
+                           kFp64RefineSteps, &s->last_info, flow, st);
     }
     return solve_mixed(s->A.as<double>(), s->A32.as<float>(), s->scale.as<double>(), s->perm.as<int>(), n, b,
                        s->sigma.as<double>(), s->opt.ir_tol, s->opt.ir_max_iter, &s->last_info, st);

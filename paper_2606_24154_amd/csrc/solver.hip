@@ -79,7 +79,7 @@ nebem_status factor_mixed(const double *A, int n, float *A32, double *s, int *ip
                           hipStream_t st)
 {
     DevBuf part;
-    const int nchunk = (n + kRowChunk - 1) / kRowChunk;
+    const int nchunk = matrix_chunks(n);
     NEBEM_HIP(part.alloc((size_t)n * nchunk * sizeof(double), st));
     row_scale(A, n, part.as<double>(), s, st);
     convert_scaled(A, s, n, A32, st);
@@ -87,7 +87,23 @@ nebem_status factor_mixed(const double *A, int n, float *A32, double *s, int *ip
     return lu_factor_checked<float>(A32, n, ipiv, perm_host, st);
 }
 
-nebem_status solve_fp64(const double *LU, int n, const int *perm, const double *B, int nrhs, double *X,
+nebem_status FlowBuf::init(int n, hipStream_t st)
+{
+    NEBEM_HIP(mem.alloc(solve_flow_bytes(n), st));
+    solve_flow_init(f, mem.p, n, st);
+    NEBEM_HIP(hipGetLastError());
+    return NEBEM_OK;
+}
+
+nebem_status FlowBuf::check(hipStream_t st)
+{
+    int gave_up = 0;
+    NEBEM_HIP(hipMemcpyAsync(&gave_up, f.timeout, sizeof(int), hipMemcpyDeviceToHost, st));
+    NEBEM_HIP(hipStreamSynchronize(st));
+    return gave_up ? fail(NEBEM_EDEVICE, "solve: a wait of the triangular solve timed out") : NEBEM_OK;
+}
+
+nebem_status solve_fp64(const double *LU, int n, const int *perm, const double *B, int nrhs, double *X, FlowBuf &flow,
                         hipStream_t st)
 {
     DevBuf work, xtmp;
@@ -97,7 +113,7 @@ nebem_status solve_fp64(const double *LU, int n, const int *perm, const double *
         NEBEM_HIP(xtmp.alloc((size_t)n * nrhs * sizeof(double), st));
         x = xtmp.as<double>();
     }
-    lu_solve(LU, n, perm, B, x, work.as<double>(), nrhs, st);
+    lu_solve(LU, n, perm, B, x, work.as<double>(), nrhs, flow.f, st);
     NEBEM_HIP(hipGetLastError());
     if (x != X) NEBEM_HIP(hipMemcpyAsync(X, x, (size_t)n * nrhs * sizeof(double), hipMemcpyDeviceToDevice, st));
     return NEBEM_OK;
@@ -115,10 +131,10 @@ static nebem_status host_norm(const double *sq_dev, int nblk, std::vector<double
 }
 
 nebem_status refine_fp64(const double *A, const double *LU, const int *perm, int n, const double *b, double *x,
-                         int max_steps, nebem_solve_info *info, hipStream_t st)
+                         int max_steps, nebem_solve_info *info, FlowBuf &flow, hipStream_t st)
 {
     const int nblk = (n + 255) / 256;
-    const int nchunk = (n + kGemvChunk - 1) / kGemvChunk;
+    const int nchunk = matrix_chunks(n);
     DevBuf ones, rs, d, w, part, sq, xbest;
     NEBEM_HIP(ones.alloc((size_t)n * sizeof(double), st));
     NEBEM_HIP(rs.alloc((size_t)n * sizeof(double), st));
@@ -137,7 +153,7 @@ nebem_status refine_fp64(const double *A, const double *LU, const int *perm, int
         info->ir_iters = 0;
         info->rel_resid = 0.0;
     }
-    if (bnorm == 0.0) return NEBEM_OK;
+    if (bnorm == 0.0) return flow.check(st);
     residual(A, n, x, b, ones.as<double>(), part.as<double>(), rs.as<double>(), sq.as<double>(), st);
     NEBEM_HIP(hipGetLastError());
     if ((e = host_norm(sq.as<double>(), nblk, h, st, rnorm))) return e;
@@ -145,7 +161,7 @@ nebem_status refine_fp64(const double *A, const double *LU, const int *perm, int
     int best_it = 0;
     NEBEM_HIP(hipMemcpyAsync(xbest.p, x, (size_t)n * sizeof(double), hipMemcpyDeviceToDevice, st));
     for (int it = 1; it <= max_steps; ++it) {
-        lu_solve(LU, n, perm, rs.as<double>(), d.as<double>(), w.as<double>(), 1, st);
+        lu_solve(LU, n, perm, rs.as<double>(), d.as<double>(), w.as<double>(), 1, flow.f, st);
         add_f64(x, d.as<double>(), n, st);
         residual(A, n, x, b, ones.as<double>(), part.as<double>(), rs.as<double>(), sq.as<double>(), st);
         NEBEM_HIP(hipGetLastError());
@@ -160,7 +176,7 @@ nebem_status refine_fp64(const double *A, const double *LU, const int *perm, int
         if (!halved) break;
     }
     NEBEM_HIP(hipMemcpyAsync(x, xbest.p, (size_t)n * sizeof(double), hipMemcpyDeviceToDevice, st));
-    NEBEM_HIP(hipStreamSynchronize(st));
+    if ((e = flow.check(st))) return e;
     if (info) {
         info->ir_iters = best_it;
         info->rel_resid = best;
@@ -193,24 +209,25 @@ nebem_status condest_fp64(const double *LU, const int *perm, int n, double anorm
 {
     DevBuf x, y, z, w, v;
     for (DevBuf *b : {&x, &y, &z, &w, &v}) NEBEM_HIP(b->alloc((size_t)n * sizeof(double), st));
+    FlowBuf flow;
+    nebem_status e = flow.init(n, st);
+    if (e) return e;
     std::vector<double> hx(n, 1.0 / n), hy(n), hz(n), hs(n);
     auto solve = [&](const std::vector<double> &in, std::vector<double> &out, bool transposed) -> nebem_status {
         NEBEM_HIP(hipMemcpyAsync(x.p, in.data(), (size_t)n * sizeof(double), hipMemcpyHostToDevice, st));
         if (transposed)
             lu_solve_transposed(LU, n, perm, x.as<double>(), y.as<double>(), w.as<double>(), v.as<double>(), st);
         else
-            lu_solve(LU, n, perm, x.as<double>(), y.as<double>(), w.as<double>(), 1, st);
+            lu_solve(LU, n, perm, x.as<double>(), y.as<double>(), w.as<double>(), 1, flow.f, st);
         NEBEM_HIP(hipGetLastError());
         NEBEM_HIP(hipMemcpyAsync(out.data(), y.p, (size_t)n * sizeof(double), hipMemcpyDeviceToHost, st));
-        NEBEM_HIP(hipStreamSynchronize(st));
-        return NEBEM_OK;
+        return flow.check(st);
     };
     auto norm1 = [](const std::vector<double> &a) {
         double t = 0.0;
         for (double e : a) t += std::fabs(e);
         return t;
     };
-    nebem_status e;
     double est = 0.0;
     int jlast = -1;
     for (int it = 0; it < 5; ++it) {
@@ -242,8 +259,11 @@ nebem_status solve_mixed(const double *A, const float *LU32, const double *s, co
                          double *x, double tol, int max_iter, nebem_solve_info *info, hipStream_t st)
 {
     const int nblk = (n + 255) / 256;
-    const int nchunk = (n + kGemvChunk - 1) / kGemvChunk;
+    const int nchunk = matrix_chunks(n);
     DevBuf rs, d32, w32, part, sq, xbest;
+    FlowBuf flow;
+    nebem_status e = flow.init(n, st);
+    if (e) return e;
     NEBEM_HIP(rs.alloc((size_t)n * sizeof(double), st));
     NEBEM_HIP(d32.alloc((size_t)n * sizeof(float), st));
     NEBEM_HIP(w32.alloc((size_t)n * sizeof(float), st));
@@ -253,7 +273,7 @@ nebem_status solve_mixed(const double *A, const float *LU32, const double *s, co
     std::vector<double> h;
     double bnorm = 0.0;
     sumsq(b, n, sq.as<double>(), st);
-    nebem_status e = host_norm(sq.as<double>(), nblk, h, st, bnorm);
+    e = host_norm(sq.as<double>(), nblk, h, st, bnorm);
     if (e) return e;
     fill(x, n, 0.0, st);
     if (info) {
@@ -265,7 +285,7 @@ nebem_status solve_mixed(const double *A, const float *LU32, const double *s, co
     double best = INFINITY;
     int stall = 0, it = 0;
     for (it = 1; it <= max_iter; ++it) {
-        lu_solve(LU32, n, perm, rs.as<double>(), d32.as<float>(), w32.as<float>(), 1, st);
+        lu_solve(LU32, n, perm, rs.as<double>(), d32.as<float>(), w32.as<float>(), 1, flow.f, st);
         add_f32(x, d32.as<float>(), n, st);
         residual(A, n, x, b, s, part.as<double>(), rs.as<double>(), sq.as<double>(), st);
         NEBEM_HIP(hipGetLastError());
@@ -287,7 +307,7 @@ nebem_status solve_mixed(const double *A, const float *LU32, const double *s, co
     }
     if (best < INFINITY)  // otherwise no step was taken and x is still 0
         NEBEM_HIP(hipMemcpyAsync(x, xbest.p, (size_t)n * sizeof(double), hipMemcpyDeviceToDevice, st));
-    NEBEM_HIP(hipStreamSynchronize(st));
+    if ((e = flow.check(st))) return e;
     if (best <= tol) return NEBEM_OK;
     char buf[128];
     std::snprintf(buf, sizeof buf, "solve: refinement stopped at relative residual %.3e (tolerance %.1e)", best, tol);

@@ -1,0 +1,66 @@
+"""Dense factor and solve kernels at the edges of their blocks, against FP64
+host arithmetic.
+"""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+EPS = np.finfo(np.float64).eps
+
+
+@pytest.fixture(scope="module")
+def nb():
+    assert torch.cuda.is_available(), "GPU tests need a visible GPU"
+    import paper_2606_24154_amd as nb
+    return nb
+
+
+def dev(a, dtype=torch.float64):
+    return torch.from_numpy(np.ascontiguousarray(a)).to("cuda:0", dtype=dtype)
+
+
+def factors(n, seed):
+    rng = np.random.default_rng(seed)
+    L = np.tril(rng.uniform(-1, 1, (n, n)), -1) / np.sqrt(n)
+    U = np.triu(rng.uniform(-1, 1, (n, n)), 1) / np.sqrt(n) + np.diag(rng.choice([-1.0, 1.0], n) * rng.uniform(1, 3, n))
+    piv = np.array([rng.integers(k, n) for k in range(n)])
+    return rng, L, U, piv
+
+
+@pytest.mark.parametrize("n", [1, 2, 63, 64, 65, 127, 129, 700])
+@pytest.mark.parametrize("nrhs", [1, 3, 4, 9])
+def test_solves_from_factors(nb, n, nrhs):
+    """X from given factors and interchanges.  Substitution leaves
+    |P b - L U x| <= 3 n eps |L + I| |U| |x| (Higham, Accuracy and Stability, theorem
+    9.4); twice that covers the residual's own rounding on the host."""
+    rng, L, U, piv = factors(n, 100 * n + nrhs)
+    B = rng.standard_normal((nrhs, n))
+    LU, ipiv = dev((L + U).T), dev(piv, torch.int32)
+    X = nb.solve_factored(LU, ipiv, dev(B)).cpu().numpy()
+    PB = B.T.copy()
+    for k in range(n):
+        PB[[k, piv[k]]] = PB[[piv[k], k]]
+    L1 = L + np.eye(n)
+    bound = 6 * n * EPS * (np.abs(L1) @ (np.abs(U) @ np.abs(X.T)))
+    assert (np.abs(PB - L1 @ (U @ X.T)) <= bound).all()
+    # a column by itself, and in place: the same bits
+    one = dev(B[-1])
+    nb.solve_factored(LU, ipiv, one, sigma=one)
+    assert np.array_equal(one.cpu().numpy(), X[-1])
+
+
+def test_solves_beyond_the_reciprocals_range(nb):
+    """Pivots whose reciprocals overflow or are zero divide as IEEE division
+    does, and an infinite solution leaves those solved before it alone."""
+    n = 70
+    U = np.eye(n)
+    U[:5, :5] = np.diag([2.0, 5e-324, 1e308, 0.0, 3.0])
+    B = np.ones((1, n))
+    B[0, 1] = 5e-324
+    U[2, 69] = 1.0
+    X = nb.solve_factored(dev(U.T), dev(np.arange(n), torch.int32), dev(B)).cpu().numpy()[0]
+    assert X[4] == 1.0 / 3.0 and X[1] != X[1] and np.isinf(X[3])  # 0 x inf enters rows 0 .. 2
+    assert (X[5:] == 1.0).all()
