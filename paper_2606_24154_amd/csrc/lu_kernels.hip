@@ -11,9 +11,9 @@
 // once per outer block instead of once per panel:
 //   for each outer block [K0, K1):
 //     for each panel [k, k+kb) of it:
-//       1. panel factorisation: every workgroup owns 256 consecutive rows.
+//       1. panel factorisation: every workgroup owns 64 or 256 consecutive rows.
 //          Normally one cooperative launch for the whole panel, the rows kept
-//          in LDS and the columns separated by grid barriers (k_panel_fused);
+//          in LDS and the pivots agreed on through memory (k_panel_fused);
 //          if the device cannot hold all of the panel's workgroups at once,
 //          one launch per column: a launch eliminates column c on its rows
 //          (scale by the pivot, rank-1 update of the rest of the panel) and
@@ -171,151 +171,291 @@ __global__ __launch_bounds__(kPB) void k_panel(T *__restrict__ A, int n, int k, 
     }
 }
 
+// --------------------------------------------- values passed between workgroups
+// Values that workgroups of one launch pass to each other are published as
+// 64-bit words with a tag in the low half -- the two halves of a double, or a
+// float -- so that a reader knows from the words themselves that they are the
+// ones it waits for, with no flag to order after the data and no fence.  Every
+// wait is bounded (kSpinLimit polls, seconds): one that gives up sets *timeout,
+// every wait that then sees the flag returns, the launches run to their end and
+// the host reports an error instead of the device hanging.
+constexpr unsigned kSpinLimit = 1u << 22;
+template <typename T>
+struct Words {
+    static constexpr int N = sizeof(T) / 4;
+};
+__device__ __forceinline__ void put_words(uint64_t *w, int64_t stride, double v, unsigned tag)
+{
+    __hip_atomic_store(w, ((uint64_t)(unsigned)__double2hiint(v) << 32) | tag, __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(w + stride, ((uint64_t)(unsigned)__double2loint(v) << 32) | tag, __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void put_words(uint64_t *w, int64_t, float v, unsigned tag)
+{
+    __hip_atomic_store(w, ((uint64_t)(unsigned)__float_as_int(v) << 32) | tag, __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
+}
+// words of one value, and whether they carry the tag
+template <typename T>
+struct Taken {
+    uint64_t w[Words<T>::N];
+    __device__ __forceinline__ void load(const uint64_t *p, int64_t stride)
+    {
+#pragma unroll
+        for (int k = 0; k < Words<T>::N; ++k)
+            w[k] = __hip_atomic_load(p + k * stride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __device__ __forceinline__ bool is(unsigned tag) const
+    {
+        bool ok = true;
+#pragma unroll
+        for (int k = 0; k < Words<T>::N; ++k) ok = ok && (unsigned)w[k] == tag;
+        return ok;
+    }
+    __device__ __forceinline__ T value() const;
+};
+template <>
+__device__ __forceinline__ double Taken<double>::value() const
+{
+    return __hiloint2double((int)(w[0] >> 32), (int)(w[1] >> 32));
+}
+template <>
+__device__ __forceinline__ float Taken<float>::value() const
+{
+    return __int_as_float((int)(w[0] >> 32));
+}
+// after a failed poll: whether to give up
+__device__ __forceinline__ bool gives_up(unsigned polls, int *timeout)
+{
+    if (polls < kSpinLimit &&
+        !((polls & 63) == 63 && __hip_atomic_load(timeout, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)))
+        return false;
+    atomicExch(timeout, 1);
+    return true;
+}
+
+// Largest value over the wave (no NaN among them), by DPP: rows of 16, then
+// the rows' last lanes broadcast; lane 63 holds the result.
+template <int CTRL>
+__device__ __forceinline__ double dpp(double v)
+{
+    const int lo = __builtin_amdgcn_update_dpp(__double2loint(v), __double2loint(v), CTRL, 0xf, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp(__double2hiint(v), __double2hiint(v), CTRL, 0xf, 0xf, false);
+    return __hiloint2double(hi, lo);
+}
+template <int CTRL>
+__device__ __forceinline__ float dpp(float v)
+{
+    return __int_as_float(
+        __builtin_amdgcn_update_dpp(__float_as_int(v), __float_as_int(v), CTRL, 0xf, 0xf, false));
+}
+template <typename T>
+__device__ __forceinline__ T wave_max(T v)
+{
+    v = fmax(v, dpp<0x111>(v));  // row_shr 1, 2, 4, 8
+    v = fmax(v, dpp<0x112>(v));
+    v = fmax(v, dpp<0x114>(v));
+    v = fmax(v, dpp<0x118>(v));
+    v = fmax(v, dpp<0x142>(v));  // row_bcast 15, 31
+    v = fmax(v, dpp<0x143>(v));
+    return lane_bcast(v, 63);
+}
+
 // --------------------------------------------- single-launch panel
 // The whole panel [k, k+kb) x rows [k, n) factored by one cooperative launch
-// (all G workgroups resident at once): workgroup b keeps its 256 rows of the
-// panel in LDS for all kb columns, and the columns are separated by grid
-// barriers instead of launches.  Per column c:
+// (all G workgroups resident at once): workgroup b keeps its 64 NW rows of the
+// panel in LDS for all kb columns.  Per column c:
 //   1. each workgroup finds its candidate (largest |a_rc|, r >= c, first
-//      index among equal maxima) and publishes it with the candidate's row;
-//      the owner of row c publishes row c;
-//   2. grid barrier;
-//   3. every workgroup reduces the G candidates in the same total order, so
-//      all agree on the pivot row p, takes p's entries as the U row, swaps
-//      rows c and p if it owns either, and eliminates column c on its rows.
-// Published values are double-buffered by column parity: a slot is written
-// again two columns later, after a barrier that every reader of it has
-// passed.  Each barrier wait is bounded (kSpinLimit polls, well under a
-// second); a wait that gives up sets *timeout, and every later wait of the
-// factorisation that sees the flag returns at once, so the launches run to
-// their end and the host reports an error instead of the device hanging.
-constexpr unsigned kSpinLimit = 1u << 17;
+//      index among equal maxima) and publishes it; then the previous column's
+//      update of the columns past c is made up for, and the candidate's row
+//      is published, and row c by the workgroup that owns it;
+//   2. every wave reads the G candidates and reduces them in the same total
+//      order, so all agree on the pivot row p, and takes p's row;
+//   3. it swaps rows c and p if it owns either, divides, and eliminates column
+//      c from column c + 1 alone: the next candidates need no more.
+// What bounds it is the chain of a write and two dependent reads through memory
+// per column, ~1.5 us of 2.2 us at n = 8064 (panels 18.2 ms; with a fenced grid
+// barrier, a reduction over the workgroup and the whole update inside the chain
+// 5.8 us, 47 ms).  NW = 1 has no workgroup barrier at all and spreads the rows over
+// the most CUs: 144 us a panel at n = 8064 where NW = 4 takes 163.  It is taken
+// while G stays at most kLoneWaves, the four candidates that a lane reads at once.
+// A wave of its own for the reads was slower (two barriers a column: 204 us).
+// Slots are double-buffered by column parity: a slot is written again two
+// columns later, when the writer has read the next column's candidates of all
+// workgroups, and each published those after its last read of the slot.  Tags are
+// column numbers, so the words are cleared once per factorisation.
+constexpr int kLoneWaves = 256;
+constexpr int kKeySets = 4;  // candidates per lane, G <= 64 kKeySets
 
-template <typename T>
-__device__ __forceinline__ void argmax_take(T &v, int &i, T v2, int i2)
-{
-    if (v2 > v || (v2 == v && i2 < i)) {
-        v = v2;
-        i = i2;
-    }
-}
+constexpr int kPanelPad = 8;
 
-// (largest value, smallest index among equal) over the workgroup; every
-// thread receives the result.  sv, si: kPB/64 entries of LDS.
-template <typename T>
-__device__ __forceinline__ void block_argmax(T &v, int &i, T *sv, int *si)
+// s[u stride] -= l u[u] for N columns of a row
+template <int N, typename T>
+__device__ __forceinline__ void update_columns(T *s, int stride, const T *u, T l)
 {
+    T v[N], w[N];
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-        const T v2 = __shfl_xor(v, off);
-        const int i2 = __shfl_xor(i, off);
-        argmax_take(v, i, v2, i2);
+    for (int q = 0; q < N; ++q) {
+        v[q] = s[q * stride];
+        w[q] = u[q];
     }
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) {
-        sv[threadIdx.x >> 6] = v;
-        si[threadIdx.x >> 6] = i;
-    }
-    __syncthreads();
-    v = sv[0];
-    i = si[0];
 #pragma unroll
-    for (int q = 1; q < kPB / 64; ++q) argmax_take(v, i, sv[q], si[q]);
+    for (int q = 0; q < N; ++q) s[q * stride] = fma(-l, w[q], v[q]);
 }
 
-// The workgroup barrier completes every wave's stores to L2 (write-through
-// L1); thread 0's agent-scope fences then write L2 back for the other dies
-// before it arrives, and invalidate the CU's caches after the wait.
-__device__ __forceinline__ void grid_barrier(unsigned *bar, unsigned target, int *timeout)
+template <typename T, int NW>
+__global__ __launch_bounds__(64 * NW) void k_panel_fused(T *__restrict__ A, int n, int k, int kb,
+                                                         int *__restrict__ ipiv, int *__restrict__ info,
+                                                         uint64_t *__restrict__ words, int *__restrict__ timeout)
 {
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        __threadfence();
-        atomicAdd(bar, 1u);
-        unsigned polls = 0;
-        while (__hip_atomic_load(bar, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target) {
-            if (__hip_atomic_load(timeout, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) break;
-            __builtin_amdgcn_s_sleep(2);
-            if (++polls == kSpinLimit) {
-                atomicExch(timeout, 1);
-                break;
-            }
-        }
-        __threadfence();
-    }
-    __syncthreads();
-}
-
-template <typename T>
-__global__ __launch_bounds__(kPB) void k_panel_fused(T *__restrict__ A, int n, int k, int kb, int *__restrict__ ipiv,
-                                                     int *__restrict__ info, T *__restrict__ cval,
-                                                     int *__restrict__ cidx, T *__restrict__ crow,
-                                                     T *__restrict__ trow, unsigned *__restrict__ bar,
-                                                     int *__restrict__ timeout, unsigned base)
-{
-    __shared__ T S[kNB * kPB];  // this workgroup's rows of the panel, S[col * kPB + row]
-    __shared__ T urow[kNB];
-    __shared__ T sv[kPB / 64];
-    __shared__ int si[kPB / 64];
-    const int t = threadIdx.x, b = blockIdx.x, G = gridDim.x;
-    const int r = k + b * kPB + t;
+    constexpr int W = Words<T>::N, R = 64 * NW, LD = R + 1;  // odd: a row's entries lie in different banks
+    // this workgroup's rows of the panel, S[col * LD + row]; an update's last batch
+    // may reach past the panel's columns, into slots that nothing else uses
+    __shared__ T S[(kNB + kPanelPad) * LD];
+    __shared__ T urow[NW][kNB + kPanelPad];
+    __shared__ T sv[2][NW];
+    __shared__ int si[2][NW];
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6, b = blockIdx.x, G = gridDim.x;
+    const int r = k + b * R + t;
     const bool live = r < n;
-    for (int j0 = 0; j0 < kb; j0 += 16) {  // 16 loads in flight per thread
-        T v[16];
+    uint64_t *const keys = words, *const rows = words + (size_t)2 * (W + 1) * G;
+    uint64_t *const tops = rows + (size_t)2 * G * W * kNB;
+    const T *Ar = A + (size_t)k * n + min(r, n - 1);
+    for (int j0 = 0; j0 < kb; j0 += 32) {  // 32 loads in flight per thread
+        T v[32];
 #pragma unroll
-        for (int u = 0; u < 16; ++u) v[u] = (live && j0 + u < kb) ? A[(size_t)(k + j0 + u) * n + r] : T(0);
+        for (int u = 0; u < 32; ++u) v[u] = Ar[(size_t)min(j0 + u, kb - 1) * n];
 #pragma unroll
-        for (int u = 0; u < 16; ++u)
-            if (j0 + u < kb) S[(j0 + u) * kPB + t] = v[u];
+        for (int u = 0; u < 32; ++u) S[(j0 + u) * LD + t] = live ? v[u] : T(0);
     }
+    T cur = S[t], l = T(0);
+    bool act = false;  // the last column's elimination reaches this row
     for (int j = 0; j < kb; ++j) {
         const int c = k + j, sl = j & 1;
+        const unsigned tag = (unsigned)c + 1;
         // 1. this workgroup's candidate (a NaN entry never wins)
-        const T x = fabs(S[j * kPB + t]);
-        const bool valid = live && r >= c;
-        T v = (valid && x == x) ? x : T(-1);
-        int i = valid ? r : INT_MAX;
-        block_argmax(v, i, sv, si);
-        if (t == 0) {
-            cval[sl * G + b] = v;
-            cidx[sl * G + b] = i;
+        const T x0 = fabs(cur);
+        const T x = (live && r >= c && x0 == x0) ? x0 : T(-1);
+        T mx = wave_max(x);
+        int il = 64 * wave + __ffsll((unsigned long long)__ballot(x == mx)) - 1;
+        if constexpr (NW > 1) {
+            if (lane == 0) {
+                sv[sl][wave] = mx;
+                si[sl][wave] = il;
+            }
+            __syncthreads();
+            mx = sv[sl][0];
+            il = si[sl][0];
+#pragma unroll
+            for (int q = 1; q < NW; ++q)
+                if (sv[sl][q] > mx) {
+                    mx = sv[sl][q];
+                    il = si[sl][q];
+                }
         }
-        // the candidate's row and row c, one entry per thread
-        const int il = i - k - b * kPB;  // candidate's slot in S (i valid: 0 <= il < kPB)
-        if (i != INT_MAX && t < kb) crow[((size_t)sl * G + b) * kNB + t] = S[t * kPB + il];
-        const int cl = c - k - b * kPB;
-        if (cl >= 0 && cl < kPB && t < kb) trow[sl * kNB + t] = S[t * kPB + cl];
-        // 2. every candidate published
-        grid_barrier(bar, base + (unsigned)(j + 1) * (unsigned)G, timeout);
-        // 3. pivot, row swap, elimination
-        T pv = T(-1);
-        int p = INT_MAX;
-        for (int g = t; g < G; g += kPB) argmax_take(pv, p, cval[sl * G + g], cidx[sl * G + g]);
-        block_argmax(pv, p, sv, si);
-        if (p < c || p >= n) p = c;
-        const int bw = (p - k) / kPB;
-        if (t < kb) urow[t] = (p == c) ? trow[sl * kNB + t] : crow[((size_t)sl * G + bw) * kNB + t];
-        __syncthreads();
-        if (p != c) {
-            if (r == c)
-                for (int jj = 0; jj < kb; ++jj) S[jj * kPB + t] = urow[jj];
-            else if (r == p)
-                for (int jj = 0; jj < kb; ++jj) S[jj * kPB + t] = trow[sl * kNB + jj];
+        il = __builtin_amdgcn_readfirstlane(il);
+        if (wave == 0) {
+            if (lane == 0) put_words(keys + (size_t)sl * (W + 1) * G + b, G, mx, tag);
+            if (lane == 1)
+                __hip_atomic_store(keys + ((size_t)sl * (W + 1) + W) * G + b,
+                                   ((uint64_t)(unsigned)(k + b * R + il) << 32) | tag, __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT);
+        }
+        if (act) {
+            const T *up = urow[wave];
+            int j0 = j + 1;
+            for (; j0 + 8 < kb; j0 += 16) update_columns<16>(S + j0 * LD + t, LD, up + j0, l);
+            if (j0 < kb) update_columns<8>(S + j0 * LD + t, LD, up + j0, l);
+        }
+        if (wave == il >> 6 && lane < kb)
+            put_words(rows + (((size_t)sl * G + b) * W) * kNB + lane, kNB, S[lane * LD + il], tag);
+        if (b == 0 && wave == 0 && lane < kb) put_words(tops + (size_t)sl * W * kNB + lane, kNB, S[lane * LD + j], tag);
+        // 2. the pivot
+        T kv[kKeySets];
+        int ki[kKeySets];
+        for (unsigned polls = 0;; ++polls) {
+            Taken<T> q[kKeySets];
+            uint64_t qi[kKeySets];
+#pragma unroll
+            for (int u = 0; u < kKeySets; ++u)
+                if (64 * u < G) {
+                    const uint64_t *key = keys + (size_t)sl * (W + 1) * G + min(64 * u + lane, G - 1);
+                    q[u].load(key, G);
+                    qi[u] = __hip_atomic_load(key + (size_t)W * G, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                }
+            bool ok = true;
+#pragma unroll
+            for (int u = 0; u < kKeySets; ++u) {
+                kv[u] = T(-1);
+                ki[u] = INT_MAX;
+                if (64 * u < G) {
+                    ok = ok && q[u].is(tag) && (unsigned)qi[u] == tag;
+                    kv[u] = q[u].value();
+                    ki[u] = (int)(qi[u] >> 32);
+                }
+            }
+            if (__ballot(!ok) == 0 || gives_up(polls, timeout)) break;
+        }
+        T pv = kv[0];
+#pragma unroll
+        for (int u = 1; u < kKeySets; ++u) pv = fmax(pv, kv[u]);
+        pv = wave_max(pv);
+        int p = c;  // no usable pivot (column all NaN): no swap, flagged below
+#pragma unroll
+        for (int u = kKeySets - 1; u >= 0; --u) {
+            const unsigned long long m = __ballot(kv[u] == pv);
+            if (m) p = __builtin_amdgcn_readlane(ki[u], __ffsll(m) - 1);
+        }
+        if (pv < T(0) || p < c || p >= n) p = c;
+        // its row, and row c where that goes
+        const int bw = (p - k) / R;
+        const bool mine = p != c && (p - k) >> 6 == b * NW + wave;
+        const uint64_t *top = tops + (size_t)sl * W * kNB + min(lane, kb - 1);
+        const uint64_t *win = p == c ? top : rows + (((size_t)sl * G + bw) * W) * kNB + min(lane, kb - 1);
+        Taken<T> uw, tw;
+        for (unsigned polls = 0;; ++polls) {
+            uw.load(win, kNB);
+            bool ok = true;
+            if (mine) {
+                tw.load(top, kNB);
+                ok = tw.is(tag);
+            }
+            ok = ok && uw.is(tag);
+            if (__ballot(!ok) == 0 || gives_up(polls, timeout)) break;
+        }
+        const T u = uw.value();
+        if (lane < kb) {
+            urow[wave][lane] = u;
+            if (p != c && b == 0 && wave == 0) S[lane * LD + j] = u;
+            if (mine) S[lane * LD + (p - k - b * R)] = tw.value();
         }
         if (b == 0 && t == 0) {
             ipiv[c] = p;
             if (!(pv > T(0))) atomicMin(info, c);
         }
-        const T piv = urow[j];
-        if (live && r > c) {
-            T l = S[j * kPB + t];
-            l = (piv != T(0)) ? l / piv : l;
-            S[j * kPB + t] = l;
-            for (int jj = j + 1; jj < kb; ++jj) S[jj * kPB + t] -= l * urow[jj];
+        // 3. elimination from the next column
+        const T piv = lane_bcast(u, j), un = lane_bcast(u, min(j + 1, kb - 1));
+        act = live && r > c;
+        if (act) {
+            const T s = S[j * LD + t];
+            l = (piv != T(0)) ? s / piv : s;
+            S[j * LD + t] = l;
+            if (j + 1 < kb) {
+                cur = fma(-l, un, S[(j + 1) * LD + t]);
+                S[(j + 1) * LD + t] = cur;
+            }
         }
     }
     if (live)
-        for (int jj = 0; jj < kb; ++jj) A[(size_t)(k + jj) * n + r] = S[jj * kPB + t];
+        for (int jj = 0; jj < kb; ++jj) A[(size_t)(k + jj) * n + r] = S[jj * LD + t];
+}
+
+size_t panel_words(int n, int word_per_value)
+{
+    const int g1 = (n + 63) / 64, g4 = (n + kPB - 1) / kPB;
+    const size_t G = (size_t)(g1 < kLoneWaves ? g1 : (g4 > kLoneWaves ? g4 : kLoneWaves));
+    return 2 * ((size_t)word_per_value + 1) * G + 2 * (G + 1) * (size_t)word_per_value * kNB;
 }
 
 // Row swaps of panel [k, k+kb) applied to every column outside the panel.
@@ -681,61 +821,10 @@ static void trsm(T *A, int n, int k, int kb, int jb, int je, hipStream_t s)
 // substitution to the chain, ~5 us, and the factors stream through beside it.
 // Three solves and two residuals of n = 8064: 18.0 -> 4.4 ms.
 //
-// Values are published as 64-bit words with a tag in the low half -- the two
-// halves of a double, or a float -- so that a reader knows from the words
-// themselves that they are this launch's, with no flag to order after the data
-// and no fence.  Tags are never reused within a workspace (SolveFlow), so it
-// is cleared once.  Workgroups take their blocks from a counter: a block only
-// waits for blocks whose workgroups have started before its own, so the waits
-// end whatever the device holds at once; each wait is bounded all the same
-// (kFlowLimit polls, seconds), sets *timeout when it gives up and lets the launch
-// drain.
-constexpr unsigned kFlowLimit = 1u << 22;
-template <typename T>
-struct Words {
-    static constexpr int N = sizeof(T) / 4;
-};
-__device__ __forceinline__ void put_words(uint64_t *w, int64_t stride, double v, unsigned tag)
-{
-    __hip_atomic_store(w, ((uint64_t)(unsigned)__double2hiint(v) << 32) | tag, __ATOMIC_RELAXED,
-                       __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(w + stride, ((uint64_t)(unsigned)__double2loint(v) << 32) | tag, __ATOMIC_RELAXED,
-                       __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ void put_words(uint64_t *w, int64_t, float v, unsigned tag)
-{
-    __hip_atomic_store(w, ((uint64_t)(unsigned)__float_as_int(v) << 32) | tag, __ATOMIC_RELAXED,
-                       __HIP_MEMORY_SCOPE_AGENT);
-}
-// words of one value, and whether they carry the tag
-template <typename T>
-struct Taken {
-    uint64_t w[Words<T>::N];
-    __device__ __forceinline__ void load(const uint64_t *p, int64_t stride)
-    {
-#pragma unroll
-        for (int k = 0; k < Words<T>::N; ++k)
-            w[k] = __hip_atomic_load(p + k * stride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    __device__ __forceinline__ bool is(unsigned tag) const
-    {
-        bool ok = true;
-#pragma unroll
-        for (int k = 0; k < Words<T>::N; ++k) ok = ok && (unsigned)w[k] == tag;
-        return ok;
-    }
-    __device__ __forceinline__ T value() const;
-};
-template <>
-__device__ __forceinline__ double Taken<double>::value() const
-{
-    return __hiloint2double((int)(w[0] >> 32), (int)(w[1] >> 32));
-}
-template <>
-__device__ __forceinline__ float Taken<float>::value() const
-{
-    return __int_as_float((int)(w[0] >> 32));
-}
+// Tags are never reused within a workspace (SolveFlow), so it is cleared once.
+// Workgroups take their blocks from a counter: a block only waits for blocks
+// whose workgroups have started before its own, so the waits end whatever the
+// device holds at once; each wait is bounded all the same.
 
 // v / d from inv = 1/d with a residual correction, for d with |d| in a range
 // whose reciprocals are exact to rounding (quotient_takes); an infinite or NaN
@@ -796,12 +885,7 @@ __global__ __launch_bounds__(256) void k_trsv_flow(const T *__restrict__ LU, int
             bool ok = true;
 #pragma unroll
             for (int q = 0; q < NR; ++q) ok = ok && x[q].is(tag);
-            if (__ballot(!ok) == 0) break;
-            if (polls >= kFlowLimit ||
-                ((polls & 63) == 63 && __hip_atomic_load(timeout, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))) {
-                atomicExch(timeout, 1);
-                break;
-            }
+            if (__ballot(!ok) == 0 || gives_up(polls, timeout)) break;
             __builtin_amdgcn_s_sleep(1);
             load_x(j, x);
         }
@@ -942,8 +1026,8 @@ __global__ __launch_bounds__(256) void k_unpermute(const double *__restrict__ v,
 }
 
 // --------------------------------------------------------------- launchers
-// Workgroups of k_panel_fused<T> the device holds at once (0 if unknown).
-template <typename T>
+// Workgroups of k_panel_fused<T, NW> the device holds at once (0 if unknown).
+template <typename T, int NW>
 static int fused_capacity()
 {
     int dev = 0, cus = 0, per_cu = 0;
@@ -951,7 +1035,7 @@ static int fused_capacity()
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
     int coop = 0;
     if (hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, dev) != hipSuccess || !coop) return 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_panel_fused<T>, kPB, 0) != hipSuccess) return 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_panel_fused<T, NW>, 64 * NW, 0) != hipSuccess) return 0;
     return per_cu * cus;
 }
 
@@ -967,23 +1051,24 @@ static bool per_column_forced()
 template <typename T>
 void lu_factor_launch(T *A, int n, int *ipiv, LUWork &w, hipStream_t s)
 {
-    const int cap = (w.cval && !per_column_forced()) ? fused_capacity<T>() : 0;
-    unsigned base = 0;  // barrier arrivals so far (bar starts at 0)
-    bool fused_ok = cap > 0;
+    const bool one_launch = w.words && !per_column_forced();
+    const int cap1 = one_launch ? fused_capacity<T, 1>() : 0, cap4 = one_launch ? fused_capacity<T, 4>() : 0;
+    bool fused_ok = cap4 > 0;
     for (int K0 = 0; K0 < n; K0 += kOuterNB) {
         const int K1 = (n - K0 < kOuterNB) ? n : K0 + kOuterNB;
         for (int k = K0; k < K1; k += kNB) {
             const int kb = (K1 - k < kNB) ? K1 - k : kNB;
-            const unsigned gp = (unsigned)((n - k + kPB - 1) / kPB);
+            const unsigned gp = (unsigned)((n - k + kPB - 1) / kPB), g1 = (unsigned)((n - k + 63) / 64);
+            const bool lone = (int)g1 <= kLoneWaves && (int)g1 <= cap1;
             bool done = false;
-            if (fused_ok && (int)gp <= cap) {
-                T *cval = (T *)w.cval, *crow = (T *)w.crow, *trow = (T *)w.trow;
+            if (fused_ok && (lone || ((int)gp <= cap4 && gp <= 64 * kKeySets))) {
                 int a_n = n, a_k = k, a_kb = kb;
-                void *args[] = {&A,      &a_n,  &a_k,  &a_kb,  &ipiv,      &w.info, &cval,
-                                &w.cidx, &crow, &trow, &w.bar, &w.timeout, &base};
-                if (hipLaunchCooperativeKernel((const void *)k_panel_fused<T>, dim3(gp), dim3(kPB), args, 0, s) ==
-                    hipSuccess) {
-                    base += (unsigned)kb * gp;
+                void *args[] = {&A, &a_n, &a_k, &a_kb, &ipiv, &w.info, &w.words, &w.timeout};
+                const hipError_t e =
+                    lone ? hipLaunchCooperativeKernel((const void *)k_panel_fused<T, 1>, dim3(g1), dim3(64), args, 0, s)
+                         : hipLaunchCooperativeKernel((const void *)k_panel_fused<T, 4>, dim3(gp), dim3(kPB), args, 0,
+                                                      s);
+                if (e == hipSuccess) {
                     done = true;
                 } else {
                     (void)hipGetLastError();
@@ -1018,6 +1103,11 @@ __global__ __launch_bounds__(256) void k_clear_words(uint64_t *__restrict__ w, i
     if (i < len) w[i] = 0;
 }
 
+void clear_words(uint64_t *w, int64_t len, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_clear_words, dim3((unsigned)((len + 255) / 256)), dim3(256), 0, s, w, len);
+}
+
 size_t solve_flow_bytes(int n) { return 256 + (size_t)n * kSolveCols * 2 * sizeof(uint64_t); }
 
 void solve_flow_init(SolveFlow &f, void *mem, int n, hipStream_t s)
@@ -1026,8 +1116,7 @@ void solve_flow_init(SolveFlow &f, void *mem, int n, hipStream_t s)
     f.timeout = (int *)mem + 1;
     f.words = (uint64_t *)((char *)mem + 256);
     f.launches = 0;
-    const int64_t len = (int64_t)(solve_flow_bytes(n) / sizeof(uint64_t));
-    hipLaunchKernelGGL(k_clear_words, dim3((unsigned)((len + 255) / 256)), dim3(256), 0, s, (uint64_t *)mem, len);
+    clear_words((uint64_t *)mem, (int64_t)(solve_flow_bytes(n) / sizeof(uint64_t)), s);
 }
 
 template <typename T, typename TB, int NR, bool LOWER>

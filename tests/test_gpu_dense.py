@@ -64,3 +64,51 @@ def test_solves_beyond_the_reciprocals_range(nb):
     X = nb.solve_factored(dev(U.T), dev(np.arange(n), torch.int32), dev(B)).cpu().numpy()[0]
     assert X[4] == 1.0 / 3.0 and X[1] != X[1] and np.isinf(X[3])  # 0 x inf enters rows 0 .. 2
     assert (X[5:] == 1.0).all()
+
+
+def factor(nb, A):
+    """(LU, ipiv) of P A = L U, A a (n, n) float64 tensor on the GPU."""
+    At = A.T.contiguous()
+    _, ipiv, _ = nb.solve(At, torch.ones(len(A), dtype=torch.float64, device="cuda:0"))
+    return At.T, ipiv
+
+
+@pytest.mark.parametrize("n", [1, 2, 63, 64, 65, 128, 257, 700])
+def test_pivots(nb, n):
+    """The interchanges of partial pivoting as LAPACK finds them, and among
+    equal candidates the first row: in the second matrix every column is all ties, and
+    each value is a power of two, so that the factors are exact."""
+    import scipy.linalg
+    rng = np.random.default_rng(n)
+    A = rng.standard_normal((n, n))
+    LU, ipiv = factor(nb, dev(A))
+    ref, piv = scipy.linalg.lu_factor(A)
+    assert np.array_equal(ipiv.cpu().numpy(), piv)
+    # both factorisations are backward stable; their difference is rounding times the
+    # condition of the leading blocks, random ones here: 1e-16 n^2 times 1e3
+    assert np.abs(LU.cpu().numpy() - ref).max() <= 1e-13 * max(n, 10) ** 2
+    W = np.eye(n) - np.tril(np.ones((n, n)), -1)
+    W[:, -1] = 1.0
+    LU, ipiv = factor(nb, dev(W))
+    assert np.array_equal(ipiv.cpu().numpy(), np.arange(n))
+    ref = W.copy()
+    ref[:, -1] = 2.0 ** np.arange(n)
+    assert np.array_equal(LU.cpu().numpy(), ref)
+
+
+def test_factor_large(nb):
+    """Past 256 waves' rows a panel's workgroups own 256 rows each: n = 16384
+    + 70 begins there and ends with one wave per workgroup."""
+    n = 16384 + 70
+    g = torch.Generator(device="cuda:0").manual_seed(5)
+    A = torch.randn(n, n, dtype=torch.float64, device="cuda:0", generator=g)
+    x = torch.randn(n, dtype=torch.float64, device="cuda:0", generator=g)
+    b = A @ x
+    At = A.T.contiguous()
+    y, ipiv, _ = nb.solve(At, b)
+    assert float(torch.tril(At.T, -1).abs().max()) <= 1.0
+    # backward error of the refined solve: a few n eps of |A| |x|
+    bound = 4 * n * EPS * (A.abs() @ y.abs())
+    assert bool(((A @ y - b).abs() <= bound).all())
+    p = ipiv.cpu().numpy()
+    assert (p >= np.arange(n)).all() and (p < n).all()
