@@ -513,9 +513,7 @@ nebem_status nebem_assemble(const nebem_panels *panels, const nebem_images *imag
     if ((st = make_img_args(images, &ia))) return st;
     DevBuf drec;
     if ((st = derive(panels, stream, drec))) return st;
-    launch_assemble(drec.as<double>(), panels->n, ia, cx, cy, cz, A, stream);
-    NEBEM_HIP(hipGetLastError());
-    return NEBEM_OK;
+    return assemble_matrix(drec.as<double>(), panels->n, ia, cx, cy, cz, A, stream);
 }
 
 nebem_status nebem_solve(double *A, int64_t n, const double *b, int64_t nrhs, double *sigma, int32_t *ipiv,

@@ -20,7 +20,7 @@
 
 #include "nebem_internal.hpp"
 #include "farfield_mixed.hpp"
-#include "group_far.hpp"
+#include "lattice_far.hpp"
 #include "panel_fp64.hpp"
 
 namespace nebem {
@@ -1628,10 +1628,267 @@ __global__ __launch_bounds__(kBlock) void k_assemble(const double *__restrict__ 
     }
 }
 
+// The same with the far copies of each group of 64 elements by lattice sums of
+// harmonics (lattice_far.hpp): 64 rows, one per lane, x one group per workgroup.
+//   1. The waves scan the lattice for the copies near any of the rows (closer
+//      than ~7.6 group radii) and keep the range of i2 they span in each row (r,
+//      i1) of the lattice: the near copies, all others are far.
+//   2. Each wave sums its orders' harmonics over the far copies in registers,
+//      at the degree that the farthest tier of all lanes allows; dielectric
+//      rows exchange orders through LDS for the normal component.
+//   3. The sums times the moments of the 64 elements (uniform: scalar loads, an
+//      SGPR operand per product), added over the waves through LDS.
+//   4. The near copies by closed forms, element by element.
+// FP64 VALU bound.  Direct: C x 64 closed forms of ~75 instructions per row and
+// group, C = 121; here ~1000 per far copy at degree 14, ~400 at degree 6, ~15 000
+// for the products, and the near copies' closed forms.  n = 8064 (GEM cell, 121
+// copies): 22.9 ms direct; now 4.4 ms for the far copies, of which the products take
+// 1.8, and 3.1 ms for the near ones (k_assemble_near).
+constexpr int kLatticeRows = 512;  // lattice rows (reflection, i1) that the lists hold
+struct NearRow {
+    int row;  // r (2 n1 + 1) + i1 + n1
+    int lo, hi;
+};
+
+__device__ const NormalFactors kNormalFactors = make_normal_factors();
+
+template <int W>
+__device__ __forceinline__ void assemble_far(cdouble_p h, cdouble_p coef, int cnt, const ImgArgs &img,
+                                             const int2 *range, const GroupVec &P, const double *__restrict__ ri,
+                                             double *x, double *__restrict__ A, int n, int i)
+{
+    const bool diel = ri[R_BC] != 0.0;
+    const int lane = threadIdx.x & 63, nrow = 2 * img.n1 + 1;
+    const bool any = __ballot(diel) != 0;
+    const double a = h[3];
+    const double scale = diel ? kKe / (a * a) : kKe / a;
+    int buf = 0;
+#pragma unroll 1
+    for (int r = 0; r < img.nref; ++r) {
+        LatticeSums<W> F;
+        F.clear();
+        const int ax = img.axes[r];
+        const double par = img.parity[r];
+        const GroupVec v0 = group_origin(img, ax, P.x, P.y, P.z, h);
+#pragma unroll 1
+        for (int i1 = -img.n1; i1 <= img.n1; ++i1) {
+            const GroupVec v1 = group_step(v0, -(double)i1, img.a1[r]);
+            const int2 near = range[r * nrow + i1 + img.n1];
+            const int lo = uni(near.x), hi = uni(near.y);
+#pragma unroll 1
+            for (int i2 = -img.n2; i2 <= img.n2; ++i2) {
+                if (i2 == lo) {
+                    i2 = hi;
+                    continue;
+                }
+                const GroupVec d = group_step(v1, -(double)i2, img.a2[r]);
+                const double r2 = group_r2(d);
+                const int deg = __ballot(!(r2 >= h[kHeadTier + 4])) == 0   ? 7
+                                : __ballot(!(r2 >= h[kHeadTier + 2])) == 0 ? 11
+                                                                           : kGroupL;
+                F.add(d, r2, a, par, deg);
+            }
+        }
+        if (any) {
+            __syncthreads();  // the products' buffers of the last reflection are read
+            F.put_exchange(x);
+            __syncthreads();
+            const double Nx = ri[R_E3X], Ny = ri[R_E3Y], Nz = ri[R_E3Z];
+            F.normal_component(x, in_loop(uniform_ptr(kNormalFactors.f)), diel,
+                               (ax & 1) ? -Nx : Nx, (ax & 2) ? -Ny : Ny, (ax & 4) ? -Nz : Nz);
+            __syncthreads();
+        }
+#pragma unroll 1
+        for (int j0 = 0; j0 < cnt; j0 += 8) {
+            double *red = x + buf * (kSets * 8 * 64);
+            buf ^= 1;
+#pragma unroll 1
+            for (int q = 0; q < 8; ++q)
+                red[(W * 8 + q) * 64 + lane] =
+                    F.dot(in_loop(coef + (int64_t)min(j0 + q, cnt - 1) * kElemCoefs + set_offset(W)));
+            __syncthreads();
+#pragma unroll
+            for (int q = W; q < 8; q += kSets) {
+                if (j0 + q >= cnt || i >= n) continue;
+                double s = red[q * 64 + lane];
+#pragma unroll
+                for (int w = 1; w < kSets; ++w) s += red[(w * 8 + q) * 64 + lane];
+                double *e = A + (size_t)(j0 + q) * n + i;
+                *e = r == 0 ? scale * s : fma(scale, s, *e);
+            }
+        }
+    }
+}
+
+// What both kernels below derive from their block: one row per lane, the group
+// of columns, and the range of near i2 in each row of the lattice.
+struct AsmBlock {
+    int i, e0, cnt;
+    GroupVec P;
+    cdouble_p head;
+};
+__device__ __forceinline__ AsmBlock assemble_block(const double *__restrict__ drec, const double *__restrict__ heads,
+                                                   int n, const ImgArgs &img, int2 *range)
+{
+    const int lane = threadIdx.x & 63, wave = uni((int)(threadIdx.x >> 6));
+    AsmBlock b;
+    b.i = blockIdx.x * 64 + lane;
+    b.e0 = blockIdx.y * kGroupElems;
+    b.cnt = min(kGroupElems, n - b.e0);
+    const double *ri = drec + (size_t)min(b.i, n - 1) * R_STRIDE;
+    b.P = {ri[R_CX], ri[R_CY], ri[R_CZ]};
+    b.head = uniform_ptr(heads + (size_t)blockIdx.y * kGroupHead);
+    const int nrow = 2 * img.n1 + 1, rows = img.nref * nrow;
+#pragma unroll 1
+    for (int q = wave; q < rows; q += 4) {
+        const int r = q / nrow, i1 = q % nrow - img.n1;
+        const GroupVec v1 =
+            group_step(group_origin(img, img.axes[r], b.P.x, b.P.y, b.P.z, b.head), -(double)i1, img.a1[r]);
+        int lo = img.n2 + 1, hi = img.n2;
+#pragma unroll 1
+        for (int i2 = -img.n2; i2 <= img.n2; ++i2)
+            if (__ballot(!(group_r2(group_step(v1, -(double)i2, img.a2[r])) >= b.head[kHeadTier]))) {
+                lo = min(lo, i2);
+                hi = i2;
+            }
+        if (lane == 0) range[q] = make_int2(lo, hi);
+    }
+    __syncthreads();
+    return b;
+}
+
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_assemble_grouped(
+    const double *__restrict__ drec, const double *__restrict__ heads, const double *__restrict__ coef, int n,
+    ImgArgs img, double *__restrict__ A)
+{
+    __shared__ double x[kExchange * 128];  // exchanged orders, then two buffers of 8 columns' products
+    __shared__ int2 range[kLatticeRows];
+    const AsmBlock b = assemble_block(drec, heads, n, img, range);
+    double *const Ag = A + (size_t)b.e0 * n;
+    const cdouble_p cg = uniform_ptr(coef + (size_t)b.e0 * kElemCoefs);
+    const double *ri = drec + (size_t)min(b.i, n - 1) * R_STRIDE;
+    switch (uni((int)(threadIdx.x >> 6))) {
+    case 0: assemble_far<0>(b.head, cg, b.cnt, img, range, b.P, ri, x, Ag, n, b.i); break;
+    case 1: assemble_far<1>(b.head, cg, b.cnt, img, range, b.P, ri, x, Ag, n, b.i); break;
+    case 2: assemble_far<2>(b.head, cg, b.cnt, img, range, b.P, ri, x, Ag, n, b.i); break;
+    default: assemble_far<3>(b.head, cg, b.cnt, img, range, b.P, ri, x, Ag, n, b.i); break;
+    }
+}
+
+// The near copies by closed forms, added to what k_assemble_grouped stored.
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_assemble_near(
+    const double *__restrict__ drec, const double *__restrict__ heads, int n, ImgArgs img, double *__restrict__ A)
+{
+    __shared__ int2 range[kLatticeRows];
+    __shared__ NearRow list[kLatticeRows];
+    __shared__ int s_count;
+    const AsmBlock blk = assemble_block(drec, heads, n, img, range);
+    const int lane = threadIdx.x & 63, wave = uni((int)(threadIdx.x >> 6));
+    const int i = blk.i, e0 = blk.e0, cnt = blk.cnt;
+    const bool in = i < n;
+    const GroupVec P = blk.P;
+    const double *ri = drec + (size_t)min(i, n - 1) * R_STRIDE;
+    const GroupVec N = {ri[R_E3X], ri[R_E3Y], ri[R_E3Z]};
+    const bool diel = ri[R_BC] != 0.0;
+    const double jump = ri[R_JUMP];
+    const int nrow = 2 * img.n1 + 1, rows = img.nref * nrow;
+    if (wave == 0) {  // the lattice rows with near copies, in order
+        int count = 0;
+        for (int q0 = 0; q0 < rows; q0 += 64) {
+            const int q = q0 + lane;
+            const int2 e = range[min(q, rows - 1)];
+            const bool has = q < rows && e.x <= e.y;
+            const uint64_t m = __ballot(has);
+            if (has) list[count + __popcll(m & ((1ull << lane) - 1))] = {q, e.x, e.y};
+            count += __popcll(m);
+        }
+        if (lane == 0) s_count = count;
+    }
+    __syncthreads();
+    double *const Ag = A + (size_t)e0 * n;
+    const int count = uni(s_count);
+    if (count == 0) return;
+#pragma unroll 1
+    for (int j = wave + kSets * blockIdx.z; j < cnt; j += kSets * gridDim.z) {
+        const Elem e = load_elem_c(uniform_ptr(drec + (size_t)(e0 + j) * R_STRIDE));
+        const double far2 = (kFarDiam * kFarDiam) * (e.diam * e.diam);
+        const double vfar2 = (kVeryFarDiam * kVeryFarDiam) * (e.diam * e.diam);
+        const bool self = i == e0 + j;
+        double sum = 0.0;
+        for (int l = 0; l < count;) {
+            const int r = uni(list[l].row) / nrow, ax = img.axes[r];
+            const double Qx = (ax & 1) ? 2.0 * img.mpos[0] - P.x : P.x;
+            const double Qy = (ax & 2) ? 2.0 * img.mpos[1] - P.y : P.y;
+            const double Qz = (ax & 4) ? 2.0 * img.mpos[2] - P.z : P.z;
+            const double rx = Qx - e.ox, ry = Qy - e.oy, rz = Qz - e.oz;
+            const double X0 = rx * e.e1x + ry * e.e1y + rz * e.e1z;
+            const double Z0 = rx * e.e2x + ry * e.e2y + rz * e.e2z;
+            const double H0 = rx * e.e3x + ry * e.e3y + rz * e.e3z;
+            const double *a = img.a1[r], *b = img.a2[r];
+            const double aX = a[0] * e.e1x + a[1] * e.e1y + a[2] * e.e1z;
+            const double aZ = a[0] * e.e2x + a[1] * e.e2y + a[2] * e.e2z;
+            const double aH = a[0] * e.e3x + a[1] * e.e3y + a[2] * e.e3z;
+            const double bX = b[0] * e.e1x + b[1] * e.e1y + b[2] * e.e1z;
+            const double bZ = b[0] * e.e2x + b[1] * e.e2y + b[2] * e.e2z;
+            const double bH = b[0] * e.e3x + b[1] * e.e3y + b[2] * e.e3z;
+            double s[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 1
+            for (; l < count; ++l) {
+                const int row = uni(list[l].row) - r * nrow;
+                if (row >= nrow) break;
+                const int i1 = row - img.n1, hi = uni(list[l].hi);
+                const double f1 = -(double)i1;
+                const double X1 = fma(f1, aX, X0), Z1 = fma(f1, aZ, Z0), H1 = fma(f1, aH, H0);
+#pragma unroll 1
+                for (int i2 = uni(list[l].lo); i2 <= hi; ++i2) {
+                    const double f2 = -(double)i2;
+                    const double X = fma(f2, bX, X1), Z = fma(f2, bZ, Z1);
+                    double H = fma(f2, bH, H1);
+                    H = (self && r == 0 && i1 == 0 && i2 == 0) ? 0.0 : H;
+                    if (e.kind == 0)
+                        copy_fp64<0>(e, X, Z, H, far2, vfar2, s);
+                    else
+                        copy_fp64<1>(e, X, Z, H, far2, vfar2, s);
+                }
+            }
+            const double gx = s[1] * e.e1x + s[2] * e.e2x + s[3] * e.e3x;
+            const double gy = s[1] * e.e1y + s[2] * e.e2y + s[3] * e.e3y;
+            const double gz = s[1] * e.e1z + s[2] * e.e2z + s[3] * e.e3z;
+            const double field =
+                N.x * ((ax & 1) ? -gx : gx) + N.y * ((ax & 2) ? -gy : gy) + N.z * ((ax & 4) ? -gz : gz);
+            sum = fma(img.parity[r], diel ? field : s[0], sum);
+        }
+        if (in) {
+            double *p = Ag + (size_t)j * n + i;
+            *p += kKe * sum + (diel && self ? jump : 0.0);
+        }
+    }
+}
+
+// With 25 copies per element the two ways take the same time (n = 8064 5.7 and 5.8
+// ms, n = 1242 0.58 and 0.53), with 121 7.5 and 22.9 ms.  The direct kernel also takes
+// lattices with more rows than the lists hold, and collocation points of the
+// caller's own, which need not lie on their elements.
+bool assemble_grouped(int64_t n, const ImgArgs &img)
+{
+    return n >= 2 * kGroupElems && img_copies(img) >= 36 && (int64_t)img.nref * (2 * img.n1 + 1) <= kLatticeRows;
+}
+
 void launch_assemble(const double *drec, int64_t n, const ImgArgs &img, const double *cx, const double *cy,
-                     const double *cz, double *A, hipStream_t s)
+                     const double *cz, double *A, double *scratch, hipStream_t s)
 {
     if (n <= 0) return;
+    if (scratch && !cx && assemble_grouped(n, img)) {
+        const int ng = (int)((n + kGroupElems - 1) / kGroupElems);
+        double *heads = scratch, *coef = scratch + (size_t)ng * kGroupHead;
+        launch_element_moments(drec, n, heads, coef, s);
+        const dim3 g((unsigned)((n + 63) / 64), (unsigned)ng);
+        hipLaunchKernelGGL(k_assemble_grouped, g, dim3(256), 0, s, drec, heads, coef, (int)n, img, A);
+        // elements of a group over several workgroups where there are few groups
+        const unsigned parts = (uint64_t)g.x * g.y >= 2048 ? 1u : 4u;
+        hipLaunchKernelGGL(k_assemble_near, dim3(g.x, g.y, parts), dim3(256), 0, s, drec, heads, (int)n, img, A);
+        return;
+    }
     const dim3 g((unsigned)((n + kBlock - 1) / kBlock), (unsigned)((n + kTileA - 1) / kTileA));
     hipLaunchKernelGGL(k_assemble, g, dim3(kBlock), 0, s, drec, (int)n, img, cx, cy, cz, A);
 }

@@ -18,7 +18,7 @@
 // 1.7e-14 before, 1.5e-14 now.
 #include <hip/hip_runtime.h>
 
-#include "group_far.hpp"
+#include "lattice_far.hpp"
 #include "nebem_internal.hpp"
 
 namespace nebem {
@@ -58,11 +58,48 @@ struct MomElem {
     bool tri;
 };
 
-// sums over the group of q (s/a)^n J_n^m for n = m .. kGroupP, in bre / bim[n]
-template <int M>
-__device__ __forceinline__ void moment_order(const MomElem &e, double *__restrict__ bre, double *__restrict__ bim)
+// The group's centre c and squared radius a2, and the lane's element (record
+// r, density sg) in that frame.
+__device__ __forceinline__ MomElem group_frame(const double *r, double sg, double (&c)[3], double &a2)
 {
-    double ar[kGroupP + 1 - M], ai[kGroupP + 1 - M];
+    const double lx = r[R_LX], lz = r[R_LZ];
+    const double o[3] = {r[R_OX], r[R_OY], r[R_OZ]};
+    const double u[3] = {lx * r[R_E1X], lx * r[R_E1Y], lx * r[R_E1Z]};
+    const double w[3] = {lz * r[R_E2X], lz * r[R_E2Y], lz * r[R_E2Z]};
+    const bool tri = r[R_KIND] != 0.0;
+    double d2[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        const double v1 = o[k] + u[k], v2 = o[k] + w[k], v3 = tri ? v2 : v1 + w[k];
+        const double lo = wave_min(fmin(fmin(o[k], v1), fmin(v2, v3)));
+        const double hi = -wave_min(fmin(fmin(-o[k], -v1), fmin(-v2, -v3)));
+        c[k] = 0.5 * (lo + hi);
+        const double d[4] = {o[k] - c[k], v1 - c[k], v2 - c[k], v3 - c[k]};
+#pragma unroll
+        for (int q = 0; q < 4; ++q) d2[q] = fma(d[q], d[q], d2[q]);
+    }
+    a2 = -wave_min(-fmax(fmax(d2[0], d2[1]), fmax(d2[2], d2[3])));
+    const double ia = 1.0 / sqrt(a2);
+    MomElem e;
+    e.ox = (o[0] - c[0]) * ia;
+    e.oy = (o[1] - c[1]) * ia;
+    e.oz = (o[2] - c[2]) * ia;
+    e.ux = u[0] * ia;
+    e.uy = u[1] * ia;
+    e.uz = u[2] * ia;
+    e.wx = w[0] * ia;
+    e.wy = w[1] * ia;
+    e.wz = w[2] * ia;
+    e.q = sg * (lx * lz);
+    e.tri = tri;
+    return e;
+}
+
+// q (s/a)^n J_n^m(s/|s|) integrated over the lane's element, n = M .. kGroupP
+template <int M>
+__device__ __forceinline__ void element_order(const MomElem &e, double (&ar)[kGroupP + 1 - M],
+                                              double (&ai)[kGroupP + 1 - M])
+{
 #pragma unroll
     for (int k = 0; k <= kGroupP - M; ++k) ar[k] = ai[k] = 0.0;
 #pragma unroll 1
@@ -98,6 +135,14 @@ __device__ __forceinline__ void moment_order(const MomElem &e, double *__restric
             }
         }
     }
+}
+
+// the group's sums times their factors, in bre / bim[n]
+template <int M>
+__device__ __forceinline__ void moment_order(const MomElem &e, double *__restrict__ bre, double *__restrict__ bim)
+{
+    double ar[kGroupP + 1 - M], ai[kGroupP + 1 - M];
+    element_order<M>(e, ar, ai);
 #pragma unroll
     for (int n = M; n <= kGroupP; ++n) {
         const double r = wave_sum(ar[n - M]), i = M > 0 ? wave_sum(ai[n - M]) : 0.0;
@@ -105,6 +150,22 @@ __device__ __forceinline__ void moment_order(const MomElem &e, double *__restric
             bre[n * (kGroupP + 1) + M] = kHarm.bf[n][M] * r;
             bim[n * (kGroupP + 1) + M] = kHarm.bf[n][M] * i;
         }
+    }
+}
+
+// an element's moments (lattice_far.hpp) of order M, lane by lane
+template <int M>
+__device__ __forceinline__ void coef_order(const MomElem &e, double *__restrict__ out)
+{
+    constexpr int W = M / 3 < kSets ? M / 3 : kSets - 1;
+    double ar[kGroupP + 1 - M], ai[kGroupP + 1 - M];
+    element_order<M>(e, ar, ai);
+#pragma unroll
+    for (int n = M; n <= kGroupP; ++n) {
+        const double f = kHarm.bf[n][M] / kHarm.lam[n][M];
+        double *q = out + set_offset(W) + 2 * set_slot(W, n, M, kGroupP);
+        q[0] = f * ar[n - M];
+        q[1] = f * ai[n - M];
     }
 }
 
@@ -127,38 +188,10 @@ __global__ __launch_bounds__(64 * kMomWaves) void k_group_moments(const double *
     const int cnt = min(kGroupElems, end - e0);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     if (threadIdx.x == 0) bad = 0;
-    const double *r = drec + (size_t)(e0 + min(lane, cnt - 1)) * R_STRIDE;
-    const double lx = r[R_LX], lz = r[R_LZ];
-    const double o[3] = {r[R_OX], r[R_OY], r[R_OZ]};
-    const double u[3] = {lx * r[R_E1X], lx * r[R_E1Y], lx * r[R_E1Z]};
-    const double w[3] = {lz * r[R_E2X], lz * r[R_E2Y], lz * r[R_E2Z]};
-    const bool tri = r[R_KIND] != 0.0;
     const double sg = lane < cnt ? sigma[(size_t)blockIdx.y * sig_stride + e0 + lane] : 0.0;
-    double c[3], d2[4] = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        const double v1 = o[k] + u[k], v2 = o[k] + w[k], v3 = tri ? v2 : v1 + w[k];
-        const double lo = wave_min(fmin(fmin(o[k], v1), fmin(v2, v3)));
-        const double hi = -wave_min(fmin(fmin(-o[k], -v1), fmin(-v2, -v3)));
-        c[k] = 0.5 * (lo + hi);
-        const double d[4] = {o[k] - c[k], v1 - c[k], v2 - c[k], v3 - c[k]};
-#pragma unroll
-        for (int q = 0; q < 4; ++q) d2[q] = fma(d[q], d[q], d2[q]);
-    }
-    const double a2 = -wave_min(-fmax(fmax(d2[0], d2[1]), fmax(d2[2], d2[3])));
-    const double a = sqrt(a2), ia = 1.0 / a;
-    MomElem e;
-    e.ox = (o[0] - c[0]) * ia;
-    e.oy = (o[1] - c[1]) * ia;
-    e.oz = (o[2] - c[2]) * ia;
-    e.ux = u[0] * ia;
-    e.uy = u[1] * ia;
-    e.uz = u[2] * ia;
-    e.wx = w[0] * ia;
-    e.wy = w[1] * ia;
-    e.wz = w[2] * ia;
-    e.q = sg * (lx * lz);
-    e.tri = tri;
+    double c[3], a2;
+    const MomElem e = group_frame(drec + (size_t)(e0 + min(lane, cnt - 1)) * R_STRIDE, sg, c, a2);
+    const double a = sqrt(a2);
     __syncthreads();
     if (!isfinite(sg) || !(a2 > 0.0) || !isfinite(a2)) bad = 1;  // any lane, the same value
     switch (wave) {
@@ -229,6 +262,63 @@ void launch_group_moments(const double *drec, const double *sigma, int64_t n, in
     hipLaunchKernelGGL(k_group_moments, dim3((unsigned)(sp.nseg * gps), (unsigned)ncol), dim3(64 * kMomWaves), 0, s,
                        drec, sigma, (int)n, sig_stride, sp.segsz, gps, gdata,
                        (int64_t)sp.nseg * gps * kGroupStride);
+}
+
+// Moments of every element about its group's centre, kElemCoefs each, and
+// the groups' heads: the assembly's far field.  As k_group_moments, but each lane
+// keeps its element's integrals; the 2 KB per element are a 32nd of a matrix column
+// of 8000 rows.
+__global__ __launch_bounds__(64 * kMomWaves) void k_element_moments(const double *__restrict__ drec, int n,
+                                                                    double *__restrict__ heads,
+                                                                    double *__restrict__ coef)
+{
+    const int e0 = blockIdx.x * kGroupElems, cnt = min(kGroupElems, n - e0);
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    double c[3], a2;
+    const MomElem e = group_frame(drec + (size_t)(e0 + min(lane, cnt - 1)) * R_STRIDE, 1.0, c, a2);
+    if (threadIdx.x < kGroupHead) {
+        const int k = threadIdx.x;
+        const double inf = __builtin_inf();
+        const bool bad = !(a2 > 0.0) || !isfinite(a2);
+        const double t = k < kHeadTier + kTiers ? a2 * tier_ratio2(k - kHeadTier) : 0.0;
+        heads[(size_t)blockIdx.x * kGroupHead + k] = k < 3 ? c[min(k, 2)] : k == 3 ? sqrt(a2) : bad ? inf : t;
+    }
+    if (lane >= cnt) return;
+    double *out = coef + (size_t)(e0 + lane) * kElemCoefs;
+    switch (__builtin_amdgcn_readfirstlane(wave)) {
+    case 0: coef_order<0>(e, out); break;
+    case 1: coef_order<1>(e, out); break;
+    case 2: coef_order<2>(e, out); break;
+    case 3: coef_order<3>(e, out); break;
+    case 4: coef_order<4>(e, out); break;
+    case 5: coef_order<5>(e, out); break;
+    case 6: coef_order<6>(e, out); break;
+    case 7: coef_order<7>(e, out); break;
+    case 8: coef_order<8>(e, out); break;
+    case 9: coef_order<9>(e, out); break;
+    case 10: coef_order<10>(e, out); break;
+    case 11: coef_order<11>(e, out); break;
+    case 12: coef_order<12>(e, out); break;
+    case 13: coef_order<13>(e, out); break;
+    default: coef_order<14>(e, out); break;
+    }
+    // the sets' padding is read with them
+    if (wave < kSets) {
+        int used = 0;
+        for (int m = set_lo(wave); m <= set_hi(wave) && m <= kGroupP; ++m) used += kGroupP + 1 - m;
+        for (int k = 2 * used; k < set_coefs(wave); ++k) out[set_offset(wave) + k] = 0.0;
+    }
+}
+
+size_t assemble_scratch_doubles(int64_t n)
+{
+    return (size_t)((n + kGroupElems - 1) / kGroupElems) * kGroupHead + (size_t)n * kElemCoefs;
+}
+
+void launch_element_moments(const double *drec, int64_t n, double *heads, double *coef, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_element_moments, dim3((unsigned)((n + kGroupElems - 1) / kGroupElems)), dim3(64 * kMomWaves),
+                       0, s, drec, (int)n, heads, coef);
 }
 
 // --------------------------------------------------------------------- far

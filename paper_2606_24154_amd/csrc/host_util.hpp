@@ -52,6 +52,9 @@ void pivots_to_perm(const std::vector<int> &ipiv, std::vector<int> &perm);
 nebem_status factor_fp64(double *A, int n, int *ipiv, std::vector<int> &perm_host, hipStream_t st);
 nebem_status factor_mixed(const double *A, int n, float *A32, double *s, int *ipiv, std::vector<int> &perm_host,
                           hipStream_t st);
+// launch_assemble with its scratch, or without where the device has no memory left
+nebem_status assemble_matrix(const double *drec, int64_t n, const ImgArgs &img, const double *cx, const double *cy,
+                             const double *cz, double *A, hipStream_t st);
 // The triangular solves' workspace for one sequence of solves on a stream, and
 // whether a wait in any of them gave up (synchronises the stream).
 struct FlowBuf {

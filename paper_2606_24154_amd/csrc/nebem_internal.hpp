@@ -250,8 +250,13 @@ int eval_items_slots(int mixed);
 // items/imgs in device memory; one 64-lane workgroup per item
 void launch_eval_items(const WorkItem *items, int nitems, const ImgArgs *imgs, int mixed, double near_factor,
                        hipStream_t s);
-// A (n x n col-major), exact closed forms.  cx/cy/cz may be null (centroids).
+// A (n x n col-major), FP64 in both precisions.  cx/cy/cz may be null (centroids).
+// scratch: assemble_scratch_doubles(n) doubles if assemble_grouped(n, img), else (or
+// if there is no memory for them) null.
+bool assemble_grouped(int64_t n, const ImgArgs &img);
+size_t assemble_scratch_doubles(int64_t n);
+void launch_element_moments(const double *drec, int64_t n, double *heads, double *coef, hipStream_t s);
 void launch_assemble(const double *drec, int64_t n, const ImgArgs &img, const double *cx, const double *cy,
-                     const double *cz, double *A, hipStream_t s);
+                     const double *cz, double *A, double *scratch, hipStream_t s);
 
 }  // namespace nebem

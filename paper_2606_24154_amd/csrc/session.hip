@@ -55,12 +55,11 @@ static nebem_status session_build(nebem_session *s, const nebem_panels *panels, 
     }
     const bool mixed = s->opt.precision == NEBEM_MIXED;
     NEBEM_HIP(s->A.ensure((size_t)n * n * sizeof(double)));
-    launch_assemble(s->drec.as<double>(), n, s->img, nullptr, nullptr, nullptr, s->A.as<double>(), st);
-    NEBEM_HIP(hipGetLastError());
+    nebem_status e = assemble_matrix(s->drec.as<double>(), n, s->img, nullptr, nullptr, nullptr, s->A.as<double>(), st);
+    if (e) return e;
     NEBEM_HIP(s->ipiv.ensure((size_t)n * sizeof(int)));
     NEBEM_HIP(s->perm.ensure((size_t)n * sizeof(int)));
     std::vector<int> perm;
-    nebem_status e;
     if (!mixed) {  // A stays unfactored for the refinement residuals
         NEBEM_HIP(s->LU.ensure((size_t)n * n * sizeof(double)));
         NEBEM_HIP(hipMemcpyAsync(s->LU.p, s->A.p, (size_t)n * n * sizeof(double), hipMemcpyDeviceToDevice, st));

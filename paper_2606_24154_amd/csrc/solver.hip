@@ -78,6 +78,20 @@ nebem_status factor_mixed(const double *A, int n, float *A32, double *s, int *ip
     return lu_factor_checked<float>(A32, n, ipiv, perm_host, st);
 }
 
+nebem_status assemble_matrix(const double *drec, int64_t n, const ImgArgs &img, const double *cx, const double *cy,
+                             const double *cz, double *A, hipStream_t st)
+{
+    DevBuf scratch;
+    if (!cx && assemble_grouped(n, img) &&
+        scratch.alloc(assemble_scratch_doubles(n) * sizeof(double), st) != hipSuccess) {
+        (void)hipGetLastError();
+        scratch.p = nullptr;
+    }
+    launch_assemble(drec, n, img, cx, cy, cz, A, scratch.as<double>(), st);
+    NEBEM_HIP(hipGetLastError());
+    return NEBEM_OK;
+}
+
 nebem_status FlowBuf::init(int n, hipStream_t st)
 {
     NEBEM_HIP(mem.alloc(solve_flow_bytes(n), st));

@@ -112,3 +112,42 @@ def test_factor_large(nb):
     assert bool(((A @ y - b).abs() <= bound).all())
     p = ipiv.cpu().numpy()
     assert (p >= np.arange(n)).all() and (p < n).all()
+
+
+def assembly_geometry(kind):
+    """1242 elements, conductor and dielectric rows, the last group ragged: one
+    cell's copies as usual, on a skewed lattice with more copies one way, with
+    reflections, and with one row of 41."""
+    from synth import Images, gem_cell
+    g = gem_cell(k=17, nr=2, n_images=5)
+    im = g.images
+    if kind == "skew":
+        return g.with_images(Images(a1=im.a1, a2=im.a2 + 0.3 * im.a1, n1=2, n2=30))
+    if kind == "mirror":
+        return g.with_images(Images(a1=im.a1, a2=im.a2, n1=2, n2=3, mirror_mask=5,
+                                    mirror_pos=np.array([-2e-4, 0.0, -1.5e-3]),
+                                    mirror_parity=np.array([1, 1, -1], np.int32)))
+    if kind == "line":
+        return g.with_images(Images(a1=im.a1, a2=im.a2, n1=0, n2=20))
+    return g
+
+
+@pytest.mark.parametrize("kind", ["cell", "skew", "mirror", "line"])
+def test_grouped_assembly(nb, kind):
+    """The matrix with far copies by lattice sums against the closed forms
+    throughout, which collocation points handed in by the caller take, and
+    sampled rows against the oracle.  1e-11 of a row's largest entry, as every
+    assembly here; entry by entry 1e-10 where all copies count with one sign (an
+    expansion is truncated below 1e-12, the closed forms round at 1e-11)."""
+    import oracle
+    g = assembly_geometry(kind)
+    dp = nb.DevicePanels.from_geometry(g, "cuda:0")
+    A = nb.assemble(dp).cpu().numpy().T
+    D = nb.assemble(dp, colloc=[dev(c) for c in g.centroids().T]).cpu().numpy().T
+    rows = np.unique(np.concatenate([np.arange(0, g.n, 97), [63, 64, g.n - 1]]))
+    ref = oracle.assemble_rows(g, rows)
+    assert (np.abs(A[rows] - ref).max(axis=1) <= 1e-11 * np.abs(ref).max(axis=1)).all()
+    assert (np.abs(A - D).max(axis=1) <= 1e-11 * np.abs(D).max(axis=1)).all()
+    if kind != "mirror":
+        c = g.bc == 0
+        assert (np.abs(A[c] - D[c]) <= 1e-10 * np.abs(D[c])).all()
