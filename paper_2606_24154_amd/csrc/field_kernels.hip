@@ -1535,38 +1535,64 @@ void launch_group_near(const double *drec, const double *sigma, const double *gd
 
 // Continuous-batching evaluation: workgroup (one wave) b takes work item b --
 // up to 64 points of one request against one segment of the elements of one
-// resident geometry -- and writes the segment's unscaled partial sums.  The
-// per-point arithmetic does not depend on which other items share the launch.
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_eval_items_fp64(const WorkItem *__restrict__ items,
-                                                       const ImgArgs *__restrict__ imgs, double near_factor)
+// resident geometry -- and writes the segment's unscaled partial sums; or, with
+// `units`, unit y of it (a group's near part, or 16 elements), whose sums go to
+// units[b][y][component][lane].  The per-point arithmetic does not depend on which
+// other items share the launch, nor on the split.
+template <bool MIXED>
+__device__ __forceinline__ void eval_item(const WorkItem &w, const ImgArgs &img, double near_factor, double *units)
+{
+    double *phi = w.phi, *ex = w.ex, *ey = w.ey, *ez = w.ez;
+    int p0 = 0, p1 = w.n;
+    if (units) {
+        p0 = blockIdx.y * kSubElems;
+        p1 = min(p0 + kSubElems, w.n);
+        if (p0 >= w.n) return;
+        phi = units + ((size_t)blockIdx.x * gridDim.y + blockIdx.y) * kUnitDoubles;
+        ex = phi + 64;
+        ey = phi + 128;
+        ez = phi + 192;
+    }
+    eval_block<MIXED>(w.drec, w.sigma, w.n, p0, p1, img, near_factor, w.px, w.py, w.pz, w.count, threadIdx.x, 1.0, phi,
+                      ex, ey, ez);
+}
+
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_eval_items_fp64(
+    const WorkItem *__restrict__ items, const ImgArgs *__restrict__ imgs, double near_factor,
+    double *__restrict__ units)
 {
     __shared__ NearList list;
     const WorkItem &w = items[blockIdx.x];
-    if (w.gdata) {  // grouped geometry: the near part, added to k_items_far's
-        const int j = min((int)threadIdx.x, w.count - 1);
-        double acc[1][4];
-        near_unit<1>(list, uniform_ptr(w.drec), uniform_ptr(w.sigma), 0, uniform_ptr(w.gdata), w.n, imgs[w.geom],
-                     w.px[j], w.py[j], w.pz[j], 0, (w.n + kGroupElems - 1) / kGroupElems, 0, kNearParts, acc);
-        if ((int)threadIdx.x >= w.count) return;
-        w.phi[threadIdx.x] += acc[0][0];
-        w.ex[threadIdx.x] += acc[0][1];
-        w.ey[threadIdx.x] += acc[0][2];
-        w.ez[threadIdx.x] += acc[0][3];
+    if (!w.gdata) {
+        eval_item<false>(w, imgs[w.geom], near_factor, units);
         return;
     }
-    eval_block<false>(w.drec, w.sigma, w.n, 0, w.n, imgs[w.geom], near_factor, w.px, w.py, w.pz, w.count,
-                      threadIdx.x, 1.0, w.phi,
-                          w.ex, w.ey, w.ez);
+    // grouped geometry: the near part, added to k_items_far's
+    const int j = min((int)threadIdx.x, w.count - 1);
+    const int ng = (w.n + kGroupElems - 1) / kGroupElems;
+    const int g0 = units ? (int)blockIdx.y : 0, g1 = units ? g0 + 1 : ng;
+    if (g0 >= ng) return;
+    double acc[1][4];
+    near_unit<1>(list, uniform_ptr(w.drec), uniform_ptr(w.sigma), 0, uniform_ptr(w.gdata), w.n, imgs[w.geom], w.px[j],
+                 w.py[j], w.pz[j], g0, g1, 0, kNearParts, acc);
+    if ((int)threadIdx.x >= w.count) return;
+    if (units) {
+        double *u = units + ((size_t)blockIdx.x * gridDim.y + blockIdx.y) * kUnitDoubles + threadIdx.x;
+        for (int c = 0; c < 4; ++c) u[64 * c] = acc[0][c];
+        return;
+    }
+    w.phi[threadIdx.x] += acc[0][0];
+    w.ex[threadIdx.x] += acc[0][1];
+    w.ey[threadIdx.x] += acc[0][2];
+    w.ez[threadIdx.x] += acc[0][3];
 }
 
 // two waves per SIMD, as k_eval_mixed
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_eval_items_mixed(
-    const WorkItem *__restrict__ items, const ImgArgs *__restrict__ imgs, double near_factor)
+    const WorkItem *__restrict__ items, const ImgArgs *__restrict__ imgs, double near_factor,
+    double *__restrict__ units)
 {
-    const WorkItem &w = items[blockIdx.x];
-    eval_block<true>(w.drec, w.sigma, w.n, 0, w.n, imgs[w.geom], near_factor, w.px, w.py, w.pz, w.count,
-                      threadIdx.x, 1.0, w.phi,
-                         w.ex, w.ey, w.ez);
+    eval_item<true>(items[blockIdx.x], imgs[items[blockIdx.x].geom], near_factor, units);
 }
 
 int eval_items_slots(int mixed)
@@ -1581,14 +1607,23 @@ int eval_items_slots(int mixed)
 }
 
 void launch_eval_items(const WorkItem *items, int nitems, const ImgArgs *imgs, int mixed, double near_factor,
-                       hipStream_t s)
+                       double *units, int64_t cap, int per, hipStream_t s)
 {
-    if (nitems <= 0) return;
-    if (mixed) {
-        hipLaunchKernelGGL(k_eval_items_mixed, dim3(nitems), dim3(64), 0, s, items, imgs, near_factor);
-    } else {
-        launch_items_far(items, nitems, imgs, s);
-        hipLaunchKernelGGL(k_eval_items_fp64, dim3(nitems), dim3(64), 0, s, items, imgs, near_factor);
+    // whole items, or as many at a time as have their units in the scratch
+    const int64_t batch = units && per > 0 ? cap / per : 0;
+    const int step = batch > 0 ? (int)(batch < nitems ? batch : nitems) : nitems;
+    double *near = batch > 0 ? units : nullptr, *far = near ? units + cap * kUnitDoubles : nullptr;
+    for (int i = 0; i < nitems; i += step) {
+        const int c = nitems - i < step ? nitems - i : step;
+        const WorkItem *it = items + i;
+        const dim3 g(c, near ? per : 1);
+        if (mixed) {
+            hipLaunchKernelGGL(k_eval_items_mixed, g, dim3(64), 0, s, it, imgs, near_factor, near);
+        } else {
+            launch_items_far(it, c, imgs, far, per, s);
+            hipLaunchKernelGGL(k_eval_items_fp64, g, dim3(64), 0, s, it, imgs, near_factor, near);
+        }
+        if (near) launch_items_fold(it, c, far, near, per, s);
     }
 }
 

@@ -424,28 +424,63 @@ void launch_group_far(const double *gdata, int64_t n, int ncol, const SegPlan &s
 }
 
 // Serving: workgroup (one wave) b takes work item b where its geometry is
-// grouped -- the far part of one segment at up to 64 points of one request.
+// grouped -- the far part of one segment at up to 64 points of one request, or
+// (units set) of group y of it, whose sums go to units[b][y][component][lane].
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3, 3))) void k_items_far(
-    const WorkItem *__restrict__ items, const ImgArgs *__restrict__ imgs)
+    const WorkItem *__restrict__ items, const ImgArgs *__restrict__ imgs, double *__restrict__ units)
 {
     const WorkItem &w = items[blockIdx.x];
     if (!w.gdata) return;
     const ImgArgs &img = imgs[w.geom];
     const int j = min((int)threadIdx.x, w.count - 1);
+    const int ng = (w.n + kGroupElems - 1) / kGroupElems;
+    const int g0 = units ? (int)blockIdx.y : 0, g1 = units ? g0 + 1 : ng;
+    if (g0 >= ng) return;
     double acc[4];
-    far_unit(uniform_ptr(w.gdata), img, w.px[j], w.py[j], w.pz[j], 0, (w.n + kGroupElems - 1) / kGroupElems, 0,
-             img.nref * (2 * img.n1 + 1), acc);
+    far_unit(uniform_ptr(w.gdata), img, w.px[j], w.py[j], w.pz[j], g0, g1, 0, img.nref * (2 * img.n1 + 1), acc);
     if ((int)threadIdx.x >= w.count) return;
+    if (units) {
+        double *u = units + ((size_t)blockIdx.x * gridDim.y + blockIdx.y) * kUnitDoubles + threadIdx.x;
+        for (int c = 0; c < 4; ++c) u[64 * c] = acc[c];
+        return;
+    }
     w.phi[threadIdx.x] = acc[0];
     w.ex[threadIdx.x] = acc[1];
     w.ey[threadIdx.x] = acc[2];
     w.ez[threadIdx.x] = acc[3];
 }
 
-void launch_items_far(const WorkItem *items, int nitems, const ImgArgs *imgs, hipStream_t s)
+void launch_items_far(const WorkItem *items, int nitems, const ImgArgs *imgs, double *units, int per, hipStream_t s)
 {
     if (nitems <= 0) return;
-    hipLaunchKernelGGL(k_items_far, dim3(nitems), dim3(64), 0, s, items, imgs);
+    hipLaunchKernelGGL(k_items_far, dim3(nitems, units ? per : 1), dim3(64), 0, s, items, imgs, units);
+}
+
+// The items' units back to one value per point, in the order in which a whole
+// item adds them.
+__global__ __launch_bounds__(256) void k_items_fold(const WorkItem *__restrict__ items,
+                                                    const double *__restrict__ far,
+                                                    const double *__restrict__ near, int per)
+{
+    const WorkItem &w = items[blockIdx.x];
+    const int c = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    if (lane >= w.count) return;
+    const int64_t o = (int64_t)blockIdx.x * per * kUnitDoubles + threadIdx.x;
+    const int cnt = item_units(w.n, w.gdata != nullptr);
+    double f = 0.0, n = 0.0;
+    for (int u = 0; u < cnt; ++u) n += near[o + (int64_t)u * kUnitDoubles];
+    if (w.gdata) {
+        for (int u = 0; u < cnt; ++u) f += far[o + (int64_t)u * kUnitDoubles];
+        n = f + n;
+    }
+    (c == 0 ? w.phi : c == 1 ? w.ex : c == 2 ? w.ey : w.ez)[lane] = n;
+}
+
+void launch_items_fold(const WorkItem *items, int nitems, const double *far, const double *near, int per,
+                       hipStream_t s)
+{
+    if (nitems <= 0) return;
+    hipLaunchKernelGGL(k_items_fold, dim3(nitems), dim3(256), 0, s, items, far, near, per);
 }
 
 // ------------------------------------------------------------ finer units

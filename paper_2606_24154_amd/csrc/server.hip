@@ -26,7 +26,11 @@
 //      interactions per point, so that one heavy point is not a long serial
 //      chain in a single lane), taken round-robin (one item per request per
 //      round) until the iteration's interaction budget is used; items of
-//      different requests and geometries go into ONE launch;
+//      different requests and geometries go into ONE launch, which runs as
+//      finer units (a group, or 16 elements, x 64 points) while it holds few
+//      items: a whole item is 10 to 30 ms of one wave, and a burst of 16
+//      requests, 16 000 points on a GEM cell, left most of the device idle
+//      (72 ms FP64; 19 ms in units);
 //   3. completion: a request whose items are all done has its segment
 //      partial sums reduced in a fixed order (and scattered back to the
 //      submission order if sorted), its results copied back to the
@@ -114,6 +118,8 @@ struct nebem_server {
     nebem::WorkItem *items_host = nullptr;  // pinned, 2 x items_cap
     void *sort_ws = nullptr;                // scratch of the point sort (grown on demand)
     size_t sort_ws_bytes = 0;
+    double *units_dev = nullptr;            // units' partial sums, 2 x 2 unit_cap units: one set per launch stream
+    int64_t unit_cap = 0;
     int items_cap = 0;
     int round_items = 1;  // work items (waves) the device runs at once
     std::mutex mu;
@@ -187,11 +193,11 @@ static void worker_main(nebem_server *s)
                 const size_t wb = order_points_workspace(r->m);
                 if (wb == 0) e = hipErrorInvalidValue;
                 if (e == hipSuccess && wb > s->sort_ws_bytes) {
-                    if (s->sort_ws) e = hipStreamSynchronize(s->stream);
-                    if (e == hipSuccess && s->sort_ws) e = hipFree(s->sort_ws);
+                    // stream-ordered: a plain free would wait for the launches in flight
+                    if (s->sort_ws) e = hipFreeAsync(s->sort_ws, s->stream);
                     s->sort_ws = nullptr;
                     s->sort_ws_bytes = 0;
-                    if (e == hipSuccess) e = hipMalloc(&s->sort_ws, wb);
+                    if (e == hipSuccess) e = hipMallocAsync(&s->sort_ws, wb, s->stream);
                     if (e == hipSuccess) s->sort_ws_bytes = wb;
                 }
                 if (e == hipSuccess)
@@ -272,7 +278,14 @@ static void worker_main(nebem_server *s)
                         launch_group_moments(s->geoms[k]->drec.as<double>(), s->geoms[k]->sigma.as<double>(),
                                              s->geoms[k]->n, 0, 1, {s->geom_nseg[k], s->geom_segsz[k]},
                                              group_cur + s->geom_groups[k], s->lst[cur]);
-                launch_eval_items(items_dev, nitems, s->imgs_dev, s->mixed, s->near_factor, s->lst[cur]);
+                int per = 0;
+                for (size_t k = 0; k < s->geoms.size(); ++k)
+                    if (used[k]) per = std::max(per, item_units(s->geom_segsz[k], s->geom_groups[k] != SIZE_MAX));
+                // past four rounds of whole items the last round's waste is small
+                const bool split = s->unit_cap > 0 && nitems <= 4 * s->round_items;
+                launch_eval_items(items_dev, nitems, s->imgs_dev, s->mixed, s->near_factor,
+                                  split ? s->units_dev + (size_t)cur * 2 * s->unit_cap * kUnitDoubles : nullptr,
+                                  s->unit_cap, per, s->lst[cur]);
                 e = hipGetLastError();
             }
             if (e == hipSuccess) e = hipEventRecord(s->ev_launch[cur], s->lst[cur]);
@@ -432,6 +445,17 @@ nebem_status nebem_server_create(nebem_session *const *sessions, int32_t nsessio
     if ((e = hipHostMalloc((void **)&s->items_host, 2 * sizeof(WorkItem) * s->items_cap, hipHostMallocDefault)) !=
         hipSuccess)
         return bail(e, "hipHostMalloc(work list)");
+    // units' scratch, 64 MB per launch stream; without it items run whole
+    int per = 1;
+    for (int k = 0; k < nsessions; ++k)
+        per = std::max(per, item_units(s->geom_segsz[k], s->geom_groups[k] != SIZE_MAX));
+    s->unit_cap = std::min<int64_t>(16384, (int64_t)s->items_cap * per);
+    if (s->unit_cap >= per &&
+        hipMalloc((void **)&s->units_dev, 4 * (size_t)s->unit_cap * kUnitDoubles * sizeof(double)) != hipSuccess) {
+        (void)hipGetLastError();
+        s->units_dev = nullptr;
+    }
+    if (!s->units_dev) s->unit_cap = 0;
     s->worker = std::thread(worker_main, s);
     *out = s;
     return NEBEM_OK;
@@ -531,7 +555,11 @@ void nebem_server_destroy(nebem_server *s)
     for (auto &kv : s->all) delete kv.second;
     if (s->items_host) (void)hipHostFree(s->items_host);
     if (s->items_dev) (void)hipFree(s->items_dev);
-    if (s->sort_ws) (void)hipFree(s->sort_ws);
+    if (s->sort_ws) {
+        (void)hipFreeAsync(s->sort_ws, s->stream);
+        (void)hipStreamSynchronize(s->stream);
+    }
+    if (s->units_dev) (void)hipFree(s->units_dev);
     if (s->imgs_dev) (void)hipFree(s->imgs_dev);
     if (s->group_dev) (void)hipFree(s->group_dev);
     if (s->arena_dev) (void)hipFree(s->arena_dev);

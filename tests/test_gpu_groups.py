@@ -117,3 +117,24 @@ def test_density_that_is_not_finite(nb):
     assert np.all(np.isinf(got[:, 1:]))
     sigma[100] = np.nan
     assert np.all(np.isnan(evaluate(nb, g, sigma, points(g, 200))))
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("copies", ["121", "none"])
+def test_server_units_give_equal_bits(nb, copies, precision):
+    """A launch of few items runs as groups or 16-element runs, one of many as
+    whole items: a short request alone, and the same points at the head of one
+    that fills several rounds, agree with the session's evaluation."""
+    g = geometry(copies)
+    if copies == "121":  # a mesh of 7 groups, or the long request takes seconds
+        g = gem_cell(k=8, nr=2, n_images=6)
+    ses = nb.Session(nb.DevicePanels.from_geometry(g, "cuda:0"), precision=precision)
+    srv = nb.Server([ses], hbm_budget=1 << 30)
+    p = np.ascontiguousarray(points(g, 64 * 9000 if copies == "none" else 64 * 8300))
+    for m in (1, 64, 100, len(p)):
+        q = np.ascontiguousarray(p[:m])
+        got = srv.wait(srv.submit(0, q))[0]
+        ref = torch.stack(ses.eval_points(*[dev(q[:, k]) for k in range(3)]), 1).cpu().numpy()
+        assert np.array_equal(np.stack([got[k] for k in ("phi", "ex", "ey", "ez")], 1), ref)
+    srv.close()
+    ses.close()
