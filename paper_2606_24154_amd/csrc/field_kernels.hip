@@ -27,6 +27,7 @@ namespace nebem {
 
 constexpr int kBlock = 256;
 constexpr int kTileE = kGroupElems;  // elements per LDS tile, evaluation
+constexpr int kRunElems = kGroupElems / kNearRuns;    // elements per unit of a split near pass
 constexpr int kSubElems = kGroupElems / kNearParts;  // elements per unit of a split evaluation
 constexpr int kTileA = 32;   // elements (columns) per workgroup, assembly
 
@@ -1293,7 +1294,8 @@ __device__ __forceinline__ int list_near(NearList &nl, cdouble_p h, const ImgArg
 #pragma unroll 1
         for (int q = lo; q < hi; ++q) {
             const double r2 = group_r2(group_step(v1, -(double)i2, img.a2[r]));
-            const uint64_t b = __ballot(!(r2 >= h[kHeadTier]));
+            uint64_t b = __ballot(!(r2 >= h[kHeadTier]));
+            if (b) b &= ~__ballot(super_far(img, r, i1, i2, Px, Py, Pz, h));
             if (b) {
                 nl.f1[cnt] = -(double)i1;
                 nl.f2[cnt] = -(double)i2;
@@ -1385,8 +1387,8 @@ __device__ __forceinline__ void near_element(const NearList &nl, const Elem &e, 
 }
 
 // Near copies of groups [g0, g1) of one segment (records drec, densities
-// sigma of the segment's n elements), quarters [u0, u1) of each group:
-// quarters added into the group's sum, groups into acc, in that order.
+// sigma of the segment's n elements), runs [u0, u1) of each group:
+// runs added into the group's sum, groups into acc, in that order.
 template <int K>
 __device__ __forceinline__ void near_unit(NearList &nl, cdouble_p drec, cdouble_p sigma, int64_t sig_stride,
                                           cdouble_p gd, int n, const ImgArgs &img, double Px, double Py, double Pz,
@@ -1427,9 +1429,9 @@ __device__ __forceinline__ void near_unit(NearList &nl, cdouble_p drec, cdouble_
                 if (ncopy > kNearCopies)
                     listed = list_near(nl, h, img, c0, min(c0 + kNearCopies, ncopy), Px, Py, Pz);
                 if (listed == 0) continue;
-                const int i1 = min((u + 1) * kSubElems, cnt);
+                const int i1 = min((u + 1) * kRunElems, cnt);
 #pragma unroll 1
-                for (int i = u * kSubElems; i < i1; ++i) {
+                for (int i = u * kRunElems; i < i1; ++i) {
                     if ((second >> i) & 1) continue;
                     cdouble_p p = drec + (int64_t)(e0 + i) * R_STRIDE;
                     const bool pair = (first >> i) & 1;
@@ -1464,7 +1466,9 @@ __device__ __forceinline__ void near_unit(NearList &nl, cdouble_p drec, cdouble_
 }
 
 // Grid: x over points, y over units -- segments (split 0: added to the far
-// pass's sums), groups (split 1) or quarters of groups (split 2).
+// pass's sums), groups (split 1) or runs of 8 of their elements (split
+// 2: with runs of 16 the near pass of 64 points took 505 us, with 8 280, with 4 158, but
+// 2003 points 1.34, 1.30 and 1.45 ms: each unit scans the lattice anew).
 template <int K>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_group_near(const double *__restrict__ drec,
                                                        const double *__restrict__ sigma,
@@ -1477,11 +1481,11 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     __shared__ NearList lists[kBlock / 64];
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     const int j = min(i, m - 1);
-    int y = blockIdx.y, u0 = 0, u1 = kNearParts;
+    int y = blockIdx.y, u0 = 0, u1 = kNearRuns;
     if (split == 2) {
-        u0 = y % (kNearParts);
+        u0 = y % kNearRuns;
         u1 = u0 + 1;
-        y /= kNearParts;
+        y /= kNearRuns;
     }
     const int seg = split ? y / gps : y;
     const int ns = min(segsz, n - seg * segsz);
@@ -1490,7 +1494,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     double acc[K][4];
     near_unit<K>(lists[threadIdx.x >> 6], uniform_ptr(drec + (int64_t)seg * segsz * R_STRIDE),
                  uniform_ptr(sigma + (int64_t)seg * segsz), sig_stride,
-                 uniform_ptr(gdata + (int64_t)seg * gps * kGroupStride), ns, img, px[j], py[j], pz[j], g0, g1, u0, u1,
+                 uniform_ptr(gdata + (int64_t)seg * records_of(gps) * kGroupStride), ns, img, px[j], py[j], pz[j], g0,
+                 g1, u0, u1,
                  acc);
     if (i >= m) return;
     const int64_t o = (int64_t)blockIdx.y * unit_stride + i;
@@ -1511,7 +1516,7 @@ static void launch_near_k(const double *drec, const double *sigma, const double 
 {
     const int gps = groups_per_seg(sp);
     const int64_t ng = (int64_t)sp.nseg * gps;
-    const int64_t units = split == 0 ? sp.nseg : split == 1 ? ng : ng * (kNearParts);
+    const int64_t units = split == 0 ? sp.nseg : split == 1 ? ng : ng * kNearRuns;
     const int bs = split == 0 ? kBlock : 64;
     hipLaunchKernelGGL(k_group_near<K>, dim3((unsigned)((m + bs - 1) / bs), (unsigned)units), dim3(bs), 0, s, drec,
                        sigma, gdata, (int)n, sig_stride, sp.segsz, gps, img, split, px, py, pz, (int)m, out,
@@ -1574,7 +1579,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
     if (g0 >= ng) return;
     double acc[1][4];
     near_unit<1>(list, uniform_ptr(w.drec), uniform_ptr(w.sigma), 0, uniform_ptr(w.gdata), w.n, imgs[w.geom], w.px[j],
-                 w.py[j], w.pz[j], g0, g1, 0, kNearParts, acc);
+                 w.py[j], w.pz[j], g0, g1, 0, kNearRuns, acc);
     if ((int)threadIdx.x >= w.count) return;
     if (units) {
         double *u = units + ((size_t)blockIdx.x * gridDim.y + blockIdx.y) * kUnitDoubles + threadIdx.x;

@@ -46,6 +46,7 @@ constexpr int kGroupL = kGroupP + 1;  // highest degree of the field's
 constexpr int kGroupHead = 16;
 constexpr int kHeadTier = 4;  // index of the first threshold
 constexpr int kTiers = 6;
+constexpr int kHeadSuper = 10;  // of a group: its super-group's centre and far threshold (super-groups: NaN, no point is)
 constexpr int kEntry = 8;
 constexpr int kOrderSplit = 8;
 // entries of the degrees below L in the first and in the second pass
@@ -145,6 +146,16 @@ __device__ __forceinline__ GroupVec group_step(const GroupVec &v, double f, cons
     return {fma(f, a[0], v.x), fma(f, a[1], v.y), fma(f, a[2], v.z)};
 }
 __device__ __forceinline__ double group_r2(const GroupVec &d) { return fma(d.x, d.x, fma(d.y, d.y, d.z * d.z)); }
+
+// Whether a copy is far from the group's super-group, whose expansion then
+// serves it.
+__device__ __forceinline__ bool super_far(const ImgArgs &img, int r, int i1, int i2, double Px, double Py, double Pz,
+                                          cdouble_p head)
+{
+    const GroupVec v0 = group_origin(img, img.axes[r], Px, Py, Pz, head + kHeadSuper);
+    const GroupVec d = group_step(group_step(v0, -(double)i1, img.a1[r]), -(double)i2, img.a2[r]);
+    return group_r2(d) >= head[kHeadSuper + 3];
+}
 
 // The expansion through degree L of the field (entries at coef), added to
 // acc = (phi, Ex, Ey, Ez).  The entries run through two buffers of kAhead

@@ -9,13 +9,17 @@
 // copies nearer than ~7.6 group radii are left to k_group_near
 // (field_kernels.hip), which evaluates them element by element.
 //
+// Copies far from four consecutive groups at once take one expansion of the
+// four, whose moments follow from theirs; with copies up to 5 cells away that is
+// nearly all of them, at a degree two to four higher.
+//
 // Measured (double THGEM, 41 600 elements, 121 copies, 40 000 points): 469 ms
-// with the closed forms everywhere, 102 ms grouped (far pass 74 ms, near pass 26
-// ms, moments 0.18 ms); the far pass issues at ~75 % of the FP64 rate.  Three waves
-// per SIMD and two entries ahead: two waves 79 ms, four 76, one entry ahead 87,
-// three 83.  64 points of the GEM cell, one row or quarter of a group per
-// wave: 23.5 ms -> 0.76 ms.  Error of 2003 GEM points' field against a 64-bit sum:
-// 1.7e-14 before, 1.5e-14 now.
+// with the closed forms everywhere, 102 ms with groups (far pass 74 ms, near pass
+// 26), 59 ms with four at once (far 30, near 28); the far pass issues at ~75 % of the
+// FP64 rate.  Three waves per SIMD and two entries ahead: two waves 79 ms (of 74),
+// four 76, one entry ahead 87, three 83.  64 points of the GEM cell, one row of an
+// expansion or 8 elements of a group per wave: 23.5 ms -> 0.58 ms.  Error of 2003 GEM
+// points' field against a 64-bit sum: 1.6e-14 before, 1.3e-14 now.
 #include <hip/hip_runtime.h>
 
 #include "lattice_far.hpp"
@@ -58,50 +62,82 @@ struct MomElem {
     bool tri;
 };
 
-// The group's centre c and squared radius a2, and the lane's element (record
-// r, density sg) in that frame.
-__device__ __forceinline__ MomElem group_frame(const double *r, double sg, double (&c)[3], double &a2)
+struct Quad {
+    double v[4][3];  // vertices (a triangle's third one twice)
+};
+__device__ __forceinline__ Quad element_vertices(const double *__restrict__ r)
 {
+    Quad e;
     const double lx = r[R_LX], lz = r[R_LZ];
-    const double o[3] = {r[R_OX], r[R_OY], r[R_OZ]};
-    const double u[3] = {lx * r[R_E1X], lx * r[R_E1Y], lx * r[R_E1Z]};
-    const double w[3] = {lz * r[R_E2X], lz * r[R_E2Y], lz * r[R_E2Z]};
     const bool tri = r[R_KIND] != 0.0;
-    double d2[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
-        const double v1 = o[k] + u[k], v2 = o[k] + w[k], v3 = tri ? v2 : v1 + w[k];
-        const double lo = wave_min(fmin(fmin(o[k], v1), fmin(v2, v3)));
-        const double hi = -wave_min(fmin(fmin(-o[k], -v1), fmin(-v2, -v3)));
-        c[k] = 0.5 * (lo + hi);
-        const double d[4] = {o[k] - c[k], v1 - c[k], v2 - c[k], v3 - c[k]};
-#pragma unroll
-        for (int q = 0; q < 4; ++q) d2[q] = fma(d[q], d[q], d2[q]);
+        e.v[0][k] = r[R_OX + k];
+        e.v[1][k] = e.v[0][k] + lx * r[R_E1X + k];
+        e.v[2][k] = e.v[0][k] + lz * r[R_E2X + k];
+        e.v[3][k] = tri ? e.v[2][k] : e.v[1][k] + lz * r[R_E2X + k];
     }
-    a2 = -wave_min(-fmax(fmax(d2[0], d2[1]), fmax(d2[2], d2[3])));
-    const double ia = 1.0 / sqrt(a2);
+    return e;
+}
+// least and largest coordinate k of the wave's vertices
+__device__ __forceinline__ void wave_box(const Quad &e, int k, double &lo, double &hi)
+{
+    lo = wave_min(fmin(fmin(e.v[0][k], e.v[1][k]), fmin(e.v[2][k], e.v[3][k])));
+    hi = -wave_min(-fmax(fmax(e.v[0][k], e.v[1][k]), fmax(e.v[2][k], e.v[3][k])));
+}
+// largest squared distance of the wave's vertices from c, NaN if one is
+__device__ __forceinline__ double wave_radius2(const Quad &e, const double (&c)[3])
+{
+    double a2 = 0.0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        double d2 = 0.0;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            const double d = e.v[q][k] - c[k];
+            d2 = fma(d, d, d2);
+        }
+        a2 = d2 > a2 || d2 != d2 ? d2 : a2;
+    }
+    return __ballot(a2 != a2) ? __builtin_nan("") : -wave_min(-a2);
+}
+// Centre c and squared radius a2 of up to 64 elements, one per lane, one wave.
+__device__ __forceinline__ void group_sphere(const double *__restrict__ recs, int cnt, double (&c)[3], double &a2)
+{
+    const Quad e = element_vertices(recs + (size_t)min((int)(threadIdx.x & 63), cnt - 1) * R_STRIDE);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        double lo, hi;
+        wave_box(e, k, lo, hi);
+        c[k] = 0.5 * (lo + hi);
+    }
+    a2 = wave_radius2(e, c);
+}
+
+// an element (record r, density sg) in the frame of a sphere
+__device__ __forceinline__ MomElem sphere_element(const double *r, double sg, const double (&c)[3], double ia)
+{
+    const double lx = r[R_LX], lz = r[R_LZ], x = lx * ia, z = lz * ia;
     MomElem e;
-    e.ox = (o[0] - c[0]) * ia;
-    e.oy = (o[1] - c[1]) * ia;
-    e.oz = (o[2] - c[2]) * ia;
-    e.ux = u[0] * ia;
-    e.uy = u[1] * ia;
-    e.uz = u[2] * ia;
-    e.wx = w[0] * ia;
-    e.wy = w[1] * ia;
-    e.wz = w[2] * ia;
+    e.ox = (r[R_OX] - c[0]) * ia;
+    e.oy = (r[R_OY] - c[1]) * ia;
+    e.oz = (r[R_OZ] - c[2]) * ia;
+    e.ux = x * r[R_E1X];
+    e.uy = x * r[R_E1Y];
+    e.uz = x * r[R_E1Z];
+    e.wx = z * r[R_E2X];
+    e.wy = z * r[R_E2Y];
+    e.wz = z * r[R_E2Z];
     e.q = sg * (lx * lz);
-    e.tri = tri;
+    e.tri = r[R_KIND] != 0.0;
     return e;
 }
 
-// q (s/a)^n J_n^m(s/|s|) integrated over the lane's element, n = M .. kGroupP
+// adds q (s/a)^n J_n^m(s/|s|) integrated over the lane's element, n = M .. kGroupP
 template <int M>
 __device__ __forceinline__ void element_order(const MomElem &e, double (&ar)[kGroupP + 1 - M],
                                               double (&ai)[kGroupP + 1 - M])
 {
-#pragma unroll
-    for (int k = 0; k <= kGroupP - M; ++k) ar[k] = ai[k] = 0.0;
 #pragma unroll 1
     for (int iv = 0; iv < kRule; ++iv) {
         const double v = kRuleX[iv], sv = e.tri ? 1.0 - v : 1.0;
@@ -139,10 +175,16 @@ __device__ __forceinline__ void element_order(const MomElem &e, double (&ar)[kGr
 
 // the group's sums times their factors, in bre / bim[n]
 template <int M>
-__device__ __forceinline__ void moment_order(const MomElem &e, double *__restrict__ bre, double *__restrict__ bim)
+__device__ __forceinline__ void moment_order(const double *__restrict__ recs, const double *__restrict__ sigma, int cnt,
+                                             const double (&c)[3], double ia, double *__restrict__ bre,
+                                             double *__restrict__ bim)
 {
     double ar[kGroupP + 1 - M], ai[kGroupP + 1 - M];
-    element_order<M>(e, ar, ai);
+#pragma unroll
+    for (int k = 0; k <= kGroupP - M; ++k) ar[k] = ai[k] = 0.0;
+#pragma unroll 1
+    for (int i = threadIdx.x & 63; i < cnt; i += 64)
+        element_order<M>(sphere_element(recs + (size_t)i * R_STRIDE, sigma[i], c, ia), ar, ai);
 #pragma unroll
     for (int n = M; n <= kGroupP; ++n) {
         const double r = wave_sum(ar[n - M]), i = M > 0 ? wave_sum(ai[n - M]) : 0.0;
@@ -159,6 +201,8 @@ __device__ __forceinline__ void coef_order(const MomElem &e, double *__restrict_
 {
     constexpr int W = M / 3 < kSets ? M / 3 : kSets - 1;
     double ar[kGroupP + 1 - M], ai[kGroupP + 1 - M];
+#pragma unroll
+    for (int k = 0; k <= kGroupP - M; ++k) ar[k] = ai[k] = 0.0;
     element_order<M>(e, ar, ai);
 #pragma unroll
     for (int n = M; n <= kGroupP; ++n) {
@@ -171,56 +215,22 @@ __device__ __forceinline__ void coef_order(const MomElem &e, double *__restrict_
 
 __device__ const HarmonicTables kHarmDev = make_harmonic_tables();
 
-// Records of the groups (kGroupStride doubles each, group g of segment s at
-// (s gps + g)); density column k at gdata + k gstride.  A group with a density
-// or a vertex that is not finite gets infinite thresholds: its elements are
-// all evaluated one by one.
-__global__ __launch_bounds__(64 * kMomWaves) void k_group_moments(const double *__restrict__ drec,
-                                                                  const double *__restrict__ sigma, int n,
-                                                                  int64_t sig_stride, int segsz, int gps,
-                                                                  double *__restrict__ gdata, int64_t gstride)
+// Record of a group: its head (centre c, squared radius a2; no super-group, see
+// k_super_moments) and, one (L, m) per thread, the field's coefficients from the
+// moments B = bre + i bim.
+__device__ __forceinline__ void write_record(double *__restrict__ out, const double (&c)[3], double a2, bool bad,
+                                             const double *__restrict__ bre, const double *__restrict__ bim)
 {
-    __shared__ double bre[(kGroupP + 1) * (kGroupP + 1)], bim[(kGroupP + 1) * (kGroupP + 1)];
-    __shared__ int bad;
-    const int seg = blockIdx.x / gps, g = blockIdx.x % gps;
-    const int end = min(n, (seg + 1) * segsz), e0 = seg * segsz + g * kGroupElems;
-    if (e0 >= end) return;  // uniform: this group does not exist in a short last segment
-    const int cnt = min(kGroupElems, end - e0);
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    if (threadIdx.x == 0) bad = 0;
-    const double sg = lane < cnt ? sigma[(size_t)blockIdx.y * sig_stride + e0 + lane] : 0.0;
-    double c[3], a2;
-    const MomElem e = group_frame(drec + (size_t)(e0 + min(lane, cnt - 1)) * R_STRIDE, sg, c, a2);
-    const double a = sqrt(a2);
-    __syncthreads();
-    if (!isfinite(sg) || !(a2 > 0.0) || !isfinite(a2)) bad = 1;  // any lane, the same value
-    switch (wave) {
-    case 0: moment_order<0>(e, bre, bim); break;
-    case 1: moment_order<1>(e, bre, bim); break;
-    case 2: moment_order<2>(e, bre, bim); break;
-    case 3: moment_order<3>(e, bre, bim); break;
-    case 4: moment_order<4>(e, bre, bim); break;
-    case 5: moment_order<5>(e, bre, bim); break;
-    case 6: moment_order<6>(e, bre, bim); break;
-    case 7: moment_order<7>(e, bre, bim); break;
-    case 8: moment_order<8>(e, bre, bim); break;
-    case 9: moment_order<9>(e, bre, bim); break;
-    case 10: moment_order<10>(e, bre, bim); break;
-    case 11: moment_order<11>(e, bre, bim); break;
-    case 12: moment_order<12>(e, bre, bim); break;
-    case 13: moment_order<13>(e, bre, bim); break;
-    default: moment_order<14>(e, bre, bim); break;
-    }
-    __syncthreads();
-    double *out = gdata + (int64_t)blockIdx.y * gstride + (int64_t)blockIdx.x * kGroupStride;
     if (threadIdx.x < kGroupHead) {
         const int k = threadIdx.x;
         const double inf = __builtin_inf();
         const double t = k < kHeadTier + kTiers ? a2 * tier_ratio2(k - kHeadTier) : 0.0;
-        out[k] = k == 0 ? c[0] : k == 1 ? c[1] : k == 2 ? c[2] : k == 3 ? a : bad ? inf : t;
+        double v = k < 3 ? c[min(k, 2)] : k == 3 ? sqrt(a2) : bad ? inf : t;
+        if (k >= kHeadSuper && k < kHeadSuper + 3) v = c[min(k - kHeadSuper, 2)];
+        if (k == kHeadSuper + 3) v = __builtin_nan("");
+        out[k] = v;
     }
-    // coefficients of the field's harmonics, one (L, m) per thread
-    for (int t = threadIdx.x; t < kGroupEntries; t += 64 * kMomWaves) {
+    for (int t = threadIdx.x; t < kGroupEntries; t += blockDim.x) {
         int L = 1, m = t;
         while (m > L) {
             m -= L + 1;
@@ -254,14 +264,200 @@ __global__ __launch_bounds__(64 * kMomWaves) void k_group_moments(const double *
     }
 }
 
+// Records of the groups (kGroupStride doubles each, record q of segment s at
+// (s rps + q): gps groups, then the super-groups); density column k at gdata + k
+// gstride.  A group with a density or a vertex that is not finite gets
+// infinite thresholds: its elements are all evaluated one by one, and so is a
+// super-group's share left to its groups.
+__global__ __launch_bounds__(64 * kMomWaves) void k_group_moments(const double *__restrict__ drec,
+                                                                  const double *__restrict__ sigma, int n,
+                                                                  int64_t sig_stride, int segsz, int gps, int rps,
+                                                                  double *__restrict__ gdata, int64_t gstride)
+{
+    __shared__ double bre[(kGroupP + 1) * (kGroupP + 1)], bim[(kGroupP + 1) * (kGroupP + 1)];
+    const int seg = blockIdx.x / gps, q = blockIdx.x % gps;
+    const int end = min(n, (seg + 1) * segsz), e0 = seg * segsz + q * kGroupElems;
+    if (e0 >= end) return;  // uniform: this group does not exist in a short last segment
+    const int cnt = min(kGroupElems, end - e0);
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const double *recs = drec + (size_t)e0 * R_STRIDE;
+    const double *sg = sigma + (size_t)blockIdx.y * sig_stride;
+    double c[3], a2;
+    group_sphere(recs, cnt, c, a2);
+    const bool bad = !(a2 > 0.0) || !isfinite(a2) || __ballot(lane < cnt && !isfinite(sg[e0 + lane])) != 0;
+    const double ia = 1.0 / sqrt(a2);
+    sg += e0;
+    switch (wave) {
+    case 0: moment_order<0>(recs, sg, cnt, c, ia, bre, bim); break;
+    case 1: moment_order<1>(recs, sg, cnt, c, ia, bre, bim); break;
+    case 2: moment_order<2>(recs, sg, cnt, c, ia, bre, bim); break;
+    case 3: moment_order<3>(recs, sg, cnt, c, ia, bre, bim); break;
+    case 4: moment_order<4>(recs, sg, cnt, c, ia, bre, bim); break;
+    case 5: moment_order<5>(recs, sg, cnt, c, ia, bre, bim); break;
+    case 6: moment_order<6>(recs, sg, cnt, c, ia, bre, bim); break;
+    case 7: moment_order<7>(recs, sg, cnt, c, ia, bre, bim); break;
+    case 8: moment_order<8>(recs, sg, cnt, c, ia, bre, bim); break;
+    case 9: moment_order<9>(recs, sg, cnt, c, ia, bre, bim); break;
+    case 10: moment_order<10>(recs, sg, cnt, c, ia, bre, bim); break;
+    case 11: moment_order<11>(recs, sg, cnt, c, ia, bre, bim); break;
+    case 12: moment_order<12>(recs, sg, cnt, c, ia, bre, bim); break;
+    case 13: moment_order<13>(recs, sg, cnt, c, ia, bre, bim); break;
+    default: moment_order<14>(recs, sg, cnt, c, ia, bre, bim); break;
+    }
+    __syncthreads();
+    write_record(gdata + (int64_t)blockIdx.y * gstride + (int64_t)(seg * rps + q) * kGroupStride, c, a2, bad, bre, bim);
+}
+
+// Records of the super-groups from those of their groups: the moments about
+// the common centre are exact finite sums over the groups' (addition theorem of
+// R_n^m = r^n P_n^m e^(i m phi) / (n+m)!, with R_n^-m = (-1)^m conj R_n^m and the
+// Condon-Shortley sign),
+//   R_n^m(s + d) = sum_{k,l} R_k^l(d) R_{n-k}^{m-l}(s).
+// One thread per group and (n, m).  Integrating the elements again about the
+// common centre took 150 us for 8064 elements; this takes 26.
+constexpr int kTerms = (kGroupP + 1) * (kGroupP + 2) / 2;
+constexpr int kOrders = (kGroupP + 1) * (kGroupP + 1);
+__device__ __forceinline__ int order(int n, int m) { return n * (n + 1) + m; }
+// (n, m) and (n, -m), m >= 0, from R_n^m without the Condon-Shortley sign
+__device__ __forceinline__ void put_orders(double2 *t, int n, int m, double re, double im)
+{
+    const double s = m & 1 ? -1.0 : 1.0;
+    t[order(n, m)] = {s * re, s * im};
+    if (m > 0) t[order(n, -m)] = {re, -im};
+}
+__global__ __launch_bounds__(128 * kSuper) void k_super_moments(const double *__restrict__ drec, int n, int segsz, int gps,
+                                                                int rps, double *__restrict__ gdata, int64_t gstride)
+{
+    __shared__ double2 R[kSuper][kOrders];  // a group's sums, orders -n .. n
+    __shared__ double2 T[kSuper][kOrders];  // R of its offset
+    __shared__ double bre[(kGroupP + 1) * (kGroupP + 1)], bim[(kGroupP + 1) * (kGroupP + 1)];
+    __shared__ double fact[kGroupP + 1];
+    const int sps = rps - gps, seg = blockIdx.x / sps, sq = blockIdx.x % sps;
+    const int end = min(n, (seg + 1) * segsz), s0 = seg * segsz + sq * (kSuper * kGroupElems);
+    if (s0 >= end) return;
+    double *const seg_data = gdata + (int64_t)blockIdx.y * gstride + (int64_t)seg * rps * kGroupStride;
+    double sc[3], sa2;
+    {  // the sphere, every wave a group's elements
+        __shared__ double box[kSuper][6], rad[kSuper];
+        const int w = threadIdx.x >> 6, g = w & (kSuper - 1);
+        const Quad e = element_vertices(
+            drec + (size_t)min(s0 + g * kGroupElems + (int)(threadIdx.x & 63), end - 1) * R_STRIDE);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            double lo, hi;
+            wave_box(e, k, lo, hi);
+            if ((threadIdx.x & 63) == 0 && w < kSuper) {
+                box[g][k] = lo;
+                box[g][3 + k] = hi;
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            double lo = box[0][k], hi = box[0][3 + k];
+#pragma unroll
+            for (int j = 1; j < kSuper; ++j) {
+                lo = fmin(lo, box[j][k]);
+                hi = fmax(hi, box[j][3 + k]);
+            }
+            sc[k] = 0.5 * (lo + hi);
+        }
+        const double a2 = wave_radius2(e, sc);
+        if ((threadIdx.x & 63) == 0 && w < kSuper) rad[g] = a2;
+        __syncthreads();
+        sa2 = rad[0];
+#pragma unroll
+        for (int j = 1; j < kSuper; ++j) sa2 = rad[j] > sa2 || rad[j] != rad[j] ? rad[j] : sa2;
+    }
+    const double ia = 1.0 / sqrt(sa2);
+    const int child = threadIdx.x >> 7, q = threadIdx.x & 127;
+    const bool has = s0 + child * kGroupElems < end;
+    double *rec = seg_data + (int64_t)(sq * kSuper + (has ? child : 0)) * kGroupStride;
+    if (threadIdx.x == 0) {
+        double f = 1.0;
+        for (int k = 0; k <= kGroupP; ++k) {
+            fact[k] = f;
+            f *= k + 1;
+        }
+    }
+    int tn = 0, tm = q;
+    while (tm > tn) {
+        tm -= tn + 1;
+        ++tn;
+    }
+    __syncthreads();
+    if (q < kTerms) {  // from the coefficient of Ez at (n + 1, m)
+        const double *e = rec + kGroupHead + kEntry * entry_index(tn + 1, tm);
+        double f = kHarmDev.lam[tn + 1][tm] / ((tn + 1 - tm) * (tm ? 2.0 : 1.0) * fact[tn - tm]);
+        const double ratio = rec[3] * ia;
+        for (int k = 0; k < tn; ++k) f *= ratio;
+        put_orders(R[child], tn, tm, has ? f * e[4] : 0.0, has ? f * e[5] : 0.0);
+    }
+    if (q <= kGroupP) {  // column q of the offset's table
+        const double x = (rec[0] - sc[0]) * ia, y = (rec[1] - sc[1]) * ia, z = (rec[2] - sc[2]) * ia;
+        const double r2 = fma(x, x, fma(y, y, z * z));
+        double cr = 1.0, ci = 0.0, pr = 0.0, pi = 0.0;
+        for (int k = 1; k <= q; ++k) {
+            const double h = 0.5 / k, t = h * fma(cr, x, -(ci * y));
+            ci = h * fma(cr, y, ci * x);
+            cr = t;
+        }
+        for (int k = q; k <= kGroupP; ++k) {
+            put_orders(T[child], k, q, cr, ci);
+            const double d = 1.0 / ((k + q + 1.0) * (k - q + 1.0)), w = (2 * k + 1) * z;
+            const double nr = d * fma(w, cr, -(r2 * pr)), ni = d * fma(w, ci, -(r2 * pi));
+            pr = cr;
+            pi = ci;
+            cr = nr;
+            ci = ni;
+        }
+    }
+    __syncthreads();
+    double sr = 0.0, si = 0.0;
+    if (q < kTerms)
+        for (int k = 0; k <= tn; ++k) {
+            const int j = tn - k, l0 = max(-k, tm - j), l1 = min(k, tm + j);
+            const double2 *t = &T[child][order(k, 0)], *r = &R[child][order(j, tm)];
+#pragma unroll 4
+            for (int l = l0; l <= l1; ++l) {
+                const double2 u = t[l], v = r[-l];
+                sr = fma(u.x, v.x, fma(-u.y, v.y, sr));
+                si = fma(u.x, v.y, fma(u.y, v.x, si));
+            }
+        }
+    __syncthreads();
+    if (q < kTerms) T[child][q] = {sr, si};
+    __syncthreads();
+    if (child == 0 && q < kTerms) {
+        const double f = (tm ? 2.0 : 1.0) * fact[tn - tm] * (tm & 1 ? -1.0 : 1.0);
+        double r = T[0][q].x, i = T[0][q].y;
+#pragma unroll
+        for (int c = 1; c < kSuper; ++c) {
+            r += T[c][q].x;
+            i += T[c][q].y;
+        }
+        bre[tn * (kGroupP + 1) + tm] = f * r;
+        bim[tn * (kGroupP + 1) + tm] = f * i;
+    }
+    __syncthreads();
+    // a group that is not fit leaves its super-group's share to the groups
+    bool bad = !(sa2 > 0.0) || !isfinite(sa2);
+    for (int k = 0; k < kSuper && s0 + k * kGroupElems < end; ++k)
+        bad = bad || seg_data[(int64_t)(sq * kSuper + k) * kGroupStride + kHeadTier] == __builtin_inf();
+    if (has && q < 4) rec[kHeadSuper + q] = q < 3 ? sc[min(q, 2)] : bad ? __builtin_inf() : sa2 * tier_ratio2(0);
+    write_record(seg_data + (int64_t)(gps + sq) * kGroupStride, sc, sa2, bad, bre, bim);
+}
+
 void launch_group_moments(const double *drec, const double *sigma, int64_t n, int64_t sig_stride, int ncol,
                           const SegPlan &sp, double *gdata, hipStream_t s)
 {
     if (n <= 0 || ncol <= 0) return;
-    const int gps = groups_per_seg(sp);
+    const int gps = groups_per_seg(sp), rps = records_per_seg(sp);
+    const int64_t gstride = (int64_t)sp.nseg * rps * kGroupStride;
     hipLaunchKernelGGL(k_group_moments, dim3((unsigned)(sp.nseg * gps), (unsigned)ncol), dim3(64 * kMomWaves), 0, s,
-                       drec, sigma, (int)n, sig_stride, sp.segsz, gps, gdata,
-                       (int64_t)sp.nseg * gps * kGroupStride);
+                       drec, sigma, (int)n, sig_stride, sp.segsz, gps, rps, gdata, gstride);
+    hipLaunchKernelGGL(k_super_moments, dim3((unsigned)(sp.nseg * (rps - gps)), (unsigned)ncol), dim3(128 * kSuper), 0,
+                       s, drec, (int)n, sp.segsz, gps, rps, gdata, gstride);
 }
 
 // Moments of every element about its group's centre, kElemCoefs each, and
@@ -275,7 +471,8 @@ __global__ __launch_bounds__(64 * kMomWaves) void k_element_moments(const double
     const int e0 = blockIdx.x * kGroupElems, cnt = min(kGroupElems, n - e0);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     double c[3], a2;
-    const MomElem e = group_frame(drec + (size_t)(e0 + min(lane, cnt - 1)) * R_STRIDE, 1.0, c, a2);
+    group_sphere(drec + (size_t)e0 * R_STRIDE, cnt, c, a2);
+    const MomElem e = sphere_element(drec + (size_t)(e0 + min(lane, cnt - 1)) * R_STRIDE, 1.0, c, 1.0 / sqrt(a2));
     if (threadIdx.x < kGroupHead) {
         const int k = threadIdx.x;
         const double inf = __builtin_inf();
@@ -322,21 +519,22 @@ void launch_element_moments(const double *drec, int64_t n, double *heads, double
 }
 
 // --------------------------------------------------------------------- far
-// Far copies of groups [g0, g1) of a segment at one point per lane, lattice
-// rows [q0, q1) (row q: reflection q / (2 n1 + 1), translation i1 = q % (2 n1 +
+// Far copies of the expansions [g0, g1) of a segment (its ng groups, then its
+// super-groups, whose records follow those of gps groups) at one point per lane,
+// lattice rows [q0, q1) (row q: reflection q / (2 n1 + 1), translation i1 = q % (2 n1 +
 // 1) - n1): rows added into the group's sum, groups into acc, in that order.
 // FP64 VALU bound; the coefficients come through the scalar cache (64 bytes per
 // nine vector instructions), nothing is staged in LDS and the waves of a
 // workgroup run independently.
-__device__ __forceinline__ void far_unit(cdouble_p gd, const ImgArgs &img, double Px, double Py, double Pz, int g0,
-                                         int g1, int q0, int q1, double (&acc)[4])
+__device__ __forceinline__ void far_unit(cdouble_p gd, int ng, int gps, const ImgArgs &img, double Px, double Py,
+                                         double Pz, int g0, int g1, int q0, int q1, double (&acc)[4])
 {
 #pragma clang fp contract(off)
     for (int c = 0; c < 4; ++c) acc[c] = 0.0;
     const int nrow = 2 * img.n1 + 1;
 #pragma unroll 1
     for (int g = g0; g < g1; ++g) {
-        cdouble_p h = gd + (int64_t)g * kGroupStride;
+        cdouble_p h = gd + (int64_t)(g < ng ? g : gps + g - ng) * kGroupStride;
         const double a = h[3];
         double grp[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll 1
@@ -345,12 +543,17 @@ __device__ __forceinline__ void far_unit(cdouble_p gd, const ImgArgs &img, doubl
             const int ax = img.axes[r];
             const GroupVec v0 = group_origin(img, ax, Px, Py, Pz, h);
             const GroupVec v1 = group_step(v0, -(double)i1, img.a1[r]);
+            const GroupVec s1 =
+                group_step(group_origin(img, ax, Px, Py, Pz, h + kHeadSuper), -(double)i1, img.a1[r]);
             double row[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll 1
             for (int i2 = -img.n2; i2 <= img.n2; ++i2) {
+                // copies far from the super-group are not a group's
+                const bool own = !(group_r2(group_step(s1, -(double)i2, img.a2[r])) >= h[kHeadSuper + 3]);
+                if (__ballot(own) == 0) continue;
                 const GroupVec d = group_step(v1, -(double)i2, img.a2[r]);
                 const double r2 = group_r2(d);
-                if (r2 >= h[kHeadTier]) {
+                if (own && r2 >= h[kHeadTier]) {
                     if (r2 >= h[kHeadTier + 3]) {
                         if (r2 >= h[kHeadTier + 5])
                             group_far<5>(d, r2, a, h + kGroupHead, row);
@@ -378,13 +581,13 @@ __device__ __forceinline__ void far_unit(cdouble_p gd, const ImgArgs &img, doubl
     }
 }
 
-// Grid: x over points, y over units -- whole segments (split 0), groups
-// (split 1) or lattice rows of groups (split 2; y = group * rows + row) --, z
+// Grid: x over points, y over units -- whole segments (split 0), expansions
+// (split 1) or lattice rows of them (split 2; y = record * rows + row) --, z
 // over density columns (their shared harmonics are a third of the work, but
 // two columns at once need more registers than three waves per SIMD leave).
 // Unit y's unscaled sums go to the outputs + y * unit_stride.
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void k_group_far(
-    const double *__restrict__ gdata, int64_t gstride, int n, int segsz, int gps, ImgArgs img, int split,
+    const double *__restrict__ gdata, int64_t gstride, int n, int segsz, int gps, int rps, ImgArgs img, int split,
     const double *__restrict__ px, const double *__restrict__ py, const double *__restrict__ pz, int m, OutCols out,
     int64_t unit_stride)
 {
@@ -397,12 +600,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
         q1 = q0 + 1;
         y /= rows;
     }
-    const int seg = split ? y / gps : y;
+    const int seg = split ? y / rps : y;
     const int ng = (min(segsz, n - seg * segsz) + kGroupElems - 1) / kGroupElems;
-    const int g0 = split ? y % gps : 0, g1 = split ? min(g0 + 1, ng) : ng;
+    int g0 = 0, g1 = records_of(ng);
+    if (split) {  // record q of the segment, if it exists
+        const int q = y % rps, k = q < gps ? q : ng + q - gps;
+        g0 = k;
+        g1 = (q < gps ? q < ng : k < g1) ? k + 1 : k;
+    }
     double acc[4];
-    far_unit(uniform_ptr(gdata + (int64_t)blockIdx.z * gstride + (int64_t)seg * gps * kGroupStride), img, px[j], py[j],
-             pz[j], g0, g1, q0, q1, acc);
+    far_unit(uniform_ptr(gdata + (int64_t)blockIdx.z * gstride + (int64_t)seg * rps * kGroupStride), ng, gps, img, px[j],
+             py[j], pz[j], g0, g1, q0, q1, acc);
     if (i >= m) return;
     const int64_t o = (int64_t)blockIdx.y * unit_stride + (int64_t)blockIdx.z * out.stride + i;
     for (int c = 0; c < 4; ++c)
@@ -414,18 +622,18 @@ void launch_group_far(const double *gdata, int64_t n, int ncol, const SegPlan &s
                       int64_t unit_stride, hipStream_t s)
 {
     if (m <= 0 || n <= 0) return;
-    const int gps = groups_per_seg(sp);
-    const int64_t ng = (int64_t)sp.nseg * gps, rows = (int64_t)img.nref * (2 * img.n1 + 1);
-    const int64_t units = split == 0 ? sp.nseg : split == 1 ? ng : ng * rows;
+    const int gps = groups_per_seg(sp), rps = records_per_seg(sp);
+    const int64_t nrec = (int64_t)sp.nseg * rps, rows = (int64_t)img.nref * (2 * img.n1 + 1);
+    const int64_t units = split == 0 ? sp.nseg : split == 1 ? nrec : nrec * rows;
     const int bs = split == 0 ? 256 : 64;
     hipLaunchKernelGGL(k_group_far, dim3((unsigned)((m + bs - 1) / bs), (unsigned)units, (unsigned)ncol), dim3(bs), 0,
-                       s, gdata, ng * kGroupStride, (int)n, sp.segsz, gps, img, split, px, py, pz, (int)m, out,
+                       s, gdata, nrec * kGroupStride, (int)n, sp.segsz, gps, rps, img, split, px, py, pz, (int)m, out,
                        unit_stride);
 }
 
 // Serving: workgroup (one wave) b takes work item b where its geometry is
 // grouped -- the far part of one segment at up to 64 points of one request, or
-// (units set) of group y of it, whose sums go to units[b][y][component][lane].
+// (units set) of expansion y of it, whose sums go to units[b][y][component][lane].
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3, 3))) void k_items_far(
     const WorkItem *__restrict__ items, const ImgArgs *__restrict__ imgs, double *__restrict__ units)
 {
@@ -434,10 +642,12 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3, 3))) void
     const ImgArgs &img = imgs[w.geom];
     const int j = min((int)threadIdx.x, w.count - 1);
     const int ng = (w.n + kGroupElems - 1) / kGroupElems;
-    const int g0 = units ? (int)blockIdx.y : 0, g1 = units ? g0 + 1 : ng;
-    if (g0 >= ng) return;
+    const int nrec = records_of(ng);
+    const int g0 = units ? (int)blockIdx.y : 0, g1 = units ? g0 + 1 : nrec;
+    if (g0 >= nrec) return;
     double acc[4];
-    far_unit(uniform_ptr(w.gdata), img, w.px[j], w.py[j], w.pz[j], g0, g1, 0, img.nref * (2 * img.n1 + 1), acc);
+    far_unit(uniform_ptr(w.gdata), ng, w.groups, img, w.px[j], w.py[j], w.pz[j], g0, g1, 0,
+             img.nref * (2 * img.n1 + 1), acc);
     if ((int)threadIdx.x >= w.count) return;
     if (units) {
         double *u = units + ((size_t)blockIdx.x * gridDim.y + blockIdx.y) * kUnitDoubles + threadIdx.x;
@@ -466,11 +676,12 @@ __global__ __launch_bounds__(256) void k_items_fold(const WorkItem *__restrict__
     const int c = threadIdx.x >> 6, lane = threadIdx.x & 63;
     if (lane >= w.count) return;
     const int64_t o = (int64_t)blockIdx.x * per * kUnitDoubles + threadIdx.x;
-    const int cnt = item_units(w.n, w.gdata != nullptr);
+    const int nfar = item_units(w.n, w.gdata != nullptr);
+    const int cnt = w.gdata ? (w.n + kGroupElems - 1) / kGroupElems : nfar;
     double f = 0.0, n = 0.0;
     for (int u = 0; u < cnt; ++u) n += near[o + (int64_t)u * kUnitDoubles];
     if (w.gdata) {
-        for (int u = 0; u < cnt; ++u) f += far[o + (int64_t)u * kUnitDoubles];
+        for (int u = 0; u < nfar; ++u) f += far[o + (int64_t)u * kUnitDoubles];
         n = f + n;
     }
     (c == 0 ? w.phi : c == 1 ? w.ex : c == 2 ? w.ey : w.ez)[lane] = n;
@@ -485,7 +696,7 @@ void launch_items_fold(const WorkItem *items, int nitems, const double *far, con
 
 // ------------------------------------------------------------ finer units
 // Sums of a split evaluation back to one value per segment, in the order the
-// unsplit kernels add them: rows / quarters into their group, groups into their
+// unsplit kernels add them: rows / runs into their group, groups into their
 // segment, the segment's far and near sums added last.
 __global__ __launch_bounds__(256) void k_fold_units(const double *__restrict__ in, int per, int64_t len,
                                                     double *__restrict__ out)
@@ -499,16 +710,15 @@ __global__ __launch_bounds__(256) void k_fold_units(const double *__restrict__ i
 }
 
 __global__ __launch_bounds__(256) void k_fold_groups(const double *__restrict__ far, const double *__restrict__ near,
-                                                     int gps, int64_t len, double *__restrict__ out)
+                                                     int rps, int gps, int64_t len, double *__restrict__ out)
 {
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (i >= len) return;
-    const int64_t o = (int64_t)blockIdx.y * gps * len + i;
+    far += (int64_t)blockIdx.y * rps * len + i;
+    near += (int64_t)blockIdx.y * gps * len + i;
     double f = 0.0, n = 0.0;
-    for (int g = 0; g < gps; ++g) {
-        f += far[o + g * len];
-        n += near[o + g * len];
-    }
+    for (int g = 0; g < rps; ++g) f += far[g * len];
+    for (int g = 0; g < gps; ++g) n += near[g * len];
     out[(int64_t)blockIdx.y * len + i] = f + n;
 }
 
@@ -522,7 +732,7 @@ void launch_fold_groups(const double *far, const double *near, const SegPlan &sp
                         hipStream_t s)
 {
     hipLaunchKernelGGL(k_fold_groups, dim3((unsigned)((len + 255) / 256), (unsigned)sp.nseg), dim3(256), 0, s, far,
-                       near, groups_per_seg(sp), len, out);
+                       near, records_per_seg(sp), groups_per_seg(sp), len, out);
 }
 
 // ----------------------------------------------------------------- the rule
@@ -538,7 +748,7 @@ bool eval_grouped(int64_t n, const ImgArgs &img)
 
 size_t group_data_bytes(const SegPlan &sp, int ncol)
 {
-    return (size_t)sp.nseg * groups_per_seg(sp) * kGroupStride * (size_t)ncol * sizeof(double);
+    return (size_t)sp.nseg * records_per_seg(sp) * kGroupStride * (size_t)ncol * sizeof(double);
 }
 
 }  // namespace nebem

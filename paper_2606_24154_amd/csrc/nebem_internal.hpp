@@ -72,7 +72,7 @@ struct WorkItem {
     int n;      // elements in the segment
     int geom;   // index into the image-argument array
     int count;  // points in this item (<= 64)
-    int pad;
+    int groups; // groups of a full segment of its geometry
 };
 
 // ---- field kernels (field_kernels.hip)
@@ -166,8 +166,14 @@ struct SegPlan {
 // kGroupElems consecutive elements of a segment, groups_per_seg of them per
 // segment (fewer in a short last one).
 constexpr int kGroupElems = 64;
-constexpr int kNearParts = 4;  // parts of a group (16 elements) that a split near pass makes units of
+constexpr int kNearParts = 4;  // runs of 16 elements per group, units of an ungrouped split evaluation
+constexpr int kNearRuns = 8;   // runs of 8 elements per group, units of a split near pass
 inline int groups_per_seg(const SegPlan &sp) { return (sp.segsz + kGroupElems - 1) / kGroupElems; }
+// Far expansions of a segment: one per group, then one per kSuper consecutive
+// groups for the copies far from all of them.
+constexpr int kSuper = 4;
+__host__ __device__ inline int records_of(int groups) { return groups + (groups + kSuper - 1) / kSuper; }
+inline int records_per_seg(const SegPlan &sp) { return records_of(groups_per_seg(sp)); }
 // Whether an FP64 evaluation takes far copies of whole groups by their
 // expansions: a function of the geometry only, like the segment plan.
 bool eval_grouped(int64_t n, const ImgArgs &img);
@@ -178,7 +184,7 @@ void launch_group_moments(const double *drec, const double *sigma, int64_t n, in
 // Far and near parts of a grouped evaluation, one pass each.  split 0: units
 // are segments, and the near pass adds to the far pass's sums; split > 0:
 // finer units, each pass with outputs of its own (far 1: groups, 2: lattice
-// rows of groups; near 1: groups, 2: quarters of groups).  Unit y's unscaled
+// rows of groups; near 1: groups, 2: runs of 8 elements).  Unit y's unscaled
 // sums go to the outputs + y * unit_stride.
 void launch_group_far(const double *gdata, int64_t n, int ncol, const SegPlan &sp, const ImgArgs &img, int split,
                       const double *px, const double *py, const double *pz, int64_t m, const OutCols &out,
@@ -249,10 +255,13 @@ hipError_t run_eval(const double *drec, const double *sigma, int64_t n, int ncol
 // work items (one wave each) the device holds at once: CUs x resident
 // workgroups of the items kernel per CU (1 when the query fails)
 int eval_items_slots(int mixed);
-// Units of an item: its groups if its geometry is grouped, else runs of 16
-// elements; per unit 4 x 64 partial sums.
+// Units of an item: its far expansions (and of the near part its groups) if its
+// geometry is grouped, else runs of 16 elements; per unit 4 x 64 partial sums.
 constexpr int kUnitDoubles = 256;
-__host__ __device__ inline int item_units(int n, bool grouped) { return grouped ? (n + 63) / 64 : (n + 15) / 16; }
+__host__ __device__ inline int item_units(int n, bool grouped)
+{
+    return grouped ? records_of((n + 63) / 64) : (n + 15) / 16;
+}
 // items/imgs in device memory; one 64-lane workgroup per item, or (units not
 // null: 2 cap kUnitDoubles doubles) per unit, at most `per` of them an item
 void launch_eval_items(const WorkItem *items, int nitems, const ImgArgs *imgs, int mixed, double near_factor,

@@ -286,7 +286,7 @@ struct EvalShape {
     SegPlan sp;
     int kc;           // columns per launch
     bool grouped;     // FP64 with far copies of whole groups (group_kernels.hip)
-    int64_t ngroup, rows;  // groups of the plan, lattice rows of a group
+    int64_t ngroup, nrec, rows;  // groups of the plan, far expansions, lattice rows of one
     size_t part_pp;   // partial-sum bytes per point (0: one segment, no partials)
 };
 
@@ -297,6 +297,7 @@ EvalShape eval_shape(int64_t n, const ImgArgs &img, int ncol, int mixed)
     sh.kc = ncol < kMultiCols ? ncol : kMultiCols;
     sh.grouped = !mixed && eval_grouped(n, img);
     sh.ngroup = (int64_t)sh.sp.nseg * groups_per_seg(sh.sp);
+    sh.nrec = (int64_t)sh.sp.nseg * records_per_seg(sh.sp);
     sh.rows = (int64_t)img.nref * (2 * img.n1 + 1);
     sh.part_pp = sh.sp.nseg > 1 || sh.grouped ? (size_t)32 * sh.kc * sh.sp.nseg : 0;
     return sh;
@@ -304,11 +305,11 @@ EvalShape eval_shape(int64_t n, const ImgArgs &img, int ncol, int mixed)
 
 // Units of a grouped evaluation of c points (launch_group_far / _near): whole
 // segments once these alone are several rounds of waves (8 segments of a GEM
-// cell: from 65 536 points), groups below that, and rows / quarters of groups
+// cell: from 65 536 points), groups below that, and rows / runs of groups
 // when even the groups leave SIMDs without a wave (1024 SIMDs; 64 points of a
-// GEM cell have 126 group waves, 1386 row waves).  No result bit depends on
+// GEM cell have 160 expansions, 1760 row waves).  No result bit depends on
 // the choice.  A split needs its unit sums in memory: at most kSplitBudget.
-constexpr size_t kSplitBudget = size_t(192) << 20;
+constexpr size_t kSplitBudget = size_t(384) << 20;
 constexpr int64_t kMaxUnits = 65535;  // grid y
 void pick_splits(const EvalShape &sh, int64_t c, int &far, int &near)
 {
@@ -322,9 +323,9 @@ void pick_splits(const EvalShape &sh, int64_t c, int &far, int &near)
         far = fits((int64_t)sh.sp.nseg * eval_subunits(sh.sp)) ? 1 : 0;
         return;
     }
-    if (!fits(sh.ngroup)) return;
-    far = waves * sh.ngroup < 2048 && fits(sh.ngroup * sh.rows) ? 2 : 1;
-    near = waves * sh.ngroup < 8192 && fits(sh.ngroup * kNearParts) ? 2 : 1;
+    if (!fits(sh.nrec)) return;
+    far = waves * sh.nrec < 2048 && fits(sh.nrec * sh.rows) ? 2 : 1;
+    near = waves * sh.ngroup < 8192 && fits(sh.ngroup * kNearRuns) ? 2 : 1;
 }
 
 // workspace layout of one chunk of c points: [sort scratch | perm | sorted
@@ -360,10 +361,10 @@ bool chunk_layout(const EvalShape &sh, int64_t c, size_t limit, ChunkLayout &L)
     const size_t base = off;
     pick_splits(sh, c, L.fsplit, L.nsplit);
     for (;;) {
-        const size_t unit = (size_t)32 * sh.kc * (size_t)c, g = (size_t)sh.ngroup;
-        L.far = take(!L.fsplit ? 0 : !sh.grouped ? unit * g * kNearParts : unit * g * (L.fsplit == 2 ? sh.rows : 1));
-        L.near = take(L.nsplit ? unit * g * (L.nsplit == 2 ? kNearParts : 1) : 0);
-        L.ffold = take(L.fsplit == 2 ? unit * g : 0);
+        const size_t unit = (size_t)32 * sh.kc * (size_t)c, g = (size_t)sh.ngroup, f = (size_t)sh.nrec;
+        L.far = take(!L.fsplit ? 0 : !sh.grouped ? unit * g * kNearParts : unit * f * (L.fsplit == 2 ? sh.rows : 1));
+        L.near = take(L.nsplit ? unit * g * (L.nsplit == 2 ? kNearRuns : 1) : 0);
+        L.ffold = take(L.fsplit == 2 ? unit * f : 0);
         L.nfold = take(L.nsplit == 2 ? unit * g : 0);
         L.total = off;
         if (off <= limit || !L.fsplit) return true;
@@ -405,12 +406,12 @@ void eval_grouped_chunk(const double *drec, const double *sg, int64_t n, int k, 
     launch_group_near(drec, sg, gd, n, n, k, sh.sp, img, L.nsplit, px, py, pz, c, cols(near), seg_stride, s);
     if (L.fsplit == 2) {
         double *f = reinterpret_cast<double *>(w + L.ffold);
-        launch_fold_units(far, sh.ngroup, (int)sh.rows, seg_stride, f, s);
+        launch_fold_units(far, sh.nrec, (int)sh.rows, seg_stride, f, s);
         far = f;
     }
     if (L.nsplit == 2) {
         double *f = reinterpret_cast<double *>(w + L.nfold);
-        launch_fold_units(near, sh.ngroup, kNearParts, seg_stride, f, s);
+        launch_fold_units(near, sh.ngroup, kNearRuns, seg_stride, f, s);
         near = f;
     }
     launch_fold_groups(far, near, sh.sp, seg_stride, reinterpret_cast<double *>(w + L.part), s);

@@ -242,11 +242,11 @@ static void worker_main(nebem_server *s)
                 w.n = ne;
                 w.geom = r->geom;
                 w.count = cnt;
-                w.pad = 0;
                 const size_t go = s->geom_groups[r->geom];
                 const SegPlan gp = {r->nseg, s->geom_segsz[r->geom]};
+                w.groups = groups_per_seg(gp);
                 w.gdata = go == SIZE_MAX ? nullptr
-                                         : group_cur + go + (size_t)seg * groups_per_seg(gp) * kGroupStride;
+                                         : group_cur + go + (size_t)seg * records_per_seg(gp) * kGroupStride;
                 used[r->geom] = 1;
                 w.px = stage(s, r, 0) + p0;
                 w.py = stage(s, r, 1) + p0;
