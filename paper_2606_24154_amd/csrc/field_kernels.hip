@@ -1473,7 +1473,7 @@ template <int K>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_group_near(const double *__restrict__ drec,
                                                        const double *__restrict__ sigma,
                                                        const double *__restrict__ gdata, int n, int64_t sig_stride,
-                                                       int segsz, int gps, ImgArgs img, int split,
+                                                       int segsz, int gps, int rps, ImgArgs img, int split,
                                                        const double *__restrict__ px, const double *__restrict__ py,
                                                        const double *__restrict__ pz, int m, OutCols out,
                                                        int64_t unit_stride)
@@ -1494,7 +1494,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     double acc[K][4];
     near_unit<K>(lists[threadIdx.x >> 6], uniform_ptr(drec + (int64_t)seg * segsz * R_STRIDE),
                  uniform_ptr(sigma + (int64_t)seg * segsz), sig_stride,
-                 uniform_ptr(gdata + (int64_t)seg * records_of(gps) * kGroupStride), ns, img, px[j], py[j], pz[j], g0,
+                 uniform_ptr(gdata + (int64_t)seg * rps * kGroupStride), ns, img, px[j], py[j], pz[j], g0,
                  g1, u0, u1,
                  acc);
     if (i >= m) return;
@@ -1519,7 +1519,7 @@ static void launch_near_k(const double *drec, const double *sigma, const double 
     const int64_t units = split == 0 ? sp.nseg : split == 1 ? ng : ng * kNearRuns;
     const int bs = split == 0 ? kBlock : 64;
     hipLaunchKernelGGL(k_group_near<K>, dim3((unsigned)((m + bs - 1) / bs), (unsigned)units), dim3(bs), 0, s, drec,
-                       sigma, gdata, (int)n, sig_stride, sp.segsz, gps, img, split, px, py, pz, (int)m, out,
+                       sigma, gdata, (int)n, sig_stride, sp.segsz, gps, records_per_seg(sp), img, split, px, py, pz, (int)m, out,
                        unit_stride);
 }
 

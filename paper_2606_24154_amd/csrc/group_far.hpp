@@ -46,7 +46,7 @@ constexpr int kGroupL = kGroupP + 1;  // highest degree of the field's
 constexpr int kGroupHead = 16;
 constexpr int kHeadTier = 4;  // index of the first threshold
 constexpr int kTiers = 6;
-constexpr int kHeadSuper = 10;  // of a group: its super-group's centre and far threshold (super-groups: NaN, no point is)
+constexpr int kHeadSuper = 10;  // the parent's centre and far threshold (none: NaN, no point is far)
 constexpr int kEntry = 8;
 constexpr int kOrderSplit = 8;
 // entries of the degrees below L in the first and in the second pass
@@ -147,8 +147,8 @@ __device__ __forceinline__ GroupVec group_step(const GroupVec &v, double f, cons
 }
 __device__ __forceinline__ double group_r2(const GroupVec &d) { return fma(d.x, d.x, fma(d.y, d.y, d.z * d.z)); }
 
-// Whether a copy is far from the group's super-group, whose expansion then
-// serves it.
+// Whether a copy is far from the group's parent, whose expansion (or whose own
+// parent's) then serves it.
 __device__ __forceinline__ bool super_far(const ImgArgs &img, int r, int i1, int i2, double Px, double Py, double Pz,
                                           cdouble_p head)
 {

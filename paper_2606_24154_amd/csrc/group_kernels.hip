@@ -216,7 +216,7 @@ __device__ __forceinline__ void coef_order(const MomElem &e, double *__restrict_
 __device__ const HarmonicTables kHarmDev = make_harmonic_tables();
 
 // Record of a group: its head (centre c, squared radius a2; no super-group, see
-// k_super_moments) and, one (L, m) per thread, the field's coefficients from the
+// k_parent_moments) and, one (L, m) per thread, the field's coefficients from the
 // moments B = bre + i bim.
 __device__ __forceinline__ void write_record(double *__restrict__ out, const double (&c)[3], double a2, bool bad,
                                              const double *__restrict__ bre, const double *__restrict__ bim)
@@ -308,13 +308,20 @@ __global__ __launch_bounds__(64 * kMomWaves) void k_group_moments(const double *
     write_record(gdata + (int64_t)blockIdx.y * gstride + (int64_t)(seg * rps + q) * kGroupStride, c, a2, bad, bre, bim);
 }
 
-// Records of the super-groups from those of their groups: the moments about
-// the common centre are exact finite sums over the groups' (addition theorem of
+// Records of the parents -- super-groups of four groups (level 1), then of four
+// super-groups (level 2) -- from those of their children: the moments about
+// the common centre are exact finite sums over the children's (addition theorem of
 // R_n^m = r^n P_n^m e^(i m phi) / (n+m)!, with R_n^-m = (-1)^m conj R_n^m and the
 // Condon-Shortley sign),
 //   R_n^m(s + d) = sum_{k,l} R_k^l(d) R_{n-k}^{m-l}(s).
-// One thread per group and (n, m).  Integrating the elements again about the
+// One thread per child and (n, m).  Integrating the elements again about the
 // common centre took 150 us for 8064 elements; this takes 26.
+//
+// A parent's radius is its elements' or, if that is more, so large that a copy
+// far from it is far from every child too (far: beyond rho radii; a copy at rho
+// a of the parent is at least rho a - |offset| from the child): so a record
+// leaves to its parent what is far from that, and nobody needs to look further
+// up.
 constexpr int kTerms = (kGroupP + 1) * (kGroupP + 2) / 2;
 constexpr int kOrders = (kGroupP + 1) * (kGroupP + 1);
 __device__ __forceinline__ int order(int n, int m) { return n * (n + 1) + m; }
@@ -325,54 +332,84 @@ __device__ __forceinline__ void put_orders(double2 *t, int n, int m, double re, 
     t[order(n, m)] = {s * re, s * im};
     if (m > 0) t[order(n, -m)] = {re, -im};
 }
-__global__ __launch_bounds__(128 * kSuper) void k_super_moments(const double *__restrict__ drec, int n, int segsz, int gps,
-                                                                int rps, double *__restrict__ gdata, int64_t gstride)
+constexpr int kParentThreads = 128 * kSuper;
+__global__ __launch_bounds__(kParentThreads) void k_parent_moments(const double *__restrict__ drec, int n, int segsz,
+                                                                  int gps, int rps, int level,
+                                                                  double *__restrict__ gdata, int64_t gstride)
 {
-    __shared__ double2 R[kSuper][kOrders];  // a group's sums, orders -n .. n
+    __shared__ double2 R[kSuper][kOrders];  // a child's sums, orders -n .. n
     __shared__ double2 T[kSuper][kOrders];  // R of its offset
     __shared__ double bre[(kGroupP + 1) * (kGroupP + 1)], bim[(kGroupP + 1) * (kGroupP + 1)];
     __shared__ double fact[kGroupP + 1];
-    const int sps = rps - gps, seg = blockIdx.x / sps, sq = blockIdx.x % sps;
-    const int end = min(n, (seg + 1) * segsz), s0 = seg * segsz + sq * (kSuper * kGroupElems);
+    constexpr int kWaves = kParentThreads / 64;
+    const int sps = parents_of(gps), count = level == 1 ? sps : parents_of(sps);
+    const int seg = blockIdx.x / count, sq = blockIdx.x % count;
+    const int span = kGroupElems * (level == 1 ? 1 : kSuper);  // elements per child
+    const int end = min(n, (seg + 1) * segsz), s0 = seg * segsz + sq * (kSuper * span);
     if (s0 >= end) return;
     double *const seg_data = gdata + (int64_t)blockIdx.y * gstride + (int64_t)seg * rps * kGroupStride;
+    double *const children = seg_data + (int64_t)((level == 1 ? 0 : gps) + sq * kSuper) * kGroupStride;
+    double *const self = seg_data + (int64_t)((level == 1 ? gps : gps + sps) + sq) * kGroupStride;
+    const int nchild = min(kSuper, (end - s0 + span - 1) / span);
+    const int wave = threadIdx.x >> 6;
     double sc[3], sa2;
-    {  // the sphere, every wave a group's elements
-        __shared__ double box[kSuper][6], rad[kSuper];
-        const int w = threadIdx.x >> 6, g = w & (kSuper - 1);
-        const Quad e = element_vertices(
-            drec + (size_t)min(s0 + g * kGroupElems + (int)(threadIdx.x & 63), end - 1) * R_STRIDE);
+    bool bad = false;
+    {  // the sphere
+        __shared__ double box[kWaves][6], rad[kWaves];
+        const int cnt = min(kSuper * span, end - s0);
+        double lo[3], hi[3];
+        for (int i0 = 0; i0 < cnt; i0 += kParentThreads) {
+            const Quad e = element_vertices(drec + (size_t)(s0 + min(i0 + (int)threadIdx.x, cnt - 1)) * R_STRIDE);
 #pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            double lo, hi;
-            wave_box(e, k, lo, hi);
-            if ((threadIdx.x & 63) == 0 && w < kSuper) {
-                box[g][k] = lo;
-                box[g][3 + k] = hi;
+            for (int k = 0; k < 3; ++k) {
+                double l, h;
+                wave_box(e, k, l, h);
+                lo[k] = i0 ? fmin(lo[k], l) : l;
+                hi[k] = i0 ? fmax(hi[k], h) : h;
             }
         }
+        if ((threadIdx.x & 63) == 0)
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                box[wave][k] = lo[k];
+                box[wave][3 + k] = hi[k];
+            }
         __syncthreads();
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
-            double lo = box[0][k], hi = box[0][3 + k];
+            double l = box[0][k], h = box[0][3 + k];
 #pragma unroll
-            for (int j = 1; j < kSuper; ++j) {
-                lo = fmin(lo, box[j][k]);
-                hi = fmax(hi, box[j][3 + k]);
+            for (int j = 1; j < kWaves; ++j) {
+                l = fmin(l, box[j][k]);
+                h = fmax(h, box[j][3 + k]);
             }
-            sc[k] = 0.5 * (lo + hi);
+            sc[k] = 0.5 * (l + h);
         }
-        const double a2 = wave_radius2(e, sc);
-        if ((threadIdx.x & 63) == 0 && w < kSuper) rad[g] = a2;
+        double a2 = 0.0;
+        for (int i0 = 0; i0 < cnt; i0 += kParentThreads) {
+            const double r2 = wave_radius2(
+                element_vertices(drec + (size_t)(s0 + min(i0 + (int)threadIdx.x, cnt - 1)) * R_STRIDE), sc);
+            a2 = r2 > a2 || r2 != r2 ? r2 : a2;
+        }
+        if ((threadIdx.x & 63) == 0) rad[wave] = a2;
         __syncthreads();
         sa2 = rad[0];
 #pragma unroll
-        for (int j = 1; j < kSuper; ++j) sa2 = rad[j] > sa2 || rad[j] != rad[j] ? rad[j] : sa2;
+        for (int j = 1; j < kWaves; ++j) sa2 = rad[j] > sa2 || rad[j] != rad[j] ? rad[j] : sa2;
+        for (int k = 0; k < nchild; ++k) {
+            const double *h = children + (int64_t)k * kGroupStride;
+            const double x = h[0] - sc[0], y = h[1] - sc[1], z = h[2] - sc[2];
+            // rho >= 7.5; the last factor is far above the rounding of a copy's distance
+            const double r = (h[3] + sqrt(x * x + y * y + z * z) * (1.0 / 7.5)) * (1.0 + 1e-9);
+            sa2 = r * r > sa2 ? r * r : sa2;
+            bad = bad || h[kHeadTier] == __builtin_inf();
+        }
+        bad = bad || !(sa2 > 0.0) || !isfinite(sa2);
     }
     const double ia = 1.0 / sqrt(sa2);
     const int child = threadIdx.x >> 7, q = threadIdx.x & 127;
-    const bool has = s0 + child * kGroupElems < end;
-    double *rec = seg_data + (int64_t)(sq * kSuper + (has ? child : 0)) * kGroupStride;
+    const bool has = child < nchild;
+    double *rec = children + (int64_t)(has ? child : 0) * kGroupStride;
     if (threadIdx.x == 0) {
         double f = 1.0;
         for (int k = 0; k <= kGroupP; ++k) {
@@ -440,12 +477,9 @@ __global__ __launch_bounds__(128 * kSuper) void k_super_moments(const double *__
         bim[tn * (kGroupP + 1) + tm] = f * i;
     }
     __syncthreads();
-    // a group that is not fit leaves its super-group's share to the groups
-    bool bad = !(sa2 > 0.0) || !isfinite(sa2);
-    for (int k = 0; k < kSuper && s0 + k * kGroupElems < end; ++k)
-        bad = bad || seg_data[(int64_t)(sq * kSuper + k) * kGroupStride + kHeadTier] == __builtin_inf();
+    // a child that is not fit leaves its parent's share to the children
     if (has && q < 4) rec[kHeadSuper + q] = q < 3 ? sc[min(q, 2)] : bad ? __builtin_inf() : sa2 * tier_ratio2(0);
-    write_record(seg_data + (int64_t)(gps + sq) * kGroupStride, sc, sa2, bad, bre, bim);
+    write_record(self, sc, sa2, bad, bre, bim);
 }
 
 void launch_group_moments(const double *drec, const double *sigma, int64_t n, int64_t sig_stride, int ncol,
@@ -456,8 +490,10 @@ void launch_group_moments(const double *drec, const double *sigma, int64_t n, in
     const int64_t gstride = (int64_t)sp.nseg * rps * kGroupStride;
     hipLaunchKernelGGL(k_group_moments, dim3((unsigned)(sp.nseg * gps), (unsigned)ncol), dim3(64 * kMomWaves), 0, s,
                        drec, sigma, (int)n, sig_stride, sp.segsz, gps, rps, gdata, gstride);
-    hipLaunchKernelGGL(k_super_moments, dim3((unsigned)(sp.nseg * (rps - gps)), (unsigned)ncol), dim3(128 * kSuper), 0,
-                       s, drec, (int)n, sp.segsz, gps, rps, gdata, gstride);
+    const int sps = parents_of(gps);
+    for (int level = 1; level <= far_levels(sp); ++level)
+        hipLaunchKernelGGL(k_parent_moments, dim3((unsigned)(sp.nseg * (level == 1 ? sps : parents_of(sps))), (unsigned)ncol),
+                           dim3(kParentThreads), 0, s, drec, (int)n, sp.segsz, gps, rps, level, gdata, gstride);
 }
 
 // Moments of every element about its group's centre, kElemCoefs each, and
@@ -519,9 +555,17 @@ void launch_element_moments(const double *drec, int64_t n, double *heads, double
 }
 
 // --------------------------------------------------------------------- far
-// Far copies of the expansions [g0, g1) of a segment (its ng groups, then its
-// super-groups, whose records follow those of gps groups) at one point per lane,
-// lattice rows [q0, q1) (row q: reflection q / (2 n1 + 1), translation i1 = q % (2 n1 +
+// Place of expansion k among a segment's records: those of gps groups, of
+// their parents and of these ones' parents, of which ng groups and their
+// ancestors exist.
+__device__ __forceinline__ int record_index(int k, int ng, int gps)
+{
+    const int ns = parents_of(ng);
+    return k < ng ? k : k < ng + ns ? gps + k - ng : gps + parents_of(gps) + k - ng - ns;
+}
+
+// Far copies of the expansions [g0, g1) of a segment at one point per lane, lattice
+// rows [q0, q1) (row q: reflection q / (2 n1 + 1), translation i1 = q % (2 n1 +
 // 1) - n1): rows added into the group's sum, groups into acc, in that order.
 // FP64 VALU bound; the coefficients come through the scalar cache (64 bytes per
 // nine vector instructions), nothing is staged in LDS and the waves of a
@@ -534,7 +578,7 @@ __device__ __forceinline__ void far_unit(cdouble_p gd, int ng, int gps, const Im
     const int nrow = 2 * img.n1 + 1;
 #pragma unroll 1
     for (int g = g0; g < g1; ++g) {
-        cdouble_p h = gd + (int64_t)(g < ng ? g : gps + g - ng) * kGroupStride;
+        cdouble_p h = gd + (int64_t)record_index(g, ng, gps) * kGroupStride;
         const double a = h[3];
         double grp[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll 1
@@ -548,7 +592,7 @@ __device__ __forceinline__ void far_unit(cdouble_p gd, int ng, int gps, const Im
             double row[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll 1
             for (int i2 = -img.n2; i2 <= img.n2; ++i2) {
-                // copies far from the super-group are not a group's
+                // copies far from the parent are its own
                 const bool own = !(group_r2(group_step(s1, -(double)i2, img.a2[r])) >= h[kHeadSuper + 3]);
                 if (__ballot(own) == 0) continue;
                 const GroupVec d = group_step(v1, -(double)i2, img.a2[r]);
@@ -587,7 +631,7 @@ __device__ __forceinline__ void far_unit(cdouble_p gd, int ng, int gps, const Im
 // two columns at once need more registers than three waves per SIMD leave).
 // Unit y's unscaled sums go to the outputs + y * unit_stride.
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void k_group_far(
-    const double *__restrict__ gdata, int64_t gstride, int n, int segsz, int gps, int rps, ImgArgs img, int split,
+    const double *__restrict__ gdata, int64_t gstride, int n, int segsz, int gps, int rps, int levels, ImgArgs img, int split,
     const double *__restrict__ px, const double *__restrict__ py, const double *__restrict__ pz, int m, OutCols out,
     int64_t unit_stride)
 {
@@ -602,11 +646,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
     }
     const int seg = split ? y / rps : y;
     const int ng = (min(segsz, n - seg * segsz) + kGroupElems - 1) / kGroupElems;
-    int g0 = 0, g1 = records_of(ng);
+    int g0 = 0, g1 = records_of(ng, levels);
     if (split) {  // record q of the segment, if it exists
-        const int q = y % rps, k = q < gps ? q : ng + q - gps;
+        const int q = y % rps, sps = parents_of(gps), ns = parents_of(ng);
+        const int k = q < gps ? q : q < gps + sps ? ng + q - gps : ng + ns + q - gps - sps;
+        const bool exists = q < gps ? q < ng : q < gps + sps ? q - gps < ns : k < g1;
         g0 = k;
-        g1 = (q < gps ? q < ng : k < g1) ? k + 1 : k;
+        g1 = exists ? k + 1 : k;
     }
     double acc[4];
     far_unit(uniform_ptr(gdata + (int64_t)blockIdx.z * gstride + (int64_t)seg * rps * kGroupStride), ng, gps, img, px[j],
@@ -627,7 +673,7 @@ void launch_group_far(const double *gdata, int64_t n, int ncol, const SegPlan &s
     const int64_t units = split == 0 ? sp.nseg : split == 1 ? nrec : nrec * rows;
     const int bs = split == 0 ? 256 : 64;
     hipLaunchKernelGGL(k_group_far, dim3((unsigned)((m + bs - 1) / bs), (unsigned)units, (unsigned)ncol), dim3(bs), 0,
-                       s, gdata, nrec * kGroupStride, (int)n, sp.segsz, gps, rps, img, split, px, py, pz, (int)m, out,
+                       s, gdata, nrec * kGroupStride, (int)n, sp.segsz, gps, rps, far_levels(sp), img, split, px, py, pz, (int)m, out,
                        unit_stride);
 }
 
@@ -642,7 +688,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3, 3))) void
     const ImgArgs &img = imgs[w.geom];
     const int j = min((int)threadIdx.x, w.count - 1);
     const int ng = (w.n + kGroupElems - 1) / kGroupElems;
-    const int nrec = records_of(ng);
+    const int nrec = records_of(ng, w.levels);
     const int g0 = units ? (int)blockIdx.y : 0, g1 = units ? g0 + 1 : nrec;
     if (g0 >= nrec) return;
     double acc[4];
@@ -676,7 +722,7 @@ __global__ __launch_bounds__(256) void k_items_fold(const WorkItem *__restrict__
     const int c = threadIdx.x >> 6, lane = threadIdx.x & 63;
     if (lane >= w.count) return;
     const int64_t o = (int64_t)blockIdx.x * per * kUnitDoubles + threadIdx.x;
-    const int nfar = item_units(w.n, w.gdata != nullptr);
+    const int nfar = item_units(w.n, w.gdata != nullptr, w.levels);
     const int cnt = w.gdata ? (w.n + kGroupElems - 1) / kGroupElems : nfar;
     double f = 0.0, n = 0.0;
     for (int u = 0; u < cnt; ++u) n += near[o + (int64_t)u * kUnitDoubles];

@@ -73,6 +73,8 @@ struct WorkItem {
     int geom;   // index into the image-argument array
     int count;  // points in this item (<= 64)
     int groups; // groups of a full segment of its geometry
+    int levels; // and levels of expansions above them
+    int pad;
 };
 
 // ---- field kernels (field_kernels.hip)
@@ -170,10 +172,18 @@ constexpr int kNearParts = 4;  // runs of 16 elements per group, units of an ung
 constexpr int kNearRuns = 8;   // runs of 8 elements per group, units of a split near pass
 inline int groups_per_seg(const SegPlan &sp) { return (sp.segsz + kGroupElems - 1) / kGroupElems; }
 // Far expansions of a segment: one per group, then one per kSuper consecutive
-// groups for the copies far from all of them.
+// groups for the copies far from all of them, and in geometries of many groups
+// (far_levels) one per kSuper of those.
 constexpr int kSuper = 4;
-__host__ __device__ inline int records_of(int groups) { return groups + (groups + kSuper - 1) / kSuper; }
-inline int records_per_seg(const SegPlan &sp) { return records_of(groups_per_seg(sp)); }
+__host__ __device__ inline int parents_of(int n) { return (n + kSuper - 1) / kSuper; }
+__host__ __device__ inline int records_of(int groups, int levels)
+{
+    return groups + parents_of(groups) + (levels > 1 ? parents_of(parents_of(groups)) : 0);
+}
+// With 650 groups (double THGEM, 40 000 points) the second level takes 59 ms to 52; with
+// 126 (GEM cell) it saves 1 % of 200 000 points and costs 64 points 6 %.
+inline int far_levels(const SegPlan &sp) { return (int64_t)sp.nseg * groups_per_seg(sp) >= 256 ? 2 : 1; }
+inline int records_per_seg(const SegPlan &sp) { return records_of(groups_per_seg(sp), far_levels(sp)); }
 // Whether an FP64 evaluation takes far copies of whole groups by their
 // expansions: a function of the geometry only, like the segment plan.
 bool eval_grouped(int64_t n, const ImgArgs &img);
@@ -258,9 +268,9 @@ int eval_items_slots(int mixed);
 // Units of an item: its far expansions (and of the near part its groups) if its
 // geometry is grouped, else runs of 16 elements; per unit 4 x 64 partial sums.
 constexpr int kUnitDoubles = 256;
-__host__ __device__ inline int item_units(int n, bool grouped)
+__host__ __device__ inline int item_units(int n, bool grouped, int levels)
 {
-    return grouped ? records_of((n + 63) / 64) : (n + 15) / 16;
+    return grouped ? records_of((n + 63) / 64, levels) : (n + 15) / 16;
 }
 // items/imgs in device memory; one 64-lane workgroup per item, or (units not
 // null: 2 cap kUnitDoubles doubles) per unit, at most `per` of them an item

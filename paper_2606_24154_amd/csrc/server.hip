@@ -157,6 +157,12 @@ static inline double *stage(nebem_server *s, const Request *r, int k)
     return reinterpret_cast<double *>(static_cast<char *>(s->arena_dev) + r->off) + (size_t)k * r->m;
 }
 
+static int units_per_item(const nebem_server *s, size_t k)
+{
+    return item_units(s->geom_segsz[k], s->geom_groups[k] != SIZE_MAX,
+                      far_levels({s->geom_nseg[k], s->geom_segsz[k]}));
+}
+
 static void worker_main(nebem_server *s)
 {
     (void)hipSetDevice(s->device);
@@ -245,6 +251,8 @@ static void worker_main(nebem_server *s)
                 const size_t go = s->geom_groups[r->geom];
                 const SegPlan gp = {r->nseg, s->geom_segsz[r->geom]};
                 w.groups = groups_per_seg(gp);
+                w.levels = far_levels(gp);
+                w.pad = 0;
                 w.gdata = go == SIZE_MAX ? nullptr
                                          : group_cur + go + (size_t)seg * records_per_seg(gp) * kGroupStride;
                 used[r->geom] = 1;
@@ -280,7 +288,7 @@ static void worker_main(nebem_server *s)
                                              group_cur + s->geom_groups[k], s->lst[cur]);
                 int per = 0;
                 for (size_t k = 0; k < s->geoms.size(); ++k)
-                    if (used[k]) per = std::max(per, item_units(s->geom_segsz[k], s->geom_groups[k] != SIZE_MAX));
+                    if (used[k]) per = std::max(per, units_per_item(s, k));
                 // past four rounds of whole items the last round's waste is small
                 const bool split = s->unit_cap > 0 && nitems <= 4 * s->round_items;
                 launch_eval_items(items_dev, nitems, s->imgs_dev, s->mixed, s->near_factor,
@@ -448,7 +456,7 @@ nebem_status nebem_server_create(nebem_session *const *sessions, int32_t nsessio
     // units' scratch, 64 MB per launch stream; without it items run whole
     int per = 1;
     for (int k = 0; k < nsessions; ++k)
-        per = std::max(per, item_units(s->geom_segsz[k], s->geom_groups[k] != SIZE_MAX));
+        per = std::max(per, units_per_item(s, k));
     s->unit_cap = std::min<int64_t>(16384, (int64_t)s->items_cap * per);
     if (s->unit_cap >= per &&
         hipMalloc((void **)&s->units_dev, 4 * (size_t)s->unit_cap * kUnitDoubles * sizeof(double)) != hipSuccess) {

@@ -36,11 +36,13 @@ def evaluate(nb, geom, sigma, pts, precision=0):
 
 def geometry(copies):
     """A ragged mesh (1242 elements: 19 groups and 26 elements over) with 121
-    copies, with more copies than one list of near ones holds (169), or with
-    reflections."""
+    copies, with more copies than one list of near ones holds (169), with
+    reflections, or with enough groups for a second level of expansions."""
     g = gem_cell(k=17, nr=2, n_images=5)
     if copies == "121":
         return g
+    if copies == "levels":  # 16 816 elements, 263 groups: expansions of 4 and of 16 groups
+        return gem_cell(k=120, nr=7, n_images=3)
     if copies == "none":  # one copy: no grouping
         return g.with_images(Images(a1=g.images.a1, a2=g.images.a2))
     im = g.images
@@ -62,7 +64,7 @@ def points(geom, m, seed=5):
     return p
 
 
-@pytest.mark.parametrize("copies", ["121", "169", "mirror"])
+@pytest.mark.parametrize("copies", ["121", "169", "mirror", "levels"])
 def test_grouped_eval_against_oracle(nb, copies):
     g = geometry(copies)
     rng = np.random.default_rng(7)
@@ -77,11 +79,11 @@ def test_grouped_eval_against_oracle(nb, copies):
     assert np.max(np.linalg.norm(got[t, 1:] - ref[t, 1:], axis=1) / en[t]) <= 1e-10
 
 
-@pytest.mark.parametrize("copies, precision", [("121", 0), ("169", 0), ("mirror", 0), ("none", 0), ("121", 1),
-                                               ("mirror", 1), ("none", 1)])
+@pytest.mark.parametrize("copies, precision", [("121", 0), ("169", 0), ("mirror", 0), ("none", 0), ("levels", 0),
+                                               ("121", 1), ("mirror", 1), ("none", 1)])
 def test_unit_sizes_give_equal_bits(nb, copies, precision):
-    """Calls of 1 to 530 000 points take units from lattice rows and quarters
-    of groups (16-element runs where nothing is grouped) to whole segments,
+    """Calls of 1 to 530 000 points take units from lattice rows and runs
+    of 8 elements (16-element runs where nothing is grouped) to whole segments,
     unordered, small-sorted and radix-sorted."""
     g = geometry(copies)
     if copies == "none":  # an odd start of the runs of pairs
