@@ -477,27 +477,33 @@ __global__ __launch_bounds__(256) void k_laswp(T *__restrict__ A, int n, int k, 
     }
 }
 
-// U = L11^-1 A[k:k+kb, j] for the columns j in [jb, je), 64 per workgroup
-// (unit lower L11 = A[k:k+kb, k:k+kb], kb <= 64).  Wave w solves columns
-// 16w .. 16w+15 with lane r holding row r of each: the entry solved at step
-// i reaches the other lanes by readlane, so the waves run without barriers;
-// every subtraction comes in the order of plain forward substitution.
-template <typename T>
+// U = L11^-1 A[k:k+kb, j] for the columns j in [jb, je), 4 NC per workgroup
+// (unit lower L11 = A[k:k+kb, k:k+kb], kb <= 64).  Wave w solves NC columns with
+// lane r holding row r of each: the entry solved at step i reaches the other lanes
+// by readlane, so the waves run without barriers; every subtraction comes in the
+// order of plain forward substitution.  VALU bound on few workgroups: 16 columns a
+// wave took 22 us for 4000 FP64 columns (63 workgroups), 4 columns 10 us, 8 columns 17; NC = 16, which
+// reads L11 a quarter as often, is taken where it gives every CU a workgroup twice
+// over.
+template <typename T, int NC>
 __global__ __launch_bounds__(256) void k_trsm(T *__restrict__ A, int n, int k, int kb, int jb, int je)
 {
     __shared__ T L[kNB][kNB + 1];
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const int j0 = jb + blockIdx.x * 64;
-    const int ncol = min(64, je - j0);
-    T x[16];
+    const int j0 = jb + blockIdx.x * (4 * NC);
+    const int ncol = min(4 * NC, je - j0);
+    T x[NC];
     {
-        // 16 + 16 loads per thread, all issued before the first is used
+        // 16 + NC loads per thread, all issued before the first is used
         T lv[16];
 #pragma unroll
         for (int u = 0; u < 16; ++u) {
             const int e = tid + 256 * u, rr = e & 63, cc = e >> 6;
             lv[u] = (rr < kb && cc < kb) ? A[(size_t)(k + cc) * n + k + rr] : T(0);
-            const int xc = 16 * w + u;
+        }
+#pragma unroll
+        for (int u = 0; u < NC; ++u) {
+            const int xc = NC * w + u;
             x[u] = (lane < kb && xc < ncol) ? A[(size_t)(j0 + xc) * n + k + lane] : T(0);
         }
 #pragma unroll
@@ -512,15 +518,15 @@ __global__ __launch_bounds__(256) void k_trsm(T *__restrict__ A, int n, int k, i
         const T l = L[lane][i];
         const bool upd = row_in && lane > i;
 #pragma unroll
-        for (int q = 0; q < 16; ++q) {
+        for (int q = 0; q < NC; ++q) {
             const T xi = lane_bcast(x[q], i);
             const T u = x[q] - l * xi;
             x[q] = upd ? u : x[q];
         }
     }
 #pragma unroll
-    for (int q = 0; q < 16; ++q) {
-        const int xc = 16 * w + q;
+    for (int q = 0; q < NC; ++q) {
+        const int xc = NC * w + q;
         if (row_in && xc < ncol) A[(size_t)(j0 + xc) * n + k + lane] = x[q];
     }
 }
@@ -806,7 +812,11 @@ template <typename T>
 static void trsm(T *A, int n, int k, int kb, int jb, int je, hipStream_t s)
 {
     if (je <= jb) return;
-    hipLaunchKernelGGL(k_trsm<T>, dim3((unsigned)((je - jb + 63) / 64)), dim3(256), 0, s, A, n, k, kb, jb, je);
+    const int cols = je - jb;
+    if (cols >= 2 * 256 * 64)
+        hipLaunchKernelGGL((k_trsm<T, 16>), dim3((unsigned)((cols + 63) / 64)), dim3(256), 0, s, A, n, k, kb, jb, je);
+    else
+        hipLaunchKernelGGL((k_trsm<T, 4>), dim3((unsigned)((cols + 15) / 16)), dim3(256), 0, s, A, n, k, kb, jb, je);
 }
 
 // ------------------------------------------------------ triangular solves
