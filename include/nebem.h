@@ -92,7 +92,7 @@ typedef struct nebem_images {
 
 typedef enum nebem_precision {
     NEBEM_FP64 = 0,  /* FP64 everywhere: exact closed forms; in evaluations, copies of a 64-element group far from the
-                        point by the group's multipole expansion, truncated below 1e-12 of the group's summed absolute
+                        point by the group's multipole expansion, truncated below 3e-12 of the group's summed absolute
                         charge over distance (less than the closed forms' own rounding there); FP64 LU + refinement */
     NEBEM_MIXED = 1  /* FP64 near field, FP64 monopole + FP32 correction far away; FP32 LU + FP64 refinement */
 } nebem_precision;

@@ -1671,7 +1671,7 @@ __global__ __launch_bounds__(kBlock) void k_assemble(const double *__restrict__ 
 // The same with the far copies of each group of 64 elements by lattice sums of
 // harmonics (lattice_far.hpp): 64 rows, one per lane, x one group per workgroup.
 //   1. The waves scan the lattice for the copies near any of the rows (closer
-//      than ~7.6 group radii) and keep the range of i2 they span in each row (r,
+//      than ~7 group radii) and keep the range of i2 they span in each row (r,
 //      i1) of the lattice: the near copies, all others are far.
 //   2. Each wave sums its orders' harmonics over the far copies in registers,
 //      at the degree that the farthest tier of all lanes allows; dielectric

@@ -24,9 +24,12 @@
 //
 // The truncation after degree p is at most ~(p+2) (a/r)^(p+1) of
 // sum |q| / r^2; tier_ratio2 gives the (r/a)^2 from which a degree keeps that
-// bound below 1e-12.  On meshes it comes out 10 to 100 times smaller at the
+// bound below 3e-12.  On meshes it comes out 10 to 100 times smaller at the
 // threshold itself, below the closed forms' own rounding (1e-11 of an element's
-// field beyond 25 diameters), and it falls with (a/r)^(p+1).
+// field beyond 25 diameters), and it falls with (a/r)^(p+1).  Fields' errors against
+// 64-bit sums, GEM and THGEM cells of 1500 to 10 000 elements: 3.1 .. 5.4e-15 with
+// closed forms throughout, 1.9 .. 3.4e-15 at 3e-12 as at 1e-12 (which takes 8 % longer),
+// 2.7 .. 4.6e-15 at 1e-11.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -70,10 +73,10 @@ __host__ __device__ constexpr int entry_index(int L, int m)
 }
 constexpr int kGroupStride = kGroupHead + kEntry * kGroupEntries;
 
-// squares of r/a = ((p + 2) / 1e-12)^(1/(p + 1)) for p = 14, 12, 10, 8, 6, 4
+// squares of r/a = ((p + 2) / 3e-12)^(1/(p + 1)) for p = 14, 12, 10, 8, 6, 4
 __host__ __device__ constexpr double tier_ratio2(int k)
 {
-    return k == 0 ? 57.62 : k == 1 ? 105.4 : k == 2 ? 238.8 : k == 3 ? 774.3 : k == 4 ? 4860.0 : 129200.0;
+    return k == 0 ? 49.77 : k == 1 ? 88.94 : k == 2 ? 195.6 : k == 3 ? 606.6 : k == 4 ? 3551.0 : 83260.0;
 }
 
 struct HarmonicTables {

@@ -6,7 +6,7 @@
 // to hundreds of element sizes away.  Here the far copies of each group of 64
 // elements cost one expansion (9 instructions per harmonic: ~390 through
 // degree 6, ~1400 through degree 14) instead of 64 closed forms (~4700); the
-// copies nearer than ~7.6 group radii are left to k_group_near
+// copies nearer than ~7 group radii are left to k_group_near
 // (field_kernels.hip), which evaluates them element by element.
 //
 // Copies far from four consecutive groups at once take one expansion of the
@@ -15,7 +15,7 @@
 //
 // Measured (double THGEM, 41 600 elements, 121 copies, 40 000 points): 469 ms
 // with the closed forms everywhere, 102 ms with groups (far pass 74 ms, near pass
-// 26), 59 ms with four at once (far 30, near 28); the far pass issues at ~75 % of the
+// 26), 59 ms with four at once (far 30, near 28), 47 with sixteen and the bound at 3e-12 (far 20, near 24); the far pass issues at ~75 % of the
 // FP64 rate.  Three waves per SIMD and two entries ahead: two waves 79 ms (of 74),
 // four 76, one entry ahead 87, three 83.  64 points of the GEM cell, one row of an
 // expansion or 8 elements of a group per wave: 23.5 ms -> 0.58 ms.  Error of 2003 GEM
@@ -399,8 +399,8 @@ __global__ __launch_bounds__(kParentThreads) void k_parent_moments(const double 
         for (int k = 0; k < nchild; ++k) {
             const double *h = children + (int64_t)k * kGroupStride;
             const double x = h[0] - sc[0], y = h[1] - sc[1], z = h[2] - sc[2];
-            // rho >= 7.5; the last factor is far above the rounding of a copy's distance
-            const double r = (h[3] + sqrt(x * x + y * y + z * z) * (1.0 / 7.5)) * (1.0 + 1e-9);
+            // rho > 7; the last factor is far above the rounding of a copy's distance
+            const double r = (h[3] + sqrt(x * x + y * y + z * z) * (1.0 / 7.0)) * (1.0 + 1e-9);
             sa2 = r * r > sa2 ? r * r : sa2;
             bad = bad || h[kHeadTier] == __builtin_inf();
         }

@@ -138,7 +138,7 @@ def test_grouped_assembly(nb, kind):
     throughout, which collocation points handed in by the caller take, and
     sampled rows against the oracle.  1e-11 of a row's largest entry, as every
     assembly here; entry by entry 1e-10 where all copies count with one sign (an
-    expansion is truncated below 1e-12, the closed forms round at 1e-11)."""
+    expansion is truncated below 3e-12, the closed forms round at 1e-11)."""
     import oracle
     g = assembly_geometry(kind)
     dp = nb.DevicePanels.from_geometry(g, "cuda:0")

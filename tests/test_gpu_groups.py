@@ -2,7 +2,7 @@
 expansions, near ones element by element, in units of several sizes.
 
 Bound against the oracle: 1e-10 pointwise on non-negligible points, the FP64
-evaluation's own (the expansions are truncated below 1e-12 of a group's summed
+evaluation's own (the expansions are truncated below 3e-12 of a group's summed
 absolute charge over distance, the closed forms round at 1e-11 of an element's
 field).  Everything that only regroups the work is held to equal bits.
 """
