@@ -1470,15 +1470,16 @@ __device__ __forceinline__ void near_unit(NearList &nl, cdouble_p drec, cdouble_
 // 2: with runs of 16 the near pass of 64 points took 505 us, with 8 280, with 4 158, but
 // 2003 points 1.34, 1.30 and 1.45 ms: each unit scans the lattice anew).
 template <int K>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_group_near(const double *__restrict__ drec,
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_group_near(const double *__restrict__ drec,
                                                        const double *__restrict__ sigma,
                                                        const double *__restrict__ gdata, int n, int64_t sig_stride,
                                                        int segsz, int gps, int rps, ImgArgs img, int split,
+                                                       const int *__restrict__ order,
                                                        const double *__restrict__ px, const double *__restrict__ py,
                                                        const double *__restrict__ pz, int m, OutCols out,
                                                        int64_t unit_stride)
 {
-    __shared__ NearList lists[kBlock / 64];
+    __shared__ NearList list;
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     const int j = min(i, m - 1);
     int y = blockIdx.y, u0 = 0, u1 = kNearRuns;
@@ -1487,18 +1488,18 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 2))) 
         u1 = u0 + 1;
         y /= kNearRuns;
     }
-    const int seg = split ? y / gps : y;
+    const int seg = split ? y / gps : order[y];
     const int ns = min(segsz, n - seg * segsz);
     const int ng = (ns + kGroupElems - 1) / kGroupElems;
     const int g0 = split ? y % gps : 0, g1 = split ? min(g0 + 1, ng) : ng;
     double acc[K][4];
-    near_unit<K>(lists[threadIdx.x >> 6], uniform_ptr(drec + (int64_t)seg * segsz * R_STRIDE),
+    near_unit<K>(list, uniform_ptr(drec + (int64_t)seg * segsz * R_STRIDE),
                  uniform_ptr(sigma + (int64_t)seg * segsz), sig_stride,
                  uniform_ptr(gdata + (int64_t)seg * rps * kGroupStride), ns, img, px[j], py[j], pz[j], g0,
                  g1, u0, u1,
                  acc);
     if (i >= m) return;
-    const int64_t o = (int64_t)blockIdx.y * unit_stride + i;
+    const int64_t o = (int64_t)(split ? (int)blockIdx.y : seg) * unit_stride + i;
 #pragma unroll
     for (int k = 0; k < K; ++k)
 #pragma unroll
@@ -1511,24 +1512,23 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 2))) 
 
 template <int K>
 static void launch_near_k(const double *drec, const double *sigma, const double *gdata, int64_t n, int64_t sig_stride,
-                          const SegPlan &sp, const ImgArgs &img, int split, const double *px, const double *py,
+                          const SegPlan &sp, const ImgArgs &img, int split, const int *order, const double *px, const double *py,
                           const double *pz, int64_t m, const OutCols &out, int64_t unit_stride, hipStream_t s)
 {
     const int gps = groups_per_seg(sp);
     const int64_t ng = (int64_t)sp.nseg * gps;
     const int64_t units = split == 0 ? sp.nseg : split == 1 ? ng : ng * kNearRuns;
-    const int bs = split == 0 ? kBlock : 64;
-    hipLaunchKernelGGL(k_group_near<K>, dim3((unsigned)((m + bs - 1) / bs), (unsigned)units), dim3(bs), 0, s, drec,
-                       sigma, gdata, (int)n, sig_stride, sp.segsz, gps, records_per_seg(sp), img, split, px, py, pz, (int)m, out,
+    hipLaunchKernelGGL(k_group_near<K>, dim3((unsigned)((m + 63) / 64), (unsigned)units), dim3(64), 0, s, drec,
+                       sigma, gdata, (int)n, sig_stride, sp.segsz, gps, records_per_seg(sp), img, split, order, px, py, pz, (int)m, out,
                        unit_stride);
 }
 
 void launch_group_near(const double *drec, const double *sigma, const double *gdata, int64_t n, int64_t sig_stride,
-                       int ncol, const SegPlan &sp, const ImgArgs &img, int split, const double *px, const double *py,
+                       int ncol, const SegPlan &sp, const ImgArgs &img, int split, const int *order, const double *px, const double *py,
                        const double *pz, int64_t m, const OutCols &out, int64_t unit_stride, hipStream_t s)
 {
     if (m <= 0 || n <= 0) return;
-#define NEAR_ARGS drec, sigma, gdata, n, sig_stride, sp, img, split, px, py, pz, m, out, unit_stride, s
+#define NEAR_ARGS drec, sigma, gdata, n, sig_stride, sp, img, split, order, px, py, pz, m, out, unit_stride, s
     switch (ncol) {
     case 1: launch_near_k<1>(NEAR_ARGS); break;
     case 2: launch_near_k<2>(NEAR_ARGS); break;

@@ -15,7 +15,8 @@
 //
 // Measured (double THGEM, 41 600 elements, 121 copies, 40 000 points): 469 ms
 // with the closed forms everywhere, 102 ms with groups (far pass 74 ms, near pass
-// 26), 59 ms with four at once (far 30, near 28), 47 with sixteen and the bound at 3e-12 (far 20, near 24); the far pass issues at ~75 % of the
+// 26), 59 ms with four at once (far 30, near 28), 37 with sixteen, the bound at 3e-12
+// and the widest segments first (far 18, near 17); the far pass issues at ~75 % of the
 // FP64 rate.  Three waves per SIMD and two entries ahead: two waves 79 ms (of 74),
 // four 76, one entry ahead 87, three 83.  64 points of the GEM cell, one row of an
 // expansion or 8 elements of a group per wave: 23.5 ms -> 0.58 ms.  Error of 2003 GEM
@@ -554,6 +555,45 @@ void launch_element_moments(const double *drec, int64_t n, double *heads, double
                        0, s, drec, (int)n, heads, coef);
 }
 
+// Segments by falling sum of their groups' squared radii, which goes with
+// their near copies: in unsplit passes a segment's waves at points near its
+// widest groups run for milliseconds (the planes of a THGEM: 16 groups of 64
+// elements x 25 copies), and started last they leave the device idle.  Near pass of
+// 40 000 THGEM points 26 ms in index order, 19 with these first (17 with
+// waves of their own workgroup); far pass 21, 18.
+__global__ __launch_bounds__(64) void k_segment_order(const double *__restrict__ gdata, int n, int nseg, int segsz,
+                                                      int rps, int *__restrict__ order)
+{
+    const int s = threadIdx.x;
+    double cost = 0.0;
+    if (s < nseg) {
+        const int ng = (min(segsz, n - s * segsz) + kGroupElems - 1) / kGroupElems;
+#pragma unroll 8
+        for (int g = 0; g < ng; ++g) {
+            const double a = gdata[((int64_t)s * rps + g) * kGroupStride + 3];
+            cost = fma(a, a, cost);
+        }
+        if (!(cost <= 1e300)) cost = 1e300;  // not finite: all its groups may be near
+    }
+    int rank = 0;
+    for (int t = 0; t < nseg; ++t) {
+        const double c = __shfl(cost, t);
+        rank += c > cost || (c == cost && t < s);
+    }
+    if (s < nseg) order[rank] = s;
+}
+
+int *segment_order(double *gdata, int ncol, const SegPlan &sp)
+{
+    return reinterpret_cast<int *>(gdata + (size_t)sp.nseg * records_per_seg(sp) * kGroupStride * (size_t)ncol);
+}
+
+void launch_segment_order(const double *gdata, int64_t n, const SegPlan &sp, int *order, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_segment_order, dim3(1), dim3(64), 0, s, gdata, (int)n, sp.nseg, sp.segsz, records_per_seg(sp),
+                       order);
+}
+
 // --------------------------------------------------------------------- far
 // Place of expansion k among a segment's records: those of gps groups, of
 // their parents and of these ones' parents, of which ng groups and their
@@ -632,6 +672,7 @@ __device__ __forceinline__ void far_unit(cdouble_p gd, int ng, int gps, const Im
 // Unit y's unscaled sums go to the outputs + y * unit_stride.
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void k_group_far(
     const double *__restrict__ gdata, int64_t gstride, int n, int segsz, int gps, int rps, int levels, ImgArgs img, int split,
+    const int *__restrict__ order,
     const double *__restrict__ px, const double *__restrict__ py, const double *__restrict__ pz, int m, OutCols out,
     int64_t unit_stride)
 {
@@ -644,7 +685,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
         q1 = q0 + 1;
         y /= rows;
     }
-    const int seg = split ? y / rps : y;
+    const int seg = split ? y / rps : order[y];
     const int ng = (min(segsz, n - seg * segsz) + kGroupElems - 1) / kGroupElems;
     int g0 = 0, g1 = records_of(ng, levels);
     if (split) {  // record q of the segment, if it exists
@@ -658,12 +699,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
     far_unit(uniform_ptr(gdata + (int64_t)blockIdx.z * gstride + (int64_t)seg * rps * kGroupStride), ng, gps, img, px[j],
              py[j], pz[j], g0, g1, q0, q1, acc);
     if (i >= m) return;
-    const int64_t o = (int64_t)blockIdx.y * unit_stride + (int64_t)blockIdx.z * out.stride + i;
+    const int64_t o = (int64_t)(split ? (int)blockIdx.y : seg) * unit_stride + (int64_t)blockIdx.z * out.stride + i;
     for (int c = 0; c < 4; ++c)
         if (out.c[c]) out.c[c][o] = acc[c];
 }
 
-void launch_group_far(const double *gdata, int64_t n, int ncol, const SegPlan &sp, const ImgArgs &img, int split,
+void launch_group_far(const double *gdata, int64_t n, int ncol, const SegPlan &sp, const ImgArgs &img, int split, const int *order,
                       const double *px, const double *py, const double *pz, int64_t m, const OutCols &out,
                       int64_t unit_stride, hipStream_t s)
 {
@@ -673,7 +714,7 @@ void launch_group_far(const double *gdata, int64_t n, int ncol, const SegPlan &s
     const int64_t units = split == 0 ? sp.nseg : split == 1 ? nrec : nrec * rows;
     const int bs = split == 0 ? 256 : 64;
     hipLaunchKernelGGL(k_group_far, dim3((unsigned)((m + bs - 1) / bs), (unsigned)units, (unsigned)ncol), dim3(bs), 0,
-                       s, gdata, nrec * kGroupStride, (int)n, sp.segsz, gps, rps, far_levels(sp), img, split, px, py, pz, (int)m, out,
+                       s, gdata, nrec * kGroupStride, (int)n, sp.segsz, gps, rps, far_levels(sp), img, split, order, px, py, pz, (int)m, out,
                        unit_stride);
 }
 
@@ -794,7 +835,7 @@ bool eval_grouped(int64_t n, const ImgArgs &img)
 
 size_t group_data_bytes(const SegPlan &sp, int ncol)
 {
-    return (size_t)sp.nseg * records_per_seg(sp) * kGroupStride * (size_t)ncol * sizeof(double);
+    return ((size_t)sp.nseg * records_per_seg(sp) * kGroupStride * (size_t)ncol + (sp.nseg + 1) / 2) * sizeof(double);
 }
 
 }  // namespace nebem

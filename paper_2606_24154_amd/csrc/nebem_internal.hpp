@@ -189,6 +189,9 @@ inline int records_per_seg(const SegPlan &sp) { return records_of(groups_per_seg
 bool eval_grouped(int64_t n, const ImgArgs &img);
 size_t group_data_bytes(const SegPlan &sp, int ncol);
 // moments of every group and density column (column k at sigma + k sig_stride)
+// order: of the segments, the costliest first (behind the records in gdata)
+void launch_segment_order(const double *gdata, int64_t n, const SegPlan &sp, int *order, hipStream_t s);
+int *segment_order(double *gdata, int ncol, const SegPlan &sp);
 void launch_group_moments(const double *drec, const double *sigma, int64_t n, int64_t sig_stride, int ncol,
                           const SegPlan &sp, double *gdata, hipStream_t s);
 // Far and near parts of a grouped evaluation, one pass each.  split 0: units
@@ -196,11 +199,11 @@ void launch_group_moments(const double *drec, const double *sigma, int64_t n, in
 // finer units, each pass with outputs of its own (far 1: groups, 2: lattice
 // rows of groups; near 1: groups, 2: runs of 8 elements).  Unit y's unscaled
 // sums go to the outputs + y * unit_stride.
-void launch_group_far(const double *gdata, int64_t n, int ncol, const SegPlan &sp, const ImgArgs &img, int split,
+void launch_group_far(const double *gdata, int64_t n, int ncol, const SegPlan &sp, const ImgArgs &img, int split, const int *order,
                       const double *px, const double *py, const double *pz, int64_t m, const OutCols &out,
                       int64_t unit_stride, hipStream_t s);
 void launch_group_near(const double *drec, const double *sigma, const double *gdata, int64_t n, int64_t sig_stride,
-                       int ncol, const SegPlan &sp, const ImgArgs &img, int split, const double *px, const double *py,
+                       int ncol, const SegPlan &sp, const ImgArgs &img, int split, const int *order, const double *px, const double *py,
                        const double *pz, int64_t m, const OutCols &out, int64_t unit_stride, hipStream_t s);
 // split evaluations back to segment sums (len values per unit)
 void launch_fold_units(const double *in, int64_t groups, int per, int64_t len, double *out, hipStream_t s);

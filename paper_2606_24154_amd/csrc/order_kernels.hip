@@ -391,8 +391,10 @@ void eval_grouped_chunk(const double *drec, const double *sg, int64_t n, int k, 
     double *gd = reinterpret_cast<double *>(w + L.groups);
     launch_group_moments(drec, sg, n, n, k, sh.sp, gd, s);
     if (!L.fsplit) {
-        launch_group_far(gd, n, k, sh.sp, img, 0, px, py, pz, c, pc, seg_stride, s);
-        launch_group_near(drec, sg, gd, n, n, k, sh.sp, img, 0, px, py, pz, c, pc, seg_stride, s);
+        int *order = segment_order(gd, k, sh.sp);
+        launch_segment_order(gd, n, sh.sp, order, s);
+        launch_group_far(gd, n, k, sh.sp, img, 0, order, px, py, pz, c, pc, seg_stride, s);
+        launch_group_near(drec, sg, gd, n, n, k, sh.sp, img, 0, order, px, py, pz, c, pc, seg_stride, s);
         return;
     }
     double *far = reinterpret_cast<double *>(w + L.far), *near = reinterpret_cast<double *>(w + L.near);
@@ -402,8 +404,8 @@ void eval_grouped_chunk(const double *drec, const double *sg, int64_t n, int k, 
         for (int q = 0; q < 4; ++q) o.c[q] = pc.c[q] ? b + (size_t)q * c : nullptr;
         return o;
     };
-    launch_group_far(gd, n, k, sh.sp, img, L.fsplit, px, py, pz, c, cols(far), seg_stride, s);
-    launch_group_near(drec, sg, gd, n, n, k, sh.sp, img, L.nsplit, px, py, pz, c, cols(near), seg_stride, s);
+    launch_group_far(gd, n, k, sh.sp, img, L.fsplit, nullptr, px, py, pz, c, cols(far), seg_stride, s);
+    launch_group_near(drec, sg, gd, n, n, k, sh.sp, img, L.nsplit, nullptr, px, py, pz, c, cols(near), seg_stride, s);
     if (L.fsplit == 2) {
         double *f = reinterpret_cast<double *>(w + L.ffold);
         launch_fold_units(far, sh.nrec, (int)sh.rows, seg_stride, f, s);
