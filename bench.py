@@ -52,8 +52,8 @@ COUNTER_CALIBRATION = {
     "thgem": {"flops_per_interaction": 101.04, "valu_per_interaction": 73.09, "traffic_bytes": 537282944,
               "points_per_launch": 200000, "source_sha16": "1b886789b31f0e81"},
 }
-EVAL_SOURCES = ("field_kernels.hip", "panel_fp64.hpp", "fastmath_fp64.hpp", "poly_coeffs.hpp", "farfield_mixed.hpp",
-                "order_kernels.hip", "nebem_internal.hpp")
+EVAL_SOURCES = ("field_kernels.hip", "group_kernels.hip", "group_far.hpp", "lattice_far.hpp", "panel_fp64.hpp",
+                "fastmath_fp64.hpp", "poly_coeffs.hpp", "farfield_mixed.hpp", "order_kernels.hip", "nebem_internal.hpp")
 
 
 def _code_only(text):
