@@ -1541,7 +1541,7 @@ void launch_group_near(const double *drec, const double *sigma, const double *gd
 // Continuous-batching evaluation: workgroup (one wave) b takes work item b --
 // up to 64 points of one request against one segment of the elements of one
 // resident geometry -- and writes the segment's unscaled partial sums; or, with
-// `units`, unit y of it (a group's near part, or 16 elements), whose sums go to
+// `units`, unit y of it (8 elements of a group, or 16 elements), whose sums go to
 // units[b][y][component][lane].  The per-point arithmetic does not depend on which
 // other items share the launch, nor on the split.
 template <bool MIXED>
@@ -1575,11 +1575,12 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
     // grouped geometry: the near part, added to k_items_far's
     const int j = min((int)threadIdx.x, w.count - 1);
     const int ng = (w.n + kGroupElems - 1) / kGroupElems;
-    const int g0 = units ? (int)blockIdx.y : 0, g1 = units ? g0 + 1 : ng;
+    const int g0 = units ? (int)blockIdx.y / kNearRuns : 0, g1 = units ? g0 + 1 : ng;
+    const int u0 = units ? (int)blockIdx.y % kNearRuns : 0, u1 = units ? u0 + 1 : kNearRuns;
     if (g0 >= ng) return;
     double acc[1][4];
     near_unit<1>(list, uniform_ptr(w.drec), uniform_ptr(w.sigma), 0, uniform_ptr(w.gdata), w.n, imgs[w.geom], w.px[j],
-                 w.py[j], w.pz[j], g0, g1, 0, kNearRuns, acc);
+                 w.py[j], w.pz[j], g0, g1, u0, u1, acc);
     if ((int)threadIdx.x >= w.count) return;
     if (units) {
         double *u = units + ((size_t)blockIdx.x * gridDim.y + blockIdx.y) * kUnitDoubles + threadIdx.x;
@@ -1612,23 +1613,24 @@ int eval_items_slots(int mixed)
 }
 
 void launch_eval_items(const WorkItem *items, int nitems, const ImgArgs *imgs, int mixed, double near_factor,
-                       double *units, int64_t cap, int per, hipStream_t s)
+                       const ItemUnits &u, hipStream_t s)
 {
     // whole items, or as many at a time as have their units in the scratch
-    const int64_t batch = units && per > 0 ? cap / per : 0;
+    int64_t batch = u.sums && u.per > 0 ? u.cap / u.per : 0;
+    if (u.far_per > 0 && u.far_cap / u.far_per < batch) batch = u.far_cap / u.far_per;
     const int step = batch > 0 ? (int)(batch < nitems ? batch : nitems) : nitems;
-    double *near = batch > 0 ? units : nullptr, *far = near ? units + cap * kUnitDoubles : nullptr;
+    double *near = batch > 0 ? u.sums : nullptr, *far = near ? u.sums + u.cap * kUnitDoubles : nullptr;
     for (int i = 0; i < nitems; i += step) {
         const int c = nitems - i < step ? nitems - i : step;
         const WorkItem *it = items + i;
-        const dim3 g(c, near ? per : 1);
+        const dim3 g(c, near ? u.per : 1);
         if (mixed) {
             hipLaunchKernelGGL(k_eval_items_mixed, g, dim3(64), 0, s, it, imgs, near_factor, near);
         } else {
-            launch_items_far(it, c, imgs, far, per, s);
+            if (!near || u.far_per > 0) launch_items_far(it, c, imgs, far, u.far_per, s);
             hipLaunchKernelGGL(k_eval_items_fp64, g, dim3(64), 0, s, it, imgs, near_factor, near);
         }
-        if (near) launch_items_fold(it, c, far, near, per, s);
+        if (near) launch_items_fold(it, c, far, near, u.far_per, u.per, s);
     }
 }
 

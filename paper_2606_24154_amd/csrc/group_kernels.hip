@@ -757,28 +757,38 @@ void launch_items_far(const WorkItem *items, int nitems, const ImgArgs *imgs, do
 // item adds them.
 __global__ __launch_bounds__(256) void k_items_fold(const WorkItem *__restrict__ items,
                                                     const double *__restrict__ far,
-                                                    const double *__restrict__ near, int per)
+                                                    const double *__restrict__ near, int far_per, int per)
 {
     const WorkItem &w = items[blockIdx.x];
-    const int c = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int lane = threadIdx.x & 63, c = threadIdx.x >> 6;
     if (lane >= w.count) return;
-    const int64_t o = (int64_t)blockIdx.x * per * kUnitDoubles + threadIdx.x;
-    const int nfar = item_units(w.n, w.gdata != nullptr, w.levels);
-    const int cnt = w.gdata ? (w.n + kGroupElems - 1) / kGroupElems : nfar;
-    double f = 0.0, n = 0.0;
-    for (int u = 0; u < cnt; ++u) n += near[o + (int64_t)u * kUnitDoubles];
-    if (w.gdata) {
-        for (int u = 0; u < nfar; ++u) f += far[o + (int64_t)u * kUnitDoubles];
+    const double *u = near + (int64_t)blockIdx.x * per * kUnitDoubles + threadIdx.x;
+    const bool grouped = w.gdata != nullptr;
+    const int cnt = item_units(w.n, grouped);
+    double n = 0.0;
+    if (grouped) {
+        for (int g = 0; g < cnt; g += kNearRuns) {
+            double t = 0.0;
+#pragma unroll
+            for (int q = 0; q < kNearRuns; ++q) t += u[(int64_t)(g + q) * kUnitDoubles];
+            n += t;
+        }
+        const double *v = far + (int64_t)blockIdx.x * far_per * kUnitDoubles + threadIdx.x;
+        const int nfar = item_far_units(w.n, w.levels);
+        double f = 0.0;
+        for (int q = 0; q < nfar; ++q) f += v[(int64_t)q * kUnitDoubles];
         n = f + n;
+    } else {
+        for (int q = 0; q < cnt; ++q) n += u[(int64_t)q * kUnitDoubles];
     }
     (c == 0 ? w.phi : c == 1 ? w.ex : c == 2 ? w.ey : w.ez)[lane] = n;
 }
 
-void launch_items_fold(const WorkItem *items, int nitems, const double *far, const double *near, int per,
+void launch_items_fold(const WorkItem *items, int nitems, const double *far, const double *near, int far_per, int per,
                        hipStream_t s)
 {
     if (nitems <= 0) return;
-    hipLaunchKernelGGL(k_items_fold, dim3(nitems), dim3(256), 0, s, items, far, near, per);
+    hipLaunchKernelGGL(k_items_fold, dim3(nitems), dim3(256), 0, s, items, far, near, far_per, per);
 }
 
 // ------------------------------------------------------------ finer units

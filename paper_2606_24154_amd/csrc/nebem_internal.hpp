@@ -210,7 +210,7 @@ void launch_fold_units(const double *in, int64_t groups, int per, int64_t len, d
 // work items of grouped geometries, far part (the near part and the other
 // items: launch_eval_items)
 void launch_items_far(const WorkItem *items, int nitems, const ImgArgs *imgs, double *units, int per, hipStream_t s);
-void launch_items_fold(const WorkItem *items, int nitems, const double *far, const double *near, int per,
+void launch_items_fold(const WorkItem *items, int nitems, const double *far, const double *near, int far_per, int per,
                        hipStream_t s);
 void launch_fold_groups(const double *far, const double *near, const SegPlan &sp, int64_t len, double *out,
                         hipStream_t s);
@@ -268,17 +268,26 @@ hipError_t run_eval(const double *drec, const double *sigma, int64_t n, int ncol
 // work items (one wave each) the device holds at once: CUs x resident
 // workgroups of the items kernel per CU (1 when the query fails)
 int eval_items_slots(int mixed);
-// Units of an item: its far expansions (and of the near part its groups) if its
-// geometry is grouped, else runs of 16 elements; per unit 4 x 64 partial sums.
+// Units of an item: its far expansions if its geometry is grouped; and runs of 8
+// elements (near part of its groups) or, ungrouped, of 16; per unit 4 x 64
+// partial sums.
 constexpr int kUnitDoubles = 256;
-__host__ __device__ inline int item_units(int n, bool grouped, int levels)
+__host__ __device__ inline int item_far_units(int n, int levels) { return records_of((n + 63) / 64, levels); }
+__host__ __device__ inline int item_units(int n, bool grouped)
 {
-    return grouped ? records_of((n + 63) / 64, levels) : (n + 15) / 16;
+    return grouped ? (n + 63) / 64 * kNearRuns : (n + 15) / 16;
 }
-// items/imgs in device memory; one 64-lane workgroup per item, or (units not
-// null: 2 cap kUnitDoubles doubles) per unit, at most `per` of them an item
+// Scratch of units: room for cap of them and, behind that, for far_cap far ones; an
+// item has at most per and far_per.
+struct ItemUnits {
+    double *sums;
+    int64_t cap, far_cap;
+    int per, far_per;
+};
+// items/imgs in device memory; one 64-lane workgroup per item, or (u.sums not
+// null) per unit
 void launch_eval_items(const WorkItem *items, int nitems, const ImgArgs *imgs, int mixed, double near_factor,
-                       double *units, int64_t cap, int per, hipStream_t s);
+                       const ItemUnits &u, hipStream_t s);
 // A (n x n col-major), FP64 in both precisions.  cx/cy/cz may be null (centroids).
 // scratch: assemble_scratch_doubles(n) doubles if assemble_grouped(n, img), else (or
 // if there is no memory for them) null.

@@ -27,10 +27,11 @@
 //      chain in a single lane), taken round-robin (one item per request per
 //      round) until the iteration's interaction budget is used; items of
 //      different requests and geometries go into ONE launch, which runs as
-//      finer units (a group, or 16 elements, x 64 points) while it holds few
-//      items: a whole item is 10 to 30 ms of one wave, and a burst of 16
-//      requests, 16 000 points on a GEM cell, left most of the device idle
-//      (72 ms FP64; 19 ms in units);
+//      finer units (an expansion, 8 elements of a group, or 16 elements, x 64
+//      points) while it holds few items: a whole item is 10 to 30 ms of one
+//      wave, and a burst of 16 requests, 16 000 points on a GEM cell, left
+//      most of the device idle (71 ms FP64; 13.6 ms in units, 16.3 with the near
+//      part group by group);
 //   3. completion: a request whose items are all done has its segment
 //      partial sums reduced in a fixed order (and scattered back to the
 //      submission order if sorted), its results copied back to the
@@ -118,8 +119,8 @@ struct nebem_server {
     nebem::WorkItem *items_host = nullptr;  // pinned, 2 x items_cap
     void *sort_ws = nullptr;                // scratch of the point sort (grown on demand)
     size_t sort_ws_bytes = 0;
-    double *units_dev = nullptr;            // units' partial sums, 2 x 2 unit_cap units: one set per launch stream
-    int64_t unit_cap = 0;
+    double *units_dev = nullptr;            // units' partial sums, one set of unit_cap + far_cap per launch stream
+    int64_t unit_cap = 0, far_cap = 0;
     int items_cap = 0;
     int round_items = 1;  // work items (waves) the device runs at once
     std::mutex mu;
@@ -157,10 +158,13 @@ static inline double *stage(nebem_server *s, const Request *r, int k)
     return reinterpret_cast<double *>(static_cast<char *>(s->arena_dev) + r->off) + (size_t)k * r->m;
 }
 
-static int units_per_item(const nebem_server *s, size_t k)
+// the most units that an item of geometry k has
+static void units_per_item(const nebem_server *s, size_t k, int &per, int &far_per)
 {
-    return item_units(s->geom_segsz[k], s->geom_groups[k] != SIZE_MAX,
-                      far_levels({s->geom_nseg[k], s->geom_segsz[k]}));
+    const bool grouped = s->geom_groups[k] != SIZE_MAX;
+    per = std::max(per, item_units(s->geom_segsz[k], grouped));
+    if (grouped)
+        far_per = std::max(far_per, item_far_units(s->geom_segsz[k], far_levels({s->geom_nseg[k], s->geom_segsz[k]})));
 }
 
 static void worker_main(nebem_server *s)
@@ -286,14 +290,13 @@ static void worker_main(nebem_server *s)
                         launch_group_moments(s->geoms[k]->drec.as<double>(), s->geoms[k]->sigma.as<double>(),
                                              s->geoms[k]->n, 0, 1, {s->geom_nseg[k], s->geom_segsz[k]},
                                              group_cur + s->geom_groups[k], s->lst[cur]);
-                int per = 0;
+                ItemUnits u = {nullptr, s->unit_cap, s->far_cap, 0, 0};
                 for (size_t k = 0; k < s->geoms.size(); ++k)
-                    if (used[k]) per = std::max(per, units_per_item(s, k));
+                    if (used[k]) units_per_item(s, k, u.per, u.far_per);
                 // past four rounds of whole items the last round's waste is small
-                const bool split = s->unit_cap > 0 && nitems <= 4 * s->round_items;
-                launch_eval_items(items_dev, nitems, s->imgs_dev, s->mixed, s->near_factor,
-                                  split ? s->units_dev + (size_t)cur * 2 * s->unit_cap * kUnitDoubles : nullptr,
-                                  s->unit_cap, per, s->lst[cur]);
+                if (s->units_dev && nitems <= 4 * s->round_items)
+                    u.sums = s->units_dev + (size_t)cur * (s->unit_cap + s->far_cap) * kUnitDoubles;
+                launch_eval_items(items_dev, nitems, s->imgs_dev, s->mixed, s->near_factor, u, s->lst[cur]);
                 e = hipGetLastError();
             }
             if (e == hipSuccess) e = hipEventRecord(s->ev_launch[cur], s->lst[cur]);
@@ -453,17 +456,16 @@ nebem_status nebem_server_create(nebem_session *const *sessions, int32_t nsessio
     if ((e = hipHostMalloc((void **)&s->items_host, 2 * sizeof(WorkItem) * s->items_cap, hipHostMallocDefault)) !=
         hipSuccess)
         return bail(e, "hipHostMalloc(work list)");
-    // units' scratch, 64 MB per launch stream; without it items run whole
-    int per = 1;
-    for (int k = 0; k < nsessions; ++k)
-        per = std::max(per, units_per_item(s, k));
-    s->unit_cap = std::min<int64_t>(16384, (int64_t)s->items_cap * per);
-    if (s->unit_cap >= per &&
-        hipMalloc((void **)&s->units_dev, 4 * (size_t)s->unit_cap * kUnitDoubles * sizeof(double)) != hipSuccess) {
+    // units' scratch, up to 160 MB per launch stream; without it items run whole
+    int per = 1, far_per = 0;
+    for (int k = 0; k < nsessions; ++k) units_per_item(s, k, per, far_per);
+    s->unit_cap = std::min<int64_t>(65536, (int64_t)s->items_cap * per);
+    s->far_cap = std::min<int64_t>(16384, (int64_t)s->items_cap * far_per);
+    if (hipMalloc((void **)&s->units_dev, 2 * (size_t)(s->unit_cap + s->far_cap) * kUnitDoubles * sizeof(double)) !=
+        hipSuccess) {
         (void)hipGetLastError();
         s->units_dev = nullptr;
     }
-    if (!s->units_dev) s->unit_cap = 0;
     s->worker = std::thread(worker_main, s);
     *out = s;
     return NEBEM_OK;
