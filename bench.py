@@ -12,12 +12,12 @@ timed region holds the job exactly once.
 value = (assembly + evaluation interactions of the job) / timed seconds,
 where an interaction is one (observation point, element copy) pair.
 
-Prints one JSON line.  Extra keys: per-stage times, the evaluation kernel's
-roofline (FP64 vector ALU bound, against the closed forms' algorithmic
-operation count), the CPU oracle timed on this host's cores on a bounded
-sample of the same evaluation, the mixed-precision job on the same input
-(rate, speedup, largest relative difference from the FP64 results), and a
-bounded serving replay (continuous batching over resident sessions of the
+Prints one JSON line.  Extra keys: per-stage times, the evaluation's roofline
+(FP64 vector ALU bound, executed operations from the committed counters),
+the CPU oracle timed on this host's cores on a bounded sample of the same
+evaluation, the mixed-precision job on the same input (rate, speedup,
+largest relative difference from the FP64 results), and a bounded serving
+replay (continuous batching over resident sessions of the
 plates, the GEM cell and this workload, Poisson arrivals) with p50/p99
 request latency.
 """
@@ -40,17 +40,18 @@ sys.path.insert(0, ROOT)
 # 4 log + 2 atan + 4 div; right triangle ~90 + 3 + 3 + 1 + 3.
 ALG_FLOPS_RECT = 124.0
 ALG_FLOPS_TRI = 100.0
-# Counter figures of the FP64 evaluation kernel per workload, from the
-# rocprofv3 runs summarised under profiles/ (FP64 FLOP per interaction =
-# 64 x (ADD + MUL + TRANS + 2 FMA) FP64 instructions / interactions; HBM
-# bytes per launch = FETCH_SIZE x 2 + WRITE_SIZE, the factors that make a
-# plain 1 GiB copy read 1 GiB and write 1 GiB), valid for launches of
-# points_per_launch points and only while the evaluation kernel's sources
-# hash to source_sha16 (otherwise the counter figures are not reported).
+# Counter figures of the FP64 evaluation (k_group_far + k_group_near) per
+# workload, from the rocprofv3 runs summarised under profiles/ (FP64 FLOP per
+# interaction = 64 x (ADD + MUL + TRANS + 2 FMA) FP64 instructions /
+# interactions; HBM bytes per launch = FETCH_SIZE x 2 + WRITE_SIZE, the factors
+# that make a plain 1 GiB copy read 1 GiB and write 1 GiB, of the moments' and
+# the reduction's kernels too), valid for launches of points_per_launch points
+# and only while the evaluation's sources hash to source_sha16 (otherwise the
+# counter figures are not reported).
 COUNTER_CALIBRATION = {
     # profiles/eval_fp64_thgem_200k.md: one 2e5-point launch, 1.00672e12 interactions
-    "thgem": {"flops_per_interaction": 101.04, "valu_per_interaction": 73.09, "traffic_bytes": 537282944,
-              "points_per_launch": 200000, "source_sha16": "1b886789b31f0e81"},
+    "thgem": {"flops_per_interaction": 4.9004, "valu_per_interaction": 3.612, "traffic_bytes": 1840716800,
+              "points_per_launch": 200000, "source_sha16": "9cd0d85c2a8b156b"},
 }
 EVAL_SOURCES = ("field_kernels.hip", "group_kernels.hip", "group_far.hpp", "lattice_far.hpp", "panel_fp64.hpp",
                 "fastmath_fp64.hpp", "poly_coeffs.hpp", "farfield_mixed.hpp", "order_kernels.hip", "nebem_internal.hpp")
@@ -788,9 +789,11 @@ def headline(args):
 
     roof = None
     if prec == nb.FP64:
-        # algorithmic FLOP per interaction: the closed forms' operation counts,
-        # a transcendental or division counted as one operation, over this
-        # geometry's mix of rectangles and right triangles
+        # executed FP64 FLOP (counted), and what closed forms throughout would
+        # need: their operation counts, a transcendental or division counted as
+        # one operation, over this geometry's mix of rectangles and right
+        # triangles.  The far copies are summed group by group, so the second
+        # exceeds what the device executes.
         kind = np.asarray(geom.kind)
         n_rect, n_tri = int((kind == 0).sum()), int((kind == 1).sum())
         f_alg = (n_rect * ALG_FLOPS_RECT + n_tri * ALG_FLOPS_TRI) / n
@@ -798,21 +801,21 @@ def headline(args):
         # differ by at most one), HIP events on the launching stream
         per_launch_ms = t_eval / K
         per_launch_inter = inter_eval / K
-        ach = f_alg * per_launch_inter / (per_launch_ms * 1e-3)
         cal = COUNTER_CALIBRATION.get(args.workload)
         sha = eval_source_sha16()
-        if cal and cal.get("source_sha16") != sha:
-            cal = None  # the kernel changed since the counters were taken
-        roof = {"bound": "alu", "kernel": "k_eval_fp64", "achieved": ach / 1e12, "peak": FP64_VALU_PEAK / 1e12,
-                "unit": "TFLOP/s", "frac": ach / FP64_VALU_PEAK,
-                "traffic": cal["traffic_bytes"] if (cal and cal["points_per_launch"] == round(M / K)) else None,
-                "flops_per_interaction": f_alg, "flops_per_interaction_kind": "algorithmic",
+        if cal and (cal.get("source_sha16") != sha or cal["points_per_launch"] != round(M / K)):
+            cal = None  # the kernels or the launch changed since the counters were taken
+        ach = cal["flops_per_interaction"] * eval_rate if cal else None
+        roof = {"bound": "alu", "kernel": "k_group_far + k_group_near",
+                "achieved": ach / 1e12 if cal else None, "peak": FP64_VALU_PEAK / 1e12,
+                "unit": "TFLOP/s", "frac": ach / FP64_VALU_PEAK if cal else None,
+                "traffic": cal["traffic_bytes"] if cal else None,
+                "flops_per_interaction": cal["flops_per_interaction"] if cal else None,
+                "flops_per_interaction_kind": "counted",
+                "method_flops_per_interaction": f_alg, "method_tflops": f_alg * eval_rate / 1e12,
                 "elements": {"rectangles": n_rect, "right_triangles": n_tri},
                 "launches": K, "avg_launch_ms": per_launch_ms, "interactions_per_launch": per_launch_inter,
                 "eval_source_sha16": sha}
-        if cal:
-            roof["counter_flops_per_interaction"] = cal["flops_per_interaction"]
-            roof["counter_frac"] = cal["flops_per_interaction"] * eval_rate / FP64_VALU_PEAK
 
     mixed = None
     if not args.no_mixed and prec == nb.FP64:

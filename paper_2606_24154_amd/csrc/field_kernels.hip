@@ -1638,7 +1638,7 @@ void launch_eval_items(const WorkItem *items, int nitems, const ImgArgs *imgs, i
 // Grid: x over blocks of 256 rows, y over blocks of kTileA columns.  Each
 // lane writes A[i + j n] for its row i and the block's columns j: the 256
 // lanes of a workgroup store 256 consecutive doubles of a column (2 KB).
-// The matrix is assembled with the exact closed forms in both precision
+// The matrix is assembled in FP64 to the same accuracy in both precision
 // modes: it is a small share of a step's interactions, and far-field
 // truncation in its entries would carry into sigma through the solve.
 __global__ __launch_bounds__(kBlock) void k_assemble(const double *__restrict__ drec, int n, ImgArgs img,
