@@ -16,6 +16,7 @@
 
 #include <rocprim/device/device_radix_sort.hpp>
 
+#include <algorithm>
 #include <cmath>
 
 #include "nebem_internal.hpp"
@@ -1465,10 +1466,39 @@ __device__ __forceinline__ void near_unit(NearList &nl, cdouble_p drec, cdouble_
     }
 }
 
+// Unit y of a near pass: groups [g0, g1) and runs [u0, u1) of a segment.
+struct NearRange {
+    int seg, ns, g0, g1, u0, u1;
+};
+__device__ __forceinline__ NearRange near_range(int y, int n, int segsz, int gps, int split, const int *order)
+{
+    NearRange r = {0, 0, 0, 0, 0, kNearRuns};
+    if (split == 2) {
+        r.u0 = y % kNearRuns;
+        r.u1 = r.u0 + 1;
+        y /= kNearRuns;
+    }
+    r.seg = split ? y / gps : order[y];
+    r.ns = min(segsz, n - r.seg * segsz);
+    const int ng = (r.ns + kGroupElems - 1) / kGroupElems;
+    r.g0 = split ? y % gps : 0;
+    r.g1 = split ? min(r.g0 + 1, ng) : ng;
+    return r;
+}
+__device__ __forceinline__ bool columns_differ(cdouble_p gd, const NearRange &r)
+{
+    bool d = false;
+    for (int g = r.g0; g < r.g1; ++g) d = d || gd[(int64_t)g * kGroupStride + kHeadDiffer] != 0.0;
+    return d;
+}
+
 // Grid: x over points, y over units -- segments (split 0: added to the far
 // pass's sums), groups (split 1) or runs of 8 of their elements (split
 // 2: with runs of 16 the near pass of 64 points took 505 us, with 8 280, with 4 158, but
 // 2003 points 1.34, 1.30 and 1.45 ms: each unit scans the lattice anew).
+// The columns share column 0's walk through the near copies, unless a density is not
+// finite in some of them only, and with it what is near differs (kHeadDiffer):
+// then the others are left to k_near_columns.
 template <int K>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_group_near(const double *__restrict__ drec,
                                                        const double *__restrict__ sigma,
@@ -1482,32 +1512,64 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
     __shared__ NearList list;
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     const int j = min(i, m - 1);
-    int y = blockIdx.y, u0 = 0, u1 = kNearRuns;
-    if (split == 2) {
-        u0 = y % kNearRuns;
-        u1 = u0 + 1;
-        y /= kNearRuns;
-    }
-    const int seg = split ? y / gps : order[y];
-    const int ns = min(segsz, n - seg * segsz);
-    const int ng = (ns + kGroupElems - 1) / kGroupElems;
-    const int g0 = split ? y % gps : 0, g1 = split ? min(g0 + 1, ng) : ng;
+    const NearRange r = near_range(blockIdx.y, n, segsz, gps, split, order);
+    const cdouble_p gd = uniform_ptr(gdata + (int64_t)r.seg * rps * kGroupStride);
     double acc[K][4];
-    near_unit<K>(list, uniform_ptr(drec + (int64_t)seg * segsz * R_STRIDE),
-                 uniform_ptr(sigma + (int64_t)seg * segsz), sig_stride,
-                 uniform_ptr(gdata + (int64_t)seg * rps * kGroupStride), ns, img, px[j], py[j], pz[j], g0,
-                 g1, u0, u1,
-                 acc);
+    near_unit<K>(list, uniform_ptr(drec + (int64_t)r.seg * segsz * R_STRIDE),
+                 uniform_ptr(sigma + (int64_t)r.seg * segsz), sig_stride, gd, r.ns, img, px[j], py[j], pz[j], r.g0, r.g1,
+                 r.u0, r.u1, acc);
+    const bool only0 = K > 1 && columns_differ(gd, r);
     if (i >= m) return;
-    const int64_t o = (int64_t)(split ? (int)blockIdx.y : seg) * unit_stride + i;
+    const int64_t o = (int64_t)(split ? (int)blockIdx.y : r.seg) * unit_stride + i;
 #pragma unroll
     for (int k = 0; k < K; ++k)
 #pragma unroll
         for (int c = 0; c < 4; ++c)
-            if (out.c[c]) {
+            if (out.c[c] && !(k > 0 && only0)) {
                 double *d = out.c[c] + o + k * out.stride;
                 *d = split ? acc[k][c] : *d + acc[k][c];
             }
+}
+
+// Columns 1 .. ncol - 1 of the units in which they differ from column 0, by
+// their own records (column k's at gdata + k gstride).  Mostly there are none, and the
+// launch ends with the scan of the groups' flags: 3 us of the 4.0 ms of three columns
+// at 4507 points.  (With this in k_group_near, as a loop or as workgroups of their
+// own, that call took 1 to 2 % longer.)
+__global__ __launch_bounds__(64) void k_near_columns(const double *__restrict__ drec, const double *__restrict__ sigma,
+                                                     const double *__restrict__ gdata, int64_t gstride, int n,
+                                                     int64_t sig_stride, int ncol, int nseg, int segsz, int gps, int rps,
+                                                     ImgArgs img, int split, int units, const int *__restrict__ order,
+                                                     const double *__restrict__ px, const double *__restrict__ py,
+                                                     const double *__restrict__ pz, int m, OutCols out,
+                                                     int64_t unit_stride)
+{
+    __shared__ NearList list;
+    bool any = false;
+    for (int g = threadIdx.x; g < nseg * gps; g += 64) {
+        const int seg = g / gps, q = g % gps;
+        if (seg * segsz + q * kGroupElems < min(n, (seg + 1) * segsz))
+            any = any || gdata[((int64_t)seg * rps + q) * kGroupStride + kHeadDiffer] != 0.0;
+    }
+    if (__ballot(any) == 0) return;
+    const int blocks = (m + 63) / 64;
+    const int64_t items = (int64_t)units * blocks * (ncol - 1);
+    for (int64_t it = blockIdx.x; it < items; it += gridDim.x) {
+        const int k = 1 + (int)(it % (ncol - 1));
+        const int64_t v = it / (ncol - 1);
+        const int y = (int)(v / blocks), i = (int)(v % blocks) * 64 + (int)threadIdx.x, j = min(i, m - 1);
+        const NearRange r = near_range(y, n, segsz, gps, split, order);
+        const double *g = gdata + (int64_t)r.seg * rps * kGroupStride;
+        if (!columns_differ(uniform_ptr(g), r)) continue;
+        double acc[1][4];
+        near_unit<1>(list, uniform_ptr(drec + (int64_t)r.seg * segsz * R_STRIDE),
+                     uniform_ptr(sigma + k * sig_stride + (int64_t)r.seg * segsz), 0, uniform_ptr(g + k * gstride), r.ns,
+                     img, px[j], py[j], pz[j], r.g0, r.g1, r.u0, r.u1, acc);
+        if (i >= m) continue;
+        const int64_t o = (int64_t)(split ? y : r.seg) * unit_stride + k * out.stride + i;
+        for (int c = 0; c < 4; ++c)
+            if (out.c[c]) out.c[c][o] = split ? acc[0][c] : out.c[c][o] + acc[0][c];
+    }
 }
 
 template <int K>
@@ -1515,12 +1577,18 @@ static void launch_near_k(const double *drec, const double *sigma, const double 
                           const SegPlan &sp, const ImgArgs &img, int split, const int *order, const double *px, const double *py,
                           const double *pz, int64_t m, const OutCols &out, int64_t unit_stride, hipStream_t s)
 {
-    const int gps = groups_per_seg(sp);
+    const int gps = groups_per_seg(sp), rps = records_per_seg(sp);
     const int64_t ng = (int64_t)sp.nseg * gps;
     const int64_t units = split == 0 ? sp.nseg : split == 1 ? ng : ng * kNearRuns;
-    hipLaunchKernelGGL(k_group_near<K>, dim3((unsigned)((m + 63) / 64), (unsigned)units), dim3(64), 0, s, drec,
-                       sigma, gdata, (int)n, sig_stride, sp.segsz, gps, records_per_seg(sp), img, split, order, px, py, pz, (int)m, out,
-                       unit_stride);
+    const unsigned blocks = (unsigned)((m + 63) / 64);
+    hipLaunchKernelGGL(k_group_near<K>, dim3(blocks, (unsigned)units), dim3(64), 0, s, drec, sigma, gdata, (int)n,
+                       sig_stride, sp.segsz, gps, rps, img, split, order, px, py, pz, (int)m, out, unit_stride);
+    if (K > 1) {  // two waves per SIMD
+        const unsigned waves = (unsigned)std::min<int64_t>(2048, units * blocks * (K - 1));
+        hipLaunchKernelGGL(k_near_columns, dim3(waves), dim3(64), 0, s, drec, sigma, gdata,
+                           (int64_t)sp.nseg * rps * kGroupStride, (int)n, sig_stride, K, sp.nseg, sp.segsz, gps, rps, img,
+                           split, (int)units, order, px, py, pz, (int)m, out, unit_stride);
+    }
 }
 
 void launch_group_near(const double *drec, const double *sigma, const double *gdata, int64_t n, int64_t sig_stride,

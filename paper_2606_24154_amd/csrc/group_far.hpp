@@ -50,6 +50,7 @@ constexpr int kGroupHead = 16;
 constexpr int kHeadTier = 4;  // index of the first threshold
 constexpr int kTiers = 6;
 constexpr int kHeadSuper = 10;  // the parent's centre and far threshold (none: NaN, no point is far)
+constexpr int kHeadDiffer = 14;  // of a group, column 0: not 0 if the columns' thresholds differ
 constexpr int kEntry = 8;
 constexpr int kOrderSplit = 8;
 // entries of the degrees below L in the first and in the second pass

@@ -217,10 +217,11 @@ __device__ __forceinline__ void coef_order(const MomElem &e, double *__restrict_
 __device__ const HarmonicTables kHarmDev = make_harmonic_tables();
 
 // Record of a group: its head (centre c, squared radius a2; no super-group, see
-// k_parent_moments) and, one (L, m) per thread, the field's coefficients from the
-// moments B = bre + i bim.
+// k_parent_moments; differ: kHeadDiffer) and, one (L, m) per thread, the field's
+// coefficients from the moments B = bre + i bim.
 __device__ __forceinline__ void write_record(double *__restrict__ out, const double (&c)[3], double a2, bool bad,
-                                             const double *__restrict__ bre, const double *__restrict__ bim)
+                                             bool differ, const double *__restrict__ bre,
+                                             const double *__restrict__ bim)
 {
     if (threadIdx.x < kGroupHead) {
         const int k = threadIdx.x;
@@ -229,6 +230,7 @@ __device__ __forceinline__ void write_record(double *__restrict__ out, const dou
         double v = k < 3 ? c[min(k, 2)] : k == 3 ? sqrt(a2) : bad ? inf : t;
         if (k >= kHeadSuper && k < kHeadSuper + 3) v = c[min(k - kHeadSuper, 2)];
         if (k == kHeadSuper + 3) v = __builtin_nan("");
+        if (k == kHeadDiffer) v = differ ? 1.0 : 0.0;
         out[k] = v;
     }
     for (int t = threadIdx.x; t < kGroupEntries; t += blockDim.x) {
@@ -285,7 +287,12 @@ __global__ __launch_bounds__(64 * kMomWaves) void k_group_moments(const double *
     const double *sg = sigma + (size_t)blockIdx.y * sig_stride;
     double c[3], a2;
     group_sphere(recs, cnt, c, a2);
-    const bool bad = !(a2 > 0.0) || !isfinite(a2) || __ballot(lane < cnt && !isfinite(sg[e0 + lane])) != 0;
+    const bool inf = __ballot(lane < cnt && !isfinite(sg[e0 + lane])) != 0;
+    const bool bad = !(a2 > 0.0) || !isfinite(a2) || inf;
+    bool differ = false;  // column 0 knows for all
+    if (blockIdx.y == 0)
+        for (unsigned k = 1; k < gridDim.y; ++k)
+            differ = differ || (__ballot(lane < cnt && !isfinite(sg[(size_t)k * sig_stride + e0 + lane])) != 0) != inf;
     const double ia = 1.0 / sqrt(a2);
     sg += e0;
     switch (wave) {
@@ -306,7 +313,8 @@ __global__ __launch_bounds__(64 * kMomWaves) void k_group_moments(const double *
     default: moment_order<14>(recs, sg, cnt, c, ia, bre, bim); break;
     }
     __syncthreads();
-    write_record(gdata + (int64_t)blockIdx.y * gstride + (int64_t)(seg * rps + q) * kGroupStride, c, a2, bad, bre, bim);
+    write_record(gdata + (int64_t)blockIdx.y * gstride + (int64_t)(seg * rps + q) * kGroupStride, c, a2, bad, differ, bre,
+                 bim);
 }
 
 // Records of the parents -- super-groups of four groups (level 1), then of four
@@ -480,7 +488,7 @@ __global__ __launch_bounds__(kParentThreads) void k_parent_moments(const double 
     __syncthreads();
     // a child that is not fit leaves its parent's share to the children
     if (has && q < 4) rec[kHeadSuper + q] = q < 3 ? sc[min(q, 2)] : bad ? __builtin_inf() : sa2 * tier_ratio2(0);
-    write_record(self, sc, sa2, bad, bre, bim);
+    write_record(self, sc, sa2, bad, false, bre, bim);
 }
 
 void launch_group_moments(const double *drec, const double *sigma, int64_t n, int64_t sig_stride, int ncol,

@@ -121,6 +121,23 @@ def test_density_that_is_not_finite(nb):
     assert np.all(np.isnan(evaluate(nb, g, sigma, points(g, 200))))
 
 
+@pytest.mark.parametrize("copies", ["121", "169", "levels"])
+@pytest.mark.parametrize("bad", [(0,), (1,), (0, 2), (2, 3)])
+def test_columns_with_densities_that_are_not_finite(nb, copies, bad):
+    """Which copies of a group are near differs by column where a density is not
+    finite: the finite columns and the others each equal their single evaluation."""
+    g = geometry(copies)
+    sigma = 1e-5 * np.random.default_rng(10).standard_normal((4, g.n))
+    for k, v in zip(bad, (np.nan, -np.inf)):
+        sigma[k, 100 + 300 * k] = v
+    p = points(g, 131)
+    dp = nb.DevicePanels.from_geometry(g, "cuda:0")
+    out = torch.stack(nb.eval_points_multi(dp, dev(sigma), *[dev(p[:, k]) for k in range(3)]), 2).cpu().numpy()
+    for k in range(4):
+        assert np.isfinite(out[k]).all() == (k not in bad)
+        assert np.array_equal(out[k], evaluate(nb, g, sigma[k], p), equal_nan=True), k
+
+
 @pytest.mark.parametrize("precision", [0, 1])
 @pytest.mark.parametrize("copies", ["121", "none"])
 def test_server_units_give_equal_bits(nb, copies, precision):
