@@ -73,6 +73,7 @@ __host__ __device__ constexpr int entry_index(int L, int m)
     return m < kOrderSplit ? pass1_entries(L) + m : kPass2 + pass2_entries(L) + m - kOrderSplit;
 }
 constexpr int kGroupStride = kGroupHead + kEntry * kGroupEntries;
+static_assert(kGroupHead % kEntry == 0, "entries are read 64 bytes at a time, from records at such boundaries");
 
 // squares of r/a = ((p + 2) / 3e-12)^(1/(p + 1)) for p = 14, 12, 10, 8, 6, 4
 __host__ __device__ constexpr double tier_ratio2(int k)

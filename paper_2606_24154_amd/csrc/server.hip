@@ -105,8 +105,8 @@ struct nebem_server {
     std::vector<int> geom_nseg;   // element segments per geometry
     std::vector<int> geom_segsz;  // elements per segment (last may be shorter)
     std::vector<size_t> geom_groups;  // offset of a grouped geometry's records in group_dev, else SIZE_MAX
-    double *group_dev = nullptr;      // group records, 2 x group_len: one set per launch stream
-    size_t group_len = 0;             // doubles
+    double *group_dev = nullptr;      // group records, 2 x groups.len: one set per launch stream
+    nebem::RecordBlocks groups;
     int mixed = 0;
     double near_factor = 4.0;
     hipStream_t stream = nullptr;            // admission: point copies and sorts
@@ -229,7 +229,7 @@ static void worker_main(nebem_server *s)
         // This stream's previous list (launch nlaunch - 2) has completed.
         WorkItem *items_host = s->items_host + (size_t)cur * s->items_cap;
         WorkItem *items_dev = s->items_dev + (size_t)cur * s->items_cap;
-        double *group_cur = s->group_dev + (size_t)cur * s->group_len;
+        double *group_cur = s->group_dev + (size_t)cur * s->groups.len;
         std::vector<char> used(s->geoms.size(), 0);
         int nitems = 0;
         double budget = s->opt.batch_interactions;
@@ -417,8 +417,7 @@ nebem_status nebem_server_create(nebem_session *const *sessions, int32_t nsessio
         s->geom_segsz.push_back(sp.segsz);
         s->geom_nseg.push_back(sp.nseg);
         const bool grouped = !mixed && eval_grouped(sessions[k]->n, sessions[k]->img);
-        s->geom_groups.push_back(grouped ? s->group_len : SIZE_MAX);
-        if (grouped) s->group_len += group_data_bytes(sp, 1) / sizeof(double);
+        s->geom_groups.push_back(grouped ? s->groups.add((size_t)sp.nseg * records_per_seg(sp) * kGroupStride) : SIZE_MAX);
     }
     auto bail = [&](hipError_t e, const char *what) {
         nebem_status st = hip_fail(e, what);
@@ -445,8 +444,8 @@ nebem_status nebem_server_create(nebem_session *const *sessions, int32_t nsessio
         return bail(e, "hipMalloc(images)");
     if ((e = hipMemcpy(s->imgs_dev, imgs.data(), sizeof(ImgArgs) * nsessions, hipMemcpyHostToDevice)) != hipSuccess)
         return bail(e, "hipMemcpy(images)");
-    if (s->group_len &&
-        (e = hipMalloc((void **)&s->group_dev, 2 * s->group_len * sizeof(double))) != hipSuccess)
+    if (s->groups.len &&
+        (e = hipMalloc((void **)&s->group_dev, 2 * s->groups.len * sizeof(double))) != hipSuccess)
         return bail(e, "hipMalloc(group records)");
     s->items_cap = o.max_items;
     s->round_items = eval_items_slots(mixed);

@@ -1,5 +1,6 @@
-// server_admission.hpp -- the evaluation server's staging arena and
-// admission policy (host code only, no HIP calls).
+// server_admission.hpp -- the evaluation server's staging arena, the places of
+// its geometries' group records, and its admission policy (host code only, no HIP
+// calls).
 //
 // Arena: offsets into one device allocation, handed out in 256-byte granules
 // (the arena's size is rounded down to a whole granule, so every offset is
@@ -82,6 +83,19 @@ struct Arena {
                 free_.erase(it);
             }
         }
+    }
+};
+
+// Places of the geometries' group records, in doubles, within one launch stream's
+// set.  Records are read 64 bytes at a time: every geometry's start at a 256-byte
+// boundary, and `len` is a multiple of it too, so that the next set's do.
+struct RecordBlocks {
+    size_t len = 0;
+    size_t add(size_t doubles)
+    {
+        const size_t at = len;
+        len += (doubles + 31) & ~size_t(31);
+        return at;
     }
 };
 
