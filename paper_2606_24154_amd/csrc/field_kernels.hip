@@ -800,16 +800,6 @@ __device__ __forceinline__ void eval_block(const double *__restrict__ drec, cons
     }
 }
 
-// Element segments.  Every evaluation path (stateless, session, ordered,
-// several-column, serving) splits a geometry's elements into the same
-// contiguous segments of about kSegWork interactions per point, evaluates
-// each (point, segment) pair as an independent unit and adds the segments'
-// partial sums in segment order.  The plan depends on the element count and
-// the copies only, so a point's result does not depend on how many other
-// points share its launch; and a launch of a few hundred thousand points
-// over tens of thousands of elements still has ~10^5 workgroups, so its last
-// round of waves is a small share of it (one workgroup per 256 points over
-// all elements would leave a 200 000-point launch at 1.5 rounds).
 int64_t img_copies(const ImgArgs &img)
 {
     int64_t t = (int64_t)(2 * img.n1 + 1) * (2 * img.n2 + 1);
@@ -821,18 +811,7 @@ int64_t img_copies(const ImgArgs &img)
     return (int64_t)img.nref * t;
 }
 
-SegPlan seg_plan(int64_t n, const ImgArgs &img)
-{
-    SegPlan p = {1, (int)(n > 0 ? n : 1)};
-    if (n <= 0) return p;
-    const double per_pt = (double)n * (double)img_copies(img);
-    int nseg = (int)(per_pt / kSegWork + 0.5);
-    nseg = nseg < 1 ? 1 : (nseg > kMaxSeg ? kMaxSeg : nseg);
-    if (nseg > n) nseg = (int)n;
-    p.segsz = (int)((n + nseg - 1) / nseg);
-    p.nseg = (int)((n + p.segsz - 1) / p.segsz);
-    return p;
-}
+SegPlan seg_plan(int64_t n, const ImgArgs &img) { return seg_plan(n, img_copies(img)); }
 
 // FP64: the default allocation (about 250 VGPRs, two waves per SIMD) keeps every
 // value in registers; a three-wave target made the allocator spill part of
@@ -888,8 +867,6 @@ static void launch_eval_bs(const double *drec, const double *sigma, int64_t n, c
     hipLaunchKernelGGL(k, g, dim3(BS), 0, s, drec, sigma, (int)n, sp.segsz, units, img, near_factor, px, py, pz,
                        (int)m, scale, phi, ex, ey, ez, seg_stride);
 }
-
-int eval_subunits(const SegPlan &sp) { return groups_per_seg(sp) * kNearParts; }
 
 void launch_eval_seg(const double *drec, const double *sigma, int64_t n, const SegPlan &sp, const ImgArgs &img,
                      int mixed, double near_factor, bool split, const double *px, const double *py, const double *pz,

@@ -841,19 +841,8 @@ void launch_fold_groups(const double *far, const double *near, const SegPlan &sp
 }
 
 // ----------------------------------------------------------------- the rule
-// Grouping pays when a point meets many copies far from it: from about 65 000
-// element copies (a GEM cell with its first two rings of copies has 200 000) the
-// moments' launch is a small share even of a 64-point call.  Below, and for
-// geometries without copies and fewer elements, nearly every group is near and
-// the plain kernels do the same work without the tests.
-bool eval_grouped(int64_t n, const ImgArgs &img)
-{
-    return img.hole < 0 && (double)n * (double)img_copies(img) >= 65536.0;
-}
+bool eval_grouped(int64_t n, const ImgArgs &img) { return img.hole < 0 && grouping_pays(n, img_copies(img)); }
 
-size_t group_data_bytes(const SegPlan &sp, int ncol)
-{
-    return ((size_t)sp.nseg * records_per_seg(sp) * kGroupStride * (size_t)ncol + (sp.nseg + 1) / 2) * sizeof(double);
-}
+size_t group_record_bytes() { return kGroupStride * sizeof(double); }
 
 }  // namespace nebem

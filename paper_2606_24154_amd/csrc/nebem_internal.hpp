@@ -6,6 +6,7 @@
 #include <cstdint>
 #include <string>
 
+#include "eval_plan.hpp"
 #include "nebem.h"
 
 namespace nebem {
@@ -153,41 +154,11 @@ struct OutCols {
     double *c[4];
     int64_t stride;
 };
-constexpr int kMultiCols = 4;  // density columns per evaluation launch
 
-// Element segments of an evaluation (field_kernels.hip): nseg contiguous
-// ranges of segsz elements (the last may be shorter), about kSegWork
-// interactions per point each; a function of the element count and copies
-// only, shared by every evaluation path and the server.
-constexpr double kSegWork = 1.2e5;
-constexpr int kMaxSeg = 64;
-struct SegPlan {
-    int nseg, segsz;
-};
-// Groups of an FP64 evaluation (group_kernels.hip, group_far.hpp): runs of
-// kGroupElems consecutive elements of a segment, groups_per_seg of them per
-// segment (fewer in a short last one).
-constexpr int kGroupElems = 64;
-constexpr int kNearParts = 4;  // runs of 16 elements per group, units of an ungrouped split evaluation
-constexpr int kNearRuns = 8;   // runs of 8 elements per group, units of a split near pass
-inline int groups_per_seg(const SegPlan &sp) { return (sp.segsz + kGroupElems - 1) / kGroupElems; }
-// Far expansions of a segment: one per group, then one per kSuper consecutive
-// groups for the copies far from all of them, and in geometries of many groups
-// (far_levels) one per kSuper of those.
-constexpr int kSuper = 4;
-__host__ __device__ inline int parents_of(int n) { return (n + kSuper - 1) / kSuper; }
-__host__ __device__ inline int records_of(int groups, int levels)
-{
-    return groups + parents_of(groups) + (levels > 1 ? parents_of(parents_of(groups)) : 0);
-}
-// With 650 groups (double THGEM, 40 000 points) the second level takes 59 ms to 52; with
-// 126 (GEM cell) it saves 1 % of 200 000 points and costs 64 points 6 %.
-inline int far_levels(const SegPlan &sp) { return (int64_t)sp.nseg * groups_per_seg(sp) >= 256 ? 2 : 1; }
-inline int records_per_seg(const SegPlan &sp) { return records_of(groups_per_seg(sp), far_levels(sp)); }
 // Whether an FP64 evaluation takes far copies of whole groups by their
 // expansions: a function of the geometry only, like the segment plan.
 bool eval_grouped(int64_t n, const ImgArgs &img);
-size_t group_data_bytes(const SegPlan &sp, int ncol);
+size_t group_record_bytes();
 // moments of every group and density column (column k at sigma + k sig_stride)
 // order: of the segments, the costliest first (behind the records in gdata)
 void launch_segment_order(const double *gdata, int64_t n, const SegPlan &sp, int *order, hipStream_t s);
@@ -224,7 +195,6 @@ SegPlan seg_plan(int64_t n, const ImgArgs &img);
 // outputs + y * seg_stride (nseg == 1, scale k_e: the final results); split:
 // the same for the eval_subunits 16-element runs of every segment, whose sums
 // add up to the segment's in order, bit for bit.
-int eval_subunits(const SegPlan &sp);
 void launch_eval_seg(const double *drec, const double *sigma, int64_t n, const SegPlan &sp, const ImgArgs &img,
                      int mixed, double near_factor, bool split, const double *px, const double *py, const double *pz,
                      int64_t m, double scale, double *phi, double *ex, double *ey, double *ez, int64_t seg_stride,

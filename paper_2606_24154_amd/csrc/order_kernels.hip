@@ -25,7 +25,6 @@ namespace nebem {
 
 constexpr int kOB = 256;         // threads per block of the helper kernels
 constexpr int kBoxParts = 256;   // partial bounding boxes (first reduction pass)
-constexpr int64_t kOrderMin = 65;  // more than one wave
 
 // per-block bounding box of a strided share of the points (min / max are
 // exact, so the result does not depend on the reduction order)
@@ -280,117 +279,21 @@ void launch_unorder4(const double *src, const int *perm, int64_t m, double *d0, 
 
 // ------------------------------------------------------- evaluation driver
 namespace {
-constexpr size_t kPartBudget = size_t(512) << 20;  // preferred bytes of segment partial sums per chunk
-
-struct EvalShape {
-    SegPlan sp;
-    int kc;           // columns per launch
-    bool grouped;     // FP64 with far copies of whole groups (group_kernels.hip)
-    int64_t ngroup, nrec, rows;  // groups of the plan, far expansions, lattice rows of one
-    size_t part_pp;   // partial-sum bytes per point (0: one segment, no partials)
-};
-
-EvalShape eval_shape(int64_t n, const ImgArgs &img, int ncol, int mixed)
+EvalShape shape_of(int64_t n, const ImgArgs &img, int ncol, int mixed)
 {
-    EvalShape sh;
-    sh.sp = seg_plan(n, img);
-    sh.kc = ncol < kMultiCols ? ncol : kMultiCols;
-    sh.grouped = !mixed && eval_grouped(n, img);
-    sh.ngroup = (int64_t)sh.sp.nseg * groups_per_seg(sh.sp);
-    sh.nrec = (int64_t)sh.sp.nseg * records_per_seg(sh.sp);
-    sh.rows = (int64_t)img.nref * (2 * img.n1 + 1);
-    sh.part_pp = sh.sp.nseg > 1 || sh.grouped ? (size_t)32 * sh.kc * sh.sp.nseg : 0;
-    return sh;
+    return eval_shape(seg_plan(n, img), !mixed && eval_grouped(n, img), (int64_t)img.nref * (2 * img.n1 + 1), ncol,
+                      group_record_bytes());
 }
 
-// Units of a grouped evaluation of c points (launch_group_far / _near): whole
-// segments once these alone are several rounds of waves (8 segments of a GEM
-// cell: from 65 536 points), groups below that, and rows / runs of groups
-// when even the groups leave SIMDs without a wave (1024 SIMDs; 64 points of a
-// GEM cell have 160 expansions, 1760 row waves; at 2003 points, 5120 and 56 320 waves, the
-// call takes 3.14 ms by expansions and 2.96 by rows).  No result bit depends on
-// the choice.  A split needs its unit sums in memory: at most kSplitBudget.
-constexpr size_t kSplitBudget = size_t(384) << 20;
-constexpr int64_t kMaxUnits = 65535;  // grid y
-void pick_splits(const EvalShape &sh, int64_t c, int &far, int &near)
-{
-    const int64_t waves = (c + 63) / 64;
-    far = near = 0;
-    if (waves * sh.sp.nseg >= 8192) return;
-    const int64_t pp = (int64_t)32 * sh.kc * c;
-    const int64_t most = (int64_t)(sh.grouped ? kSplitBudget : kPartBudget);
-    auto fits = [&](int64_t units) { return units <= kMaxUnits && units * pp <= most; };
-    if (!sh.grouped) {
-        far = fits((int64_t)sh.sp.nseg * eval_subunits(sh.sp)) ? 1 : 0;
-        return;
-    }
-    if (!fits(sh.nrec)) return;
-    far = waves * sh.nrec < 16384 && fits(sh.nrec * sh.rows) ? 2 : 1;
-    near = waves * sh.ngroup < 8192 && fits(sh.ngroup * kNearRuns) ? 2 : 1;
-}
-
-// workspace layout of one chunk of c points: [sort scratch | perm | sorted
-// points | sorted results (kc columns)] when ordered, then the partial sums,
-// the groups' records and the finer units' sums
-struct ChunkLayout {
-    bool ordered;
-    int fsplit, nsplit;
-    size_t sort_ws, perm, pts, res, part, groups, far, near, ffold, nfold, total;
-};
-
-bool chunk_layout(const EvalShape &sh, int64_t c, size_t limit, ChunkLayout &L)
-{
-    L.ordered = eval_ordering_pays(c);
-    size_t off = 0;
-    auto take = [&](size_t b) {
-        const size_t o = off;
-        off += align256(b);
-        return o;
-    };
-    L.sort_ws = L.perm = L.pts = L.res = 0;
-    if (L.ordered) {
-        const size_t w = order_points_workspace(c);
-        if (!w) return false;
-        L.sort_ws = w;
-        off = w;
-        L.perm = take(4 * (size_t)c);
-        L.pts = take(24 * (size_t)c);
-        L.res = take(32 * (size_t)sh.kc * (size_t)c);
-    }
-    L.part = take(sh.part_pp * (size_t)c);
-    L.groups = take(sh.grouped ? group_data_bytes(sh.sp, sh.kc) : 0);
-    const size_t base = off;
-    pick_splits(sh, c, L.fsplit, L.nsplit);
-    for (;;) {
-        const size_t unit = (size_t)32 * sh.kc * (size_t)c, g = (size_t)sh.ngroup, f = (size_t)sh.nrec;
-        L.far = take(!L.fsplit ? 0 : !sh.grouped ? unit * g * kNearParts : unit * f * (L.fsplit == 2 ? sh.rows : 1));
-        L.near = take(L.nsplit ? unit * g * (L.nsplit == 2 ? kNearRuns : 1) : 0);
-        L.ffold = take(L.fsplit == 2 ? unit * f : 0);
-        L.nfold = take(L.nsplit == 2 ? unit * g : 0);
-        L.total = off;
-        if (off <= limit || !L.fsplit) return true;
-        off = base;  // no room for the unit sums
-        L.fsplit = L.nsplit = 0;
-    }
-}
-
-int64_t preferred_chunk(const EvalShape &sh, int64_t m)
-{
-    int64_t c = m;
-    if (sh.part_pp) {
-        const int64_t lim = (int64_t)(kPartBudget / sh.part_pp) & ~(int64_t)255;
-        c = std::min<int64_t>(m, std::max<int64_t>(lim, 256));
-    }
-    return c;
-}
-
-// one column block of a grouped chunk: unscaled segment sums into part
+// one column block of a grouped chunk: unscaled segment sums into part; `fresh`:
+// the groups' records are not there yet
 void eval_grouped_chunk(const double *drec, const double *sg, int64_t n, int k, const EvalShape &sh,
                         const ImgArgs &img, const double *px, const double *py, const double *pz, int64_t c,
-                        const OutCols &pc, int64_t seg_stride, char *w, const ChunkLayout &L, hipStream_t s)
+                        const OutCols &pc, int64_t seg_stride, char *w, const ChunkLayout &L, bool fresh,
+                        hipStream_t s)
 {
     double *gd = reinterpret_cast<double *>(w + L.groups);
-    launch_group_moments(drec, sg, n, n, k, sh.sp, gd, s);
+    if (fresh) launch_group_moments(drec, sg, n, n, k, sh.sp, gd, s);
     if (!L.fsplit) {
         int *order = segment_order(gd, k, sh.sp);
         launch_segment_order(gd, n, sh.sp, order, s);
@@ -420,10 +323,12 @@ void eval_grouped_chunk(const double *drec, const double *sg, int64_t n, int k, 
     launch_fold_groups(far, near, sh.sp, seg_stride, reinterpret_cast<double *>(w + L.part), s);
 }
 
-// one chunk of c points (unsorted input px.., outputs o.c[comp] + col * ostride)
+// one chunk of c points (unsorted input px.., outputs o.c[comp] + col * ostride);
+// first: the first one of the call
 void eval_chunk(const double *drec, const double *sigma, int64_t n, int ncol, const EvalShape &sh,
                 const ImgArgs &img, int mixed, double near_factor, const double *px, const double *py,
-                const double *pz, int64_t c, const OutCols &o, char *w, const ChunkLayout &L, hipStream_t s)
+                const double *pz, int64_t c, const OutCols &o, char *w, const ChunkLayout &L, bool first,
+                hipStream_t s)
 {
     double *part = sh.part_pp ? reinterpret_cast<double *>(w + L.part) : nullptr;
     for (int c0 = 0; c0 < ncol; c0 += kMultiCols) {
@@ -449,7 +354,7 @@ void eval_chunk(const double *drec, const double *sigma, int64_t n, int ncol, co
                            (int64_t)(4 * cc)};
         };
         if (sh.grouped) {
-            eval_grouped_chunk(drec, sg, n, k, sh, img, px, py, pz, c, cols(part), seg_stride, w, L, s);
+            eval_grouped_chunk(drec, sg, n, k, sh, img, px, py, pz, c, cols(part), seg_stride, w, L, first, s);
         } else {
             const bool split = L.fsplit != 0;
             double *units = split ? reinterpret_cast<double *>(w + L.far) : part;
@@ -474,18 +379,19 @@ void eval_chunk(const double *drec, const double *sigma, int64_t n, int ncol, co
 size_t eval_workspace(int64_t n, const ImgArgs &img, int64_t m, int ncol, int mixed)
 {
     if (m <= 0 || ncol <= 0 || n <= 0) return 0;
-    const EvalShape sh = eval_shape(n, img, ncol, mixed);
+    const EvalShape sh = shape_of(n, img, ncol, mixed);
+    const int64_t c = chunk_points(sh, m, SIZE_MAX, order_points_workspace);
     ChunkLayout L;
-    if (!chunk_layout(sh, preferred_chunk(sh, m), SIZE_MAX, L)) return 0;
+    if (!c || !chunk_layout(sh, c, SIZE_MAX, order_points_workspace, L)) return 0;
     return L.total;
 }
 
 size_t eval_workspace_min(int64_t n, const ImgArgs &img, int64_t m, int ncol, int mixed)
 {
     if (m <= 0 || ncol <= 0 || n <= 0) return 0;
-    const EvalShape sh = eval_shape(n, img, ncol, mixed);
+    const EvalShape sh = shape_of(n, img, ncol, mixed);
     ChunkLayout L;
-    if (!chunk_layout(sh, std::min<int64_t>(m, 256), 0, L)) return 0;
+    if (!chunk_layout(sh, std::min<int64_t>(m, 256), 0, order_points_workspace, L)) return 0;
     return L.total;
 }
 
@@ -503,34 +409,23 @@ hipError_t run_eval(const double *drec, const double *sigma, int64_t n, int ncol
             }
         return hipSuccess;
     }
-    const EvalShape sh = eval_shape(n, img, ncol, mixed);
-    // the largest chunk (up to the preferred one) whose workspace fits
-    int64_t c = preferred_chunk(sh, m);
-    ChunkLayout L;
-    for (;;) {
-        if (!chunk_layout(sh, c, ws_bytes, L)) return hipErrorInvalidValue;
-        if (L.total <= ws_bytes || (L.total == 0)) break;
-        if (c <= 256) return hipErrorInvalidValue;
-        c = std::max<int64_t>(256, (c / 2) & ~(int64_t)255);
-    }
-    if (L.total > 0 && !ws) return hipErrorInvalidValue;
-    // as many chunks as needed, of equal size (a short last chunk would be a
-    // launch too small to fill the device)
-    {
-        const int64_t nch = (m + c - 1) / c;
-        const int64_t even = ((m + nch - 1) / nch + 255) & ~(int64_t)255;
-        if (even < c) c = even;
-    }
+    const EvalShape sh = shape_of(n, img, ncol, mixed);
+    const int64_t c = chunk_points(sh, m, ws_bytes, order_points_workspace);
+    if (!c || (!ws && ws_bytes)) return hipErrorInvalidValue;
     char *w = static_cast<char *>(ws);
     for (int64_t p0 = 0; p0 < m; p0 += c) {
         const int64_t cnt = std::min<int64_t>(c, m - p0);
         ChunkLayout Lc;
-        if (!chunk_layout(sh, cnt, ws_bytes, Lc) || Lc.total > ws_bytes) return hipErrorInvalidValue;
+        if (!chunk_layout(sh, cnt, ws_bytes, order_points_workspace, Lc) || Lc.total > ws_bytes)
+            return hipErrorInvalidValue;
+        // one column block: its records serve all chunks
+        const bool first = p0 == 0 || ncol > kMultiCols;
         if (!Lc.ordered) {
             OutCols o = {{phi ? phi + p0 : nullptr, ex ? ex + p0 : nullptr, ey ? ey + p0 : nullptr,
                           ez ? ez + p0 : nullptr},
                          m};
-            eval_chunk(drec, sigma, n, ncol, sh, img, mixed, near_factor, px + p0, py + p0, pz + p0, cnt, o, w, Lc, s);
+            eval_chunk(drec, sigma, n, ncol, sh, img, mixed, near_factor, px + p0, py + p0, pz + p0, cnt, o, w, Lc,
+                       first, s);
             continue;
         }
         const size_t cc = (size_t)cnt;
@@ -538,7 +433,7 @@ hipError_t run_eval(const double *drec, const double *sigma, int64_t n, int ncol
         double *sp = reinterpret_cast<double *>(w + Lc.pts);
         double *so = reinterpret_cast<double *>(w + Lc.res);
         hipError_t e = launch_order_points(px + p0, py + p0, pz + p0, cnt, sp, sp + cc, sp + 2 * cc, perm, true,
-                                           ws, Lc.sort_ws, s);
+                                           w + Lc.sort, Lc.sort_ws, s);
         if (e != hipSuccess) return e;
         for (int c0 = 0; c0 < ncol; c0 += kMultiCols) {
             const int k = ncol - c0 < kMultiCols ? ncol - c0 : kMultiCols;
@@ -547,7 +442,7 @@ hipError_t run_eval(const double *drec, const double *sigma, int64_t n, int ncol
                           ez ? so + 3 * cc : nullptr},
                          (int64_t)(4 * cc)};
             eval_chunk(drec, sigma + (size_t)c0 * n, n, k, sh, img, mixed, near_factor, sp, sp + cc, sp + 2 * cc,
-                       cnt, o, w, Lc, s);
+                       cnt, o, w, Lc, first, s);
             for (int j = 0; j < k; ++j) {
                 const size_t col = (size_t)(c0 + j) * mm + (size_t)p0;
                 launch_unorder4(so + 4 * (size_t)j * cc, perm, cnt, phi ? phi + col : nullptr,

@@ -97,6 +97,37 @@ def test_unit_sizes_give_equal_bits(nb, copies, precision):
         assert np.array_equal(evaluate(nb, g, sigma, p[at], precision), full[at]), m
 
 
+@pytest.mark.parametrize("precision", [0, 1])
+def test_fewer_points_at_a_time_give_equal_bits(nb, precision):
+    """67 216 elements without copies are one segment of 1051 groups: the unit
+    sums of 20 000 points are taken a few thousand points at a time."""
+    g = gem_cell(k=360, nr=10, n_images=1)
+    g = g.with_images(Images(a1=g.images.a1, a2=g.images.a2))
+    sigma = 1e-5 * np.random.default_rng(11).standard_normal((3, g.n))
+    p = points(g, 20_000)
+    dp = nb.DevicePanels.from_geometry(g, "cuda:0")
+    out = nb.eval_points_multi(dp, dev(sigma), *[dev(p[:, k]) for k in range(3)], precision=precision)
+    out = torch.stack(out, 2).cpu().numpy()
+    at = np.arange(7, len(p), 33)
+    for k in range(3):
+        assert np.array_equal(evaluate(nb, g, sigma[k], p[at], precision), out[k][at]), k
+    assert np.array_equal(evaluate(nb, g, sigma[1], p, precision), out[1])
+
+
+def test_units_within_the_fixed_scratch(nb):
+    """The allocation-free evaluation takes the finer units that its scratch has
+    room for: rows of expansions, expansions, and whole segments."""
+    ses = nb.Session(nb.DevicePanels.from_geometry(geometry("121"), "cuda:0"))
+    p = points(geometry("121"), 70_000)
+    for m in (64, 1000, 6000, 20_000, 70_000):
+        q = [dev(p[:m, k]) for k in range(3)]
+        out = [torch.empty_like(q[0]) for _ in range(4)]
+        ses.eval_points_noalloc(*q, out)
+        for a, b in zip(out, ses.eval_points(*q)):
+            assert torch.equal(a, b), m
+    ses.close()
+
+
 @pytest.mark.parametrize("ncol", [2, 3, 5])
 def test_columns_equal_single_evaluations(nb, ncol):
     g = geometry("121")
