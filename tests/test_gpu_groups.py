@@ -128,6 +128,25 @@ def test_units_within_the_fixed_scratch(nb):
     ses.close()
 
 
+def test_lattice_of_several_lists(nb):
+    """441 copies, listed 128 at a time: all are near the group that spans the foil
+    and the drift plane, a few rows of them the others."""
+    g = geometry("121")
+    g = g.with_images(Images(a1=g.images.a1, a2=g.images.a2, n1=10, n2=10))
+    sigma = 1e-5 * (0.5 + np.random.default_rng(12).random(g.n))
+    p = points(g, 270_000)
+    full = evaluate(nb, g, sigma, p)
+    ref = oracle.eval_points(g, sigma, p[:40])
+    assert np.max(np.abs(full[:40, 0] / ref[:, 0] - 1)) <= 1e-10
+    en = np.linalg.norm(ref[:, 1:], axis=1)
+    t = en >= 1e-3 * en.max()
+    assert np.max(np.linalg.norm(full[:40, 1:] - ref[:, 1:], axis=1)[t] / en[t]) <= 1e-10
+    rng = np.random.default_rng(13)
+    for m in (1, 64, 700, 4097):
+        at = rng.choice(len(p), m, replace=False)
+        assert np.array_equal(evaluate(nb, g, sigma, p[at]), full[at]), m
+
+
 @pytest.mark.parametrize("ncol", [2, 3, 5])
 def test_columns_equal_single_evaluations(nb, ncol):
     g = geometry("121")
