@@ -1334,7 +1334,6 @@ __device__ __forceinline__ void near_element(const NearList &nl, const Elem &e, 
                                              const double (&sg2)[K], const ImgArgs &img, double Px, double Py,
                                              double Pz, double (&acc)[K][4])
 {
-    const int lane = threadIdx.x & 63;
     const double dp = PAIR ? fmax(e.diam, f.diam) : e.diam;
     const double far2 = (kFarDiam * kFarDiam) * (dp * dp), vfar2 = (kVeryFarDiam * kVeryFarDiam) * (dp * dp);
 #pragma unroll 1
@@ -1360,7 +1359,12 @@ __device__ __forceinline__ void near_element(const NearList &nl, const Elem &e, 
 #pragma unroll 1
         for (int l = lo; l < hi; ++l) {
             const double f1 = nl.f1[l], f2 = nl.f2[l];
-            if ((nl.lanes[l] >> lane) & 1) {
+            // the mask itself as the branch's lanes, no test in each: on a mesh in random order,
+            // where all groups are wide and all copies near, the lists took 249.5 ms where
+            // closed forms without them take 247.1, now 246.7 (THGEM, 9 copies, 200 000 points)
+            const uint64_t lanes = nl.lanes[l];
+            if (__builtin_amdgcn_inverse_ballot_w64(((uint64_t)(unsigned)uni((int)(lanes >> 32)) << 32) |
+                                                    (unsigned)uni((int)lanes))) {
                 const double X = fma(f2, bX, fma(f1, aX, X0)), Z = fma(f2, bZ, fma(f1, aZ, Z0)),
                              H = fma(f2, bH, fma(f1, aH, H0));
                 if (PAIR)
