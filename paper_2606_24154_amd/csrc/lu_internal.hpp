@@ -4,9 +4,10 @@
 
 #include <cstdint>
 
+#include "panel_rule.hpp"
+
 namespace nebem {
 
-constexpr int kNB = 64;        // LU panel width
 constexpr int kOuterNB = 256;  // LU outer block width (multiple of kNB)
 
 // Device scratch of one factorisation: per-workgroup pivot candidates
@@ -25,7 +26,6 @@ struct LUWork {
     uint64_t *words = nullptr;
     int *timeout = nullptr;
 };
-size_t panel_words(int n, int word_per_value);
 void clear_words(uint64_t *w, int64_t len, hipStream_t s);
 
 void lu_factor(double *A, int n, int *ipiv, LUWork &w, hipStream_t s);

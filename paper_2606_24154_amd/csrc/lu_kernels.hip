@@ -40,7 +40,6 @@
 
 namespace nebem {
 
-constexpr int kPB = 256;  // rows per panel workgroup
 
 // Lane i's value broadcast to the wave (i uniform): v_readlane, no LDS.
 __device__ __forceinline__ double lane_bcast(double v, int i)
@@ -279,15 +278,13 @@ __device__ __forceinline__ T wave_max(T v)
 // barrier, a reduction over the workgroup and the whole update inside the chain
 // 5.8 us, 47 ms).  NW = 1 has no workgroup barrier at all and spreads the rows over
 // the most CUs: 144 us a panel at n = 8064 where NW = 4 takes 163.  It is taken
-// while G stays at most kLoneWaves, the four candidates that a lane reads at once.
+// while G stays at most kLoneWaves, the four candidates that a lane reads at once
+// (panel_rule.hpp).
 // A wave of its own for the reads was slower (two barriers a column: 204 us).
 // Slots are double-buffered by column parity: a slot is written again two
 // columns later, when the writer has read the next column's candidates of all
 // workgroups, and each published those after its last read of the slot.  Tags are
 // column numbers, so the words are cleared once per factorisation.
-constexpr int kLoneWaves = 256;
-constexpr int kKeySets = 4;  // candidates per lane, G <= 64 kKeySets
-
 constexpr int kPanelPad = 8;
 
 // s[u stride] -= l u[u] for N columns of a row
@@ -309,6 +306,7 @@ __global__ __launch_bounds__(64 * NW) void k_panel_fused(T *__restrict__ A, int 
                                                          int *__restrict__ ipiv, int *__restrict__ info,
                                                          uint64_t *__restrict__ words, int *__restrict__ timeout)
 {
+    constexpr int kKeySets = panel_key_sets(NW, sizeof(T));
     constexpr int W = Words<T>::N, R = 64 * NW, LD = R + 1;  // odd: a row's entries lie in different banks
     // this workgroup's rows of the panel, S[col * LD + row]; an update's last batch
     // may reach past the panel's columns, into slots that nothing else uses
@@ -449,13 +447,6 @@ __global__ __launch_bounds__(64 * NW) void k_panel_fused(T *__restrict__ A, int 
     }
     if (live)
         for (int jj = 0; jj < kb; ++jj) A[(size_t)(k + jj) * n + r] = S[jj * LD + t];
-}
-
-size_t panel_words(int n, int word_per_value)
-{
-    const int g1 = (n + 63) / 64, g4 = (n + kPB - 1) / kPB;
-    const size_t G = (size_t)(g1 < kLoneWaves ? g1 : (g4 > kLoneWaves ? g4 : kLoneWaves));
-    return 2 * ((size_t)word_per_value + 1) * G + 2 * (G + 1) * (size_t)word_per_value * kNB;
 }
 
 // Row swaps of panel [k, k+kb) applied to every column outside the panel.  Each
@@ -1106,15 +1097,15 @@ void lu_factor_launch(T *A, int n, int *ipiv, LUWork &w, hipStream_t s)
         for (int k = K0; k < K1; k += kNB) {
             const int kb = (K1 - k < kNB) ? K1 - k : kNB;
             const unsigned gp = (unsigned)((n - k + kPB - 1) / kPB), g1 = (unsigned)((n - k + 63) / 64);
-            const bool lone = (int)g1 <= kLoneWaves && (int)g1 <= cap1;
+            const int nw = fused_ok ? panel_waves(n - k, sizeof(T), cap1, cap4) : 0;
             bool done = false;
-            if (fused_ok && (lone || ((int)gp <= cap4 && gp <= 64 * kKeySets))) {
+            if (nw) {
                 int a_n = n, a_k = k, a_kb = kb;
                 void *args[] = {&A, &a_n, &a_k, &a_kb, &ipiv, &w.info, &w.words, &w.timeout};
                 const hipError_t e =
-                    lone ? hipLaunchCooperativeKernel((const void *)k_panel_fused<T, 1>, dim3(g1), dim3(64), args, 0, s)
-                         : hipLaunchCooperativeKernel((const void *)k_panel_fused<T, 4>, dim3(gp), dim3(kPB), args, 0,
-                                                      s);
+                    nw == 1 ? hipLaunchCooperativeKernel((const void *)k_panel_fused<T, 1>, dim3(g1), dim3(64), args, 0, s)
+                            : hipLaunchCooperativeKernel((const void *)k_panel_fused<T, 4>, dim3(gp), dim3(kPB), args, 0,
+                                                         s);
                 if (e == hipSuccess) {
                     done = true;
                 } else {

@@ -114,6 +114,29 @@ def test_factor_large(nb):
     assert (p >= np.arange(n)).all() and (p < n).all()
 
 
+@pytest.mark.parametrize("n, precision", [(33_100, 0), (65_700, 1)])
+def test_factor_larger(nb, n, precision):
+    """Sizes whose first outer blocks take U rows 16 columns to a wave, and in FP32
+    panels of more than 256 workgroups.  A is 3 sqrt(n) times a permutation plus
+    normal entries, whose singular values end near 2 sqrt(n): |A^-1| <= 1.1 / sqrt(n),
+    |A| <= 5.1 sqrt(n), and the pivot rows are the permutation's (elsewhere a column's
+    entries stay some standard deviations, 3 sqrt(n) is hundreds).  So |x - y| is at most
+    5.7 times |y| x (the refinement's 1e-10, or the FP64 solve's rounding)."""
+    g = torch.Generator(device="cuda:0").manual_seed(6)
+    At = torch.randn(n, n, dtype=torch.float64, device="cuda:0", generator=g)  # column-major A
+    row = torch.randperm(n, device="cuda:0", generator=g)  # of each column's large entry
+    At[torch.arange(n, device="cuda:0"), row] += 3 * n**0.5
+    y = torch.randn(n, dtype=torch.float64, device="cuda:0", generator=g)
+    b = At.T @ y
+    x, ipiv, info = nb.solve(At, b, precision)
+    assert info.rel_resid <= (1e-10 if precision else 1e-13)
+    assert float((x - y).norm() / y.norm()) <= 5.7 * (1e-10 if precision else 1e-13)
+    perm = np.arange(n)
+    for k, p in enumerate(ipiv.cpu().numpy()):
+        perm[[k, p]] = perm[[p, k]]
+    assert np.array_equal(perm, row.cpu().numpy())
+
+
 def assembly_geometry(kind):
     """1242 elements, conductor and dielectric rows, the last group ragged: one
     cell's copies as usual, on a skewed lattice with more copies one way, with

@@ -11,7 +11,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "..", "paper_2606_24154_amd", "csrc")
 
 
-@pytest.mark.parametrize("name", ["record_blocks", "eval_plan"])
+@pytest.mark.parametrize("name", ["record_blocks", "eval_plan", "panel_rule"])
 def test_rules(tmp_path, name):
     cxx = shutil.which("g++") or shutil.which("c++")
     if cxx is None:
