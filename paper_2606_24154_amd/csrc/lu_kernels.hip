@@ -509,17 +509,19 @@ __global__ __launch_bounds__(256) void k_laswp(T *__restrict__ A, int n, int k, 
     }
 }
 
-// U = L11^-1 A[k:k+kb, j] for the columns j in [jb, je), 4 NC per workgroup
-// (unit lower L11 = A[k:k+kb, k:k+kb], kb <= 64).  Wave w solves NC columns with
+// U = L11^-1 A[k:k+kb, j] for the columns j in [jb, je), 4 kTrsmCols per workgroup
+// (unit lower L11 = A[k:k+kb, k:k+kb], kb <= 64).  Wave w solves kTrsmCols columns with
 // lane r holding row r of each: the entry solved at step i reaches the other lanes
 // by readlane, so the waves run without barriers; every subtraction comes in the
 // order of plain forward substitution.  VALU bound on few workgroups: 16 columns a
-// wave took 22 us for 4000 FP64 columns (63 workgroups), 4 columns 10 us, 8 columns 17; NC = 16, which
-// reads L11 a quarter as often, is taken where it gives every CU a workgroup twice
-// over.
-template <typename T, int NC>
+// wave took 22 us for 4000 FP64 columns (63 workgroups), 4 columns 10 us, 8 columns 17.
+// More columns, which read L11 less often, do not pay at large sizes either: 38 000 FP64
+// columns 46.5 us at 16 a wave, 39.7 at 4; 68 000 FP32 columns 45.5, 40.7.
+constexpr int kTrsmCols = 4;
+template <typename T>
 __global__ __launch_bounds__(256) void k_trsm(T *__restrict__ A, int n, int k, int kb, int jb, int je)
 {
+    constexpr int NC = kTrsmCols;
     __shared__ T L[kNB][kNB + 1];
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int j0 = jb + blockIdx.x * (4 * NC);
@@ -844,11 +846,8 @@ template <typename T>
 static void trsm(T *A, int n, int k, int kb, int jb, int je, hipStream_t s)
 {
     if (je <= jb) return;
-    const int cols = je - jb;
-    if (cols >= 2 * 256 * 64)
-        hipLaunchKernelGGL((k_trsm<T, 16>), dim3((unsigned)((cols + 63) / 64)), dim3(256), 0, s, A, n, k, kb, jb, je);
-    else
-        hipLaunchKernelGGL((k_trsm<T, 4>), dim3((unsigned)((cols + 15) / 16)), dim3(256), 0, s, A, n, k, kb, jb, je);
+    hipLaunchKernelGGL(k_trsm<T>, dim3((unsigned)((je - jb + 4 * kTrsmCols - 1) / (4 * kTrsmCols))), dim3(256), 0, s, A,
+                       n, k, kb, jb, je);
 }
 
 // ------------------------------------------------------ triangular solves

@@ -116,8 +116,8 @@ def test_factor_large(nb):
 
 @pytest.mark.parametrize("n, precision", [(33_100, 0), (65_700, 1)])
 def test_factor_larger(nb, n, precision):
-    """Sizes whose first outer blocks take U rows 16 columns to a wave, and in FP32
-    panels of more than 256 workgroups.  A is 3 sqrt(n) times a permutation plus
+    """Thousands of workgroups for a panel's rows of U, and in FP32 panels of more than
+    256 workgroups.  A is 3 sqrt(n) times a permutation plus
     normal entries, whose singular values end near 2 sqrt(n): |A^-1| <= 1.1 / sqrt(n),
     |A| <= 5.1 sqrt(n), and the pivot rows are the permutation's (elsewhere a column's
     entries stay some standard deviations, 3 sqrt(n) is hundreds).  So |x - y| is at most
