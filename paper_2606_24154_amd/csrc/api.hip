@@ -159,10 +159,17 @@ nebem_status eval_with_workspace(const double *drec, const double *sigma, int64_
                                  int64_t m, double *phi, double *ex, double *ey, double *ez, hipStream_t stream,
                                  const char *what)
 {
-    const size_t wb = eval_workspace(n, ia, m, ncol, mixed);
+    size_t wb = eval_workspace(n, ia, m, ncol, mixed);
     DevBuf ws;
-    if (wb && ws.alloc(wb, stream) != hipSuccess)
-        return fail(NEBEM_ENOMEM, std::string(what) + ": evaluation workspace");
+    if (wb) {
+        wb = take_workspace(wb, eval_workspace_min(n, ia, m, ncol, mixed), [&](size_t b) {
+            if (ws.alloc(b, stream) == hipSuccess) return true;
+            (void)hipGetLastError();
+            ws.p = nullptr;
+            return false;
+        });
+        if (!wb) return fail(NEBEM_ENOMEM, std::string(what) + ": evaluation workspace");
+    }
     NEBEM_HIP(run_eval(drec, sigma, n, ncol, ia, mixed, near_factor, px, py, pz, m, phi, ex, ey, ez, ws.p, wb,
                        stream));
     return NEBEM_OK;

@@ -220,4 +220,18 @@ int64_t chunk_points(const EvalShape &sh, int64_t m, size_t limit, SortBytes &&s
     return even < c ? even : c;
 }
 
+// Workspace of a call: `want` bytes, or where the device has no room for them
+// half as many and so on, at least `least` (a call then takes coarser units and fewer
+// points at a time).  The finer units' sums are most of what a mid-sized call wants:
+// 20 000 points of a GEM cell 0.2 GB, its partial sums alone 5 MB.  alloc(bytes):
+// whether it was given.  Returns the bytes, 0 if there is no room for `least`.
+template <class Alloc>
+size_t take_workspace(size_t want, size_t least, Alloc &&alloc)
+{
+    for (size_t b = want;; b = std::max(least, b / 2)) {
+        if (alloc(b)) return b;
+        if (b <= least) return 0;
+    }
+}
+
 }  // namespace nebem

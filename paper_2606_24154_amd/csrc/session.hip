@@ -89,7 +89,13 @@ static nebem_status session_eval_points(nebem_session *s, const double *px, cons
 {
     const int mixed = s->opt.precision == NEBEM_MIXED;
     const size_t wb = eval_workspace(s->n, s->img, m, 1, mixed);
-    if (wb) NEBEM_HIP(s->ows.ensure(wb));
+    hipError_t e = hipSuccess;
+    if (wb && !take_workspace(wb, eval_workspace_min(s->n, s->img, m, 1, mixed), [&](size_t b) {
+            if ((e = s->ows.ensure(b)) == hipSuccess) return true;
+            (void)hipGetLastError();
+            return false;
+        }))
+        return hip_fail(e, "session: evaluation workspace");
     NEBEM_HIP(run_eval(s->drec.as<double>(), s->sigma.as<double>(), s->n, 1, s->img, mixed, s->opt.near_factor, px,
                        py, pz, m, phi, ex, ey, ez, s->ows.p, s->ows.bytes, st));
     return NEBEM_OK;

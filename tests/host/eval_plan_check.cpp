@@ -96,6 +96,21 @@ int main()
         const int64_t c = chunk_points(flat, 20000, limit, sort_bytes);
         CHECK(c < 20000 && chunk_layout(flat, c, limit, sort_bytes, L) && L.fsplit);
     }
+    // a device with less room than a call would like: half as much, down to the least
+    for (size_t room : {size_t(0), size_t(999), size_t(1000), size_t(50000), size_t(1) << 40}) {
+        const size_t got = take_workspace(900000, 1000, [&](size_t b) { return b <= room; });
+        CHECK(got == (room < 1000 ? 0 : room < 50000 ? 1000 : room < 900000 ? got : 900000));
+        CHECK(got <= room && (got == 0 || got >= 1000));
+        if (room == 50000) CHECK(got > 25000);
+    }
+    // and there is a plan for every such size
+    for (int64_t m : {100, 2003, 20000, 300000}) {
+        ChunkLayout least;
+        CHECK(chunk_layout(gem, std::min<int64_t>(m, 256), 0, sort_bytes, least));
+        const int64_t c = chunk_points(gem, m, SIZE_MAX, sort_bytes);
+        CHECK(chunk_layout(gem, c, SIZE_MAX, sort_bytes, L));
+        for (size_t b = L.total; b > least.total; b = std::max(least.total, b / 2)) CHECK(chunk_points(gem, m, b, sort_bytes) > 0);
+    }
     std::printf("%s\n", failures ? "FAIL" : "checks passed");
     return failures != 0;
 }
