@@ -47,7 +47,8 @@ void solve_flow_init(SolveFlow &f, void *mem, int n, hipStream_t s);
 // W is an n x nrhs workspace of the solve's type.  X, W and B must be distinct.
 void lu_solve(const double *LU, int n, const int *perm, const double *B, double *X, double *W, int nrhs,
               SolveFlow &f, hipStream_t s);
-void lu_solve(const float *LU, int n, const int *perm, const double *B, float *X, float *W, int nrhs, SolveFlow &f,
+// the same with FP32 factors, one column
+void lu_solve(const float *LU, int n, const int *perm, const double *B, float *X, float *W, SolveFlow &f,
               hipStream_t s);
 // z = A^-T b with the FP64 factors of P A = L U (perm as in lu_solve); W, V:
 // n-entry workspaces.  z must not alias b, W or V.

@@ -1170,22 +1170,27 @@ static void trsv_flow(const T *LU, int n, const int *perm, const TB *B, T *Y, So
                        f.ticket, base, tag, f.timeout);
 }
 
-// X = A^-1 P B, kSolveCols right-hand sides per pass over the factors.  W: n x
-// nrhs workspace.
-template <typename T>
-static void lu_solve_launch(const T *LU, int n, const int *perm, const double *B, T *X, T *W, int nrhs, SolveFlow &f,
-                            hipStream_t s)
+// X = A^-1 P B, up to kSolveCols right-hand sides per pass over the factors.  W: n x
+// nrhs workspace.  A pass is bound by the chain of blocks, so that 2 or 3 columns take
+// little more than one: 3 columns of n = 200 0.15 ms (singly 0.21), 7 of n = 8064 3.2
+// (the last three singly 5.4).
+template <typename T, int NR>
+static void lu_solve_columns(const T *LU, int n, const int *perm, const double *B, T *X, T *W, SolveFlow &f, hipStream_t s)
 {
-    int q = 0;
-    for (; q + kSolveCols <= nrhs; q += kSolveCols) {
+    trsv_flow<T, double, NR, true>(LU, n, perm, B, W, f, s);
+    trsv_flow<T, T, NR, false>(LU, n, perm, W, X, f, s);
+}
+void lu_solve(const double *LU, int n, const int *perm, const double *B, double *X, double *W, int nrhs, SolveFlow &f,
+              hipStream_t s)
+{
+    for (int q = 0; q < nrhs; q += kSolveCols) {
         const size_t o = (size_t)q * n;
-        trsv_flow<T, double, kSolveCols, true>(LU, n, perm, B + o, W + o, f, s);
-        trsv_flow<T, T, kSolveCols, false>(LU, n, perm, W + o, X + o, f, s);
-    }
-    for (; q < nrhs; ++q) {
-        const size_t o = (size_t)q * n;
-        trsv_flow<T, double, 1, true>(LU, n, perm, B + o, W + o, f, s);
-        trsv_flow<T, T, 1, false>(LU, n, perm, W + o, X + o, f, s);
+        switch (nrhs - q) {
+        case 1: lu_solve_columns<double, 1>(LU, n, perm, B + o, X + o, W + o, f, s); break;
+        case 2: lu_solve_columns<double, 2>(LU, n, perm, B + o, X + o, W + o, f, s); break;
+        case 3: lu_solve_columns<double, 3>(LU, n, perm, B + o, X + o, W + o, f, s); break;
+        default: lu_solve_columns<double, kSolveCols>(LU, n, perm, B + o, X + o, W + o, f, s); break;
+        }
     }
 }
 
@@ -1212,15 +1217,9 @@ void lu_solve_transposed(const double *LU, int n, const int *perm, const double 
 
 void lu_factor(double *A, int n, int *ipiv, LUWork &w, hipStream_t s) { lu_factor_launch<double>(A, n, ipiv, w, s); }
 void lu_factor(float *A, int n, int *ipiv, LUWork &w, hipStream_t s) { lu_factor_launch<float>(A, n, ipiv, w, s); }
-void lu_solve(const double *LU, int n, const int *perm, const double *B, double *X, double *W, int nrhs,
-              SolveFlow &f, hipStream_t s)
+void lu_solve(const float *LU, int n, const int *perm, const double *B, float *X, float *W, SolveFlow &f, hipStream_t s)
 {
-    lu_solve_launch<double>(LU, n, perm, B, X, W, nrhs, f, s);
-}
-void lu_solve(const float *LU, int n, const int *perm, const double *B, float *X, float *W, int nrhs, SolveFlow &f,
-              hipStream_t s)
-{
-    lu_solve_launch<float>(LU, n, perm, B, X, W, nrhs, f, s);
+    lu_solve_columns<float, 1>(LU, n, perm, B, X, W, f, s);
 }
 
 }  // namespace nebem

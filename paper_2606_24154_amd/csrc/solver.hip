@@ -290,7 +290,7 @@ nebem_status solve_mixed(const double *A, const float *LU32, const double *s, co
     double best = INFINITY;
     int stall = 0, it = 0;
     for (it = 1; it <= max_iter; ++it) {
-        lu_solve(LU32, n, perm, rs.as<double>(), d32.as<float>(), w32.as<float>(), 1, flow.f, st);
+        lu_solve(LU32, n, perm, rs.as<double>(), d32.as<float>(), w32.as<float>(), flow.f, st);
         add_f32(x, d32.as<float>(), n, st);
         residual(A, n, x, b, s, part.as<double>(), rs.as<double>(), sq.as<double>(), st);
         NEBEM_HIP(hipGetLastError());

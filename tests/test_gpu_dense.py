@@ -52,6 +52,18 @@ def test_solves_from_factors(nb, n, nrhs):
     assert np.array_equal(one.cpu().numpy(), X[-1])
 
 
+@pytest.mark.parametrize("n", [1, 65, 200])
+@pytest.mark.parametrize("nrhs", [2, 6, 7])
+def test_columns_of_a_last_pass(nb, n, nrhs):
+    """Two or three columns solved together have the bits of each by itself."""
+    rng, L, U, piv = factors(n, 100 * n + nrhs)
+    B = rng.standard_normal((nrhs, n))
+    LU, ipiv = dev((L + U).T), dev(piv, torch.int32)
+    X = nb.solve_factored(LU, ipiv, dev(B))
+    for k in range(nrhs):
+        assert torch.equal(nb.solve_factored(LU, ipiv, dev(B[k])), X[k]), k
+
+
 def test_solves_beyond_the_reciprocals_range(nb):
     """Pivots whose reciprocals overflow or are zero divide as IEEE division
     does, and an infinite solution leaves those solved before it alone."""
