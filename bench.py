@@ -54,7 +54,8 @@ COUNTER_CALIBRATION = {
               "points_per_launch": 200000, "source_sha16": "9cd0d85c2a8b156b"},
 }
 EVAL_SOURCES = ("field_kernels.hip", "group_kernels.hip", "group_far.hpp", "lattice_far.hpp", "panel_fp64.hpp",
-                "fastmath_fp64.hpp", "poly_coeffs.hpp", "farfield_mixed.hpp", "order_kernels.hip", "nebem_internal.hpp")
+                "fastmath_fp64.hpp", "poly_coeffs.hpp", "farfield_mixed.hpp", "order_kernels.hip", "nebem_internal.hpp",
+                "eval_plan.hpp")
 
 
 def _code_only(text):

@@ -91,10 +91,16 @@ typedef struct nebem_images {
 } nebem_images;
 
 typedef enum nebem_precision {
-    NEBEM_FP64 = 0,  /* FP64 everywhere: exact closed forms; in evaluations, copies of a 64-element group far from the
-                        point by the group's multipole expansion, truncated below 3e-12 of the group's summed absolute
-                        charge over distance (less than the closed forms' own rounding there); FP64 LU + refinement */
-    NEBEM_MIXED = 1  /* FP64 near field, FP64 monopole + FP32 correction far away; FP32 LU + FP64 refinement */
+    /* FP64 everywhere: exact closed forms; copies of a group of 64 consecutive elements far from the point by the
+       group's multipole expansion, truncated below 3e-12 of the group's summed absolute charge over distance (less
+       than the closed forms' own rounding there): in evaluations from 65 536 element copies on (elements x copies of
+       each), in the matrix from 36 copies of each element on (n >= 128; not with collocation points of the caller's).
+       Elements in spatial order make narrow groups, whose copies are nearly all far; elements in random order are
+       evaluated by closed forms throughout.  FP64 LU + refinement */
+    NEBEM_FP64 = 0,
+    /* evaluation: FP64 near field, FP64 monopole + FP32 correction far away; the matrix as in NEBEM_FP64;
+       FP32 LU + FP64 refinement */
+    NEBEM_MIXED = 1
 } nebem_precision;
 
 typedef struct nebem_options {
@@ -434,7 +440,11 @@ nebem_status nebem_spacecharge_step_lines(nebem_session *s, double *qx, double *
  * segments, added in the same order). */
 typedef struct nebem_server nebem_server;
 typedef struct nebem_server_options {
-    int64_t hbm_budget;         /* bytes of device staging for admitted requests (2 GiB) */
+    int64_t hbm_budget;         /* bytes of device staging for admitted requests (2 GiB).  Beside it a server holds
+                                   the partial sums of launches in finer units, up to 320 MB (without them, if there
+                                   is no room at creation, such launches run as whole items and take longer), in FP64
+                                   two sets of group records, 9 KB each, about n / 48 per grouped geometry and set,
+                                   the work lists, and the sort's scratch of the largest request */
     double batch_interactions;  /* work per launch, interactions (1e10) */
     int32_t max_items;          /* work items per launch (65536) */
     double large_interactions;  /* a request of at least this much work (interactions) is large (1e11) */

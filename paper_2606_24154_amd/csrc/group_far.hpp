@@ -26,10 +26,15 @@
 // sum |q| / r^2; tier_ratio2 gives the (r/a)^2 from which a degree keeps that
 // bound below 3e-12.  On meshes it comes out 10 to 100 times smaller at the
 // threshold itself, below the closed forms' own rounding (1e-11 of an element's
-// field beyond 25 diameters), and it falls with (a/r)^(p+1).  Fields' errors against
-// 64-bit sums, GEM and THGEM cells of 1500 to 10 000 elements: 3.1 .. 5.4e-15 with
-// closed forms throughout, 1.9 .. 3.4e-15 at 3e-12 as at 1e-12 (which takes 8 % longer),
-// 2.7 .. 4.6e-15 at 1e-11.
+// field beyond 25 diameters), and it falls with (a/r)^(p+1).  Errors against 64-bit
+// sums (closed forms near, Gauss rules far) over field-map points and, a third, points
+// in the GEM's hole, GEM cells of 1648 x 121, 2960 x 49, 8064 x 121 and 8064 x 9 copies,
+// THGEM of 5792 x 49 and 41 600 x 121: of E, in the 2-norm over the points, 1.1, 1.2, 1.7,
+// 2.1, 1.4, 1.8e-15 (closed forms throughout 1.3, 2.4, 1.9, 3.7, 2.1, 1.8e-15), of phi
+// 0.7, 1.2, 1.1, 4.0, 0.5, 0.7e-15 (2.6, 5.8, 2.6, 11, 1.2, 0.9e-15); largest pointwise
+// of E 1e-14 .. 1e-13 both.  With a bound of 1e-12 E's are 1.0, 1.2, 1.8, 2.0, 1.4,
+// 1.8e-15 and calls take 4 to 7 % longer; with 1e-11 2.7, 1.3, 1.8, 2.2, 1.8, 1.9e-15,
+// on the first mesh twice the closed forms'.
 #pragma once
 #include <hip/hip_runtime.h>
 

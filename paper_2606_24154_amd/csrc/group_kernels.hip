@@ -19,8 +19,8 @@
 // and the widest segments first (far 18, near 17); the far pass issues at ~75 % of the
 // FP64 rate.  Three waves per SIMD and two entries ahead: two waves 79 ms (of 74),
 // four 76, one entry ahead 87, three 83.  64 points of the GEM cell, one row of an
-// expansion or 8 elements of a group per wave: 23.5 ms -> 0.58 ms.  Error of 2003 GEM
-// points' field against a 64-bit sum: 1.6e-14 before, 1.3e-14 now.
+// expansion or 8 elements of a group per wave: 23.5 ms -> 0.58 ms.  Errors against
+// 64-bit sums: group_far.hpp.
 #include <hip/hip_runtime.h>
 
 #include "lattice_far.hpp"

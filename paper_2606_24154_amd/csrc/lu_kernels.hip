@@ -997,7 +997,8 @@ __global__ __launch_bounds__(256) void k_trsv_flow(const T *__restrict__ LU, int
 // of U), lower = 0 solves L^T v = w backward (unit diagonal).  Row r of a
 // transposed factor is column r of LU, so the block's entries of row r are
 // LU[r n + b0 .. b0 + 63], contiguous.  X is reduced in place on the
-// unsolved side and the block's solution goes to Y (as in k_trsv_step).
+// unsolved side and the block's solution goes to Y: solved rows are never written to
+// X, so no workgroup reads a half-updated block.
 __global__ __launch_bounds__(256) void k_trsv_t_step(const double *__restrict__ LU, int n, double *__restrict__ X,
                                                      double *__restrict__ Y, int b0, int bsz, int lower)
 {

@@ -15,8 +15,8 @@ constexpr double kEps0 = 8.8541878128e-12;  // vacuum permittivity, F/m
 constexpr double kKe = 1.0 / (4.0 * 3.14159265358979323846 * kEps0);
 
 // Derived element record in HBM, 24 doubles (192 B) per element, built once
-// per geometry by the prep kernel and streamed through LDS by the field
-// kernels.
+// per geometry by the prep kernel and read by the field kernels as scalar loads
+// (the direct assembly stages them in LDS).
 enum DRec : int {
     R_OX = 0, R_OY, R_OZ,      // corner o
     R_E1X, R_E1Y, R_E1Z,       // unit vector along u
@@ -159,12 +159,13 @@ struct OutCols {
 // expansions: a function of the geometry only, like the segment plan.
 bool eval_grouped(int64_t n, const ImgArgs &img);
 size_t group_record_bytes();
-// moments of every group and density column (column k at sigma + k sig_stride)
-// order: of the segments, the costliest first (behind the records in gdata)
-void launch_segment_order(const double *gdata, int64_t n, const SegPlan &sp, int *order, hipStream_t s);
-int *segment_order(double *gdata, int ncol, const SegPlan &sp);
+// records of every group and density column (column k at sigma + k sig_stride)
 void launch_group_moments(const double *drec, const double *sigma, int64_t n, int64_t sig_stride, int ncol,
                           const SegPlan &sp, double *gdata, hipStream_t s);
+// order: of the segments, the costliest first (segment_order: its place behind
+// the records of ncol columns in gdata)
+void launch_segment_order(const double *gdata, int64_t n, const SegPlan &sp, int *order, hipStream_t s);
+int *segment_order(double *gdata, int ncol, const SegPlan &sp);
 // Far and near parts of a grouped evaluation, one pass each.  split 0: units
 // are segments, and the near pass adds to the far pass's sums; split > 0:
 // finer units, each pass with outputs of its own (far 1: groups, 2: lattice
