@@ -1556,7 +1556,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
 
 // Columns 1 .. ncol - 1 of the units in which they differ from column 0, by
 // their own records (column k's at gdata + k gstride).  Mostly there are none, and the
-// launch ends with the scan of the groups' flags: 3 us of the 4.0 ms of three columns
+// launch ends with the scan of the groups' flags: 4.6 us of the 4.0 ms of three columns
 // at 4507 points.  (With this in k_group_near, as a loop or as workgroups of their
 // own, that call took 1 to 2 % longer.)
 __global__ __launch_bounds__(64) void k_near_columns(const double *__restrict__ drec, const double *__restrict__ sigma,
