@@ -51,7 +51,7 @@ ALG_FLOPS_TRI = 100.0
 COUNTER_CALIBRATION = {
     # profiles/eval_fp64_thgem_200k.md: one 2e5-point launch, 1.00672e12 interactions
     "thgem": {"flops_per_interaction": 4.9004, "valu_per_interaction": 3.628, "traffic_bytes": 1841930588,
-              "points_per_launch": 200000, "source_sha16": "d8990eeba8c355f2"},
+              "points_per_launch": 200000, "source_sha16": "ac620d55685316e1"},
 }
 EVAL_SOURCES = ("field_kernels.hip", "group_kernels.hip", "group_far.hpp", "lattice_far.hpp", "panel_fp64.hpp",
                 "fastmath_fp64.hpp", "poly_coeffs.hpp", "farfield_mixed.hpp", "order_kernels.hip", "nebem_internal.hpp",

@@ -78,7 +78,6 @@ __host__ __device__ constexpr int entry_index(int L, int m)
     return m < kOrderSplit ? pass1_entries(L) + m : kPass2 + pass2_entries(L) + m - kOrderSplit;
 }
 constexpr int kGroupStride = kGroupHead + kEntry * kGroupEntries;
-static_assert(kGroupHead % kEntry == 0, "entries are read 64 bytes at a time, from records at such boundaries");
 
 // squares of r/a = ((p + 2) / 3e-12)^(1/(p + 1)) for p = 14, 12, 10, 8, 6, 4
 __host__ __device__ constexpr double tier_ratio2(int k)
@@ -117,7 +116,8 @@ inline constexpr HarmonicTables kHarm = make_harmonic_tables();
 // Uniform reads of data that no kernel in flight writes: the constant
 // address space makes them scalar loads.
 typedef const __attribute__((address_space(4))) double *cdouble_p;
-typedef double d8 __attribute__((ext_vector_type(8)));
+typedef double d8 __attribute__((ext_vector_type(8), aligned(8)));  // scalar loads need no more, nor do its users
+static_assert(alignof(d8) == alignof(double), "group records start at any double");
 typedef const __attribute__((address_space(4))) d8 *cd8_p;
 __device__ __forceinline__ cdouble_p uniform_ptr(const double *p)
 {

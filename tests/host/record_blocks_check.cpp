@@ -6,18 +6,18 @@
 
 int main()
 {
-    // the records of a mesh of every size take a multiple of 8 doubles; odd lengths
-    // must not matter either
+    // geometries' blocks follow each other without overlap, whatever their lengths,
+    // and so do the two streams' sets of len doubles
     int failures = 0;
     for (size_t first = 1; first < 3000; first += 7) {
         nebem::RecordBlocks b;
         size_t end = 0;
         for (size_t n = first, k = 0; k < 5; ++k, n = n * 3 % 1777 + 1) {
             const size_t at = b.add(n);
-            if (at % 32 || at < end || b.len < at + n || b.len % 32) ++failures;
+            if (at < end || b.len < at + n) ++failures;
             end = at + n;
         }
-        if (b.len > end + 31) ++failures;
+        if (b.len > end + 4) ++failures;
     }
     std::printf("%s\n", failures ? "FAIL" : "checks passed");
     return failures != 0;
